@@ -57,7 +57,7 @@ constexpr int kRankMaxTenants = 512;
 constexpr int kHistEntries = 8192;  // histogram words the batcher holds in LDS (waves or ranking workgroups x padded tenants)
 constexpr int kListKinds = 3;       // tile lists per layer index: FC (streaming), conv, FC (big tiles)
 constexpr int kActBuffers = 4;      // most activation buffers of a run: layer outputs that may be alive at once
-constexpr int kLayerGroup = 8;      // the batcher builds the tile lists of this many layer indices per pass
+constexpr int kLayerGroup = 8;      // a tenant's table rows are installed this many layers per launch; layer indices per word of BatchArgs::list_mask
 constexpr int kBigMaxLayer = 32;    // layer indices from here on never take big tiles (their decisions travel in one 32-bit mask)
 constexpr int kRowBytes = 128;      // conv path: bytes of K one pipeline step consumes per row
 constexpr int kChanPad = 8;         // conv input channels are padded to a multiple of this
@@ -157,8 +157,7 @@ struct BatchArgs {
     uint32_t big_enabled;  // 0: no tenant-layer is given big tiles in this run (small batches)
     uint32_t big_min_tiles; // a layer index uses big tiles only when its qualifying tenants make at least this many
     const TenantDev* tenants;
-    // What the tile lists need to know of every tenant-layer: two words per layer, 64 bytes per
-    // tenant, facts[tenant][layer][2].  Word 0: column groups of the layer's tiles (0: no tiles:
+    // What the tile lists need to know of every tenant-layer: two words, facts[tenant][layer][2].  Word 0: column groups of the layer's tiles (0: no tiles:
     // pooling, or no such layer), bit 31: convolution, bit 30: FC tiles of 32 rows instead of 64.
     // Word 1: GEMM rows per request (convolution) or padded outputs (FC).
     const uint32_t* facts;
