@@ -1212,6 +1212,15 @@ static uint32_t row_slices(uint64_t units, uint32_t per_wg)
 {
     return (uint32_t)std::min<uint64_t>(std::max<uint64_t>((units + per_wg - 1) / per_wg, 1), 64);
 }
+// The same for the image kernels, whose threads take eight units each where there are rows enough to fill the chip
+// with such workgroups, down to one where there are not (the max-pool of one 112x112x64 image on 13 workgroups of 2048
+// chunks took 29.7 us, on 98 of 256 it takes 10.6, part of which is the loads of a window being in flight together).
+static uint32_t image_slices(uint64_t units, uint32_t R)
+{
+    constexpr uint64_t kThreads = 256, kMostPerThread = 8, kFill = 2048, kMost = 256;
+    const uint64_t per_wg = std::min(std::max(units * R / kFill, kThreads) / kThreads, kMostPerThread) * kThreads;
+    return (uint32_t)std::min(std::max<uint64_t>((units + per_wg - 1) / per_wg, 1), kMost);
+}
 
 uint32_t packed_rows_bound(const mt_ctx* c, uint32_t R)
 {
@@ -1394,13 +1403,12 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     const uint32_t P = packed_rows_bound(c, R);
     {
         GatherArgs g{};
-        g.row_src = c->d_row_src; g.P = P; g.tenants = c->d_tenants; g.layers = c->d_layers; g.row_tenant = c->d_row_tenant;
-        g.perm = c->d_perm; g.off = c->d_off; g.T = T; g.act = c->d_act[0]; g.S = c->S; g.elem_size = c->elem_size; g.zeros = c->d_zeros;
+        g.row_src = c->d_row_src; g.P = P; g.tenants = c->d_tenants; g.layers = c->d_layers;
+        g.perm = c->d_perm; g.off = c->d_off; g.M = c->d_M; g.T = T; g.act = c->d_act[0]; g.S = c->S; g.elem_size = c->elem_size; g.zeros = c->d_zeros;
         // workgroups per block of 32 rows: each takes ~64 KiB of it, so that long rows have enough loads in flight
         const uint32_t gs = row_slices((uint64_t)c->max_in_len * c->elem_size * kBrickRows, 65536);      // c5: 146 -> 133 us with four
         if (c->any_fc_first && !fuse_gather) TIMED(kProfGather, launch_gather(g, gs, s));
-        // workgroups per image row: each takes ~2048 pixels (eight per thread), so that a few large images fill the chip too
-        if (c->any_conv_first) TIMED(kProfGatherImg, launch_gather_image(g, row_slices(c->max_image_pixels, 2048), s));
+        if (c->any_conv_first) TIMED(kProfGatherImg, launch_gather_image(g, image_slices(c->max_image_pixels / 2, R), s));       // in pairs of pixels
     }
 
     ActBufs bufs{};                        // every layer names the buffers it reads and writes (LayerDev::in_buf ...)
@@ -1431,17 +1439,17 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
         }
         if (c->has_gap[l]) {
             GapArgs pa{};
-            pa.layer = l; pa.P = P; pa.layers = c->d_layers; pa.tenants = c->d_tenants; pa.row_tenant = c->d_row_tenant;
-            pa.perm = c->d_perm; pa.off = c->d_off; pa.T = T; pa.act = bufs; pa.S = c->S;
+            pa.layer = l; pa.P = P; pa.layers = c->d_layers; pa.tenants = c->d_tenants;
+            pa.off = c->d_off; pa.M = c->d_M; pa.T = T; pa.act = bufs; pa.S = c->S;
             pa.elem_size = c->elem_size;
             TIMED(kProfGap + l, launch_gap(pa, s));
         }
         if (c->has_image_ops[l]) {         // max-pooling and residual additions of this layer index
             GapArgs pa{};
-            pa.layer = l; pa.P = P; pa.layers = c->d_layers; pa.tenants = c->d_tenants; pa.row_tenant = c->d_row_tenant;
-            pa.perm = c->d_perm; pa.off = c->d_off; pa.T = T; pa.act = bufs; pa.S = c->S;
+            pa.layer = l; pa.P = P; pa.layers = c->d_layers; pa.tenants = c->d_tenants;
+            pa.off = c->d_off; pa.M = c->d_M; pa.T = T; pa.act = bufs; pa.S = c->S;
             pa.elem_size = c->elem_size;
-            TIMED(kProfImageOps + l, launch_image_ops(pa, row_slices(c->image_op_fill[l] * c->elem_size / 16, 2048), s));   // eight 16-byte chunks per thread
+            TIMED(kProfImageOps + l, launch_image_ops(pa, image_slices(c->image_op_fill[l] * c->elem_size / 16, R), s));   // in 16-byte chunks
         }
     }
 

@@ -186,8 +186,8 @@ struct ActBufs { void* p[kActBuffers]; };
 
 struct GatherArgs {
     const void* const* row_src; uint32_t P;      // P = upper bound of packed rows (multiple of 32)
-    const TenantDev* tenants; const LayerDev* layers; const int32_t* row_tenant; const int32_t* perm;
-    const uint32_t* off; uint32_t T;
+    const TenantDev* tenants; const LayerDev* layers; const int32_t* perm;
+    const uint32_t* off; const uint32_t* M; uint32_t T;
     void* act; uint32_t S; uint32_t elem_size;
     const void* zeros;     // >= 16 readable zero bytes
 };
@@ -213,7 +213,7 @@ struct GemmArgs {
 
 struct GapArgs {
     uint32_t layer; uint32_t P; const LayerDev* layers; const TenantDev* tenants;
-    const int32_t* row_tenant; const int32_t* perm; const uint32_t* off; uint32_t T;
+    const uint32_t* off; const uint32_t* M; uint32_t T;
     ActBufs act; uint32_t S; uint32_t elem_size;
 };
 

@@ -1,0 +1,59 @@
+"""Edges of the kernels' own tilings and dispatch rules, against the fp64 oracle: counts around powers of two and
+multiples of the wave, channel counts that do not divide a workgroup, images of one pixel."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from gpu_common import compare, gpu_run, make_context, oracle_rows
+from paper_1901_06887_amd import torch_io
+
+pytestmark = pytest.mark.gpu
+
+
+def mlp_fleet(n_tenants, n_requests, dims, dtype="f32", act=wl.ACT_RELU, seed=301, ids=None):
+    tenants = {t: wl.make_model(wl.mlp_layers(list(dims), act), dtype, seed, t) for t in range(n_tenants)}
+    rng = np.random.default_rng(seed)
+    ids = rng.integers(0, n_tenants, n_requests) if ids is None else ids
+    x = rng.standard_normal((n_requests, dims[0])).astype(np.float32)
+    return wl.Workload("mlp", dtype, tenants, ids.astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
+
+
+def check(w, what, ctx=None):
+    ctx = ctx or make_context(w)
+    gpu = gpu_run(ctx, w, poison=True)
+    assert np.array_equal(ctx.last_counts(), np.bincount(w.tenant_ids, minlength=ctx.cfg.max_tenants)), what
+    print("%s: worst per-tensor rel fro %.2e" % (what, compare(w, gpu, oracle_rows(w), what=what)), flush=True)
+    return gpu
+
+
+# tenants: one lane each up to 64, tables in LDS beyond; rows: 1024 is one row per lane of every wave
+@pytest.mark.parametrize("n_tenants", [1, 63, 64, 65, 300])
+@pytest.mark.parametrize("n_requests", [1, 64, 1024, 1025, 4097])
+def test_segmentation_at_the_edges_of_its_register_paths(n_tenants, n_requests):
+    w = mlp_fleet(n_tenants, n_requests, (8, 12, 5), seed=310 + n_tenants)
+    ctx = make_context(w)
+    one = check(w, "%d tenants, %d requests" % (n_tenants, n_requests), ctx)
+    # the same rows as several submissions: same bits
+    x, ids = torch_io.to_device(w.inputs, w.dtype), torch.from_numpy(w.tenant_ids).cuda()
+    out = torch_io.alloc_outputs(n_requests, ctx.cfg.max_classes)
+    cuts = sorted({0, n_requests // 3, n_requests // 2, n_requests})
+    for a, b in zip(cuts[:-1], cuts[1:]):
+        ctx.submit_batch(ids.data_ptr() + 4 * a, x.data_ptr() + a * x.stride(0) * x.element_size(), b - a, x.shape[1])
+    ctx.run(torch.cuda.current_stream().cuda_stream, out.labels.data_ptr(), out.probs.data_ptr(), out.logits.data_ptr(),
+            out.n_classes.data_ptr(), n_requests, ctx.cfg.max_classes)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.logits.cpu().numpy().astype(np.float64), one[0]) and np.array_equal(out.labels.cpu().numpy(), one[2])
+
+
+@pytest.mark.parametrize("hw,channels,dtype", [((1, 1), 8, "f32"), ((9, 13), 72, "f32"), ((9, 13), 72, "bf16"), ((5, 7), 8, "bf16"),
+                                               ((3, 3), 520, "bf16"), ((2, 5), 2056, "f32")])
+def test_average_pooling_of_any_channel_count(hw, channels, dtype):
+    h, w_ = hw
+    layers = [wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, channels, h, w_, 1, ksize=1, pad=0), wl.LayerSpec(wl.GAP, wl.ACT_NONE, channels, channels, h, w_),
+              wl.LayerSpec(wl.FC, wl.ACT_NONE, channels, 7)]
+    tenants = {t: wl.make_model(layers, dtype, 320, t) for t in range(2)}
+    rng = np.random.default_rng(320)
+    x = rng.standard_normal((37, layers[0].in_len())).astype(np.float32)
+    w = wl.Workload("gap", dtype, tenants, rng.integers(0, 2, 37).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
+    check(w, "%dx%dx%d %s" % (h, w_, channels, dtype))
