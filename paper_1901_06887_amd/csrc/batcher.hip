@@ -194,20 +194,20 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
         for (uint32_t it = 0; it < kRegIters; ++it) tq[it] = fetch_id(begin + it * 64 + lane);
     }
     // The tile lists of layer index l (three kinds) belong to wave l % 16, which walks them 64 tenants at a time:
-    // step i of the wave is chunk i % n_chunks of its (i / n_chunks)-th layer index.  A step needs the two fact words
+    // step i of the wave is chunk i % n_chunks of its (i / n_chunks)-th layer index.  A step needs the fact words
     // of its 64 tenant-layers (BatchArgs::facts); the first kPre steps' are fetched here.
     constexpr uint32_t kPre = 4;
     const uint32_t n_chunks = ceil_div(T, 64), n_steps = w < a.n_layer_slots ? ceil_div(a.n_layer_slots - w, kWaves) * n_chunks : 0;
-    auto load_facts = [&](uint32_t l, uint32_t c) -> uint2 {
+    auto load_facts = [&](uint32_t l, uint32_t c) -> uint4 {
         const uint32_t t = c * 64 + lane;
-        return t < T ? ((const uint2*)a.facts)[(size_t)t * MT_MAX_LAYERS + l] : uint2{0, 0};
+        return t < T ? ((const uint4*)a.facts)[(size_t)t * MT_MAX_LAYERS + l] : uint4{0, 0, 0, 0};
     };
     auto next_step = [&](uint32_t& l, uint32_t& c) { if (++c == n_chunks) { c = 0; l += kWaves; } };
-    uint2 fq[kPre];
+    uint4 fq[kPre];
     uint32_t l = w, c = 0;
 #pragma unroll
     for (uint32_t i = 0; i < kPre; ++i) {
-        fq[i] = i < n_steps ? load_facts(l, c) : uint2{0, 0};
+        fq[i] = i < n_steps ? load_facts(l, c) : uint4{0, 0, 0, 0};
         next_step(l, c);
     }
     for (uint32_t t = tid; t < Tp; t += kBatchThreads) regl[t] = t < T && a.tenants[t].registered;
@@ -335,14 +335,14 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
     uint32_t run_fc = 0, run_conv = 0, run_big = 0;            // tiles of the tenants before this chunk
     bool big_here = false;
     auto tenant_rows = [&](uint32_t c) { return one_wave ? Mt1 : (c * 64 + lane < T ? Ml[c * 64 + lane] : 0u); };
-    auto list_step = [&](uint32_t l, uint32_t c, uint2 f) {
+    auto list_step = [&](uint32_t l, uint32_t c, uint4 f) {
         const uint32_t lm = a.list_mask[l / kLayerGroup] >> (l % kLayerGroup);      // bit kind * kLayerGroup: some registered model has such tiles here
         if (c == 0) {
             run_fc = run_conv = run_big = 0; big_here = false;
             if (a.big_enabled && l < (uint32_t)kBigMaxLayer && ((lm >> (2 * kLayerGroup)) & 1)) {
                 uint32_t n = 0;
                 for (uint32_t i = 0; i < n_chunks; ++i) {
-                    const uint2 g = i == 0 ? f : load_facts(l, i);
+                    const uint4 g = i == 0 ? f : load_facts(l, i);
                     const uint32_t Mt = tenant_rows(i);
                     const bool big = g.x && !(g.x >> 31) && fc_is_big(Mt, g.y);
                     n += __builtin_amdgcn_readlane(wave_inclusive_scan(big ? ceil_div(big_rows(Mt), kBigTile) * ceil_div(g.y, kBigTile) : 0), 63);
@@ -353,7 +353,8 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
         }
         const uint32_t t = c * 64 + lane, Mt = tenant_rows(c);
         const bool conv = f.x >> 31, sk = a.fc_split_k && !conv && f.x;                // this run's FC tiles: one column block each, 32 rows
-        const uint32_t groups = sk ? f.y / kBrickRows : f.x & 0x3fffffffu;
+        const bool split = (a.conv_split[l / 32] >> (l % 32)) & 1;      // this run's convolution tiles: 32 pixels, one channel block
+        const uint32_t groups = sk ? f.y / kBrickRows : conv ? ceil_div(f.x & 0x7fffffffu, split ? 1 : kTileCols / kBrickRows) : f.x & 0x3fffffffu;
         const bool big = big_here && !conv && f.x && fc_is_big(Mt, f.y);
         // conv: rows = requests * output pixels per tile; FC: tiles of 64 or 32 rows over the rows that big tiles leave
         // (the few rows that big tiles leave in a narrow layer are tiled one column block and 32 rows at a time,
@@ -371,7 +372,7 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
             if (c + 1 == n_chunks && lane == 0) base[T] = run;
         };
         emit(0, !conv && groups && Mt ? ((Mt - Mb + (1u << sh) - 1) >> sh) * gq : 0, run_fc);
-        emit(1, conv && Mt ? ceil_div(Mt * f.y, kConvTileRows) * groups : 0, run_conv);
+        emit(1, conv && Mt ? (split ? ceil_div(Mt * f.z, kBrickRows) : ceil_div(Mt * f.y, kConvTileRows)) * groups : 0, run_conv);
         emit(2, ceil_div(Mb, kBigTile) * ceil_div(f.y, kBigTile), run_big);
     };
     l = w; c = 0;

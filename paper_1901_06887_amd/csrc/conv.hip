@@ -25,17 +25,18 @@ struct TapWalk {
     uint32_t lin, th, run, lo, hi, tlo, thi, step;
     int32_t cur, jump;
     // (ih0, iw0): the input coordinate of the window's top-left tap (may lie outside the image);
-    // first: the lane's first element inside the run; step_el: elements per call of next()
+    // first: the lane's first element in K; step_el: elements per call of next()
     // (at most two runs end per call: step_el <= 2 * k * cin, which holds for every window and
     // channel count the layer set admits: a run is at least 8 elements, a step at most 32, and
     // steps of 32 are only taken where cin is a multiple of 32)
     __device__ __forceinline__ void init(const LayerDev& L, int32_t ih0, int32_t iw0, bool row_ok, uint32_t first, uint32_t step_el)
     {
         const int32_t cin = (int32_t)L.cin, k = (int32_t)L.ksize;
-        run = L.ksize * L.cin; lin = first; th = 0; step = step_el;
+        run = L.ksize * L.cin; th = 0; lin = first; step = step_el;
+        if (first >= 2 * run) { th = first / run; lin = first - th * run; }
         lo = (uint32_t)max(0, -iw0) * L.cin; hi = (uint32_t)max(0, min(k, (int32_t)L.in_w - iw0)) * L.cin;
         tlo = (uint32_t)max(0, -ih0); thi = row_ok ? (uint32_t)max(0, min(k, (int32_t)L.in_h - ih0)) : 0;
-        cur = (ih0 * (int32_t)L.in_w + iw0) * cin + (int32_t)lin;
+        cur = ((ih0 + (int32_t)th) * (int32_t)L.in_w + iw0) * cin + (int32_t)lin;
         jump = ((int32_t)L.in_w - k) * cin;
         wrap(); wrap();                                            // a first element past the first run (1x1 windows of 8 channels)
     }
@@ -793,7 +794,112 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     }
 }
 
+// ---- convolution launches of few tiles: K split among the waves of a tile -------------------------
+// A launch that leaves most of the chip idle lasts as long as one wave's walk through K: 0.1-0.2 us per k step with
+// a single wave per SIMD (one image of 7x7x512: 288 steps, 27 us).  Such launches take tiles of 32 pixels and one channel
+// block whose WAVES waves each walk a share of K, gathering their pixels and streaming their filter bricks straight into
+// registers as conv_kernel does: many times the workgroups, a fraction of the walk, and other waves on the SIMD while
+// one waits.  A pixel's 16-byte pieces cost the texture path 64 clocks per brick however they are used, here for a single
+// MFMA, so the tiles are five to six times as expensive as those of the other kernels once the chip is full: the launcher
+// takes them up to a number of tiles only.  The partial sums meet in LDS and are added in wave order by four
+// waves, each lane of which then holds four consecutive channels of a pixel.
+// One request to a 26-layer residual net on a 224x224 image, kernel trace: 56x56x64 10.0-11.2 -> 6.4 us, 28x28x128
+// 16.8-19.2 -> 8.8, 14x14x256 24.7 -> 11, 7x7x512 27.3 -> 13.9, the stride-2 layers 12.2 / 18.2 / 23.2 -> 6.3 / 8.5 / 10.3, the
+// 1x1 projections 11-12 -> 4.6.  (Tiles of 128 pixels with their input in LDS frames and sixteen waves were slower up to
+// 144 k steps, 10-12 us each, and 12 us at 288: eight barriers, the frame's zeroing and one workgroup per CU.)
+template <typename T, uint32_t WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 16 ? 4 : 6, WAVES == 16 ? 4 : 6))) void conv_split_kernel(GemmArgs a)
+{
+    constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC, P = 4, THREADS = 64 * WAVES;
+    typedef const __attribute__((address_space(1))) u32x4* gptr_t;
+    __shared__ __attribute__((aligned(16))) uint8_t red[WAVES * 4096];
+    __shared__ uint32_t owner_part[WAVES];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
+    TileOwner<THREADS> lookup;
+    lookup.fetch(a.tile_base, a.T);
+    const uint32_t n_tiles = a.tile_base[a.T];
+    uint32_t idx;
+    if (!logical_tile(n_tiles, &idx)) return;
+    const uint32_t t = lookup.owner(a.T, idx, owner_part);   // uniform: the tenant's facts come through scalar loads
+    const LayerDev L = a.layers[t * MT_MAX_LAYERS + a.layer];
+    const uint32_t seg0 = a.off[t], Mt = a.M[t];
+    const uint32_t local = idx - a.tile_base[t];
+    const uint32_t rpr = L.rows_per_req, rows_total = Mt * rpr;
+    const uint32_t mt_ = ceil_div(rows_total, kBrickRows), nb = local / mt_, m0 = (local - nb * mt_) * kBrickRows;
+    const uint32_t nKB = L.K / KB, nKBv = ceil_div(L.k_valid, KB);
+    const uint32_t k0 = wave * nKBv / WAVES, cnt = (wave + 1) * nKBv / WAVES - k0;     // this wave's k steps (none where K is short)
+
+    const uint32_t m = m0 + li;
+    const bool row_ok = m < rows_total;
+    uint32_t req, pix, oh, ow;
+    divmod_uniform(row_ok ? m : m0, rpr, &req, &pix);              // rows past the end repeat the first one and are dropped
+    divmod_uniform(pix, L.out_w, &oh, &ow);
+    const size_t at = (size_t)(seg0 + req) * a.S;
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    if (cnt) {
+        gptr_t wp = (gptr_t)((const u32x4*)(a.arena + L.w_off) + ((size_t)nb * nKB + k0) * 64 + lane);
+        gptr_t src = (gptr_t)((const T*)act_of(a.act, L.in_buf) + at), zeros = (gptr_t)a.zeros;
+        TapWalk<T> walk;
+        walk.init(L, (int32_t)(oh * L.stride) - (int32_t)L.pad, (int32_t)(ow * L.stride) - (int32_t)L.pad, row_ok, k0 * KB + lh * EPC, KB);
+        auto load_a = [&]() -> u32x4 {
+            const int32_t chunk = walk.next();
+            gptr_t p = chunk >= 0 ? src + chunk : zeros;
+            return *p;
+        };
+        u32x4 aq[P], wq[P];
+#pragma unroll
+        for (uint32_t j = 0; j < P; ++j) { wq[j] = wp[(size_t)min(j, cnt - 1) * 64]; aq[j] = load_a(); }
+        uint32_t s = 0;
+        for (; s + P <= cnt; s += P) {
+#pragma unroll
+            for (uint32_t j = 0; j < P; ++j) {
+                Mma<T>::run(acc, wq[j], aq[j]);                    // rows = channels, columns = pixels
+                aq[j] = load_a();
+                wq[j] = wp[(size_t)min(s + j + P, cnt - 1) * 64];
+                __builtin_amdgcn_sched_barrier(0);                 // keeps the refills here, P steps ahead of their use
+            }
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < P; ++j)
+            if (s + j < cnt) Mma<T>::run(acc, wq[j], aq[j]);
+    }
+
+    // thread (g = wave, lane) of the first four waves: channels 8g + 4 lh + {0..3} of pixel li
+    const uint32_t g = wave & 3, nbase = nb * kBrickRows, ch0 = 8 * g + 4 * lh;
+    const f32x4 bias = *(const f32x4*)((const float*)(a.arena + L.b_off) + nbase + ch0);   // bias is padded to N_pad
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q)
+        *(f32x4*)(red + wave * 4096 + q * 1024 + lane * 16) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    __syncthreads();
+    if (wave >= 4 || !row_ok || ch0 >= L.N - nbase) return;        // channel counts are multiples of 8: a run of four exists whole or not at all
+    f32x4 y[1] = {bias};
+#pragma unroll
+    for (uint32_t w = 0; w < WAVES; ++w) y[0] += *(const f32x4*)(red + w * 4096 + g * 1024 + lane * 16);
+    const size_t to = at + (size_t)pix * L.N + nbase + ch0;
+    activate_block<1>(y, L.act);
+    if (L.fuse_add) {                                              // see add_residual: rounded first, as the addition would have read it
+        T sv[4];
+        const T* skip = (const T*)act_of(a.act, L.in2_buf) + to;
+        if constexpr (sizeof(T) == 2) *(uint64_t*)sv = *(const uint64_t*)skip; else *(u32x4*)sv = *(const u32x4*)skip;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[0][e] = (float)(T)y[0][e] + (float)sv[e];
+        activate_block<1>(y, L.fuse_add - 1);
+    }
+    T o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (T)y[0][e];
+    T* out = (T*)act_of(a.act, L.out_buf) + to;
+    if constexpr (sizeof(T) == 2) *(uint64_t*)out = __builtin_bit_cast(uint64_t, o); else *(u32x4*)out = __builtin_bit_cast(u32x4, o);
+}
+
 // ---- launcher ------------------------------------------------------------
+// Waves of a tile that splits K: a wave should have a few steps to itself (a 7x7x8 window is 25 steps: 784 tiles of 16 waves,
+// one workgroup per CU, took 14.6 us, of 8 waves 8.5), a long walk is worth all 16 (1x1 over 64 channels: 4.9 us with
+// 16 waves, 4.6 with 4).
+constexpr uint32_t kSplitFewSteps = 24, kSplitSomeSteps = 64;
+
 template <typename T, bool FAST>
 static void launch_conv_lds_t(const GemmArgs& a, uint32_t max_cb, bool quad, bool loaders, uint32_t grid, hipStream_t s)
 {
@@ -846,6 +952,23 @@ static hipError_t prepare_conv_t()
     return e;
 }
 hipError_t prepare_conv(uint32_t dtype) { return dtype == MT_BF16 ? prepare_conv_t<__bf16>() : prepare_conv_t<float>(); }
+
+template <typename T>
+static void launch_conv_split_t(const GemmArgs& a, uint32_t k_steps, uint32_t grid, hipStream_t s)
+{
+    if (k_steps <= kSplitFewSteps) hipLaunchKernelGGL((conv_split_kernel<T, 4>), dim3(grid), dim3(256), 0, s, a);
+    else if (k_steps <= kSplitSomeSteps) hipLaunchKernelGGL((conv_split_kernel<T, 8>), dim3(grid), dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((conv_split_kernel<T, 16>), dim3(grid), dim3(1024), 0, s, a);
+}
+
+// k_steps: the longest reduction of the layer index in bricks
+hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, uint32_t grid, hipStream_t s)
+{
+    if (grid == 0) return hipSuccess;
+    grid = (grid + 7) / 8 * 8;
+    if (dtype == MT_BF16) launch_conv_split_t<__bf16>(a, k_steps, grid, s); else launch_conv_split_t<float>(a, k_steps, grid, s);
+    return hipGetLastError();
+}
 
 // img_lds_bytes > 0: every convolution of the layer index qualifies for the LDS-resident-input kernel, whose largest frame is that
 // size; img_two: their pixels are one 16-byte chunk (else none is)

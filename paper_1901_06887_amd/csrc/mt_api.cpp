@@ -29,6 +29,12 @@ constexpr uint32_t kMaxTenants = 2048;
 constexpr uint32_t kSegSlots = MT_SEG_SLOTS;   // pinned segment tables: runs of several submissions in flight at once
 constexpr uint32_t kMaxRunSlots = 4;      // runs in flight at once (each with its own device scratch); <= kSegSlots
 constexpr uint64_t kArenaAlign = 256;
+// Convolution launches of at most so many tiles of 32 pixels and one channel block (as the host expects them) take such
+// tiles, K split among their waves.  Passes with the line at 0 / 256 / 512 / 768 / 1024 tiles: 26-layer residual nets on
+// 224x224 images, one request 403 / 210 / 212 / 210 / 207 us, 4 requests 431 / 300 / 276 / 276 / 283, 8 requests 446 / 375 /
+// 348 / 346 / 364, 16 requests 491 / 491 / 456 / 459 / 488, 32 requests 549 / 546 / 546 / 546 / 613 (the deep layers' launches
+// of 112 tiles of 128x128 against 1600 of 32x32); MLPs, CNNs and small residual nets side by side 401 / 229 / 224 / 223 / 223.
+constexpr uint32_t kConvSplitTiles = 768;
 // profiling slots: batcher, gather, head, then gemm and gap of every layer index
 constexpr uint32_t kProfBatcher = 0, kProfGather = 1, kProfHead = 2, kProfFc = 3, kProfConv = 3 + MT_MAX_LAYERS,
                    kProfGap = 3 + 2 * MT_MAX_LAYERS, kProfBig = 3 + 3 * MT_MAX_LAYERS, kProfGatherImg = 3 + 4 * MT_MAX_LAYERS,
@@ -128,6 +134,12 @@ struct mt_ctx {
     uint32_t min_fc_k[MT_MAX_LAYERS]{};        // shortest padded fan-in among the registered FC layers of a layer index
     uint32_t no_conv_uniform = 0;  // tuning/testing: convolution gathers always walk the window lane by lane
     uint32_t no_conv_loaders = 0;  // tuning/testing: convolution tiles never get waves of their own for the loads
+    uint32_t max_conv_blocks[MT_MAX_LAYERS]{};  // widest convolution of a layer index over the registered models, in blocks of 32 channels
+    uint32_t max_conv_rows[MT_MAX_LAYERS]{};    // most output pixels of a convolution of the layer index
+    uint64_t sum_conv_work[MT_MAX_LAYERS]{};    // sum over the registered models of output pixels x channel blocks
+    uint64_t sum_conv_blocks[MT_MAX_LAYERS]{};  // ... and their sum
+    uint32_t max_conv_k[MT_MAX_LAYERS]{};      // longest reduction among the registered convolutions of a layer index
+    uint32_t conv_split_tiles = kConvSplitTiles;   // testing: MT_CONV_SPLIT_TILES (0: no convolution launch splits K)
     uint32_t min_conv_k[MT_MAX_LAYERS]{};      // shortest reduction among the registered convolutions of a layer index
     uint32_t big_min_tiles = kBigMinTiles;   // testing: MT_BIG_MIN_TILES=1 sends every qualifying tenant-layer to big tiles
     uint32_t P_cap = 0;        // packed rows incl. per-tenant padding to 32
@@ -141,7 +153,7 @@ struct mt_ctx {
     TenantDev* d_tenants = nullptr;
     LayerDev* d_layers = nullptr;
     uint64_t* d_served = nullptr;      // [max_tenants][2]: requests served, runs with at least one request (accounting)
-    uint32_t* d_facts = nullptr;       // [max_tenants][MT_MAX_LAYERS][2]: the batcher's view of the layers (BatchArgs::facts)
+    uint32_t* d_facts = nullptr;       // [max_tenants][MT_MAX_LAYERS][kFactWords]: the batcher's view of the layers (BatchArgs::facts)
     int32_t* d_row_tenant = nullptr;
     uint32_t* d_row_rank = nullptr;
     uint32_t* d_hist_g = nullptr;      // [kHistEntries] per-workgroup tenant histograms of the ranking kernel
@@ -288,18 +300,19 @@ uint32_t choose_row_tiling(const LayerDev& L, uint32_t es)
     return 0;
 }
 
-// The batcher's two words per layer of one tenant (see BatchArgs::facts).
-void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[2])
+// The batcher's words per layer of one tenant (see BatchArgs::facts).
+void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[kFactWords])
 {
-    for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) w[l][0] = w[l][1] = 0;
+    for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) for (uint32_t i = 0; i < (uint32_t)kFactWords; ++i) w[l][i] = 0;
     for (uint32_t l = 0; l < ht.n_layers; ++l) {
         const LayerDev& L = ht.layers[l].dev;
         if (L.kind == MT_FC) {
             w[l][0] = fc_groups(L.N_pad, c->fc_split_k) | (fc_tile_rows(L.N_pad, c->fc_split_k) == kTileRows ? 0u : 1u << 30);
             w[l][1] = L.N_pad;
         } else if (L.kind == MT_CONV2D) {
-            w[l][0] = (L.N + kTileCols - 1) / kTileCols | 1u << 31;
+            w[l][0] = L.N_pad / kBrickRows | 1u << 31;
             w[l][1] = conv_tile_rows(L.rows_per_req, L.row_tiles);
+            w[l][2] = L.rows_per_req;
         }
     }
 }
@@ -309,7 +322,7 @@ void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[2])
 struct StageTail {
     LayerDev rows[MT_MAX_LAYERS];
     TenantDev td;
-    uint32_t facts[MT_MAX_LAYERS][2];
+    uint32_t facts[MT_MAX_LAYERS][kFactWords];
 };
 size_t stage_tail_offset(uint64_t arena_len) { return (size_t)round_up64(arena_len, 256); }
 size_t stage_bytes(uint64_t arena_len) { return stage_tail_offset(arena_len) + sizeof(StageTail); }
@@ -322,7 +335,7 @@ size_t stage_bytes(uint64_t arena_len) { return stage_tail_offset(arena_len) + s
 // last piece, after a fence: a tenant that the batcher sees has its layer rows in place.
 struct RowsPiece {
     LayerDev rows[kLayerGroup];
-    uint32_t facts[kLayerGroup][2];
+    uint32_t facts[kLayerGroup][kFactWords];
     TenantDev td;
 };
 static_assert(sizeof(RowsPiece) <= 2048, "a piece of a tenant's table rows must fit kernel arguments");
@@ -367,7 +380,7 @@ hipError_t install_rows(mt_ctx* c, uint32_t tenant, const StageTail& tail, hipSt
         piece.td = tail.td;
         const bool with_td = tail.td.registered ? g + 1 == n_pieces : g == 0;
         hipLaunchKernelGGL(install_rows_kernel, dim3(1), dim3(256), 0, s, piece, c->d_layers + (size_t)tenant * MT_MAX_LAYERS + g * kLayerGroup,
-                           c->d_facts + ((size_t)tenant * MT_MAX_LAYERS + g * kLayerGroup) * 2, with_td ? c->d_tenants + tenant : nullptr);
+                           c->d_facts + ((size_t)tenant * MT_MAX_LAYERS + g * kLayerGroup) * kFactWords, with_td ? c->d_tenants + tenant : nullptr);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -441,7 +454,7 @@ void recompute_bounds(mt_ctx* c)
     for (uint32_t& m : c->list_mask) m = 0;
     c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
-        c->has_gap[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->min_fc_k[l] = 0xffffffffu; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
+        c->has_gap[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
         for (int k = 0; k < kListKinds; ++k) { c->max_rpr[k][l] = c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
         c->max_fc_per64[l] = 0; c->max_fc_per64_sk[l] = 0; c->sum_nt_sk[l] = 0; c->max_big_blocks[l] = 0;
     }
@@ -479,6 +492,11 @@ void recompute_bounds(mt_ctx* c)
             }
             if (k == 1) {
                 c->min_conv_k[l] = std::min(c->min_conv_k[l], L.k_valid);
+                c->max_conv_rows[l] = std::max(c->max_conv_rows[l], L.rows_per_req);
+                c->max_conv_k[l] = std::max(c->max_conv_k[l], L.k_valid);
+                c->max_conv_blocks[l] = std::max(c->max_conv_blocks[l], L.N_pad / kBrickRows);
+                c->sum_conv_work[l] += (uint64_t)L.rows_per_req * (L.N_pad / kBrickRows);
+                c->sum_conv_blocks[l] += L.N_pad / kBrickRows;
                 c->max_conv_cb[l] = std::max(c->max_conv_cb[l], std::min<uint32_t>(L.N_pad / kBrickRows, kTileCols / kBrickRows));
                 if (L.cin % (4 * (16 / c->elem_size))) c->conv_quad[l] = false;
                 if (L.cin % (2 * (16 / c->elem_size)) || L.ksize * L.ksize > 64) c->conv_uniform[l] = false;
@@ -531,6 +549,29 @@ bool run_split_k(const mt_ctx* c, uint64_t R)
     for (uint32_t l = 0; l < c->n_layer_slots; ++l)
         most = std::max(most, ((uint64_t)c->max_fc_per64[l] * R + kTileRows - 1) / kTileRows + active * c->max_nt[0][l]);
     return most > 0 && most <= kSplitKMaxTiles;
+}
+
+// How the convolutions of a layer index are launched in a run of R rows.
+struct ConvPlan {
+    bool frames;        // tiles read their input from LDS frames
+    bool split;         // tiles of 32 pixels and one channel block whose waves split K
+    uint64_t tiles;     // upper bound of the launch's tiles
+};
+ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R)
+{
+    ConvPlan p{};
+    p.frames = c->conv_img_lds[l] > 1 && !c->pool_fused[l] && !c->no_conv_img;
+    p.tiles = tile_bound(c, 1, l, R);
+    if (c->max_nt[1][l] == 0 || c->pool_fused[l]) return p;
+    // the launch's tiles of that shape if the requests spread evenly over the registered models (the host does not know
+    // which tenants a device-resident id array names), each of min(R, registered) tenants with a ragged one per channel block
+    const uint64_t active = std::min<uint64_t>(R, c->n_registered);
+    const uint64_t expected = R * c->sum_conv_work[l] / c->n_registered / kBrickRows + active * c->sum_conv_blocks[l] / c->n_registered / 2;
+    if (expected > c->conv_split_tiles) return p;
+    // sum over tenants of ceil(M_t rows_t / 32) * blocks_t <= max blocks * R * max rows / 32 + the ragged tiles of those with requests
+    p.split = true; p.frames = false;
+    p.tiles = c->max_conv_blocks[l] * (R * c->max_conv_rows[l] / kBrickRows) + std::min<uint64_t>(c->sum_conv_blocks[l], active * c->max_conv_blocks[l]);
+    return p;
 }
 
 // Most classes a last layer may have for its FC tiles to finish their rows themselves (softmax,
@@ -852,6 +893,7 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
     if (const char* e = getenv("MT_NO_FUSED_POOL")) c->no_fused_pool = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_IMG")) c->no_conv_img = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_FUSED_ADD")) c->no_fused_add = atoi(e) != 0;
+    if (const char* e = getenv("MT_CONV_SPLIT_TILES")) c->conv_split_tiles = (uint32_t)std::max(0, atoi(e));
     if (const char* e = getenv("MT_BIG_WALK")) c->big_walk = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_LOADERS")) c->no_conv_loaders = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_UNIFORM")) c->no_conv_uniform = atoi(e) != 0;
@@ -878,8 +920,8 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
     CREATE_TRY(hipMemset(c->d_tenants, 0, T * sizeof(TenantDev)));
     CREATE_TRY(hipMalloc((void**)&c->d_layers, T * MT_MAX_LAYERS * sizeof(LayerDev)));
     CREATE_TRY(hipMemset(c->d_layers, 0, T * MT_MAX_LAYERS * sizeof(LayerDev)));
-    CREATE_TRY(hipMalloc((void**)&c->d_facts, 2 * MT_MAX_LAYERS * T * 4));
-    CREATE_TRY(hipMemset(c->d_facts, 0, 2 * MT_MAX_LAYERS * T * 4));
+    CREATE_TRY(hipMalloc((void**)&c->d_facts, kFactWords * MT_MAX_LAYERS * T * 4));
+    CREATE_TRY(hipMemset(c->d_facts, 0, kFactWords * MT_MAX_LAYERS * T * 4));
     CREATE_TRY(hipMalloc((void**)&c->d_served, T * 16));
     CREATE_TRY(hipMemset(c->d_served, 0, T * 16));
     CREATE_TRY(hipMalloc(&c->d_zeros, 256));
@@ -1360,6 +1402,9 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     for (uint32_t g = 0; g < MT_MAX_LAYERS / kLayerGroup; ++g)
         b.list_mask[g] = big_enabled ? c->list_mask[g] : c->list_mask[g] & ((1u << (2 * kLayerGroup)) - 1);   // no big-tile lists to build
     b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles;
+    for (uint32_t l = 0; l < c->n_layer_slots; ++l) {
+        if (plan_conv(c, l, R).split) b.conv_split[l / 32] |= 1u << l % 32;
+    }
     const OutPtrs outp{out->labels, out->probs, out->logits, out->n_classes, out->row_stride};
     b.out = outp;
     // A last layer of at most 32 classes is one column block: its FC tiles finish their rows
@@ -1418,7 +1463,8 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
         // pooled activation is where the pooling layer would have written it
         if (l > 0 && c->pool_fused[l - 1]) continue;
         for (int kind = 0; kind < kListKinds; ++kind) {
-            const uint64_t grid = tile_bound(c, kind, l, R, split_k, big_enabled);
+            const ConvPlan conv = kind == 1 ? plan_conv(c, l, R) : ConvPlan{};
+            const uint64_t grid = kind == 1 ? conv.tiles : tile_bound(c, kind, l, R, split_k, big_enabled);
             if (grid == 0 || (kind == 2 && (!big_enabled || grid < c->big_min_tiles))) continue;   // no big tiles possible: the batcher made none
             GemmArgs ga{};
             ga.tile_base = c->d_tile_base + ((size_t)kind * MT_MAX_LAYERS + l) * (T + 1);
@@ -1431,8 +1477,9 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
                 return fail(c, MT_EUNSUPPORTED, "layer %u: %llu tiles exceed one launch", l, (unsigned long long)grid);
             const uint32_t g32 = (uint32_t)grid;
             if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, g32, s));
+            else if (conv.split) TIMED(kProfConv + l, launch_conv_split(ga, c->cfg.dtype, (c->max_conv_k[l] * c->elem_size + 31) / 32, g32, s));
             else if (kind == 1) TIMED(kProfConv + l, launch_conv(ga, c->cfg.dtype, c->max_conv_cb[l], c->conv_quad[l],
-                                                                    (c->conv_img_lds[l] > 1 && !c->pool_fused[l] && !c->no_conv_img) ? c->conv_img_lds[l] : 0, c->conv_img_two[l] == 1,
+                                                                    conv.frames ? c->conv_img_lds[l] : 0, c->conv_img_two[l] == 1,
                                                                     !c->no_conv_loaders && c->min_conv_k[l] >= kConvLongK,
                                                                     c->conv_uniform[l] && !c->no_conv_uniform && (uint64_t)c->cfg.max_requests * c->S * c->elem_size < (1ull << 31), g32, s));
             else TIMED(kProfBig + l, launch_fc_big(ga, c->cfg.dtype, g32, (c->big_walk && c->min_fc_k[l] >= kBigWalkMinK) ? c->n_cus : 0, s));
@@ -1540,6 +1587,7 @@ constexpr double kUsPerMbL2 = 0.056, kUsFcChainFixed = 4.0, kUsPerKStep = 0.12;
 constexpr double kUsBigFixed = 4.0, kUsBigTileFixed = 7.0, kUsBigTilePer4096 = 116.0;
 constexpr double kUsConvFixed = 5.0, kConvMbPerUs = 4.0, kConvMflopPerUs = 0.5e3;      // 4.0 TB/s, 0.5 PFLOP/s
 constexpr double kUsConvFramePerKStep = 0.13, kConvFrameMflopPerUs = 0.6e3;   // the same for layer indices served from LDS frames: filter bricks are the only loads in the K loop
+constexpr double kUsConvSplitFixed = 1.0, kUsConvSplitPerKStep = 0.034;     // launches whose tiles split K among their waves: per k-step of a tile, one tile per compute unit at a time
 constexpr double kUsConvPerKStep = 0.21;     // a convolution tile's walk through K, per k-step of 32 bytes per pixel: a launch lasts at least as long as its longest tile
 constexpr double kUsSmallFixed = 3.0, kCopyMbPerUs = 3.7, kHeadMbPerUs = 5.7, kUsHeadPerRow = 0.0008;
 constexpr double kComputeUnits = 256.0;
@@ -1637,7 +1685,9 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
         const bool big_layer = big_tiles >= c->big_min_tiles;
         double w_mb = 0.0, l2_mb = 0.0, chain = 0.0, big_us = 0.0, conv_mb = 0.0, conv_mflop = 0.0, gap_mb = 0.0, ops_mb = 0.0;
         double big_rounds_k = 0.0, conv_chain = 0.0;
-        const bool conv_frames = c->conv_img_lds[l] > 1 && !c->pool_fused[l] && !c->no_conv_img;     // the launch decision of run_impl
+        const ConvPlan conv_plan = plan_conv(c, l, R);                                               // the launch decision of run_impl
+        const bool conv_frames = conv_plan.frames;
+        double split_steps = 0.0, split_longest = 0.0;
         for (uint32_t t = 0; t < T; ++t) {
             if (!counts[t] || l >= c->tenants[t].n_layers) continue;
             const LayerDev& d = c->tenants[t].layers[l].dev;
@@ -1661,6 +1711,9 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
                 const double out_elems = (c->pool_fused[l] ? d.N : d.out_len) + (d.fuse_add ? d.out_len : 0);      // pooled on the way out; the other operand of an addition done here
                 conv_mb += (M * ((double)d.in_h * d.in_w * d.cin + out_elems) * es + (double)d.N_pad * d.K * es) / MB;
                 conv_mflop += 2.0 * M * d.rows_per_req * d.k_valid * d.N / 1e6;
+                const double k_steps = std::ceil(d.k_valid * es / 32.0);
+                split_longest = std::max(split_longest, k_steps);
+                split_steps += std::ceil(M * d.rows_per_req / kBrickRows) * (d.N_pad / kBrickRows) * k_steps;
                 conv_chain = std::max(conv_chain, (conv_frames ? kUsConvFramePerKStep : kUsConvPerKStep) * d.k_valid * es / 32.0);
             } else if (d.kind == MT_GAP) {
                 gap_mb += M * ((double)d.in_h * d.in_w * d.cin + d.out_len) * es / MB;
@@ -1669,7 +1722,8 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
             }
         }
         if (c->max_nt[0][l] > 0) launch(std::max(chain, kUsFcFixed + us_per_mb * w_mb + kUsPerMbL2 * l2_mb));
-        if (c->max_nt[1][l] > 0) launch(kUsConvFixed + std::max(conv_chain, std::max(conv_mb / kConvMbPerUs, conv_mflop / (conv_frames ? kConvFrameMflopPerUs : kConvMflopPerUs))));
+        if (conv_plan.split) launch(kUsConvSplitFixed + kUsConvSplitPerKStep * std::max(split_longest, split_steps / kComputeUnits));
+        else if (c->max_nt[1][l] > 0) launch(kUsConvFixed + std::max(conv_chain, std::max(conv_mb / kConvMbPerUs, conv_mflop / (conv_frames ? kConvFrameMflopPerUs : kConvMflopPerUs))));
         if (big_enabled && c->max_nt[2][l] > 0 && tile_bound(c, 2, l, R) >= c->big_min_tiles) {
             // tiles share the chip in rounds of one per compute unit; a tile's time grows with K
             if (big_layer) big_us = std::ceil(big_tiles / kComputeUnits) * kUsBigTileFixed + big_rounds_k / kComputeUnits / 4096.0 * kUsBigTilePer4096;

@@ -55,6 +55,7 @@ constexpr int kRankRows = 1024;     // rows per workgroup of the ranking kernel
 constexpr int kRankMinRows = 8192;  // smaller batches are ranked by the batcher's single workgroup (one launch less)
 constexpr int kRankMaxTenants = 512;
 constexpr int kHistEntries = 8192;  // histogram words the batcher holds in LDS (waves or ranking workgroups x padded tenants)
+constexpr int kFactWords = 4;       // words per tenant-layer that the batcher builds the tile lists from (one 16-byte load)
 constexpr int kListKinds = 3;       // tile lists per layer index: FC (streaming), conv, FC (big tiles)
 constexpr int kActBuffers = 4;      // most activation buffers of a run: layer outputs that may be alive at once
 constexpr int kLayerGroup = 8;      // a tenant's table rows are installed this many layers per launch; layer indices per word of BatchArgs::list_mask
@@ -154,12 +155,14 @@ struct BatchArgs {
     Segment first;         // copy of segs[0]: the common one-segment run never reads host memory
     uint32_t elem_size;
     uint32_t fc_split_k;   // 1: FC tiles take one column block each and split K four ways
+    uint32_t conv_split[(MT_MAX_LAYERS + 31) / 32];   // layer indices (bit l % 32 of word l / 32) whose convolution launch takes tiles of 32 pixels and one channel block
     uint32_t big_enabled;  // 0: no tenant-layer is given big tiles in this run (small batches)
     uint32_t big_min_tiles; // a layer index uses big tiles only when its qualifying tenants make at least this many
     const TenantDev* tenants;
-    // What the tile lists need to know of every tenant-layer: two words, facts[tenant][layer][2].  Word 0: column groups of the layer's tiles (0: no tiles:
-    // pooling, or no such layer), bit 31: convolution, bit 30: FC tiles of 32 rows instead of 64.
-    // Word 1: GEMM rows per request (convolution) or padded outputs (FC).
+    // What the tile lists need to know of every tenant-layer: facts[tenant][layer][kFactWords].
+    // Word 0, FC: column groups of the layer's tiles, bit 30: tiles of 32 rows instead of 64; convolution: bit 31 and the
+    // channel blocks of 32 (a tile takes four of them, or one where the launch splits K); 0: no tiles (pooling, or no such layer).
+    // Word 1: padded outputs (FC), rows per request by which the tiles are counted (convolution: conv_tile_rows).  Word 2: a convolution's output pixels.
     const uint32_t* facts;
     unsigned long long* served;   // [T][2]: requests served and runs with requests, per tenant, over all runs (atomic adds: runs may overlap)
     int32_t* row_tenant;   // [R] tenant of each submitted row, -1 if rejected
@@ -237,6 +240,7 @@ hipError_t prepare_conv(uint32_t dtype);   // once per device, before the first 
 // max_cb: the widest tile of this layer index over the registered tenants, in 32-channel blocks (1..4)
 // quad: every tenant's input channels at this layer index are a multiple of four 16-byte chunks
 hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s);
+hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, uint32_t grid, hipStream_t s);
 hipError_t launch_gap(const GapArgs& a, hipStream_t s);
 hipError_t launch_image_ops(const GapArgs& a, uint32_t slices, hipStream_t s);   // max-pool and residual add of one layer index
 hipError_t launch_head(const HeadArgs& a, hipStream_t s);

@@ -57,3 +57,28 @@ def test_average_pooling_of_any_channel_count(hw, channels, dtype):
     x = rng.standard_normal((37, layers[0].in_len())).astype(np.float32)
     w = wl.Workload("gap", dtype, tenants, rng.integers(0, 2, 37).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
     check(w, "%dx%dx%d %s" % (h, w_, channels, dtype))
+
+
+# launches whose tiles split K: every window and stride, reductions from one brick to many (4, 8 and 16 waves), channel blocks
+# with 8 of 32 channels, pixel tiles with a single pixel; against the oracle, and against the launches that do not split K
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("k,stride,ci,co,hw", [(1, 1, 8, 8, (1, 1)), (1, 2, 16, 40, (5, 7)), (3, 1, 8, 72, (11, 3)), (3, 2, 24, 32, (9, 6)), (3, 1, 64, 96, (4, 8)),
+                                               (3, 1, 200, 128, (7, 7)), (7, 2, 8, 64, (17, 13)), (7, 1, 40, 8, (6, 6))])
+def test_convolutions_that_split_their_reduction(monkeypatch, dtype, k, stride, ci, co, hw):
+    h, w_ = hw
+    first = wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, ci, h, w_, 1, ksize=3, pad=1)
+    mid = wl.LayerSpec(wl.CONV, wl.ACT_GELU, ci, co, h, w_, stride, ksize=k, pad=(k - 1) // 2)
+    oh, ow = mid.out_hw()
+    skip = [wl.LayerSpec(wl.CONV, wl.ACT_NONE, co, co, oh, ow, 1, ksize=1, pad=0), wl.LayerSpec(wl.ADD, wl.ACT_RELU, co, co, oh, ow, src2=2)]
+    layers = [first, mid, *skip, wl.LayerSpec(wl.GAP, wl.ACT_NONE, co, co, oh, ow), wl.LayerSpec(wl.FC, wl.ACT_NONE, co, 9)]
+    tenants = {t: wl.make_model(layers, dtype, 330 + k, t) for t in range(3)}
+    rng = np.random.default_rng(330)
+    x = rng.standard_normal((13, first.in_len())).astype(np.float32)
+    w = wl.Workload("split", dtype, tenants, rng.integers(0, 3, 13).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
+    got = {}
+    for tiles in ("0", "100000"):
+        monkeypatch.setenv("MT_CONV_SPLIT_TILES", tiles)
+        got[tiles] = check(w, "%dx%d s%d %d->%d %s, split up to %s tiles" % (k, k, stride, ci, co, dtype, tiles))
+    # both sum fp32 products in fp32, in another order: a row's error is rounding noise, or (bf16) one flipped activation
+    err = np.linalg.norm(got["0"][0] - got["100000"][0], axis=1) / np.linalg.norm(got["0"][0], axis=1)
+    assert err.max() <= (5e-6 if dtype == "f32" else 1e-2)
