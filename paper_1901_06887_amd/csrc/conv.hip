@@ -760,9 +760,78 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
             for (uint32_t j = 0; j < P; ++j)
                 if (full * P + j < nKBv) step(wq[j]);
         };
+        // The same where a tap is whole groups of four k steps: the position moves once per group, the four reads of a
+        // pixel block and the four filter bricks of a group lie at immediate offsets.  These tiles have few waves to a
+        // SIMD (one, where frames are large), so the loop is bound by what a wave issues: step by step, some 24 instructions
+        // and a branch take 190 clocks for the 64 of two MFMAs, 295 for the 128 of four, whatever the operands' latency.
+        // 64 images, 56x56x64: 31.7/36.4 -> 29.6/31.1 us (without and with a residual addition), 28x28x128 29.5/32.0 -> 25.5/28.1,
+        // 14x14x256 29.2/32.3 -> 26.1/28.9, 7x7x512 33.2/34.6 -> 30.3/32.2.
+        auto k_loop_groups = [&](auto NR_) {
+            constexpr uint32_t NR = decltype(NR_)::value, G = 4, GP = P / G;      // k steps of a group, groups in flight
+            static_assert(P % G == 0 && (kBrickBytes * (int)(G - 1)) < 4096, "a ring of whole groups; offsets of a load are below 4 KiB");
+            const uint32_t n_groups = nKBv / G, tap_groups = cin / (G * KB);
+            const uint64_t wbase = uniform64((uint64_t)wp - lane * 16);
+            uint32_t kw = 0, left = tap_groups, row_off = 0, off = 0;             // scalar: kernel column, groups left in the tap, byte offset of the tap's row, of the group
+            auto advance = [&] {
+                off += G * KB * (uint32_t)sizeof(T);
+                if (--left == 0) {
+                    left = tap_groups;
+                    if (++kw == 3) { kw = 0; row_off += RSB; }
+                    off = row_off + kw * PB;
+                }
+            };
+            auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+            const uint8_t* at[NR];
+            auto move = [&] {
+#pragma unroll
+                for (uint32_t r = 0; r < NR; ++r) at[r] = img + (base[r] + off);
+            };
+            auto read = [&](uint32_t q, u32x4 (&av)[NR]) {
+#pragma unroll
+                for (uint32_t r = 0; r < NR; ++r) av[r] = *(const u32x4*)(at[r] + q * KB * (uint32_t)sizeof(T));
+            };
+            // Nothing is in flight here (the first bricks were asked for before the frame), and now the compiler knows: it would
+            // wait for loads of the other loops, whose registers it shares out here, in every turn of this one.
+            __builtin_amdgcn_s_waitcnt(0x0f70);                                   // vmcnt(0)
+            u32x4 av[2][NR];
+            move();
+            read(0, av[0]);
+            auto group = [&](uint32_t g, uint32_t slot) {                         // slot: where the group's bricks are in the ring, a constant
+                uint64_t src = wbase + (uint64_t)min(g + GP, n_groups - 1) * (G * kBrickBytes);      // past the last group: repeats of it
+                uint32_t lo = lane * 16;
+                asm("" : "+s"(src));
+                asm("" : "+v"(lo));
+#pragma unroll
+                for (uint32_t q = 0; q < G; ++q) {
+                    if (q + 1 < G) read(q + 1, av[(q + 1) & 1]);
+                    else {
+                        advance();
+                        if (g + 1 < n_groups) move();                             // (behind the last group: any read inside the frame)
+                        read(0, av[0]);
+                    }
+                    fence();
+#pragma unroll
+                    for (uint32_t r = 0; r < NR; ++r) Mma<T>::run(acc[r], wq[slot * G + q], av[q & 1][r]);   // rows = channels, columns = pixels
+                    wq[slot * G + q] = *(gptr_t)(src + lo + q * kBrickBytes);
+                    fence();
+                }
+            };
+            uint32_t g = 0;
+            for (; g + GP <= n_groups; g += GP) {
+#pragma unroll
+                for (uint32_t i = 0; i < GP; ++i) group(g + i, i);
+            }
+#pragma unroll
+            for (uint32_t i = 0; i < GP; ++i)
+                if (g + i < n_groups) group(g + i, i);
+        };
         const uint32_t blocks_used = ceil_div((ni - 1) * spi + px_t, kBrickRows);     // pixel blocks of the tile with a pixel in them
-        if (RBW > 1 && blocks_used <= wr * RBW + RBW / 2) k_loop(std::integral_constant<uint32_t, (RBW > 1 ? RBW / 2 : 1)>{});
-        else k_loop(std::integral_constant<uint32_t, RBW>{});
+        const bool half = RBW > 1 && blocks_used <= wr * RBW + RBW / 2;
+        constexpr std::integral_constant<uint32_t, RBW> all_blocks{};
+        constexpr std::integral_constant<uint32_t, (RBW > 1 ? RBW / 2 : 1)> half_blocks{};
+        if (!two && cin % (4 * KB) == 0) { if (half) k_loop_groups(half_blocks); else k_loop_groups(all_blocks); }
+        else if (half) k_loop(half_blocks);
+        else k_loop(all_blocks);
     }
     const float* bias = (const float*)(a.arena + L.b_off);
     const uint32_t nbase = (nb0 + (active ? wc : 0)) * kBrickRows;

@@ -50,6 +50,12 @@ __device__ __forceinline__ void* act_of(const ActBufs& b, uint32_t i)
     return i == 0 ? b.p[0] : i == 1 ? b.p[1] : i == 2 ? b.p[2] : b.p[3];
 }
 
+// A wave-uniform value in scalar registers.
+__device__ __forceinline__ uint64_t uniform64(uint64_t x)
+{
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)x) | (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32)) << 32;
+}
+
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also drains every global
 // load in flight (it fences all address spaces), which would empty the prefetch rings of the
 // GEMM loops at each LDS hand-over; here only the LDS counter is waited on.

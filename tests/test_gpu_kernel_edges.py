@@ -82,3 +82,23 @@ def test_convolutions_that_split_their_reduction(monkeypatch, dtype, k, stride, 
     # both sum fp32 products in fp32, in another order: a row's error is rounding noise, or (bf16) one flipped activation
     err = np.linalg.norm(got["0"][0] - got["100000"][0], axis=1) / np.linalg.norm(got["0"][0], axis=1)
     assert err.max() <= (5e-6 if dtype == "f32" else 1e-2)
+
+
+# frames whose K loop moves in groups of four k steps inside a tap (64 bf16 or 32 fp32 channels): one, two and more groups per tap,
+# an odd number of them in all, one to four channel blocks, images that fill half of the pixel slots, and a tenant in the same launch
+# whose taps are not whole groups
+@pytest.mark.parametrize("hw", [(7, 7), (14, 14), (5, 9)])
+@pytest.mark.parametrize("dtype,ci,co", [("bf16", 64, 32), ("bf16", 64, 136), ("bf16", 128, 64), ("bf16", 192, 128), ("bf16", 320, 96),
+                                         ("f32", 32, 24), ("f32", 96, 64), ("f32", 64, 128)])
+def test_frame_convolutions_in_groups_of_k_steps(monkeypatch, dtype, ci, co, hw):
+    monkeypatch.setenv("MT_CONV_SPLIT_TILES", "0")
+    h, w_ = hw
+    tenants = {}
+    for t, mid in enumerate((ci, ci, ci + 16)):
+        layers = [wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, mid, h, w_, 1, ksize=3, pad=1), wl.LayerSpec(wl.CONV, wl.ACT_RELU, mid, co, h, w_, 1, ksize=3, pad=1),
+                  wl.LayerSpec(wl.GAP, wl.ACT_NONE, co, co, h, w_), wl.LayerSpec(wl.FC, wl.ACT_NONE, co, 9)]
+        tenants[t] = wl.make_model(layers, dtype, 340, t)
+    rng = np.random.default_rng(340)
+    x = rng.standard_normal((17, 3 * h * w_)).astype(np.float32)
+    w = wl.Workload("frames", dtype, tenants, rng.integers(0, 3, 17).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
+    check(w, "%dx%d %d->%d %s" % (h, w_, ci, co, dtype))
