@@ -106,7 +106,7 @@ template <typename T> constexpr uint32_t unit_row_stride() { return kBrickRows *
 template <typename T> constexpr uint32_t unit_scratch_bytes() { return kBrickRows * unit_row_stride<T>() + kBrickRows * 8; }
 
 template <typename T>
-__device__ __forceinline__ void store_unit_nhwc(const f32x4 (&y)[4], T* my_pixel_out, uint32_t n_valid, uint8_t* scratch)
+__device__ __forceinline__ void store_unit_nhwc(const f32x4 (&y)[4], T* my_pixel_out, uint32_t n_valid, uint32_t through, uint8_t* scratch)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), RS = unit_row_stride<T>();
     constexpr uint32_t CP = kBrickRows / EPC;                       // 16-byte chunks per pixel row: 4 (bf16) or 8 (fp32)
@@ -128,7 +128,10 @@ __device__ __forceinline__ void store_unit_nhwc(const f32x4 (&y)[4], T* my_pixel
         const uint32_t px = pass * (64 / CP) + lane / CP, ch = lane % CP;
         T* dst = dests[px];
         const u32x4 v = *(const u32x4*)(scratch + px * RS + ch * 16);
-        if (dst != nullptr && ch * EPC < n_valid) *(u32x4*)(dst + ch * EPC) = v;
+        if (dst != nullptr && ch * EPC < n_valid) {
+            if (through) store_through((u32x4*)(dst + ch * EPC), v);      // the same for the whole launch
+            else *(u32x4*)(dst + ch * EPC) = v;
+        }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // reads done before the next unit overwrites the scratch
 }
@@ -232,7 +235,7 @@ __device__ __forceinline__ void conv_wave(const GemmArgs& a, const LayerDev& L, 
         const uint32_t nvalid = min((uint32_t)kBrickRows, L.N - nbase);
         if (L.fuse_add)
             add_residual<T>(y, out ? (const T*)act_of(a.act, L.in2_buf) + (out - (T*)act_of(a.act, L.out_buf)) + nbase : nullptr, lh, nvalid, L.fuse_add - 1);
-        store_unit_nhwc<T>(y, out ? out + nbase : nullptr, nvalid, scratch);
+        store_unit_nhwc<T>(y, out ? out + nbase : nullptr, nvalid, a.store_through, scratch);
     }
 }
 
@@ -597,7 +600,7 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
         const uint32_t nvalid = min((uint32_t)kBrickRows, L.N - nbase);
         if (L.fuse_add)
             add_residual<T>(y, out ? (const T*)act_of(a.act, L.in2_buf) + (out - (T*)act_of(a.act, L.out_buf)) : nullptr, lh, nvalid, L.fuse_add - 1);
-        store_unit_nhwc<T>(y, out, nvalid, scratch);
+        store_unit_nhwc<T>(y, out, nvalid, a.store_through, scratch);
     }
 }
 
@@ -859,7 +862,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
         const uint32_t nvalid = min((uint32_t)kBrickRows, L.N - nbase);
         if (L.fuse_add)
             add_residual<T>(y, out ? (const T*)act_of(a.act, L.in2_buf) + (out - (T*)act_of(a.act, L.out_buf)) : nullptr, lh, nvalid, L.fuse_add - 1);
-        store_unit_nhwc<T>(y, out, nvalid, scratch);
+        store_unit_nhwc<T>(y, out, nvalid, a.store_through, scratch);
     }
 }
 

@@ -1247,6 +1247,10 @@ __global__ void fill_zero_kernel(uint32_t* p, uint32_t n)
 
 // Packed rows a run of R rows can occupy: every tenant with traffic pads its segment to a multiple of 32.
 constexpr uint32_t kBigWalkMinK = 256;     // the walking big-tile kernel needs seven stages of 32 (bf16) or 16 (fp32) per tile
+// A convolution launch that can write at most this much stores through L2 (store_through): twice what the L2s hold (8 x 4 MiB).  Passes with
+// the line at 0 / 32 / 64 / 128 MiB: residual nets, 64 images 642 / 630 / 630 us (on another box 629 / - / 616 / 613), 128 images 1110 / 1103 / 1096,
+// 1000 32x32 images through small CNNs 104.6 / 103 / 100.8 / 101.2; with no line 256 images 2090 -> 2106 and 2048 unstrided CNNs 718 -> 737.
+constexpr uint64_t kStoreThroughMaxBytes = 64u << 20;
 constexpr uint32_t kConvLongK = 1024;      // reductions from here on are worth loader waves when a launch has at most one tile per CU
 
 // Workgroups that share one packed row in the per-row kernels: `per_wg` units of work each, at most 64.
@@ -1471,6 +1475,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             ga.T = T; ga.layer = l; ga.fc_split_k = split_k; ga.big_layers = b.big_layers;
             ga.gather = (kind == 0 && l == 0 && fuse_gather); ga.perm = c->d_perm; ga.row_src = c->d_row_src;
             ga.fuse_head = fuse_head; ga.fuse_head_max = fuse_head_max; ga.out_vec_ok = out_vec_ok; ga.out = outp; ga.pool = kind == 1 && c->pool_fused[l];
+            ga.store_through = kind == 1 && R * (uint64_t)c->max_conv_rows[l] * c->max_conv_blocks[l] * kBrickRows * c->elem_size <= kStoreThroughMaxBytes;
             ga.layers = c->d_layers; ga.off = c->d_off; ga.M = c->d_M; ga.act = bufs; ga.arena = c->d_arena;
             ga.logits = c->d_logits; ga.S = c->S; ga.C_pad = c->C_pad; ga.zeros = c->d_zeros;
             if (grid > 0x7ffffff0u)          // cannot happen within the limits mt_create accepts; never launch fewer workgroups than tiles

@@ -93,6 +93,15 @@ __device__ __forceinline__ void lds_dma16_buffer(const u32x4& desc, uint32_t vof
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(m0v), "v"(voff), "s"(desc) : "memory", "m0");
 }
 
+// 16 bytes per lane through the XCD's L2 to memory (agent scope).  An ordinary store stays in L2 and is written back when the kernel
+// ends, with nothing else running: a convolution launch that writes some 10-50 MB ends 1.2-1.7 us earlier with these (residual nets, 64
+// images, 19 such launches: 30.5 -> 28.8, 36.3 -> 34.8, 20.0 -> 18.4 us).  Passes that write all the time lose (image gather 26 -> 37 us).
+// In asm: the compiler has no store of this size and scope; its wait counts only become stricter by stores that it does not know of.
+__device__ __forceinline__ void store_through(u32x4* dst, const u32x4& v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" :: "v"(dst), "v"(v) : "memory");
+}
+
 // Inclusive prefix sums across lanes with data-parallel-primitive moves (no LDS traffic): shifts
 // by 1, 2, 4, 8 inside each row of 16 lanes (lanes without a source add 0), then lane 15 of rows
 // 0 and 2 is added to rows 1 and 3, then lane 31 to the upper half.

@@ -200,6 +200,7 @@ struct GemmArgs {
     const uint32_t* big_layers;   // the batcher's decision per layer index (see BatchArgs)
     uint32_t big_vgrid;           // big-tile launch whose workgroups walk several tiles: the grid of one tile per workgroup that they walk
     uint32_t pool;                // conv launch: the layers with pool_fill write the pooled activation instead of their own
+    uint32_t store_through;       // conv launch: outputs go through L2 to memory (see store_through)
     uint32_t img_lds;             // conv launch with LDS-resident input: bytes of dynamic LDS (the largest frame)
     // FC layer 0 can read the submitted rows itself (16-byte aligned rows whose length is a
     // whole number of 16-byte chunks), which saves the staging pass:
