@@ -131,6 +131,7 @@ struct mt_ctx {
     uint32_t no_fused_add = 0;     // tuning/testing: residual additions always run as launches of their own
     uint32_t big_walk = 1;         // big FC tiles: one workgroup per CU walks several tiles (tuning/testing: MT_BIG_WALK=0 gives every tile a workgroup of its own)
     uint32_t n_cus = 256;          // compute units of the device, rounded down to a multiple of 8
+    uint32_t max_fc_cols[MT_MAX_LAYERS]{};     // widest (padded) FC layer of a layer index: up to 64 outputs split K in every run
     uint32_t min_fc_k[MT_MAX_LAYERS]{};        // shortest padded fan-in among the registered FC layers of a layer index
     uint32_t no_conv_uniform = 0;  // tuning/testing: convolution gathers always walk the window lane by lane
     uint32_t no_conv_loaders = 0;  // tuning/testing: convolution tiles never get waves of their own for the loads
@@ -454,7 +455,7 @@ void recompute_bounds(mt_ctx* c)
     for (uint32_t& m : c->list_mask) m = 0;
     c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
-        c->has_gap[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
+        c->has_gap[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
         for (int k = 0; k < kListKinds; ++k) { c->max_rpr[k][l] = c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
         c->max_fc_per64[l] = 0; c->max_fc_per64_sk[l] = 0; c->sum_nt_sk[l] = 0; c->max_big_blocks[l] = 0;
     }
@@ -485,6 +486,7 @@ void recompute_bounds(mt_ctx* c)
             c->sum_nt[k][l] += nt;
             if (k == 0) {
                 c->min_fc_k[l] = std::min(c->min_fc_k[l], L.K);
+                c->max_fc_cols[l] = std::max(c->max_fc_cols[l], L.N_pad);
                 c->max_fc_per64[l] = std::max(c->max_fc_per64[l], nt * (kTileRows / fc_tile_rows(L.N_pad, c->fc_split_k)));
                 const uint32_t nt_sk = fc_groups(L.N_pad, 1);
                 c->sum_nt_sk[l] += nt_sk;
@@ -1481,7 +1483,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             if (grid > 0x7ffffff0u)          // cannot happen within the limits mt_create accepts; never launch fewer workgroups than tiles
                 return fail(c, MT_EUNSUPPORTED, "layer %u: %llu tiles exceed one launch", l, (unsigned long long)grid);
             const uint32_t g32 = (uint32_t)grid;
-            if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, g32, s));
+            if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, split_k || c->max_fc_cols[l] <= 2 * (uint32_t)kBrickRows, g32, s));
             else if (conv.split) TIMED(kProfConv + l, launch_conv_split(ga, c->cfg.dtype, (c->max_conv_k[l] * c->elem_size + 31) / 32, g32, s));
             else if (kind == 1) TIMED(kProfConv + l, launch_conv(ga, c->cfg.dtype, c->max_conv_cb[l], c->conv_quad[l],
                                                                     conv.frames ? c->conv_img_lds[l] : 0, c->conv_img_two[l] == 1,

@@ -233,7 +233,7 @@ struct HeadArgs {
 hipError_t launch_batcher(const BatchArgs& a, hipStream_t s);   // three launches when a.n_rank_groups > 0
 hipError_t launch_gather(const GatherArgs& a, uint32_t slices, hipStream_t s);   // `slices` workgroups share a block of 32 rows
 hipError_t launch_gather_image(const GatherArgs& a, uint32_t slices, hipStream_t s);   // `slices` workgroups share a row
-hipError_t launch_fc(const GemmArgs& a, uint32_t dtype, uint32_t grid, hipStream_t s);
+hipError_t launch_fc(const GemmArgs& a, uint32_t dtype, bool narrow, uint32_t grid, hipStream_t s);
 hipError_t launch_fc_big(const GemmArgs& a, uint32_t dtype, uint32_t grid, uint32_t walk_grid, hipStream_t s);   // walk_grid > 0: that many workgroups walk the tiles (a multiple of 8)
 hipError_t launch_copy(void* dst, const void* src, uint64_t bytes, hipStream_t s);
 hipError_t launch_mfma_rate(float* out, uint32_t iters, uint32_t grid, hipStream_t s);   // out: grid * 512 floats

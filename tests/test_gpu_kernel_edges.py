@@ -102,3 +102,27 @@ def test_frame_convolutions_in_groups_of_k_steps(monkeypatch, dtype, ci, co, hw)
     x = rng.standard_normal((17, 3 * h * w_)).astype(np.float32)
     w = wl.Workload("frames", dtype, tenants, rng.integers(0, 3, 17).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
     check(w, "%dx%d %d->%d %s" % (h, w_, ci, co, dtype))
+
+
+# tiles whose waves split K finish on all their waves: one and two column blocks (64 hidden outputs), class counts at the edges of a
+# block and of the two, row counts at the edges of a tile, output rows that do not take 16-byte stores
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("classes", [1, 3, 31, 32, 33, 64, 65])
+@pytest.mark.parametrize("rows,hidden", [(1, 24), (33, 64), (95, 200)])
+def test_tiles_that_split_k_finish_their_rows(dtype, classes, rows, hidden):
+    w = mlp_fleet(2, rows, (48, hidden, 40, classes), dtype=dtype, act=wl.ACT_GELU, seed=350)
+    check(w, "%d rows, %d hidden, %d classes, %s" % (rows, hidden, classes, dtype))
+
+
+def test_head_of_a_split_k_tile_on_infinite_and_undefined_logits():
+    """A class whose logit is +-infinity or NaN: the label is what a walk from the first class finds, as the other heads."""
+    C, cases = 5, ([np.inf, 1, 2, 3, 4], [-np.inf] * 5, [0, np.nan, 1, -np.inf, 1], [np.nan, 1, 2, 3, 4])
+    w = mlp_fleet(len(cases), len(cases), (16, C), seed=351, ids=np.arange(len(cases)))
+    for t, row in enumerate(cases):
+        w.tenants[t].biases[0][:] = np.array(row, np.float32)
+        w.tenants[t].weights[0][:] = 0
+    lg, pr, lb, nc = gpu_run(make_context(w), w)
+    assert lb.tolist() == [0, 0, 2, 0]
+    assert np.isnan(pr[:, :C]).all()
+    for t, row in enumerate(cases):
+        assert np.array_equal(lg[t, :C], np.array(row), equal_nan=True)
