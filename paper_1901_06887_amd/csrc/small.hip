@@ -151,8 +151,10 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a)
 // with eight loads in flight; the G partial sums of a channel are then added in a fixed order through LDS.
 // 64 images of 7x7x512 bf16 11.9 -> 6.6 us; 150 images of 15x18x72 fp32 (18 chunks per pixel) 66.7 -> 7.6 us against a
 // form with 128 threads that took such channel counts one element per thread.
-constexpr uint32_t kGapThreads = 512;
-template <typename T>
+// Launches of many rows fill the chip with workgroups of 128 threads, which start and end sooner (2265 images of 6x7x8 fp32: 14.6 us with
+// 512 threads, 8.0 with 128).
+constexpr uint32_t kGapManyRows = 1024;
+template <typename T, uint32_t kGapThreads>
 __device__ void gap_row(const GapArgs& a, const LayerDev& L, uint32_t p, uint32_t seg0)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC, kMaxGroups = 64, kInFlight = 8;
@@ -199,6 +201,7 @@ __device__ void gap_row(const GapArgs& a, const LayerDev& L, uint32_t p, uint32_
     for (uint32_t c = C + threadIdx.x; c < L.out_fill; c += kGapThreads) put(c, 0.0f);
 }
 
+template <uint32_t kGapThreads>
 __global__ __launch_bounds__(kGapThreads) void gap_kernel(GapArgs a)
 {
     const uint32_t p = blockIdx.x;
@@ -206,7 +209,7 @@ __global__ __launch_bounds__(kGapThreads) void gap_kernel(GapArgs a)
     if (!packed_row_tenant<kGapThreads>(a.off, a.M, a.T, p, &t)) return;
     const LayerDev L = a.layers[t * MT_MAX_LAYERS + a.layer];
     if (a.tenants[t].n_layers <= a.layer || L.kind != MT_GAP) return;
-    if (a.elem_size == 2) gap_row<__bf16>(a, L, p, a.off[t]); else gap_row<float>(a, L, p, a.off[t]);
+    if (a.elem_size == 2) gap_row<__bf16, kGapThreads>(a, L, p, a.off[t]); else gap_row<float, kGapThreads>(a, L, p, a.off[t]);
 }
 
 // ---- max-pool and residual add: gridDim.y workgroups per packed row, NHWC rows in and out ----
@@ -441,7 +444,8 @@ hipError_t launch_gather_image(const GatherArgs& a, uint32_t slices, hipStream_t
 hipError_t launch_gap(const GapArgs& a, hipStream_t s)
 {
     // grid covers every packed row; rows of other layer kinds return at once
-    hipLaunchKernelGGL(gap_kernel, dim3(a.P), dim3(kGapThreads), 0, s, a);
+    if (a.P >= kGapManyRows) hipLaunchKernelGGL(gap_kernel<128>, dim3(a.P), dim3(128), 0, s, a);
+    else hipLaunchKernelGGL(gap_kernel<512>, dim3(a.P), dim3(512), 0, s, a);
     return hipGetLastError();
 }
 hipError_t launch_image_ops(const GapArgs& a, uint32_t slices, hipStream_t s)

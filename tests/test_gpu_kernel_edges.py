@@ -126,3 +126,15 @@ def test_head_of_a_split_k_tile_on_infinite_and_undefined_logits():
     assert np.isnan(pr[:, :C]).all()
     for t, row in enumerate(cases):
         assert np.array_equal(lg[t, :C], np.array(row), equal_nan=True)
+
+
+def test_average_pooling_of_many_rows():
+    """Launches of 1024 and more packed rows pool with smaller workgroups: odd channel counts, more chunks than threads."""
+    for channels, dtype in ((72, "f32"), (8, "bf16"), (520, "f32")):
+        layers = [wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, channels, 3, 5, 1, ksize=1, pad=0), wl.LayerSpec(wl.GAP, wl.ACT_NONE, channels, channels, 3, 5),
+                  wl.LayerSpec(wl.FC, wl.ACT_NONE, channels, 7)]
+        tenants = {t: wl.make_model(layers, dtype, 360, t) for t in range(2)}
+        rng = np.random.default_rng(360)
+        x = rng.standard_normal((1030, layers[0].in_len())).astype(np.float32)
+        w = wl.Workload("gap", dtype, tenants, rng.integers(0, 2, 1030).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
+        check(w, "1030 rows of %d channels, %s" % (channels, dtype))
