@@ -331,13 +331,14 @@ __device__ __forceinline__ void fc_finish_split(const GemmArgs& a, const Tile& t
                 }
             continue;
         }
-        // hidden layer (outputs past N: zero weight rows and bias, which every activation maps to 0): activation, rounding; the 32x32 block through LDS as [row][column], out as whole bricks
+        // hidden layer: activation, rounding; the 32x32 block through LDS as [row][column], out as whole bricks.  Outputs past N are
+        // masked: a zero weight row against an infinite input is NaN, and the next layer reads them with zero weights
         activate_block<MAXG>(y, L.act);
 #pragma unroll
         for (uint32_t i = 0; i < MAXG; ++i)
             if (active && i < ng) {
 #pragma unroll
-                for (uint32_t e = 0; e < 4; ++e) *(T*)(trw + (8 * (kq * ng + i) + 4 * lh + e) * TRS + li * sizeof(T)) = (T)y[i][e];
+                for (uint32_t e = 0; e < 4; ++e) *(T*)(trw + (8 * (kq * ng + i) + 4 * lh + e) * TRS + li * sizeof(T)) = (T)(n < L.N ? y[i][e] : 0.0f);
             }
         __syncthreads();
         if (active) {

@@ -128,6 +128,38 @@ def test_head_of_a_split_k_tile_on_infinite_and_undefined_logits():
         assert np.array_equal(lg[t, :C], np.array(row), equal_nan=True)
 
 
+# Padding columns of a hidden layer's activation stay zero whatever a row holds: 0 x Inf in a padding output would be NaN, and meet the
+# zero-padded K of the next layer.  Linear hidden layers (one and two column blocks, a wider one with a ragged last block), in runs that split
+# K, that do not, and that take big tiles; y = W x over the K real inputs: a row with an infinite input has infinite logits, not NaN.
+def infinite_rows(dtype, dims, rows, hot):
+    w = mlp_fleet(1, rows, dims, dtype=dtype, act=wl.ACT_NONE, seed=352)
+    m = w.tenants[0]
+    for layer in range(len(dims) - 2):
+        m.weights[layer][:] = 1
+    m.weights[-1][:] = np.array([-1, 2, 3], np.float32)[:, None]
+    for b in m.biases:
+        b[:] = 0
+    w.inputs[:] = 1
+    w.inputs[hot, 5] = np.inf
+    return w
+
+
+def check_infinite_rows(w, hot):
+    lg, _, lb, _ = gpu_run(make_context(w), w, poison=True)
+    cold = np.setdiff1d(np.arange(w.n_requests), hot)
+    assert np.array_equal(lg[hot, :3], np.tile([-np.inf, np.inf, np.inf], (len(hot), 1))) and (lb[hot] == 1).all()
+    assert np.isfinite(lg[cold]).all() and (lb[cold] == 2).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("hidden", [(1,), (40,), (100,), (100, 7, 200)])
+@pytest.mark.parametrize("no_split_k", ["0", "1"])
+def test_infinite_inputs_leave_padding_columns_at_zero(monkeypatch, dtype, hidden, no_split_k):
+    monkeypatch.setenv("MT_NO_AUTO_SPLIT_K", no_split_k)
+    hot = np.array([0, 2, 34])
+    check_infinite_rows(infinite_rows(dtype, (16, *hidden, 3), 37, hot), hot)
+
+
 def test_average_pooling_of_many_rows():
     """Launches of 1024 and more packed rows pool with smaller workgroups: odd channel counts, more chunks than threads."""
     for channels, dtype in ((72, "f32"), (8, "bf16"), (520, "f32")):
