@@ -18,6 +18,16 @@ constexpr uint32_t kBigBlocks = kBigTile / kBrickRows;                          
 constexpr uint32_t kBigStageBytes = 2 * kBigBlocks * kBigKS * kBrickBytes;        // 32 KiB
 constexpr uint32_t kBigGroup = 4;                                                 // row tiles that sweep the columns together
 
+// Zeros in the outputs from N on of a hidden layer's ragged last column block (y: the outputs first + 8 g + {0..3} of one row): their weight
+// rows are zero, but against an infinite input that is NaN, and the next layer reads them with zero weights.
+__device__ __forceinline__ void mask_padding(f32x4 (&y)[4], uint32_t first, uint32_t N)
+{
+#pragma unroll
+    for (uint32_t g = 0; g < 4; ++g)
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) y[g][e] = first + 8 * g + e < N ? y[g][e] : 0.0f;
+}
+
 // WV waves per workgroup: 8 (2x4, 128x64 per wave) or 4 (2x2, 128x128 per wave, one wave per SIMD
 // with its accumulators in the second half of the 512-entry register file).
 template <typename T, int WV>
@@ -240,9 +250,8 @@ __global__ __launch_bounds__(WV * 64) void fc_big_kernel(GemmArgs a)
             } else {
                 u32x4* out = (u32x4*)((T*)act_of(a.act, L.out_buf) + (size_t)seg0 * a.S) +
                              ((size_t)(mb / kBrickRows) * nKB_out + nb * (kBrickRows / KB)) * 64 + lane;
-                // outputs past N need no masking: their weight rows and bias are zero padding, and
-                // every activation of the layer set maps 0 to 0
                 activate_block<4>(y, L.act);
+                if (nb * kBrickRows + kBrickRows > L.N) mask_padding(y, nl, L.N);
                 if constexpr (sizeof(T) == 4) {
 #pragma unroll
                     for (int g = 0; g < 4; ++g) out[g * 64] = __builtin_bit_cast(u32x4, y[g]);   // brick g of the block, half lh
@@ -573,6 +582,7 @@ __global__ __launch_bounds__(512) void fc_big_walk_kernel(GemmArgs a)
                         u32x4* out = (u32x4*)((T*)act_of(a.act, cur.out_buf) + (size_t)cur.seg0 * a.S) +
                                      ((size_t)(mb / kBrickRows) * nKB_out + nb * (kBrickRows / KB)) * 64 + lane;
                         activate_block<4>(y, cur.act);
+                        if (nb * kBrickRows + kBrickRows > cur.N) mask_padding(y, nl, cur.N);
                         if constexpr (sizeof(T) == 4) {
 #pragma unroll
                             for (int g = 0; g < 4; ++g) out[g * 64] = __builtin_bit_cast(u32x4, y[g]);

@@ -160,6 +160,14 @@ def test_infinite_inputs_leave_padding_columns_at_zero(monkeypatch, dtype, hidde
     check_infinite_rows(infinite_rows(dtype, (16, *hidden, 3), 37, hot), hot)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("k", [64, 256])                       # a workgroup per big tile, one workgroup per CU walking them
+def test_infinite_inputs_leave_padding_columns_of_big_tiles_at_zero(monkeypatch, dtype, k):
+    monkeypatch.setenv("MT_BIG_MIN_TILES", "1")
+    hot = np.array([0, 255, 256, 8191])
+    check_infinite_rows(infinite_rows(dtype, (k, 200, 3), 8192, hot), hot)
+
+
 def test_average_pooling_of_many_rows():
     """Launches of 1024 and more packed rows pool with smaller workgroups: odd channel counts, more chunks than threads."""
     for channels, dtype in ((72, "f32"), (8, "bf16"), (520, "f32")):
