@@ -121,6 +121,7 @@ def load_library() -> ctypes.CDLL:
     L.mt_debug_big_tile_walk.restype = u32
     L.mt_debug_conv_row_tiling.argtypes = [u32, u32, u32, u32, u32, u32, ctypes.POINTER(u32), ctypes.POINTER(u32), ctypes.POINTER(u32), ctypes.POINTER(ctypes.c_uint64)]
     L.mt_debug_conv_row_tiling.restype = ctypes.c_int
+    L.mt_debug_conv_launch.argtypes = [vp, u32, u32, ctypes.POINTER(u32), ctypes.POINTER(ctypes.c_uint64)]
     L.mt_set_profiling.argtypes = [vp, ctypes.c_int]
     L.mt_get_profile.argtypes = [vp, ctypes.POINTER(mt_profile)]
     L.mt_last_error.argtypes = [vp]
@@ -128,7 +129,8 @@ def load_library() -> ctypes.CDLL:
     L.mt_version.restype = ctypes.c_char_p
     for name in ("mt_create", "mt_destroy", "mt_register_model", "mt_register_model_bn", "mt_unregister_model", "mt_submit",
                  "mt_submit_batch", "mt_run", "mt_run_static", "mt_last_counts", "mt_get_stats", "mt_tenant_account_get", "mt_estimate_run", "mt_prefetch", "mt_cache_stats_get", "mt_admit", "mt_debug_poison", "mt_debug_copy",
-                 "mt_set_profiling", "mt_get_profile", "mt_model_footprint_get", "mt_debug_mfma_rate"):
+                 "mt_set_profiling", "mt_get_profile", "mt_model_footprint_get", "mt_debug_mfma_rate",
+                 "mt_debug_conv_launch"):
         getattr(L, name).restype = ctypes.c_int
     _lib = L
     return L
@@ -252,6 +254,12 @@ class Context:
 
     def debug_poison(self):
         self._check(self._lib.mt_debug_poison(self._h))
+
+    def debug_conv_launch(self, layer: int, rows: int):
+        """(tiles split their reduction, workgroups) of the convolution launch of a layer index in a run of so many requests."""
+        split, n = ctypes.c_uint32(), ctypes.c_uint64()
+        self._check(self._lib.mt_debug_conv_launch(self._h, layer, rows, ctypes.byref(split), ctypes.byref(n)))
+        return bool(split.value), n.value
 
     def tenant_account(self, tenant: int) -> dict:
         a = mt_tenant_account()

@@ -29,6 +29,7 @@ constexpr uint32_t kMaxTenants = 2048;
 constexpr uint32_t kSegSlots = MT_SEG_SLOTS;   // pinned segment tables: runs of several submissions in flight at once
 constexpr uint32_t kMaxRunSlots = 4;      // runs in flight at once (each with its own device scratch); <= kSegSlots
 constexpr uint64_t kArenaAlign = 256;
+constexpr uint64_t kMaxLaunchItems = 0xffff0000u;   // work items of one launch (the grid is rounded up to a multiple of 8 or 512 workgroups)
 // Convolution launches of at most so many tiles of 32 pixels and one channel block (as the host expects them) take such
 // tiles, K split among their waves.  Passes with the line at 0 / 256 / 512 / 768 / 1024 tiles: 26-layer residual nets on
 // 224x224 images, one request 403 / 210 / 212 / 210 / 207 us, 4 requests 431 / 300 / 276 / 276 / 283, 8 requests 446 / 375 /
@@ -98,7 +99,7 @@ struct mt_ctx {
     uint32_t n_layer_slots = 0;
     uint32_t max_in_len = 0;
     // [kind][layer]: kind 0 = FC tiles, 1 = conv tiles, 2 = big FC tiles
-    uint32_t max_rpr[kListKinds][MT_MAX_LAYERS]{}, max_nt[kListKinds][MT_MAX_LAYERS]{}, has_gap[MT_MAX_LAYERS]{};
+    uint32_t max_nt[kListKinds][MT_MAX_LAYERS]{}, has_gap[MT_MAX_LAYERS]{};
     // pool_fused[l]: layer index l + 1 is a global average pool for every registered model that is that deep, and
     // each of their convolutions at l can pool by itself: the convolution launch writes the pooled activation
     // and nothing runs at index l + 1 (all or nothing: the activation buffers alternate per layer index)
@@ -136,7 +137,8 @@ struct mt_ctx {
     uint32_t no_conv_uniform = 0;  // tuning/testing: convolution gathers always walk the window lane by lane
     uint32_t no_conv_loaders = 0;  // tuning/testing: convolution tiles never get waves of their own for the loads
     uint32_t max_conv_blocks[MT_MAX_LAYERS]{};  // widest convolution of a layer index over the registered models, in blocks of 32 channels
-    uint32_t max_conv_rows[MT_MAX_LAYERS]{};    // most output pixels of a convolution of the layer index
+    uint64_t max_conv_work[MT_MAX_LAYERS]{};    // most output pixels x channel blocks of one convolution of the layer index
+    uint64_t max_conv_tile_rows[MT_MAX_LAYERS]{};  // ... rows by which its ordinary tiles are counted x tiles side by side
     uint64_t sum_conv_work[MT_MAX_LAYERS]{};    // sum over the registered models of output pixels x channel blocks
     uint64_t sum_conv_blocks[MT_MAX_LAYERS]{};  // ... and their sum
     uint32_t max_conv_k[MT_MAX_LAYERS]{};      // longest reduction among the registered convolutions of a layer index
@@ -455,8 +457,8 @@ void recompute_bounds(mt_ctx* c)
     for (uint32_t& m : c->list_mask) m = 0;
     c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
-        c->has_gap[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
-        for (int k = 0; k < kListKinds; ++k) { c->max_rpr[k][l] = c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
+        c->has_gap[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
+        for (int k = 0; k < kListKinds; ++k) { c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
         c->max_fc_per64[l] = 0; c->max_fc_per64_sk[l] = 0; c->sum_nt_sk[l] = 0; c->max_big_blocks[l] = 0;
     }
     for (const HostTenant& t : c->tenants) {
@@ -481,7 +483,6 @@ void recompute_bounds(mt_ctx* c)
             c->sum_macs += (double)L.k_valid * L.N * L.rows_per_req;
             c->list_mask[l / kLayerGroup] |= 1u << (k * kLayerGroup + l % kLayerGroup);
             const uint32_t nt = k == 0 ? fc_groups(L.N_pad, c->fc_split_k) : (L.N + kTileCols - 1) / kTileCols;
-            c->max_rpr[k][l] = std::max(c->max_rpr[k][l], k == 1 ? conv_tile_rows(L.rows_per_req, L.row_tiles) : L.rows_per_req);
             c->max_nt[k][l] = std::max(c->max_nt[k][l], nt);
             c->sum_nt[k][l] += nt;
             if (k == 0) {
@@ -494,10 +495,12 @@ void recompute_bounds(mt_ctx* c)
             }
             if (k == 1) {
                 c->min_conv_k[l] = std::min(c->min_conv_k[l], L.k_valid);
-                c->max_conv_rows[l] = std::max(c->max_conv_rows[l], L.rows_per_req);
+                const uint64_t work = (uint64_t)L.rows_per_req * (L.N_pad / kBrickRows);
+                c->max_conv_work[l] = std::max(c->max_conv_work[l], work);
+                c->max_conv_tile_rows[l] = std::max(c->max_conv_tile_rows[l], (uint64_t)conv_tile_rows(L.rows_per_req, L.row_tiles) * nt);
                 c->max_conv_k[l] = std::max(c->max_conv_k[l], L.k_valid);
                 c->max_conv_blocks[l] = std::max(c->max_conv_blocks[l], L.N_pad / kBrickRows);
-                c->sum_conv_work[l] += (uint64_t)L.rows_per_req * (L.N_pad / kBrickRows);
+                c->sum_conv_work[l] += work;
                 c->sum_conv_blocks[l] += L.N_pad / kBrickRows;
                 c->max_conv_cb[l] = std::max(c->max_conv_cb[l], std::min<uint32_t>(L.N_pad / kBrickRows, kTileCols / kBrickRows));
                 if (L.cin % (4 * (16 / c->elem_size))) c->conv_quad[l] = false;
@@ -529,10 +532,11 @@ uint64_t tile_bound(const mt_ctx* c, int kind, uint32_t l, uint64_t R, bool spli
         return tile_bound(c, 0, l, R) + (R / kBigMinRows) * (kBigRemRows / kBrickRows) * c->max_big_blocks[l];
     if (kind == 2)      // big FC tiles: only tenants with >= kBigMinRows rows; sum ceil(M_t/256) <= R/256 + R/kBigMinRows
         return R < (uint64_t)kBigMinBatch ? 0 : (uint64_t)c->max_nt[2][l] * (R / kBigTile + R / kBigMinRows);
-    // sum over tenants of ceil(M_t / rows_t) * groups_t <= R * max(groups_t / rows_t) + sum(groups_t)
+    // sum over tenants of ceil(M_t / rows_t) * groups_t <= R * max(groups_t / rows_t) + sum(groups_t): the maximum of the quotient, not
+    // of its two parts, which may be two models' (one with many pixels, one with many channels: a launch past 2^32 work items)
     if (kind == 0 && split_k) return ((uint64_t)c->max_fc_per64_sk[l] * R + kTileRows - 1) / kTileRows + c->sum_nt_sk[l];
     if (kind == 0) return ((uint64_t)c->max_fc_per64[l] * R + kTileRows - 1) / kTileRows + c->sum_nt[0][l];
-    return (uint64_t)c->max_nt[kind][l] * (R * c->max_rpr[kind][l] / kConvTileRows) + c->sum_nt[kind][l];
+    return R * c->max_conv_tile_rows[l] / kConvTileRows + c->sum_nt[1][l];
 }
 
 // Tile shape of the FC layers of a run over R rows.  When no layer index can have more than
@@ -570,9 +574,9 @@ ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R)
     const uint64_t active = std::min<uint64_t>(R, c->n_registered);
     const uint64_t expected = R * c->sum_conv_work[l] / c->n_registered / kBrickRows + active * c->sum_conv_blocks[l] / c->n_registered / 2;
     if (expected > c->conv_split_tiles) return p;
-    // sum over tenants of ceil(M_t rows_t / 32) * blocks_t <= max blocks * R * max rows / 32 + the ragged tiles of those with requests
+    // the same bound as in tile_bound, with the ragged tiles of those with requests
     p.split = true; p.frames = false;
-    p.tiles = c->max_conv_blocks[l] * (R * c->max_conv_rows[l] / kBrickRows) + std::min<uint64_t>(c->sum_conv_blocks[l], active * c->max_conv_blocks[l]);
+    p.tiles = R * c->max_conv_work[l] / kBrickRows + std::min<uint64_t>(c->sum_conv_blocks[l], active * c->max_conv_blocks[l]);
     return p;
 }
 
@@ -1477,10 +1481,11 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             ga.T = T; ga.layer = l; ga.fc_split_k = split_k; ga.big_layers = b.big_layers;
             ga.gather = (kind == 0 && l == 0 && fuse_gather); ga.perm = c->d_perm; ga.row_src = c->d_row_src;
             ga.fuse_head = fuse_head; ga.fuse_head_max = fuse_head_max; ga.out_vec_ok = out_vec_ok; ga.out = outp; ga.pool = kind == 1 && c->pool_fused[l];
-            ga.store_through = kind == 1 && R * (uint64_t)c->max_conv_rows[l] * c->max_conv_blocks[l] * kBrickRows * c->elem_size <= kStoreThroughMaxBytes;
+            ga.store_through = kind == 1 && R * c->max_conv_work[l] * kBrickRows * c->elem_size <= kStoreThroughMaxBytes;
             ga.layers = c->d_layers; ga.off = c->d_off; ga.M = c->d_M; ga.act = bufs; ga.arena = c->d_arena;
             ga.logits = c->d_logits; ga.S = c->S; ga.C_pad = c->C_pad; ga.zeros = c->d_zeros;
-            if (grid > 0x7ffffff0u)          // cannot happen within the limits mt_create accepts; never launch fewer workgroups than tiles
+            // a launch holds fewer than 2^32 work items; cannot be exceeded by activations that fit the device's memory
+            if (grid > kMaxLaunchItems / (conv.split ? 1024 : kind == 2 ? 512 : 256))
                 return fail(c, MT_EUNSUPPORTED, "layer %u: %llu tiles exceed one launch", l, (unsigned long long)grid);
             const uint32_t g32 = (uint32_t)grid;
             if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, split_k || c->max_fc_cols[l] <= 2 * (uint32_t)kBrickRows, g32, s));
@@ -1886,6 +1891,16 @@ int mt_debug_conv_row_tiling(uint32_t in_h, uint32_t in_w, uint32_t in_channels,
     if (tiles_per_image) *tiles_per_image = r.tpi;
     if (frame_bytes) *frame_bytes = frame;
     return r.n_oh != 0;
+}
+
+mt_status mt_debug_conv_launch(mt_ctx* c, uint32_t layer, uint32_t rows, uint32_t* split, uint64_t* workgroups)
+{
+    if (!c) return MT_EINVAL;
+    if (layer >= MT_MAX_LAYERS || rows == 0) return fail(c, MT_EINVAL, "layer %u, %u rows", layer, rows);
+    const ConvPlan p = plan_conv(c, layer, rows);
+    if (split) *split = p.split;
+    if (workgroups) *workgroups = p.tiles;
+    return MT_OK;
 }
 
 mt_status mt_debug_poison(mt_ctx* c)

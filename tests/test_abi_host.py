@@ -418,3 +418,40 @@ def test_row_tiling_of_convolution_layers():
     assert t(14, 14, 1024) is None                                                                                             # not even one row does
     assert t(56, 56, 64, stride=2) is None and t(56, 56, 64, ksize=1) is None and t(224, 224, 3, ksize=7, stride=2) is None
     assert t(8, 200, 16) is None                                                                                               # a row is wider than a tile
+
+
+def conv_fleet(n_mlps, cnns, dtype=B.MT_BF16):
+    """Host-only context with the given first convolutions (h, w, c_in, c_out), each of a tenant of its own, and small MLPs."""
+    c = host_ctx(dtype, arena=64 << 20, max_width=max(h * w * max(ci + 7 & -8, co) for h, w, ci, co in cnns), max_tenants=n_mlps + len(cnns))
+    for t, (h, w, ci, co) in enumerate(cnns):
+        specs = [B.layer_spec(B.MT_CONV2D, B.MT_ACT_RELU, ci, co, h, w, 1), B.layer_spec(B.MT_GAP, B.MT_ACT_NONE, co, co, h, w), fc(co, 10)]
+        c.register_model(t, specs, *zeros_for(specs, dtype))
+    for t in range(len(cnns), len(cnns) + n_mlps):
+        c.register_model(t, [fc(32, 10)], *zeros_for([fc(32, 10)], dtype))
+    return c
+
+
+def test_convolution_launches_cover_every_split_of_the_requests_and_little_more():
+    """One model with many pixels and few channels beside one with few pixels and many channels: the launch holds the tiles of any
+    split of the requests, no more than the heaviest model could have, and fits a launch (fewer than 2^32 work items)."""
+    cnns = [(224, 224, 3, 32), (7, 7, 512, 1024), (9, 5, 8, 40)]
+    c = conv_fleet(253, cnns)
+    rng = np.random.default_rng(7)
+    for rows in (1, 3, 31, 120, 1000):
+        split, n = c.debug_conv_launch(0, rows)
+        pixels, channels = (32, 32) if split else (128, 128)
+
+        def tiles(counts):
+            # (a launch of ordinary tiles may cut an image into whole rows: 224 pixels of a row and its neighbour per 256 slots)
+            def pix(h, w):
+                t = mt.debug_conv_row_tiling(h, w, 8 if h != 7 else 512)
+                if split or not t:
+                    return h * w
+                return 128 // t["images_per_tile"] if t["images_per_tile"] > 1 else 128 * t["tiles_per_image"]
+            return sum(-(-int(m) * pix(h, w) // pixels) * -(-co // channels) for m, (h, w, _, co) in zip(counts, cnns) if m)
+
+        worst = max(tiles([rows if i == t else 0 for i in range(3)]) for t in range(3))
+        assert worst <= n <= worst + sum(-(-co // channels) for *_, co in cnns), (rows, split, n, worst)
+        assert n * (1024 if split else 256) < 1 << 32
+        for _ in range(20):
+            assert tiles(rng.multinomial(rows, [0.3, 0.4, 0.3])) <= n
