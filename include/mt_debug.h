@@ -69,11 +69,13 @@ int mt_debug_conv_row_tiling(uint32_t in_h, uint32_t in_w, uint32_t in_channels,
                              uint32_t* rows_per_tile, uint32_t* images_per_tile, uint32_t* tiles_per_image, uint64_t* frame_bytes);
 
 /* Measurement and test aid: how a run of `rows` requests launches the convolutions of one layer index over the models
- * registered now.  *split is 1 if the launch takes tiles of 32 pixels and one block of 32 channels whose wavefronts share
- * the reduction, else 0; *workgroups is the size of the launch (a bound of the tiles over every split of the requests among
- * the tenants; 0: no registered model has a convolution there).  NULL outputs are skipped.  Works on host-only
- * contexts.  Errors: MT_EINVAL (null context, layer out of range, zero rows). */
-mt_status mt_debug_conv_launch(mt_ctx* ctx, uint32_t layer, uint32_t rows, uint32_t* split, uint64_t* workgroups);
+ * registered now.  counts[t] ([max_tenants]) is the number of requests of tenant t, adding up to `rows`, in a run whose
+ * submissions all named their tenant; NULL: the tenants stand in a device-resident id array.  *split is 1 if the launch
+ * takes tiles of 32 pixels and one block of 32 channels whose wavefronts share the reduction, else 0; *workgroups is the
+ * size of the launch (a bound of its tiles; without counts, over every split of the requests among the tenants; 0: no
+ * registered model has a convolution there).  NULL outputs are skipped.  Works on host-only contexts.
+ * Errors: MT_EINVAL (null context, layer out of range, zero rows), MT_ENOTFOUND (requests of a tenant without a model). */
+mt_status mt_debug_conv_launch(mt_ctx* ctx, uint32_t layer, uint32_t rows, const uint32_t* counts, uint32_t* split, uint64_t* workgroups);
 
 /* Measurement aid: what a loop of nothing but bf16 matrix instructions sustains on the current
  * device.  Runs, on `stream`, a kernel in which every wavefront issues v_mfma_f32_32x32x16_bf16

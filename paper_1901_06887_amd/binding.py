@@ -121,7 +121,7 @@ def load_library() -> ctypes.CDLL:
     L.mt_debug_big_tile_walk.restype = u32
     L.mt_debug_conv_row_tiling.argtypes = [u32, u32, u32, u32, u32, u32, ctypes.POINTER(u32), ctypes.POINTER(u32), ctypes.POINTER(u32), ctypes.POINTER(ctypes.c_uint64)]
     L.mt_debug_conv_row_tiling.restype = ctypes.c_int
-    L.mt_debug_conv_launch.argtypes = [vp, u32, u32, ctypes.POINTER(u32), ctypes.POINTER(ctypes.c_uint64)]
+    L.mt_debug_conv_launch.argtypes = [vp, u32, u32, ctypes.POINTER(u32), ctypes.POINTER(u32), ctypes.POINTER(ctypes.c_uint64)]
     L.mt_set_profiling.argtypes = [vp, ctypes.c_int]
     L.mt_get_profile.argtypes = [vp, ctypes.POINTER(mt_profile)]
     L.mt_last_error.argtypes = [vp]
@@ -255,10 +255,14 @@ class Context:
     def debug_poison(self):
         self._check(self._lib.mt_debug_poison(self._h))
 
-    def debug_conv_launch(self, layer: int, rows: int):
-        """(tiles split their reduction, workgroups) of the convolution launch of a layer index in a run of so many requests."""
+    def debug_conv_launch(self, layer: int, rows: int, counts=None):
+        """(tiles split their reduction, workgroups) of the convolution launch of a layer index in a run of so many requests;
+        `counts`: requests per tenant, where the run's submissions name their tenants."""
         split, n = ctypes.c_uint32(), ctypes.c_uint64()
-        self._check(self._lib.mt_debug_conv_launch(self._h, layer, rows, ctypes.byref(split), ctypes.byref(n)))
+        arr = None
+        if counts is not None:
+            arr = (ctypes.c_uint32 * self.cfg.max_tenants)(*[int(v) for v in counts])
+        self._check(self._lib.mt_debug_conv_launch(self._h, layer, rows, arr, ctypes.byref(split), ctypes.byref(n)))
         return bool(split.value), n.value
 
     def tenant_account(self, tenant: int) -> dict:

@@ -30,12 +30,6 @@ constexpr uint32_t kSegSlots = MT_SEG_SLOTS;   // pinned segment tables: runs of
 constexpr uint32_t kMaxRunSlots = 4;      // runs in flight at once (each with its own device scratch); <= kSegSlots
 constexpr uint64_t kArenaAlign = 256;
 constexpr uint64_t kMaxLaunchItems = 0xffff0000u;   // work items of one launch (the grid is rounded up to a multiple of 8 or 512 workgroups)
-// Convolution launches of at most so many tiles of 32 pixels and one channel block (as the host expects them) take such
-// tiles, K split among their waves.  Passes with the line at 0 / 256 / 512 / 768 / 1024 tiles: 26-layer residual nets on
-// 224x224 images, one request 403 / 210 / 212 / 210 / 207 us, 4 requests 431 / 300 / 276 / 276 / 283, 8 requests 446 / 375 /
-// 348 / 346 / 364, 16 requests 491 / 491 / 456 / 459 / 488, 32 requests 549 / 546 / 546 / 546 / 613 (the deep layers' launches
-// of 112 tiles of 128x128 against 1600 of 32x32); MLPs, CNNs and small residual nets side by side 401 / 229 / 224 / 223 / 223.
-constexpr uint32_t kConvSplitTiles = 768;
 // profiling slots: batcher, gather, head, then gemm and gap of every layer index
 constexpr uint32_t kProfBatcher = 0, kProfGather = 1, kProfHead = 2, kProfFc = 3, kProfConv = 3 + MT_MAX_LAYERS,
                    kProfGap = 3 + 2 * MT_MAX_LAYERS, kProfBig = 3 + 3 * MT_MAX_LAYERS, kProfGatherImg = 3 + 4 * MT_MAX_LAYERS,
@@ -68,6 +62,8 @@ struct HostTenant {
 };
 
 struct FreeBlock { uint64_t off, len; };
+
+struct NamedRows { uint32_t tenant, rows; };   // requests of a tenant in the submissions that named it
 
 // Device scratch of one run in flight: batch descriptors, activation buffers, logits.  A run owns
 // one slot from its batcher to its last kernel; the weights and model tables are shared.
@@ -142,7 +138,7 @@ struct mt_ctx {
     uint64_t sum_conv_work[MT_MAX_LAYERS]{};    // sum over the registered models of output pixels x channel blocks
     uint64_t sum_conv_blocks[MT_MAX_LAYERS]{};  // ... and their sum
     uint32_t max_conv_k[MT_MAX_LAYERS]{};      // longest reduction among the registered convolutions of a layer index
-    uint32_t conv_split_tiles = kConvSplitTiles;   // testing: MT_CONV_SPLIT_TILES (0: no convolution launch splits K)
+    int64_t conv_split_tiles = -1;              // testing: MT_CONV_SPLIT_TILES in place of conv_split_line (0: no convolution launch splits K)
     uint32_t min_conv_k[MT_MAX_LAYERS]{};      // shortest reduction among the registered convolutions of a layer index
     uint32_t big_min_tiles = kBigMinTiles;   // testing: MT_BIG_MIN_TILES=1 sends every qualifying tenant-layer to big tiles
     uint32_t P_cap = 0;        // packed rows incl. per-tenant padding to 32
@@ -187,6 +183,8 @@ struct mt_ctx {
     // pending submissions
     std::vector<Segment> pending;
     uint32_t pending_rows = 0;
+    std::vector<NamedRows> named;            // scratch of mt_run (count_named); reserved in mt_create
+    std::vector<uint32_t> named_at;          // [max_tenants] 1 + a tenant's place in it, 0 between runs
 
     uint32_t last_run_rows = 0, last_run_launches = 0;
     std::string err;
@@ -563,20 +561,57 @@ struct ConvPlan {
     bool split;         // tiles of 32 pixels and one channel block whose waves split K
     uint64_t tiles;     // upper bound of the launch's tiles
 };
-ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R)
+
+// Convolution launches of at most so many tiles of 32 pixels and one channel block take such tiles, K split among their waves.
+// Chains of eight equal layers, split over unsplit time at 512 / 640 / 800 tiles (one tenant; the tiles of 16 waves come in rounds
+// of 256): LDS frames in bf16, 18 k steps (16x16x32) 0.94 / 1.00 / 1.08, 36 (8x8x64) 0.97 / 1.14 / 1.32, 72 (28x28x128) 1.03 / 1.38 /
+// 1.64, 144 (14x14x256) 0.96 / 1.29 / 1.58, 288 (7x7x512) 1.45 / 1.64 / 2.00, and at 256 / 320 tiles 0.73 / 1.17; in fp32 0.88 / 1.05 /
+// 1.21 (16x16x32), 0.73 / 0.93 / 1.14 (8x8x64), 0.35 / 0.47 / 0.58 (28x28x128); gathers in bf16 0.68 / 0.75 / 0.79 (9x9x40), 0.86 / 0.97 / 1.08
+// (1x1 over 14x14x256), 0.87 / 0.91 / 1.13 (7x7 over 14x14x64), in fp32 0.49 .. 0.91.
+uint64_t conv_split_line(const mt_ctx* c, uint32_t l, bool frames)
+{
+    constexpr uint32_t kFewSteps = 24, kManySteps = 192;
+    if (c->conv_split_tiles >= 0) return (uint64_t)c->conv_split_tiles;
+    const uint32_t k_steps = (c->max_conv_k[l] * c->elem_size + 31) / 32;
+    if (!frames) return 768;
+    if (c->elem_size == 4) return 640;
+    return k_steps <= kFewSteps ? 768 : k_steps <= kManySteps ? 512 : 256;
+}
+// Where the host does not know whose the requests are, it takes them to be spread evenly, unless their all being the
+// heaviest model's would make more than so many times the tiles of conv_split_line.  64 tenants, one of them a chain of five convolutions
+// that all requests go to, at 1 / 2 / 4 times: 28x28x128, 8 requests 95 / 141 / 141 us, 14x14x256, 32 requests 134 / 133 / 284 (with no
+// such limit 128 requests to the first 1306 instead of 237); MLPs, CNNs and small residual nets by turns, 600 requests 246 / 214 / 206.
+constexpr uint64_t kConvSplitSkew = 2;
+
+// `named`: the requests of every tenant that has any, where each submission named its tenant; null where some stand in a
+// device-resident id array
+ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<NamedRows>* named)
 {
     ConvPlan p{};
     p.frames = c->conv_img_lds[l] > 1 && !c->pool_fused[l] && !c->no_conv_img;
     p.tiles = tile_bound(c, 1, l, R);
     if (c->max_nt[1][l] == 0 || c->pool_fused[l]) return p;
-    // the launch's tiles of that shape if the requests spread evenly over the registered models (the host does not know
-    // which tenants a device-resident id array names), each of min(R, registered) tenants with a ragged one per channel block
-    const uint64_t active = std::min<uint64_t>(R, c->n_registered);
-    const uint64_t expected = R * c->sum_conv_work[l] / c->n_registered / kBrickRows + active * c->sum_conv_blocks[l] / c->n_registered / 2;
-    if (expected > c->conv_split_tiles) return p;
-    // the same bound as in tile_bound, with the ragged tiles of those with requests
-    p.split = true; p.frames = false;
-    p.tiles = R * c->max_conv_work[l] / kBrickRows + std::min<uint64_t>(c->sum_conv_blocks[l], active * c->max_conv_blocks[l]);
+    const uint64_t line = conv_split_line(c, l, p.frames), active = std::min<uint64_t>(R, c->n_registered);
+    // at most (every request the heaviest model's): the same bound as in tile_bound, with the ragged tiles of those with requests
+    uint64_t tiles = R * c->max_conv_work[l] / kBrickRows + std::min<uint64_t>(c->sum_conv_blocks[l], active * c->max_conv_blocks[l]);
+    bool split = tiles <= line;
+    if (!split && named) {
+        uint64_t n = 0;
+        for (const NamedRows& r : *named) {
+            const HostTenant& t = c->tenants[r.tenant];
+            if (l >= t.n_layers || t.layers[l].dev.kind != MT_CONV2D) continue;
+            const LayerDev& L = t.layers[l].dev;
+            n += ((uint64_t)r.rows * L.rows_per_req + kBrickRows - 1) / kBrickRows * (L.N_pad / kBrickRows);
+            if (n > line) break;
+        }
+        split = n <= line;
+        if (split) tiles = std::max<uint64_t>(n, 1);          // (none: an empty launch, as mt_estimate_run counts them)
+    } else if (!split) {
+        // the requests spread evenly over the registered models, a ragged tile per channel block of those with requests
+        const uint64_t even = R * c->sum_conv_work[l] / c->n_registered / kBrickRows + active * c->sum_conv_blocks[l] / c->n_registered / 2;
+        split = even <= line && tiles <= kConvSplitSkew * line;
+    }
+    if (split) { p.split = true; p.frames = false; p.tiles = tiles; }
     return p;
 }
 
@@ -891,6 +926,8 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
     c->elem_size = cfg->dtype == MT_BF16 ? 2 : 4;
     c->S = round_up(cfg->max_width, kWidthAlign);
     c->C_pad = round_up(cfg->max_classes, 4);
+    c->named.reserve(cfg->max_tenants);
+    c->named_at.assign(cfg->max_tenants, 0);
     c->P_cap = round_up(cfg->max_requests, kBrickRows) + kBrickRows * std::min(cfg->max_tenants, cfg->max_requests);
     if (const char* e = getenv("MT_FC_SPLIT_K")) c->fc_split_k = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_AUTO_SPLIT_K")) c->no_auto_split_k = atoi(e) != 0;
@@ -899,7 +936,7 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
     if (const char* e = getenv("MT_NO_FUSED_POOL")) c->no_fused_pool = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_IMG")) c->no_conv_img = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_FUSED_ADD")) c->no_fused_add = atoi(e) != 0;
-    if (const char* e = getenv("MT_CONV_SPLIT_TILES")) c->conv_split_tiles = (uint32_t)std::max(0, atoi(e));
+    if (const char* e = getenv("MT_CONV_SPLIT_TILES")) c->conv_split_tiles = std::max(0, atoi(e));
     if (const char* e = getenv("MT_BIG_WALK")) c->big_walk = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_LOADERS")) c->no_conv_loaders = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_UNIFORM")) c->no_conv_uniform = atoi(e) != 0;
@@ -1306,6 +1343,24 @@ uint64_t carve_static_slot(const mt_ctx* c, uint32_t R, RunSlot* rs, uint32_t* d
     return at;
 }
 
+// The pending requests per tenant, if every submission named its tenant and some model has convolutions (which are
+// planned by them); else null.  In the order of first submission.
+const std::vector<NamedRows>* count_named(mt_ctx* c)
+{
+    bool convs = false;
+    for (uint32_t g = 0; g < MT_MAX_LAYERS / kLayerGroup; ++g) convs = convs || ((c->list_mask[g] >> kLayerGroup) & ((1u << kLayerGroup) - 1));
+    for (const Segment& s : c->pending) convs = convs && !s.ids;
+    if (!convs) return nullptr;
+    c->named.clear();
+    for (const Segment& s : c->pending) {
+        uint32_t& at = c->named_at[(uint32_t)s.tenant];
+        if (!at) { c->named.push_back({(uint32_t)s.tenant, 0}); at = (uint32_t)c->named.size(); }
+        c->named[at - 1].rows += s.n_rows;
+    }
+    for (const NamedRows& r : c->named) c->named_at[r.tenant] = 0;
+    return &c->named;
+}
+
 mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t* n_rows, bool use_static);
 
 }  // namespace
@@ -1396,6 +1451,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     const double run_flops = 2.0 * R * (c->n_registered ? c->sum_macs / c->n_registered : 0.0);
     const bool big_enabled = R >= (uint32_t)kBigMinBatch && run_flops >= kRidgeFlopsPerByte * (double)c->arena_used;
     const bool split_k = run_split_k(c, R);
+    const std::vector<NamedRows>* named = count_named(c);
     BatchArgs b{};
     b.segs = c->d_segs[slot]; b.n_segs = n_segs; b.R = R; b.T = T; b.n_layer_slots = c->n_layer_slots;
     b.first = c->pending[0]; b.row_src = c->d_row_src; b.elem_size = c->elem_size;
@@ -1413,7 +1469,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
         b.list_mask[g] = big_enabled ? c->list_mask[g] : c->list_mask[g] & ((1u << (2 * kLayerGroup)) - 1);   // no big-tile lists to build
     b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles;
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) {
-        if (plan_conv(c, l, R).split) b.conv_split[l / 32] |= 1u << l % 32;
+        if (plan_conv(c, l, R, named).split) b.conv_split[l / 32] |= 1u << l % 32;
     }
     const OutPtrs outp{out->labels, out->probs, out->logits, out->n_classes, out->row_stride};
     b.out = outp;
@@ -1473,7 +1529,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
         // pooled activation is where the pooling layer would have written it
         if (l > 0 && c->pool_fused[l - 1]) continue;
         for (int kind = 0; kind < kListKinds; ++kind) {
-            const ConvPlan conv = kind == 1 ? plan_conv(c, l, R) : ConvPlan{};
+            const ConvPlan conv = kind == 1 ? plan_conv(c, l, R, named) : ConvPlan{};
             const uint64_t grid = kind == 1 ? conv.tiles : tile_bound(c, kind, l, R, split_k, big_enabled);
             if (grid == 0 || (kind == 2 && (!big_enabled || grid < c->big_min_tiles))) continue;   // no big tiles possible: the batcher made none
             GemmArgs ga{};
@@ -1697,7 +1753,7 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
         const bool big_layer = big_tiles >= c->big_min_tiles;
         double w_mb = 0.0, l2_mb = 0.0, chain = 0.0, big_us = 0.0, conv_mb = 0.0, conv_mflop = 0.0, gap_mb = 0.0, ops_mb = 0.0;
         double big_rounds_k = 0.0, conv_chain = 0.0;
-        const ConvPlan conv_plan = plan_conv(c, l, R);                                               // the launch decision of run_impl
+        const ConvPlan conv_plan = plan_conv(c, l, R, nullptr);                                      // the launch decision of run_impl where the tenants stand in an id array
         const bool conv_frames = conv_plan.frames;
         double split_steps = 0.0, split_longest = 0.0;
         for (uint32_t t = 0; t < T; ++t) {
@@ -1893,11 +1949,17 @@ int mt_debug_conv_row_tiling(uint32_t in_h, uint32_t in_w, uint32_t in_channels,
     return r.n_oh != 0;
 }
 
-mt_status mt_debug_conv_launch(mt_ctx* c, uint32_t layer, uint32_t rows, uint32_t* split, uint64_t* workgroups)
+mt_status mt_debug_conv_launch(mt_ctx* c, uint32_t layer, uint32_t rows, const uint32_t* counts, uint32_t* split, uint64_t* workgroups)
 {
     if (!c) return MT_EINVAL;
     if (layer >= MT_MAX_LAYERS || rows == 0) return fail(c, MT_EINVAL, "layer %u, %u rows", layer, rows);
-    const ConvPlan p = plan_conv(c, layer, rows);
+    std::vector<NamedRows> named;
+    for (uint32_t t = 0; counts && t < c->cfg.max_tenants; ++t) {
+        if (!counts[t]) continue;
+        if (!c->tenants[t].registered) return fail(c, MT_ENOTFOUND, "tenant %u has no model", t);
+        named.push_back({t, counts[t]});
+    }
+    const ConvPlan p = plan_conv(c, layer, rows, counts ? &named : nullptr);
     if (split) *split = p.split;
     if (workgroups) *workgroups = p.tiles;
     return MT_OK;

@@ -455,3 +455,40 @@ def test_convolution_launches_cover_every_split_of_the_requests_and_little_more(
         assert n * (1024 if split else 256) < 1 << 32
         for _ in range(20):
             assert tiles(rng.multinomial(rows, [0.3, 0.4, 0.3])) <= n
+
+
+def test_convolutions_split_their_reduction_only_where_the_launch_has_few_tiles():
+    """One 28x28x128 layer (98 tiles of 32 pixels and 32 channels per request) among 253 small MLPs.  By an even spread 256 requests
+    would make 98 tiles, really 25088 if all are that model's: tiles that split their reduction are taken by the requests of every
+    tenant where the submissions name them, and else only if the worst case stays within twice the line."""
+    c = conv_fleet(253, [(28, 28, 128, 128)])
+
+    def counts(cnn, mlp):
+        return [cnn, mlp] + [0] * (c.cfg.max_tenants - 2)
+
+    assert c.debug_conv_launch(0, 256)[0] is False and c.debug_conv_launch(0, 11)[0] is False
+    assert c.debug_conv_launch(0, 10)[0] is True
+    assert c.debug_conv_launch(0, 5, counts(5, 0)) == (True, 490 + 4)         # the bound over every split of five requests
+    assert c.debug_conv_launch(0, 255, counts(5, 250)) == (True, 123 * 4)
+    assert c.debug_conv_launch(0, 256, counts(6, 250))[0] is False
+    assert c.debug_conv_launch(0, 256, counts(0, 256))[0] is True
+    with pytest.raises(B.MtError) as e:
+        c.unregister_model(1)
+        c.debug_conv_launch(0, 3, counts(2, 1))
+    assert e.value.status == 3
+
+
+def test_where_the_line_lies_for_split_convolutions():
+    """Few, some and many k steps from LDS frames, and gathered windows; one model, one tenant."""
+    def most_rows(dtype, h, w, ci, co):
+        c = conv_fleet(0, [(h, w, ci, co)], dtype)
+        rows = 1
+        while c.debug_conv_launch(0, rows + 1, [rows + 1])[0]:
+            rows += 1
+        return rows
+
+    assert most_rows(B.MT_BF16, 8, 4, 32, 32) == 768       # a tile per request
+    assert most_rows(B.MT_BF16, 8, 4, 64, 32) == 512
+    assert most_rows(B.MT_BF16, 8, 4, 512, 32) == 256
+    assert most_rows(B.MT_BF16, 8, 4, 40, 32) == 768       # gathered: 40 channels are not whole k steps
+    assert most_rows(B.MT_F32, 8, 4, 32, 32) == 640

@@ -84,6 +84,38 @@ def test_convolutions_that_split_their_reduction(monkeypatch, dtype, k, stride, 
     assert err.max() <= (5e-6 if dtype == "f32" else 1e-2)
 
 
+# one layer index whose convolutions differ in pixels, channel blocks and reduction, beside tenants without any; requests spread, all the
+# model's with the most pixels, all the one's with the most channels, and none a convolution's; submitted by ids and tenant by tenant
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows", [3, 70, 400])
+@pytest.mark.parametrize("share", [(0.3, 0.3, 0.3, 0.1), (1, 0, 0, 0), (0, 1, 0, 0), (0, 0, 0, 1)])
+def test_unlike_convolutions_at_one_layer_index(dtype, rows, share):
+    conv = lambda ci, co, h, s, k: wl.LayerSpec(wl.CONV, wl.ACT_RELU, ci, co, h, h, s, ksize=k, pad=(k - 1) // 2)  # noqa: E731
+    tail = lambda c, h, n: [wl.LayerSpec(wl.GAP, wl.ACT_NONE, c, c, h, h), wl.LayerSpec(wl.FC, wl.ACT_NONE, c, n)]  # noqa: E731
+    models = [[conv(3, 8, 12, 1, 3), conv(8, 8, 12, 1, 3), *tail(8, 12, 5)], [conv(3, 96, 12, 2, 3), conv(96, 160, 6, 2, 3), *tail(160, 3, 7)],
+              [conv(3, 16, 12, 2, 7), conv(16, 40, 6, 1, 1), *tail(40, 6, 3)], wl.mlp_layers([432, 40, 9], wl.ACT_RELU)]
+    tenants = {t: wl.make_model(m, dtype, 335, t) for t, m in enumerate(models)}
+    rng = np.random.default_rng(335)
+    x = rng.standard_normal((rows, 432)).astype(np.float32)
+    ids = np.sort(rng.choice(4, rows, p=share)).astype(np.int32)
+    w = wl.Workload("unlike", dtype, tenants, ids, wl.round_to_bf16(x) if dtype == "bf16" else x)
+    ctx = make_context(w, max_tenants=70)
+    what = "%s, %d rows, %s" % (dtype, rows, share)
+    check(w, what, ctx)
+    d_x, out = torch_io.to_device(w.inputs, dtype), torch_io.alloc_outputs(rows, ctx.cfg.max_classes)
+    for t in np.unique(ids):
+        first, n = int(np.argmax(ids == t)), int((ids == t).sum())
+        for at, part in ((first, n // 2), (first + n // 2, n - n // 2)):
+            if part:
+                ctx.submit(int(t), d_x.data_ptr() + at * 432 * d_x.element_size(), part)
+    ctx.debug_poison()
+    ctx.run(torch.cuda.current_stream().cuda_stream, out.labels.data_ptr(), out.probs.data_ptr(), out.logits.data_ptr(),
+            out.n_classes.data_ptr(), rows, ctx.cfg.max_classes)
+    torch.cuda.synchronize()
+    got = (out.logits.cpu().numpy().astype(np.float64), out.probs.cpu().numpy().astype(np.float64), out.labels.cpu().numpy(), out.n_classes.cpu().numpy())
+    compare(w, got, oracle_rows(w), what=what + ", by tenant")
+
+
 # frames whose K loop moves in groups of four k steps inside a tap (64 bf16 or 32 fp32 channels): one, two and more groups per tap,
 # an odd number of them in all, one to four channel blocks, images that fill half of the pixel slots, and a tenant in the same launch
 # whose taps are not whole groups
