@@ -97,9 +97,11 @@ __device__ __forceinline__ void lds_dma16_buffer(const u32x4& desc, uint32_t vof
 // ends, with nothing else running: a convolution launch that writes some 10-50 MB ends 1.2-1.7 us earlier with these (residual nets, 64
 // images, 19 such launches: 30.5 -> 28.8, 36.3 -> 34.8, 20.0 -> 18.4 us).  Passes that write all the time lose (image gather 26 -> 37 us).
 // In asm: the compiler has no store of this size and scope; its wait counts only become stricter by stores that it does not know of.
+// Two wait states, in the asm because the compiler does not know that it is a store: from gfx940 on a vector instruction
+// may overwrite the data of a store wider than 8 bytes only behind them.
 __device__ __forceinline__ void store_through(u32x4* dst, const u32x4& v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" :: "v"(dst), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(dst), "v"(v) : "memory");
 }
 
 // Inclusive prefix sums across lanes with data-parallel-primitive moves (no LDS traffic): shifts
