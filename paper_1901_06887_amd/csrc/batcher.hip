@@ -1,5 +1,6 @@
 // Tenant segmentation and grouped-work descriptors (see mt_device.h for the overview).
 #include "mt_device.h"
+#include <type_traits>
 
 namespace mt {
 
@@ -41,20 +42,6 @@ __device__ uint32_t block_exclusive_scan(uint32_t* data, uint32_t n, uint32_t* t
     return total;
 }
 
-// Tenant segmentation and grouped-work descriptors.  One workgroup; every step is
-// deterministic: rows of a tenant keep their arrival order (stable counting sort).  Equal
-// tenant ids inside a wavefront are found with one ballot per id bit, so a step costs the
-// same whatever the tenant mix is.  Latency, not bandwidth, bounds this kernel, so everything
-// that does not depend on the rows (tenant and layer facts) is fetched up front, and waves wait
-// for each other as little as possible: with at most 64 tenants every wave holds all of
-// them in its lanes and works out totals and offsets for itself (two barriers in the whole kernel),
-// and a tile list belongs to one wave, which scans it 64 tenants at a time.
-// Kernel trace, this form against one whose 1024 threads were the tenants and built the lists of eight layer indices
-// at a time with three barriers per eight: 1 request to 8 three-layer models 7.8 -> 4.0 us, 4096 requests to 64 of
-// them 13.0 -> 10.6, 1 request to 26-layer models 20.4 -> 5.8, behind the ranking kernel (32768 rows, 8 tenants)
-// 13.9 -> 6.1, with 256 tenants 14.4 -> 13.6.
-// ITERS: rows a lane may keep in registers (64 * ITERS rows per wave); the launcher picks the smallest
-// instantiation that covers the batch, because the unrolled steps of a larger one cost small batches microseconds.
 // A row's packed position is known: note it both ways; a rejected row (t < 0: unknown tenant or
 // no model) is answered at once with label -1 and zero rows.
 __device__ __forceinline__ void place_row(const BatchArgs& a, uint32_t r, int32_t t, uint32_t position)
@@ -143,12 +130,27 @@ __global__ __launch_bounds__(kBatchThreads) void rank_kernel(BatchArgs a)
     if (t >= 0) a.row_rank[r] = whist[w * Tp + t] + rank;
 }
 
+// Tenant segmentation and grouped-work descriptors.  One workgroup; every step is deterministic: rows of a tenant keep their
+// arrival order (stable counting sort).  Equal tenant ids inside a wavefront are found with one ballot per id bit, so a step
+// costs the same whatever the tenant mix is.  Latency, not bandwidth, bounds this kernel, so everything that does not depend on the
+// rows (tenant and layer facts) is fetched up front, and waves wait for each other as little as possible: with at most
+// 64 tenants every wave holds all of them in its lanes and works out totals and offsets for itself (two barriers in the whole
+// kernel, a third where big tiles are possible), and a tile list belongs to one wave.
+// Kernel trace, this form against one whose 1024 threads were the tenants and built the lists of eight layer indices
+// at a time with three barriers per eight: 1 request to 8 three-layer models 7.8 -> 4.0 us, 4096 requests to 64 of
+// them 13.0 -> 10.6, 1 request to 26-layer models 20.4 -> 5.8, behind the ranking kernel (32768 rows, 8 tenants) 13.9 -> 6.1.
+// Many tenants, three layers, 256 / 4096 / 16384 requests: 256 tenants 11.0 -> 8.8 / 15.6 -> 13.2 / 20.0 -> 15.5 (three kernels), 1024 15.1 -> 12.4 /
+// 33.2 -> 29.0 / 53.2 -> 49.8, 2048 25.0 -> 19.2 / 58.3 -> 51.0 / 118.1 -> 108.9; thirteen layers, 2048 tenants 38.2 -> 28.6 / 70.5 -> 70.1 /
+// 132.4 -> 122.4.  (Lists walked 64 tenants at a time, facts of a tenant's layers side by side, rows placed by the waves that
+// ranked them: 29.3 / 64.8 / 150.1, thirteen layers 45.0 / 84.9 / 152.5.)
+// ITERS: rows a lane may keep in registers (64 * ITERS rows per wave); the launcher picks the smallest
+// instantiation that covers the batch, because the unrolled steps of a larger one cost small batches microseconds.
 template <bool ONE_SEG, int ITERS, bool PRE = false>
 __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
 {
     constexpr uint32_t kWaves = kBatchThreads / 64;
     __shared__ uint32_t hist[kHistEntries];
-    __shared__ uint32_t Ml[kMaxTenantsPadded];
+    __shared__ __attribute__((aligned(16))) uint32_t Ml[kMaxTenantsPadded];
     __shared__ uint32_t offl[kMaxTenantsPadded];
     __shared__ uint8_t regl[kMaxTenantsPadded];
     __shared__ uint32_t tmp[17];
@@ -193,23 +195,17 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
 #pragma unroll
         for (uint32_t it = 0; it < kRegIters; ++it) tq[it] = fetch_id(begin + it * 64 + lane);
     }
-    // The tile lists of layer index l (three kinds) belong to wave l % 16, which walks them 64 tenants at a time:
-    // step i of the wave is chunk i % n_chunks of its (i / n_chunks)-th layer index.  A step needs the fact words
-    // of its 64 tenant-layers (BatchArgs::facts); the first kPre steps' are fetched here.
+    // The tile lists of layer index l (three kinds) belong to wave l % 16, which walks them 64 tenants at a time, or 256
+    // (four neighbours a lane) where there are more than 64.  A step needs the fact words of its tenant-layers
+    // (BatchArgs::facts); those of the wave's first steps are fetched here: four layer indices of up to 64 tenants, or 256 tenants of one.
     constexpr uint32_t kPre = 4;
-    const uint32_t n_chunks = ceil_div(T, 64), n_steps = w < a.n_layer_slots ? ceil_div(a.n_layer_slots - w, kWaves) * n_chunks : 0;
-    auto load_facts = [&](uint32_t l, uint32_t c) -> uint4 {
-        const uint32_t t = c * 64 + lane;
-        return t < T ? ((const uint4*)a.facts)[(size_t)t * MT_MAX_LAYERS + l] : uint4{0, 0, 0, 0};
+    static_assert(MT_MAX_LAYERS <= kPre * kWaves, "with at most 64 tenants, every step of a wave is fetched ahead");
+    auto load_fact = [&](uint32_t l, uint32_t t) -> uint4 {
+        return l < a.n_layer_slots && t < T ? ((const uint4*)a.facts)[(size_t)l * T + t] : uint4{0, 0, 0, 0};
     };
-    auto next_step = [&](uint32_t& l, uint32_t& c) { if (++c == n_chunks) { c = 0; l += kWaves; } };
     uint4 fq[kPre];
-    uint32_t l = w, c = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < kPre; ++i) {
-        fq[i] = i < n_steps ? load_facts(l, c) : uint4{0, 0, 0, 0};
-        next_step(l, c);
-    }
+    for (uint32_t i = 0; i < kPre; ++i) fq[i] = one_wave ? load_fact(w + i * kWaves, lane) : load_fact(w, lane * kPre + i);
     for (uint32_t t = tid; t < Tp; t += kBatchThreads) regl[t] = t < T && a.tenants[t].registered;
     for (uint32_t i = tid; i < nw * Tp; i += kBatchThreads) hist[i] = PRE ? a.hist_g[i] : 0;
     if (tid == 0) big_l = 0;
@@ -318,10 +314,17 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
         const uint32_t base = one_wave ? (uint32_t)__shfl((int)base1, (int)(tl & 63)) : offl[tl] + hist[w * Tp + tl];
         if (r < end) place_row(a, r, t, base + rank);
     };
+    // (unless most waves ranked none: with more than 512 tenants the histograms leave room for eight or four of the sixteen)
     if (in_regs) {
 #pragma unroll
         for (uint32_t it = 0; it < kRegIters; ++it)
             if (begin + it * 64 < end) place(begin + it * 64 + lane, tq[it] < 0 ? -1 : (tq[it] & 2047), (uint32_t)tq[it] >> 11);
+    } else if (!PRE && nw < kWaves) {
+#pragma unroll 4
+        for (uint32_t r = tid; r < R; r += kBatchThreads) {
+            const int32_t t = a.row_tenant[r];
+            place_row(a, r, t, t >= 0 ? offl[t] + hist[r / chunk * Tp + t] + a.row_rank[r] : 0);
+        }
     } else if (!PRE) {
         for (uint32_t r0 = begin; r0 < end; r0 += 64) {
             const uint32_t r = r0 + lane;
@@ -332,58 +335,107 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
 
     // pass 4: the tile lists.  Big tiles pay only when a layer index has enough of them to fill the chip; below
     // that the streaming kernel takes those tenants too, side by side with everyone else's tiles.
-    uint32_t run_fc = 0, run_conv = 0, run_big = 0;            // tiles of the tenants before this chunk
-    bool big_here = false;
-    auto tenant_rows = [&](uint32_t c) { return one_wave ? Mt1 : (c * 64 + lane < T ? Ml[c * 64 + lane] : 0u); };
-    auto list_step = [&](uint32_t l, uint32_t c, uint4 f) {
+    // One step: the J tenants a lane from t0 on, of layer index l; f: their facts, Mt: their rows.
+    uint32_t run_fc, run_conv, run_big;                        // tiles of the tenants before this step
+    auto list_step = [&](auto J_, uint32_t l, uint32_t t0, const uint4* f, const uint32_t* Mt, bool big_here, bool last) {
+        constexpr uint32_t J = decltype(J_)::value;
         const uint32_t lm = a.list_mask[l / kLayerGroup] >> (l % kLayerGroup);      // bit kind * kLayerGroup: some registered model has such tiles here
-        if (c == 0) {
-            run_fc = run_conv = run_big = 0; big_here = false;
-            if (a.big_enabled && l < (uint32_t)kBigMaxLayer && ((lm >> (2 * kLayerGroup)) & 1)) {
-                uint32_t n = 0;
-                for (uint32_t i = 0; i < n_chunks; ++i) {
-                    const uint4 g = i == 0 ? f : load_facts(l, i);
-                    const uint32_t Mt = tenant_rows(i);
-                    const bool big = g.x && !(g.x >> 31) && fc_is_big(Mt, g.y);
-                    n += __builtin_amdgcn_readlane(wave_inclusive_scan(big ? ceil_div(big_rows(Mt), kBigTile) * ceil_div(g.y, kBigTile) : 0), 63);
-                }
-                big_here = n >= a.big_min_tiles;
-                if (big_here && lane == 0) atomicOr(&big_l, 1u << l);
-            }
-        }
-        const uint32_t t = c * 64 + lane, Mt = tenant_rows(c);
-        const bool conv = f.x >> 31, sk = a.fc_split_k && !conv && f.x;                // this run's FC tiles: one column block each, 32 rows
         const bool split = (a.conv_split[l / 32] >> (l % 32)) & 1;      // this run's convolution tiles: 32 pixels, one channel block
-        const uint32_t groups = sk ? f.y / kBrickRows : conv ? ceil_div(f.x & 0x7fffffffu, split ? 1 : kTileCols / kBrickRows) : f.x & 0x3fffffffu;
-        const bool big = big_here && !conv && f.x && fc_is_big(Mt, f.y);
-        // conv: rows = requests * output pixels per tile; FC: tiles of 64 or 32 rows over the rows that big tiles leave
-        // (the few rows that big tiles leave in a narrow layer are tiled one column block and 32 rows at a time,
-        // with K split among the waves: see big_remainder_split_k)
-        static_assert(kTileRows == 64, "FC tiles have 64 or 32 rows");
-        const uint32_t Mb = big ? big_rows(Mt) : 0;
-        const bool rem_sk = big && big_remainder_split_k(f.y);
-        const uint32_t sh = sk || rem_sk || ((f.x >> 30) & 1) ? 5 : 6, gq = rem_sk ? f.y / kBrickRows : groups;
-        auto emit = [&](uint32_t kind, uint32_t n, uint32_t& run) {
+        uint32_t n_fc[J], n_conv[J], n_big[J];
+#pragma unroll
+        for (uint32_t j = 0; j < J; ++j) {
+            const uint32_t x = f[j].x, y = f[j].y, M = Mt[j];
+            const bool conv = x >> 31, sk = a.fc_split_k && !conv && x;                // this run's FC tiles: one column block each, 32 rows
+            const uint32_t blocks = x & 0x7fffffffu;                                   // (a convolution's)
+            const uint32_t groups = sk ? y / kBrickRows : x & 0x3fffffffu;
+            const bool big = big_here && !conv && x && fc_is_big(M, y);
+            // conv: rows = requests * output pixels per tile; FC: tiles of 64 or 32 rows over the rows that big tiles leave
+            // (the few rows that big tiles leave in a narrow layer are tiled one column block and 32 rows at a time,
+            // with K split among the waves: see big_remainder_split_k)
+            static_assert(kTileRows == 64, "FC tiles have 64 or 32 rows");
+            const uint32_t Mb = big ? big_rows(M) : 0;
+            const bool rem_sk = big && big_remainder_split_k(y);
+            const uint32_t sh = sk || rem_sk || ((x >> 30) & 1) ? 5 : 6, gq = rem_sk ? y / kBrickRows : groups;
+            n_fc[j] = !conv && groups && M ? ((M - Mb + (1u << sh) - 1) >> sh) * gq : 0;
+            n_conv[j] = conv && M ? (split ? ceil_div(M * f[j].z, kBrickRows) * blocks : ceil_div(M * y, kConvTileRows) * ceil_div(blocks, kTileCols / kBrickRows)) : 0;
+            n_big[j] = ceil_div(Mb, kBigTile) * ceil_div(y, kBigTile);
+        }
+        auto emit = [&](uint32_t kind, const uint32_t (&n)[J], uint32_t& run) {
             if (!((lm >> (kind * kLayerGroup)) & 1)) return;                              // lists no registered model contributes to are never read
             uint32_t* base = a.tile_base + ((size_t)kind * MT_MAX_LAYERS + l) * (T + 1);
-            const uint32_t incl = wave_inclusive_scan(n);
-            if (t < T) base[t] = run + incl - n;
-            run += __builtin_amdgcn_readlane(incl, 63);
-            if (c + 1 == n_chunks && lane == 0) base[T] = run;
-        };
-        emit(0, !conv && groups && Mt ? ((Mt - Mb + (1u << sh) - 1) >> sh) * gq : 0, run_fc);
-        emit(1, conv && Mt ? (split ? ceil_div(Mt * f.z, kBrickRows) : ceil_div(Mt * f.y, kConvTileRows)) * groups : 0, run_conv);
-        emit(2, ceil_div(Mb, kBigTile) * ceil_div(f.y, kBigTile), run_big);
-    };
-    l = w; c = 0;
+            uint32_t mine = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < kPre; ++i) {
-        if (i < n_steps) list_step(l, c, fq[i]);
-        next_step(l, c);
-    }
-    for (uint32_t i = kPre; i < n_steps; ++i) {
-        list_step(l, c, load_facts(l, c));
-        next_step(l, c);
+            for (uint32_t j = 0; j < J; ++j) mine += n[j];
+            const uint32_t incl = wave_inclusive_scan(mine);
+            uint32_t at = run + incl - mine;
+#pragma unroll
+            for (uint32_t j = 0; j < J; ++j) {
+                if (t0 + j < T) base[t0 + j] = at;
+                at += n[j];
+            }
+            run += __builtin_amdgcn_readlane(incl, 63);
+            if (last && lane == 0) base[T] = run;
+        };
+        emit(0, n_fc, run_fc);
+        emit(1, n_conv, run_conv);
+        emit(2, n_big, run_big);
+    };
+    auto big_possible = [&](uint32_t l) {
+        return a.big_enabled && l < (uint32_t)kBigMaxLayer && ((a.list_mask[l / kLayerGroup] >> (2 * kLayerGroup + l % kLayerGroup)) & 1);
+    };
+    auto big_tiles = [&](uint4 f, uint32_t M) {
+        return f.x && !(f.x >> 31) && fc_is_big(M, f.y) ? ceil_div(big_rows(M), kBigTile) * ceil_div(f.y, kBigTile) : 0u;
+    };
+    auto take_big = [&](uint32_t l, uint32_t n) {              // n: big tiles of this lane's tenants at layer index l
+        const bool yes = __builtin_amdgcn_readlane(wave_inclusive_scan(n), 63) >= a.big_min_tiles;
+        if (yes && lane == 0) atomicOr(&big_l, 1u << l);
+        return yes;
+    };
+    if (one_wave) {
+#pragma unroll
+        for (uint32_t i = 0; i < kPre; ++i) {
+            const uint32_t l = w + i * kWaves;
+            if (l >= a.n_layer_slots) break;
+            run_fc = run_conv = run_big = 0;
+            list_step(std::integral_constant<uint32_t, 1>{}, l, lane, &fq[i], &Mt1, big_possible(l) && take_big(l, big_tiles(fq[i], Mt1)), true);
+        }
+    } else {
+        constexpr uint32_t kStep = 64 * kPre;
+        auto rows_of = [&](uint32_t t0, uint32_t (&M)[kPre]) {
+            static_assert(kPre == 4 && kMaxTenantsPadded % kStep == 0, "one 16-byte read; tables of whole steps");
+            const u32x4 m = *(const u32x4*)(Ml + t0);          // (entries from T on may never have been written)
+#pragma unroll
+            for (uint32_t j = 0; j < kPre; ++j) M[j] = t0 + j < T ? m[j] : 0;
+        };
+        for (uint32_t l = w; l < a.n_layer_slots; l += kWaves) {
+            run_fc = run_conv = run_big = 0;
+            bool big_here = false;
+            if (l != w) {
+#pragma unroll
+                for (uint32_t j = 0; j < kPre; ++j) fq[j] = load_fact(l, lane * kPre + j);
+            }
+            if (big_possible(l)) {
+                uint32_t n = 0;
+                for (uint32_t t0 = lane * kPre; t0 - lane * kPre < T; t0 += kStep) {
+                    uint32_t M[kPre];
+                    rows_of(t0, M);
+#pragma unroll
+                    for (uint32_t j = 0; j < kPre; ++j) n += big_tiles(t0 < kStep ? fq[j] : load_fact(l, t0 + j), M[j]);
+                }
+                big_here = take_big(l, n);
+            }
+            for (uint32_t first = 0; first < T; first += kStep) {
+                const uint32_t t0 = first + lane * kPre;
+                uint4 ahead[kPre];                             // the next step's facts are asked for before this step's stores
+#pragma unroll
+                for (uint32_t j = 0; j < kPre; ++j) ahead[j] = load_fact(l, t0 + kStep + j);
+                uint32_t M[kPre];
+                rows_of(t0, M);
+                list_step(std::integral_constant<uint32_t, kPre>{}, l, t0, fq, M, big_here, first + kStep >= T);
+#pragma unroll
+                for (uint32_t j = 0; j < kPre; ++j) fq[j] = ahead[j];
+            }
+        }
     }
     if (a.big_enabled) __syncthreads();
     if (tid == 0) *a.big_layers = big_l;               // the FC kernels split a qualifying tenant's rows by it

@@ -152,7 +152,7 @@ struct mt_ctx {
     TenantDev* d_tenants = nullptr;
     LayerDev* d_layers = nullptr;
     uint64_t* d_served = nullptr;      // [max_tenants][2]: requests served, runs with at least one request (accounting)
-    uint32_t* d_facts = nullptr;       // [max_tenants][MT_MAX_LAYERS][kFactWords]: the batcher's view of the layers (BatchArgs::facts)
+    uint32_t* d_facts = nullptr;       // [MT_MAX_LAYERS][max_tenants][kFactWords]: the batcher's view of the layers (BatchArgs::facts)
     int32_t* d_row_tenant = nullptr;
     uint32_t* d_row_rank = nullptr;
     uint32_t* d_hist_g = nullptr;      // [kHistEntries] per-workgroup tenant histograms of the ranking kernel
@@ -340,12 +340,12 @@ struct RowsPiece {
     TenantDev td;
 };
 static_assert(sizeof(RowsPiece) <= 2048, "a piece of a tenant's table rows must fit kernel arguments");
-__global__ void install_rows_kernel(RowsPiece piece, LayerDev* rows, uint32_t* facts, TenantDev* td)
+__global__ void install_rows_kernel(RowsPiece piece, LayerDev* rows, uint32_t* facts, uint32_t n_tenants, TenantDev* td)
 {
     const uint32_t* src_rows = (const uint32_t*)piece.rows;
     for (uint32_t i = threadIdx.x; i < sizeof(piece.rows) / 4; i += blockDim.x) ((uint32_t*)rows)[i] = src_rows[i];
-    const uint32_t* src_facts = &piece.facts[0][0];
-    for (uint32_t i = threadIdx.x; i < sizeof(piece.facts) / 4; i += blockDim.x) facts[i] = src_facts[i];
+    for (uint32_t i = threadIdx.x; i < sizeof(piece.facts) / 4; i += blockDim.x)
+        facts[(size_t)(i / kFactWords) * n_tenants * kFactWords + i % kFactWords] = piece.facts[i / kFactWords][i % kFactWords];
     if (!td) return;
     __threadfence();
     __syncthreads();
@@ -381,7 +381,7 @@ hipError_t install_rows(mt_ctx* c, uint32_t tenant, const StageTail& tail, hipSt
         piece.td = tail.td;
         const bool with_td = tail.td.registered ? g + 1 == n_pieces : g == 0;
         hipLaunchKernelGGL(install_rows_kernel, dim3(1), dim3(256), 0, s, piece, c->d_layers + (size_t)tenant * MT_MAX_LAYERS + g * kLayerGroup,
-                           c->d_facts + ((size_t)tenant * MT_MAX_LAYERS + g * kLayerGroup) * kFactWords, with_td ? c->d_tenants + tenant : nullptr);
+                           c->d_facts + ((size_t)g * kLayerGroup * c->cfg.max_tenants + tenant) * kFactWords, c->cfg.max_tenants, with_td ? c->d_tenants + tenant : nullptr);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -159,7 +159,8 @@ struct BatchArgs {
     uint32_t big_enabled;  // 0: no tenant-layer is given big tiles in this run (small batches)
     uint32_t big_min_tiles; // a layer index uses big tiles only when its qualifying tenants make at least this many
     const TenantDev* tenants;
-    // What the tile lists need to know of every tenant-layer: facts[tenant][layer][kFactWords].
+    // What the tile lists need to know of every tenant-layer: facts[layer][T tenants][kFactWords], so that the 64 tenants of
+    // a wave's load lie side by side.
     // Word 0, FC: column groups of the layer's tiles, bit 30: tiles of 32 rows instead of 64; convolution: bit 31 and the
     // channel blocks of 32 (a tile takes four of them, or one where the launch splits K); 0: no tiles (pooling, or no such layer).
     // Word 1: padded outputs (FC), rows per request by which the tiles are counted (convolution: conv_tile_rows).  Word 2: a convolution's output pixels.

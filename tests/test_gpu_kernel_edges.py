@@ -46,6 +46,53 @@ def test_segmentation_at_the_edges_of_its_register_paths(n_tenants, n_requests):
     assert np.array_equal(out.logits.cpu().numpy().astype(np.float64), one[0]) and np.array_equal(out.labels.cpu().numpy(), one[2])
 
 
+# more than 256 tenants: a tile list takes several steps of 256; more than 512: the histograms leave room for eight or four ranking waves.
+# Models of one to three linear layers, a convolution, or none, at tenant numbers around the steps; few and many rows, one submission and three
+@pytest.mark.parametrize("n_tenants", [257, 513, 1023, 1025, 2048])
+@pytest.mark.parametrize("n_requests", [200, 5003])
+def test_tile_lists_of_many_tenants(n_tenants, n_requests):
+    edges = [t + d for t in range(0, n_tenants + 1, 256) for d in (-1, 0, 1, 2, 3)]
+    hosts = sorted({t for t in edges if 0 <= t < n_tenants} | {n_tenants - 1} | set(range(5, n_tenants, 37)))
+    tenants = {}
+    for i, t in enumerate(hosts):
+        if i % 4 == 3:
+            layers = [wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, 8, 4, 4, 1, ksize=3, pad=1), wl.LayerSpec(wl.GAP, wl.ACT_NONE, 8, 8, 4, 4), wl.LayerSpec(wl.FC, wl.ACT_NONE, 8, 6)]
+        else:
+            layers = wl.mlp_layers([48, 20, 100, 5][:1] + [[5], [20, 7], [20, 100, 5]][i % 4], wl.ACT_RELU)
+        tenants[t] = wl.make_model(layers, "f32", 312, t)
+    rng = np.random.default_rng(312)
+    ids = rng.choice(hosts, n_requests).astype(np.int32)
+    ids[:len(hosts)] = hosts[:n_requests]                          # every model has a request, as far as they go
+    ids = rng.permutation(ids)
+    w = wl.Workload("many", "f32", tenants, ids, rng.standard_normal((n_requests, 48)).astype(np.float32))
+    ctx = make_context(w, max_tenants=n_tenants)
+    one = check(w, "%d tenants, %d requests" % (n_tenants, n_requests), ctx)
+    x, d_ids = torch_io.to_device(w.inputs, "f32"), torch.from_numpy(ids).cuda()
+    out = torch_io.alloc_outputs(n_requests, ctx.cfg.max_classes)
+    cuts = [0, n_requests // 3, n_requests // 2, n_requests]
+    for a, b in zip(cuts[:-1], cuts[1:]):
+        ctx.submit_batch(d_ids.data_ptr() + 4 * a, x.data_ptr() + a * 48 * 4, b - a, 48)
+    ctx.debug_poison()
+    ctx.run(torch.cuda.current_stream().cuda_stream, out.labels.data_ptr(), out.probs.data_ptr(), out.logits.data_ptr(),
+            out.n_classes.data_ptr(), n_requests, ctx.cfg.max_classes)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.logits.cpu().numpy().astype(np.float64), one[0]) and np.array_equal(out.labels.cpu().numpy(), one[2])
+
+
+@pytest.mark.parametrize("n_tenants", [300, 2048])
+def test_big_tile_lists_of_many_tenants(monkeypatch, n_tenants):
+    """Big tiles of tenants in different steps of a list, beside tenants that are too small for them."""
+    monkeypatch.setenv("MT_BIG_MIN_TILES", "1")
+    hosts = [3, 255, 256, n_tenants // 2 + 130, n_tenants - 1]
+    tenants = {t: wl.make_model(wl.mlp_layers([64, 256, 200, 7], wl.ACT_GELU), "bf16", 313, t) for t in hosts}
+    rng = np.random.default_rng(313)
+    ids = rng.permutation(np.repeat(hosts, [2048, 40, 2304 + 130, 4096 + 100, 2500])).astype(np.int32)
+    x = wl.round_to_bf16(rng.standard_normal((len(ids), 64)).astype(np.float32))
+    w = wl.Workload("many-big", "bf16", tenants, ids, x)
+    ctx = make_context(w, max_tenants=n_tenants)
+    check(w, "%d tenants" % n_tenants, ctx)
+
+
 @pytest.mark.parametrize("hw,channels,dtype", [((1, 1), 8, "f32"), ((9, 13), 72, "f32"), ((9, 13), 72, "bf16"), ((5, 7), 8, "bf16"),
                                                ((3, 3), 520, "bf16"), ((2, 5), 2056, "f32")])
 def test_average_pooling_of_any_channel_count(hw, channels, dtype):
