@@ -96,6 +96,7 @@ struct mt_ctx {
     uint32_t max_in_len = 0;
     // [kind][layer]: kind 0 = FC tiles, 1 = conv tiles, 2 = big FC tiles
     uint32_t max_nt[kListKinds][MT_MAX_LAYERS]{}, has_gap[MT_MAX_LAYERS]{};
+    uint64_t gap_chunks[MT_MAX_LAYERS]{};            // most 16-byte pieces of a request that a pooling layer of the index reads
     // pool_fused[l]: layer index l + 1 is a global average pool for every registered model that is that deep, and
     // each of their convolutions at l can pool by itself: the convolution launch writes the pooled activation
     // and nothing runs at index l + 1 (all or nothing: the activation buffers alternate per layer index)
@@ -455,7 +456,7 @@ void recompute_bounds(mt_ctx* c)
     for (uint32_t& m : c->list_mask) m = 0;
     c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
-        c->has_gap[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
+        c->has_gap[l] = 0; c->gap_chunks[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
         for (int k = 0; k < kListKinds; ++k) { c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
         c->max_fc_per64[l] = 0; c->max_fc_per64_sk[l] = 0; c->sum_nt_sk[l] = 0; c->max_big_blocks[l] = 0;
     }
@@ -475,7 +476,7 @@ void recompute_bounds(mt_ctx* c)
         for (uint32_t l = 0; l < t.n_layers; ++l) {
             const LayerDev& L = t.layers[l].dev;
             if (L.kind == kKindNone) continue;
-            if (L.kind == MT_GAP) { c->has_gap[l] = 1; continue; }
+            if (L.kind == MT_GAP) { c->has_gap[l] = 1; c->gap_chunks[l] = std::max(c->gap_chunks[l], (uint64_t)L.in_h * L.in_w * L.cin * c->elem_size / 16); continue; }
             if (L.kind == MT_MAXPOOL || L.kind == MT_ADD) { c->has_image_ops[l] = 1; c->image_op_fill[l] = std::max(c->image_op_fill[l], L.out_fill); continue; }
             const int k = L.kind == MT_FC ? 0 : 1;
             c->sum_macs += (double)L.k_valid * L.N * L.rows_per_req;
@@ -1557,7 +1558,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             pa.layer = l; pa.P = P; pa.layers = c->d_layers; pa.tenants = c->d_tenants;
             pa.off = c->d_off; pa.M = c->d_M; pa.T = T; pa.act = bufs; pa.S = c->S;
             pa.elem_size = c->elem_size;
-            TIMED(kProfGap + l, launch_gap(pa, s));
+            TIMED(kProfGap + l, launch_gap(pa, c->gap_chunks[l], s));
         }
         if (c->has_image_ops[l]) {         // max-pooling and residual additions of this layer index
             GapArgs pa{};

@@ -243,7 +243,7 @@ hipError_t prepare_conv(uint32_t dtype);   // once per device, before the first 
 // quad: every tenant's input channels at this layer index are a multiple of four 16-byte chunks
 hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s);
 hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, uint32_t grid, hipStream_t s);
-hipError_t launch_gap(const GapArgs& a, hipStream_t s);
+hipError_t launch_gap(const GapArgs& a, uint64_t chunks, hipStream_t s);   // chunks: most 16-byte pieces of a row that a model of the layer index pools
 hipError_t launch_image_ops(const GapArgs& a, uint32_t slices, hipStream_t s);   // max-pool and residual add of one layer index
 hipError_t launch_head(const HeadArgs& a, hipStream_t s);
 

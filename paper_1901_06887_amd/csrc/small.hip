@@ -148,12 +148,15 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a)
 
 // ---- global average pool: one workgroup per packed row, NHWC row in, brick slice out ------
 // Bound by the latency of its few dependent loads: thread (pg, cg) sums 16-byte chunk cg of pixels pg, pg + G, ...
-// with eight loads in flight; the G partial sums of a channel are then added in a fixed order through LDS.
-// 64 images of 7x7x512 bf16 11.9 -> 6.6 us; 150 images of 15x18x72 fp32 (18 chunks per pixel) 66.7 -> 7.6 us against a
-// form with 128 threads that took such channel counts one element per thread.
-// Launches of many rows fill the chip with workgroups of 128 threads, which start and end sooner (2265 images of 6x7x8 fp32: 14.6 us with
-// 512 threads, 8.0 with 128).
-constexpr uint32_t kGapManyRows = 1024;
+// with eight loads in flight; the G partial sums of a channel are then added in a fixed order through LDS, so G is no
+// larger than what leaves every thread its eight loads.  64 registers, so that eight waves share a SIMD.  128 images, against a form
+// with 128 threads, up to four loads in flight, and one element per thread where the chunks of a pixel do not divide 128: bf16 7x7x8 4.9 ->
+// 4.3 us, 7x7x72 17.0 -> 4.2, 7x7x512 11.1 -> 4.8, 28x28x512 119 -> 18.3, fp32 16x16x72 63.7 -> 5.0, 7x7x1024 93.4 -> 6.7.
+// Threads: 512 for up to four such workgroups per compute unit, and for rows of so many chunks that they last long anyway;
+// else 128, which start and end sooner.  512 / 128 threads: bf16 7x7x32 (196 chunks a row), 960 images 5.1 / 4.7 us, 1500 7.1 / 5.0, 4096
+// 13.0 / 6.4; fp32 16x16x72 (4608) 960 images 14.5 / 13.7, 2048 25.9 / 26.0; bf16 16x16x256 (8192) 42.9 / 43.5, 4096 130.5 / 133.8; fp32 7x7x1024
+// (12544) 115 / 136.
+constexpr uint32_t kGapManyRows = 1025, kGapManyChunks = 4096;
 template <typename T, uint32_t kGapThreads>
 __device__ void gap_row(const GapArgs& a, const LayerDev& L, uint32_t p, uint32_t seg0)
 {
@@ -168,7 +171,7 @@ __device__ void gap_row(const GapArgs& a, const LayerDev& L, uint32_t p, uint32_
     const uint32_t CPP = C / EPC;                              // 16-byte chunks per pixel (channels are a multiple of 8)
     auto put = [&](uint32_t c, float v) { out[((size_t)(c / KB) * 64 + i + 32 * ((c % KB) / EPC)) * EPC + c % EPC] = (T)v; };
     for (uint32_t c0 = 0; c0 < CPP; c0 += kGapThreads) {
-        const uint32_t ncg = min(kGapThreads, CPP - c0), G = min(kGapThreads / ncg, kMaxGroups);
+        const uint32_t ncg = min(kGapThreads, CPP - c0), G = min(min(kGapThreads / ncg, kMaxGroups), ceil_div(HW, kInFlight));
         const uint32_t pg = threadIdx.x / ncg, cg = threadIdx.x - pg * ncg;
         if (pg < G) {
             float s[EPC];
@@ -178,13 +181,15 @@ __device__ void gap_row(const GapArgs& a, const LayerDev& L, uint32_t p, uint32_
             for (uint32_t q0 = pg; q0 < HW; q0 += G * kInFlight) {
                 u32x4 v[kInFlight];
 #pragma unroll
-                for (uint32_t u = 0; u < kInFlight; ++u) v[u] = src[(size_t)min(q0 + u * G, HW - 1) * CPP];
+                for (uint32_t u = 0; u < kInFlight; ++u) v[u] = src[min(q0 + u * G, HW - 1) * CPP];
+                // without this fence, or with a branch around a use, the compiler puts every load next to its use
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (uint32_t u = 0; u < kInFlight; ++u) {
-                    if (q0 + u * G >= HW) break;
+                    const bool inside = q0 + u * G < HW;
                     const T* ve = (const T*)&v[u];
 #pragma unroll
-                    for (uint32_t e = 0; e < EPC; ++e) s[e] += (float)ve[e];
+                    for (uint32_t e = 0; e < EPC; ++e) s[e] += inside ? (float)ve[e] : 0.0f;
                 }
             }
 #pragma unroll
@@ -202,7 +207,7 @@ __device__ void gap_row(const GapArgs& a, const LayerDev& L, uint32_t p, uint32_
 }
 
 template <uint32_t kGapThreads>
-__global__ __launch_bounds__(kGapThreads) void gap_kernel(GapArgs a)
+__global__ __launch_bounds__(kGapThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void gap_kernel(GapArgs a)
 {
     const uint32_t p = blockIdx.x;
     uint32_t t;
@@ -441,11 +446,11 @@ hipError_t launch_gather_image(const GatherArgs& a, uint32_t slices, hipStream_t
     hipLaunchKernelGGL(gather_image_kernel, dim3(a.P, slices), dim3(256), 0, s, a);
     return hipGetLastError();
 }
-hipError_t launch_gap(const GapArgs& a, hipStream_t s)
+hipError_t launch_gap(const GapArgs& a, uint64_t chunks, hipStream_t s)
 {
     // grid covers every packed row; rows of other layer kinds return at once
-    if (a.P >= kGapManyRows) hipLaunchKernelGGL(gap_kernel<128>, dim3(a.P), dim3(128), 0, s, a);
-    else hipLaunchKernelGGL(gap_kernel<512>, dim3(a.P), dim3(512), 0, s, a);
+    if (a.P < kGapManyRows || chunks >= kGapManyChunks) hipLaunchKernelGGL(gap_kernel<512>, dim3(a.P), dim3(512), 0, s, a);
+    else hipLaunchKernelGGL(gap_kernel<128>, dim3(a.P), dim3(128), 0, s, a);
     return hipGetLastError();
 }
 hipError_t launch_image_ops(const GapArgs& a, uint32_t slices, hipStream_t s)

@@ -257,3 +257,22 @@ def test_average_pooling_of_many_rows():
         x = rng.standard_normal((1030, layers[0].in_len())).astype(np.float32)
         w = wl.Workload("gap", dtype, tenants, rng.integers(0, 2, 1030).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
         check(w, "1030 rows of %d channels, %s" % (channels, dtype))
+
+
+# pixels per thread around the eight loads in flight (one group of pixels, two, several rounds of them), an infinite value in the last
+# pixel (taps past it are loaded and must not count), and many rows of many chunks
+@pytest.mark.parametrize("rows,hw,channels,dtype", [(33, (1, 8), 8, "bf16"), (33, (3, 3), 16, "f32"), (7, (5, 13), 8, "bf16"), (5, (23, 23), 24, "f32"), (3, (27, 41), 8, "bf16"),
+                                                    (1030, (16, 16), 72, "f32")])
+def test_average_pooling_around_its_loads_in_flight(rows, hw, channels, dtype):
+    h, w_ = hw
+    layers = [wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, channels, h, w_, 1, ksize=1, pad=0), wl.LayerSpec(wl.GAP, wl.ACT_NONE, channels, channels, h, w_),
+              wl.LayerSpec(wl.FC, wl.ACT_NONE, channels, 7)]
+    w = wl.Workload("gap", dtype, {0: wl.make_model(layers, dtype, 361, 0)}, np.zeros(rows, np.int32), None)
+    x = np.random.default_rng(361).standard_normal((rows, layers[0].in_len())).astype(np.float32)
+    w.inputs = wl.round_to_bf16(x) if dtype == "bf16" else x
+    check(w, "%d rows of %dx%dx%d, %s" % (rows, h, w_, channels, dtype))
+    w.tenants[0].weights[0][:] = 1
+    w.tenants[0].weights[2][:] = 1
+    w.inputs[-1, -1] = np.inf
+    lg = gpu_run(make_context(w), w)[0][:, :7]
+    assert (lg[-1] == np.inf).all() and np.isfinite(lg[:-1]).all()
