@@ -96,7 +96,7 @@ struct mt_ctx {
     uint32_t max_in_len = 0;
     // [kind][layer]: kind 0 = FC tiles, 1 = conv tiles, 2 = big FC tiles
     uint32_t max_nt[kListKinds][MT_MAX_LAYERS]{}, has_gap[MT_MAX_LAYERS]{};
-    uint64_t gap_chunks[MT_MAX_LAYERS]{};            // most 16-byte pieces of a request that a pooling layer of the index reads
+    uint64_t gap_chunks[MT_MAX_LAYERS]{};            // most 16-byte pieces that a workgroup of a pooling layer of the index can have in flight (launch_gap)
     // pool_fused[l]: layer index l + 1 is a global average pool for every registered model that is that deep, and
     // each of their convolutions at l can pool by itself: the convolution launch writes the pooled activation
     // and nothing runs at index l + 1 (all or nothing: the activation buffers alternate per layer index)
@@ -476,7 +476,7 @@ void recompute_bounds(mt_ctx* c)
         for (uint32_t l = 0; l < t.n_layers; ++l) {
             const LayerDev& L = t.layers[l].dev;
             if (L.kind == kKindNone) continue;
-            if (L.kind == MT_GAP) { c->has_gap[l] = 1; c->gap_chunks[l] = std::max(c->gap_chunks[l], (uint64_t)L.in_h * L.in_w * L.cin * c->elem_size / 16); continue; }
+            if (L.kind == MT_GAP) { c->has_gap[l] = 1; c->gap_chunks[l] = std::max(c->gap_chunks[l], std::min<uint64_t>((uint64_t)L.in_h * L.in_w, kGapSweepPixels) * L.cin * c->elem_size / 16); continue; }
             if (L.kind == MT_MAXPOOL || L.kind == MT_ADD) { c->has_image_ops[l] = 1; c->image_op_fill[l] = std::max(c->image_op_fill[l], L.out_fill); continue; }
             const int k = L.kind == MT_FC ? 0 : 1;
             c->sum_macs += (double)L.k_valid * L.N * L.rows_per_req;

@@ -243,7 +243,9 @@ hipError_t prepare_conv(uint32_t dtype);   // once per device, before the first 
 // quad: every tenant's input channels at this layer index are a multiple of four 16-byte chunks
 hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s);
 hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, uint32_t grid, hipStream_t s);
-hipError_t launch_gap(const GapArgs& a, uint64_t chunks, hipStream_t s);   // chunks: most 16-byte pieces of a row that a model of the layer index pools
+constexpr uint32_t kGapSweepPixels = 512;        // pixels of a row that the pooling kernel reads at once (64 groups of eight)
+// chunks: the most 16-byte pieces of that many pixels (or of all, if fewer) among the models of the layer index
+hipError_t launch_gap(const GapArgs& a, uint64_t chunks, hipStream_t s);
 hipError_t launch_image_ops(const GapArgs& a, uint32_t slices, hipStream_t s);   // max-pool and residual add of one layer index
 hipError_t launch_head(const HeadArgs& a, hipStream_t s);
 

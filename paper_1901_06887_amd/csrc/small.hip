@@ -152,15 +152,15 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a)
 // larger than what leaves every thread its eight loads.  64 registers, so that eight waves share a SIMD.  128 images, against a form
 // with 128 threads, up to four loads in flight, and one element per thread where the chunks of a pixel do not divide 128: bf16 7x7x8 4.9 ->
 // 4.3 us, 7x7x72 17.0 -> 4.2, 7x7x512 11.1 -> 4.8, 28x28x512 119 -> 18.3, fp32 16x16x72 63.7 -> 5.0, 7x7x1024 93.4 -> 6.7.
-// Threads: 512 for up to four such workgroups per compute unit, and for rows of so many chunks that they last long anyway;
-// else 128, which start and end sooner.  512 / 128 threads: bf16 7x7x32 (196 chunks a row), 960 images 5.1 / 4.7 us, 1500 7.1 / 5.0, 4096
+// Threads: 512 for up to four such workgroups per compute unit, and for rows with so many chunks to a sweep that they last long anyway;
+// else 128, which start and end sooner (64x64x8 bf16, 512 chunks a sweep, 2048 images 26.0 us with 128, 33.6 with 512).  512 / 128 threads: bf16 7x7x32 (196 chunks a row), 960 images 5.1 / 4.7 us, 1500 7.1 / 5.0, 4096
 // 13.0 / 6.4; fp32 16x16x72 (4608) 960 images 14.5 / 13.7, 2048 25.9 / 26.0; bf16 16x16x256 (8192) 42.9 / 43.5, 4096 130.5 / 133.8; fp32 7x7x1024
 // (12544) 115 / 136.
 constexpr uint32_t kGapManyRows = 1025, kGapManyChunks = 4096;
 template <typename T, uint32_t kGapThreads>
 __device__ void gap_row(const GapArgs& a, const LayerDev& L, uint32_t p, uint32_t seg0)
 {
-    constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC, kMaxGroups = 64, kInFlight = 8;
+    constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC, kInFlight = 8, kMaxGroups = kGapSweepPixels / kInFlight;
     __shared__ float part[kGapThreads * EPC];
     const T* in = (const T*)act_of(a.act, L.in_buf) + (size_t)p * a.S;
     const uint32_t C = L.cin, HW = L.in_h * L.in_w;
