@@ -284,8 +284,7 @@ __device__ __forceinline__ void fc_finish_split(const GemmArgs& a, const Tile& t
                     const int32_t ob = __shfl_xor(best, d);
                     if (omx > mx || (omx == mx && ob < best)) { mx = omx; best = ob; }
                 }
-                const float z0 = lt[row * LRS];
-                if (best == 0x7fffffff || z0 != z0) best = 0;                // as a walk through the classes from the first one would say (-inf, NaN)
+                best = head_label(best, lt[row * LRS]);
                 float sum = 0.0f;
 #pragma unroll
                 for (uint32_t q = 0; q < MAXG; ++q)
@@ -423,6 +422,7 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
                     const int32_t ob = __shfl_xor(best, d);
                     if (omx > mx || (omx == mx && ob < best)) { mx = omx; best = ob; }
                 }
+                best = head_label(best, lt[row * LRS]);
                 f32x4 e[4];
                 float sum = 0.0f;
 #pragma unroll

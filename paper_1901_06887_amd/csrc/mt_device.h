@@ -211,6 +211,10 @@ __device__ __forceinline__ void add_residual(f32x4 (&y)[4], const T* skip, uint3
     activate_block<4>(y, act);
 }
 
+// The label of a row whose classes were compared in parts with `>` from -inf on: best is the first class with the largest logit, 0x7fffffff
+// where none is above -inf; z0: the first class's logit.  A walk from the first class stays there if its logit is NaN or nothing is larger.
+__device__ __forceinline__ int32_t head_label(int32_t best, float z0) { return best == 0x7fffffff || z0 != z0 ? 0 : best; }
+
 template <typename T> struct Mma;
 // bf16: one 16-byte chunk is a whole MFMA operand (8 consecutive k of one row).
 template <> struct Mma<__bf16> {

@@ -330,7 +330,7 @@ __global__ __launch_bounds__(256) void head_kernel(HeadArgs a)
             const int32_t ob = __shfl_xor(best, d);
             if (omx > mx || (omx == mx && ob < best)) { mx = omx; best = ob; }
         }
-        label = best;
+        label = head_label(best, __shfl(v[0][0], 0));
         f32x4 e[4];
 #pragma unroll
         for (uint32_t q = 0; q < 4; ++q)
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256) void head_kernel(HeadArgs a)
             const int32_t ob = __shfl_xor(best, d);
             if (omx > mx || (omx == mx && ob < best)) { mx = omx; best = ob; }
         }
-        label = best;
+        label = head_label(best, z[0]);
         for (uint32_t c = lane; c < C; c += 64) sum += __expf(z[c] - mx);
         for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
         const float inv = 1.0f / sum;

@@ -207,6 +207,24 @@ def test_head_of_a_split_k_tile_on_infinite_and_undefined_logits():
         assert np.array_equal(lg[t, :C], np.array(row), equal_nan=True)
 
 
+# one to two column blocks finished by tiles that split K, up to four by the wide tiles, then the head kernel with a row in registers and without
+@pytest.mark.parametrize("classes,no_split_k", [(5, "0"), (40, "0"), (40, "1"), (100, "1"), (100, "0"), (300, "0"), (1030, "0")])
+def test_heads_on_infinite_and_undefined_logits(monkeypatch, classes, no_split_k):
+    """A class whose logit is +-infinity or NaN: the label is what a walk from the first class finds, whichever kernel finishes the row."""
+    monkeypatch.setenv("MT_NO_AUTO_SPLIT_K", no_split_k)
+    C, cases = 5, ([np.inf, 1, 2, 3, 4], [-np.inf] * 5, [0, np.nan, 1, -np.inf, 1], [np.nan, 1, 2, 3, 4], [np.nan] * 5)
+    w = mlp_fleet(len(cases), len(cases), (16, classes), seed=351, ids=np.arange(len(cases)))
+    for t, row in enumerate(cases):
+        w.tenants[t].biases[0][:] = np.nan if np.isnan(row).all() else -np.inf
+        w.tenants[t].biases[0][:C] = np.array(row, np.float32)
+        w.tenants[t].weights[0][:] = 0
+    lg, pr, lb, nc = gpu_run(make_context(w), w)
+    assert lb.tolist() == [0, 0, 2, 0, 0]
+    assert np.isnan(pr[:, :C]).all()
+    for t, row in enumerate(cases):
+        assert np.array_equal(lg[t, :C], np.array(row), equal_nan=True)
+
+
 # Padding columns of a hidden layer's activation stay zero whatever a row holds: 0 x Inf in a padding output would be NaN, and meet the
 # zero-padded K of the next layer.  Linear hidden layers (one and two column blocks, a wider one with a ragged last block), in runs that split
 # K, that do not, and that take big tiles; y = W x over the K real inputs: a row with an infinite input has infinite logits, not NaN.
