@@ -137,51 +137,41 @@ __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Ti
 }
 
 // split < 4: every wave reads the activation bricks of its own K range directly.
-template <typename T, int RB, int P, bool GATHER>
+template <typename T, bool GATHER>
 __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t seg0,
-                                                     uint32_t nb, uint32_t kq, uint32_t ks, f32x16 (&acc)[RB])
+                                                     uint32_t nb, uint32_t kq, uint32_t ks, f32x16& acc)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC;
+    constexpr int P = 8;                                      // bricks of either operand in flight per wave
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t nKB = L.K / KB;
-    const uint32_t nrb = (tl.rows + kBrickRows - 1) / kBrickRows;
     const uint32_t cnt = nKB / ks, kb0 = kq * cnt;
     const u32x4* wp = (const u32x4*)(a.arena + L.w_off) + ((size_t)nb * nKB + kb0) * 64 + lane;
-    const u32x4* xbase = (const u32x4*)((const T*)act_of(a.act, L.in_buf) + (size_t)seg0 * a.S) + lane;
-    const u32x4* xp[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        const uint32_t rbi = tl.m0 / kBrickRows + min((uint32_t)r, nrb - 1);
-        xp[r] = xbase + ((size_t)rbi * nKB + kb0) * 64;
-    }
+    const u32x4* xp = (const u32x4*)((const T*)act_of(a.act, L.in_buf) + (size_t)seg0 * a.S) + lane + ((size_t)(tl.m0 / kBrickRows) * nKB + kb0) * 64;
     typedef const __attribute__((address_space(1))) u32x4* gptr_t;     // submitted rows live in global memory
-    gptr_t rowp[RB]; bool row_ok[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        rowp[r] = nullptr; row_ok[r] = false;
-        if (GATHER) {
-            const uint32_t p0 = seg0 + (tl.m0 / kBrickRows + min((uint32_t)r, nrb - 1)) * kBrickRows;
-            const int32_t row = a.perm[p0 + (lane & 31)];
-            row_ok[r] = row >= 0;
-            rowp[r] = (gptr_t)a.row_src[row_ok[r] ? row : a.perm[p0]];   // padding rows read a real row and discard it
-        }
+    gptr_t rowp = nullptr;
+    bool row_ok = false;
+    if (GATHER) {
+        const uint32_t p0 = seg0 + tl.m0;
+        const int32_t row = a.perm[p0 + (lane & 31)];
+        row_ok = row >= 0;
+        rowp = (gptr_t)a.row_src[row_ok ? row : a.perm[p0]];  // padding rows read a real row and discard it
     }
-    auto load_x = [&](int r, uint32_t kk) -> u32x4 {
+    auto load_x = [&](uint32_t kk) -> u32x4 {
         if (GATHER) {
             const uint32_t k = (kb0 + kk) * KB + (lane >> 5) * EPC;
-            const bool ok = row_ok[r] && k < L.k_valid;
-            const u32x4 v = rowp[r][(ok ? k : 0) / EPC];
+            const bool ok = row_ok && k < L.k_valid;
+            const u32x4 v = rowp[(ok ? k : 0) / EPC];
             return ok ? v : u32x4{0, 0, 0, 0};
         }
-        return xp[r][(size_t)kk * 64];
+        return xp[(size_t)kk * 64];
     };
-    u32x4 bq[P], aq[RB][P];
+    u32x4 bq[P], aq[P];
 #pragma unroll
     for (int j = 0; j < P; ++j) {
         const uint32_t kk = min((uint32_t)j, cnt - 1);
         bq[j] = wp[(size_t)kk * 64];
-#pragma unroll
-        for (int r = 0; r < RB; ++r) aq[r][j] = load_x(r, kk);
+        aq[j] = load_x(kk);
     }
     // steady state: straight-line groups of P bricks, each slot refilled right after use; the
     // clamped refill index re-reads the last brick instead of branching
@@ -189,22 +179,16 @@ __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Ti
     for (uint32_t g = 0; g < full; ++g) {
 #pragma unroll
         for (int j = 0; j < P; ++j) {
-#pragma unroll
-            for (int r = 0; r < RB; ++r) Mma<T>::run(acc[r], aq[r][j], bq[j]);
+            Mma<T>::run(acc, aq[j], bq[j]);
             const uint32_t kk = min(g * P + j + P, cnt - 1);
             bq[j] = wp[(size_t)kk * 64];
-#pragma unroll
-            for (int r = 0; r < RB; ++r) aq[r][j] = load_x(r, kk);
+            aq[j] = load_x(kk);
         }
     }
     const uint32_t rem = cnt - full * P;                      // the slots already hold the remaining bricks
 #pragma unroll
-    for (int j = 0; j < P; ++j) {
-        if ((uint32_t)j < rem) {
-#pragma unroll
-            for (int r = 0; r < RB; ++r) Mma<T>::run(acc[r], aq[r][j], bq[j]);
-        }
-    }
+    for (int j = 0; j < P; ++j)
+        if ((uint32_t)j < rem) Mma<T>::run(acc, aq[j], bq[j]);
 }
 
 // End of a tile whose waves split K (split < 4; ks = 4 / split waves share a column block): the partial sums meet in LDS and are
@@ -215,15 +199,14 @@ __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Ti
 // Passes, one wave's finish -> this -> with a kernel of their own for such tiles (fc_kernel's NARROW): one request to a 784-1024-1024-10
 // model 26.6 -> 25.7 -> 24.6 us, 64 fp32 requests to 256-512-512-10 models 30.7 -> 29.7 -> 28.6, 777 requests to 301-333-520-97-37 models
 // with GELU 59.0 -> 57.1 -> 57.0; the last layer of 64 residual nets 8.6 -> 6.9.
-template <typename T, int RB>
+template <typename T>
 __device__ __forceinline__ void fc_finish_split(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t Mt, uint32_t seg0,
-                                                uint32_t nb, uint32_t kq, uint32_t ks, bool active, T* xout, const f32x16 (&acc)[RB], uint8_t* smem)
+                                                uint32_t nb, uint32_t kq, uint32_t ks, bool active, T* xout, const f32x16& acc, uint8_t* smem)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC, MAXG = 2;         // (ks is 2 or 4)
     constexpr uint32_t TRS = 32 * sizeof(T) + 16;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
     const uint32_t split = tl.split, cb = wave % split, ng = 4 / ks;
-    const uint32_t nrb = (tl.rows + kBrickRows - 1) / kBrickRows;
     const uint32_t n = nb * kBrickRows + li;
     const float bv = active ? ((const float*)(a.arena + L.b_off))[n] : 0.0f;
     float* red = (float*)smem;
@@ -232,118 +215,114 @@ __device__ __forceinline__ void fc_finish_split(const GemmArgs& a, const Tile& t
     constexpr uint32_t LRS = 2 * kBrickRows + 4;                             // floats per row of the logits tile
     static_assert(kBrickRows * LRS * 4 <= 4 * kTrBytes, "the logits tile lies where the transposition scratch does");
     float* lt = (float*)(smem + kTrOffset);
+    __syncthreads();
+    if (active) {
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        if ((uint32_t)r >= nrb) break;                                       // the same for the whole workgroup
-        __syncthreads();
-        if (active) {
+        for (uint32_t g = 0; g < 4; ++g) *(f32x4*)(red + wave * 1024 + g * 256 + lane * 4) = f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    }
+    __syncthreads();
+    f32x4 y[MAXG];
 #pragma unroll
-            for (uint32_t g = 0; g < 4; ++g) *(f32x4*)(red + wave * 1024 + g * 256 + lane * 4) = f32x4{acc[r][4 * g], acc[r][4 * g + 1], acc[r][4 * g + 2], acc[r][4 * g + 3]};
+    for (uint32_t i = 0; i < MAXG; ++i) {
+        y[i] = f32x4{0, 0, 0, 0};
+        if (active && i < ng) {
+            const float* src = red + cb * 1024 + (kq * ng + i) * 256 + lane * 4;
+            y[i] = *(const f32x4*)src;
+            for (uint32_t q = 1; q < ks; ++q) y[i] += *(const f32x4*)(src + q * split * 1024);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[i][e] += bv;
         }
-        __syncthreads();
-        f32x4 y[MAXG];
-#pragma unroll
-        for (uint32_t i = 0; i < MAXG; ++i) {
-            y[i] = f32x4{0, 0, 0, 0};
-            if (active && i < ng) {
-                const float* src = red + cb * 1024 + (kq * ng + i) * 256 + lane * 4;
-                y[i] = *(const f32x4*)src;
-                for (uint32_t q = 1; q < ks; ++q) y[i] += *(const f32x4*)(src + q * split * 1024);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) y[i][e] += bv;
-            }
-        }
-        const uint32_t mb = tl.m0 + r * kBrickRows;
-        if (head) {
-#pragma unroll
-            for (uint32_t i = 0; i < MAXG; ++i)
-                if (active && i < ng) {
-#pragma unroll
-                    for (uint32_t e = 0; e < 4; ++e) lt[(8 * (kq * ng + i) + 4 * lh + e) * LRS + cb * kBrickRows + li] = y[i][e];
-                }
-            __syncthreads();
-            const uint32_t C = L.N, row = tid >> 3, part = tid & 7, m = mb + row;
-            if (m < Mt) {                                                    // the eight threads of a row are neighbours in one wave
-                const uint32_t sub = (uint32_t)a.perm[seg0 + m];
-                f32x4 z[MAXG], ez[MAXG];
-                float mx = -INFINITY; int32_t best = 0x7fffffff;
-#pragma unroll
-                for (uint32_t q = 0; q < MAXG; ++q) {                        // thread `part` holds classes 4 part + 32 q + {0..3}
-                    z[q] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-                    if (q < split) z[q] = *(const f32x4*)(lt + row * LRS + q * kBrickRows + part * 4);
-#pragma unroll
-                    for (uint32_t e = 0; e < 4; ++e) {
-                        const uint32_t c = q * kBrickRows + part * 4 + e;
-                        if (c >= C) z[q][e] = -INFINITY;
-                        if (z[q][e] > mx) { mx = z[q][e]; best = (int32_t)c; }      // increasing index: the first hit is this thread's lowest
-                    }
-                }
-#pragma unroll
-                for (int d = 4; d >= 1; d >>= 1) {
-                    const float omx = __shfl_xor(mx, d);
-                    const int32_t ob = __shfl_xor(best, d);
-                    if (omx > mx || (omx == mx && ob < best)) { mx = omx; best = ob; }
-                }
-                best = head_label(best, lt[row * LRS]);
-                float sum = 0.0f;
-#pragma unroll
-                for (uint32_t q = 0; q < MAXG; ++q)
-#pragma unroll
-                    for (uint32_t e = 0; e < 4; ++e) { ez[q][e] = q * kBrickRows + part * 4 + e < C ? __expf(z[q][e] - mx) : 0.0f; sum += ez[q][e]; }
-#pragma unroll
-                for (int d = 4; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
-                const float inv = 1.0f / sum;
-                if (part == 0) {
-                    a.out.labels[sub] = best;
-                    if (a.out.n_classes) a.out.n_classes[sub] = (int32_t)C;
-                }
-                float* pr = a.out.probs ? a.out.probs + (size_t)sub * a.out.row_stride : nullptr;
-                float* lg = a.out.logits ? a.out.logits + (size_t)sub * a.out.row_stride : nullptr;
-#pragma unroll
-                for (uint32_t q = 0; q < MAXG; ++q) {
-                    const uint32_t c0 = q * kBrickRows + part * 4;
-                    f32x4 pv, lv;
-#pragma unroll
-                    for (uint32_t e = 0; e < 4; ++e) { const bool in = c0 + e < C; pv[e] = in ? ez[q][e] * inv : 0.0f; lv[e] = in ? z[q][e] : 0.0f; }
-                    if (a.out_vec_ok) {
-                        if (c0 < a.out.row_stride) { if (pr) *(f32x4*)(pr + c0) = pv; if (lg) *(f32x4*)(lg + c0) = lv; }
-                    } else {
-#pragma unroll
-                        for (uint32_t e = 0; e < 4; ++e)
-                            if (c0 + e < a.out.row_stride) { if (pr) pr[c0 + e] = pv[e]; if (lg) lg[c0 + e] = lv[e]; }
-                    }
-                }
-                for (uint32_t c = MAXG * kBrickRows + part; c < a.out.row_stride; c += 8) {      // wider output rows: zeros past the tile
-                    if (pr) pr[c] = 0.0f;
-                    if (lg) lg[c] = 0.0f;
-                }
-            }
-            continue;
-        }
-        if (L.is_last) {
-#pragma unroll
-            for (uint32_t i = 0; i < MAXG; ++i)
-#pragma unroll
-                for (uint32_t e = 0; e < 4; ++e) {
-                    const uint32_t m = mb + 8 * (kq * ng + i) + 4 * lh + e;
-                    if (active && i < ng && n < L.N && m < Mt) a.logits[(size_t)(seg0 + m) * a.C_pad + n] = y[i][e];
-                }
-            continue;
-        }
-        // hidden layer: activation, rounding; the 32x32 block through LDS as [row][column], out as whole bricks.  Outputs past N are
-        // masked: a zero weight row against an infinite input is NaN, and the next layer reads them with zero weights
-        activate_block<MAXG>(y, L.act);
+    }
+    const uint32_t mb = tl.m0;
+    if (head) {
 #pragma unroll
         for (uint32_t i = 0; i < MAXG; ++i)
             if (active && i < ng) {
 #pragma unroll
-                for (uint32_t e = 0; e < 4; ++e) *(T*)(trw + (8 * (kq * ng + i) + 4 * lh + e) * TRS + li * sizeof(T)) = (T)(n < L.N ? y[i][e] : 0.0f);
+                for (uint32_t e = 0; e < 4; ++e) lt[(8 * (kq * ng + i) + 4 * lh + e) * LRS + cb * kBrickRows + li] = y[i][e];
             }
         __syncthreads();
-        if (active) {
-            u32x4* out = (u32x4*)xout + ((size_t)(mb / kBrickRows) * (L.out_fill / KB) + nb * (kBrickRows / KB)) * 64 + lane;
-            for (uint32_t c = kq; c < kBrickRows / KB; c += ks) out[c * 64] = *(const u32x4*)(trw + li * TRS + (c * KB + lh * EPC) * sizeof(T));
+        const uint32_t C = L.N, row = tid >> 3, part = tid & 7, m = mb + row;
+        if (m < Mt) {                                                    // the eight threads of a row are neighbours in one wave
+            const uint32_t sub = (uint32_t)a.perm[seg0 + m];
+            f32x4 z[MAXG], ez[MAXG];
+            float mx = -INFINITY; int32_t best = 0x7fffffff;
+#pragma unroll
+            for (uint32_t q = 0; q < MAXG; ++q) {                        // thread `part` holds classes 4 part + 32 q + {0..3}
+                z[q] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+                if (q < split) z[q] = *(const f32x4*)(lt + row * LRS + q * kBrickRows + part * 4);
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e) {
+                    const uint32_t c = q * kBrickRows + part * 4 + e;
+                    if (c >= C) z[q][e] = -INFINITY;
+                    if (z[q][e] > mx) { mx = z[q][e]; best = (int32_t)c; }      // increasing index: the first hit is this thread's lowest
+                }
+            }
+#pragma unroll
+            for (int d = 4; d >= 1; d >>= 1) {
+                const float omx = __shfl_xor(mx, d);
+                const int32_t ob = __shfl_xor(best, d);
+                if (omx > mx || (omx == mx && ob < best)) { mx = omx; best = ob; }
+            }
+            best = head_label(best, lt[row * LRS]);
+            float sum = 0.0f;
+#pragma unroll
+            for (uint32_t q = 0; q < MAXG; ++q)
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e) { ez[q][e] = q * kBrickRows + part * 4 + e < C ? __expf(z[q][e] - mx) : 0.0f; sum += ez[q][e]; }
+#pragma unroll
+            for (int d = 4; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+            const float inv = 1.0f / sum;
+            if (part == 0) {
+                a.out.labels[sub] = best;
+                if (a.out.n_classes) a.out.n_classes[sub] = (int32_t)C;
+            }
+            float* pr = a.out.probs ? a.out.probs + (size_t)sub * a.out.row_stride : nullptr;
+            float* lg = a.out.logits ? a.out.logits + (size_t)sub * a.out.row_stride : nullptr;
+#pragma unroll
+            for (uint32_t q = 0; q < MAXG; ++q) {
+                const uint32_t c0 = q * kBrickRows + part * 4;
+                f32x4 pv, lv;
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e) { const bool in = c0 + e < C; pv[e] = in ? ez[q][e] * inv : 0.0f; lv[e] = in ? z[q][e] : 0.0f; }
+                if (a.out_vec_ok) {
+                    if (c0 < a.out.row_stride) { if (pr) *(f32x4*)(pr + c0) = pv; if (lg) *(f32x4*)(lg + c0) = lv; }
+                } else {
+#pragma unroll
+                    for (uint32_t e = 0; e < 4; ++e)
+                        if (c0 + e < a.out.row_stride) { if (pr) pr[c0 + e] = pv[e]; if (lg) lg[c0 + e] = lv[e]; }
+                }
+            }
+            for (uint32_t c = MAXG * kBrickRows + part; c < a.out.row_stride; c += 8) {      // wider output rows: zeros past the tile
+                if (pr) pr[c] = 0.0f;
+                if (lg) lg[c] = 0.0f;
+            }
         }
+        return;
+    }
+    if (L.is_last) {
+#pragma unroll
+        for (uint32_t i = 0; i < MAXG; ++i)
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) {
+                const uint32_t m = mb + 8 * (kq * ng + i) + 4 * lh + e;
+                if (active && i < ng && n < L.N && m < Mt) a.logits[(size_t)(seg0 + m) * a.C_pad + n] = y[i][e];
+            }
+        return;
+    }
+    // hidden layer: activation, rounding; the 32x32 block through LDS as [row][column], out as whole bricks.  Outputs past N are
+    // masked: a zero weight row against an infinite input is NaN, and the next layer reads them with zero weights
+    activate_block<MAXG>(y, L.act);
+#pragma unroll
+    for (uint32_t i = 0; i < MAXG; ++i)
+        if (active && i < ng) {
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) *(T*)(trw + (8 * (kq * ng + i) + 4 * lh + e) * TRS + li * sizeof(T)) = (T)(n < L.N ? y[i][e] : 0.0f);
+        }
+    __syncthreads();
+    if (active) {
+        u32x4* out = (u32x4*)xout + ((size_t)(mb / kBrickRows) * (L.out_fill / KB) + nb * (kBrickRows / KB)) * 64 + lane;
+        for (uint32_t c = kq; c < kBrickRows / KB; c += ks) out[c * 64] = *(const u32x4*)(trw + li * TRS + (c * KB + lh * EPC) * sizeof(T));
     }
 }
 
@@ -354,11 +333,11 @@ __device__ __forceinline__ void fc_split_tile(const GemmArgs& a, const Tile& tl,
     const uint32_t split = tl.split, ks = 4 / split, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t nb = tl.n0 / kBrickRows + (wave % split), kq = wave / split;
     const bool active = nb < L.N_pad / kBrickRows;
-    f32x16 acc[1];
+    f32x16 acc;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[0][v] = 0.0f;
-    if (active) fc_accumulate_direct<T, 1, 8, GATHER>(a, tl, L, seg0, nb, kq, ks, acc);
-    fc_finish_split<T, 1>(a, tl, L, Mt, seg0, nb, kq, ks, active, xout, acc, smem);
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    if (active) fc_accumulate_direct<T, GATHER>(a, tl, L, seg0, nb, kq, ks, acc);
+    fc_finish_split<T>(a, tl, L, Mt, seg0, nb, kq, ks, active, xout, acc, smem);
 }
 
 template <typename T, int RB, bool GATHER>
@@ -381,10 +360,9 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
 
     fc_accumulate_shared<T, RB, GATHER>(a, tl, L, seg0, nb, active, smem, acc);
 
-    const bool writer = active;
     const uint32_t n = nb * kBrickRows + li;
     const float* bias = (const float*)(a.arena + L.b_off);
-    const float bv = writer ? bias[n] : 0.0f;
+    const float bv = active ? bias[n] : 0.0f;
     if (L.is_last && a.fuse_head && L.N <= a.fuse_head_max && L.N_pad <= split * kBrickRows) {
         // 33 .. 128 classes, all of them inside this tile (one column group): the waves put their
         // 32x32 blocks of logits side by side in LDS as [row][class], then eight threads share a
@@ -397,7 +375,7 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             __syncthreads();
-            if (writer && (uint32_t)r < nrb) {
+            if (active && (uint32_t)r < nrb) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) lt[(8 * (v >> 2) + 4 * lh + (v & 3)) * LRS + n] = acc[r][v] + bv;
             }
@@ -462,7 +440,7 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
         return;
     }
     if (L.is_last) {
-        if (!writer || n >= L.N) return;
+        if (!active || n >= L.N) return;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
 #pragma unroll
@@ -482,7 +460,7 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
         __syncthreads();
-        if (writer && (uint32_t)r < nrb) {
+        if (active && (uint32_t)r < nrb) {
             f32x4 y[4];
 #pragma unroll
             for (int v = 0; v < 16; ++v) y[v >> 2][v & 3] = acc[r][v] + bv;
@@ -494,7 +472,7 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
             }
         }
         __syncthreads();
-        if (writer && (uint32_t)r < nrb) {
+        if (active && (uint32_t)r < nrb) {
 #pragma unroll
             for (uint32_t c = 0; c < kBrickRows / KB; ++c) {
                 const u32x4 chunk = *(const u32x4*)(trw + li * TRS + (c * KB + lh * EPC) * sizeof(T));

@@ -7,7 +7,8 @@
 //   fc_stream.hip   fc_kernel: one FC layer index for all tenants, weight-streaming tiles: weight
 //                   bricks go from memory into MFMA operands through a register ring, activation
 //                   bricks are shared through LDS; fused bias + activation (+ rounding), brick
-//                   output, fp32 logits, or softmax/argmax for at most 32 classes
+//                   output, fp32 logits, or softmax/argmax where one tile holds all classes (at most
+//                   128).  Narrow layers and small runs take tiles of 32 rows whose waves split K
 //   fc_big.hip      fc_big_walk_kernel / fc_big_kernel: the same layer index, compute-bound tenant-layers:
 //                   256x256 tiles, both operands through an LDS ring filled by direct global->LDS loads;
 //                   one workgroup per compute unit walks the tiles (or, for short K, one workgroup per tile)
@@ -16,8 +17,9 @@
 //                   per tile into LDS and shared by waves side by side over channels; pools on
 //                   the way out where it can) and conv_img_kernel (layers whose tiles are whole
 //                   output rows of an image or whole small images: the tile's input rows are
-//                   copied to LDS once and every tap is read from there): implicit-GEMM 3x3
-//                   convolution for all tenants
+//                   copied to LDS once and every tap is read from there) and conv_split_kernel
+//                   (launches of few tiles: 32 pixels and 32 channels to a tile, whose 4 to 16 waves
+//                   share K): implicit-GEMM convolution for all tenants
 //   small.hip       gather_kernel / gather_image_kernel (submitted rows -> bricks / padded NHWC),
 //                   gap_kernel (global average pooling), head_kernel (softmax + argmax in
 //                   submission order), copy_kernel (the yardstick for byte counters)

@@ -294,3 +294,19 @@ def test_average_pooling_around_its_loads_in_flight(rows, hw, channels, dtype):
     w.inputs[-1, -1] = np.inf
     lg = gpu_run(make_context(w), w)[0][:, :7]
     assert (lg[-1] == np.inf).all() and np.isfinite(lg[:-1]).all()
+
+
+def test_convolution_outputs_on_both_sides_of_the_line_for_stores_through_l2():
+    """44 images of 112x112x64 in bf16 are 70 MB, stored the ordinary way, 22 of them 35 MB, stored through L2: the same bits; some rows
+    against the oracle."""
+    layers = [wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, 64, 112, 112, 1, ksize=3, pad=1), wl.LayerSpec(wl.CONV, wl.ACT_RELU, 64, 64, 112, 112, 1, ksize=3, pad=1),
+              wl.LayerSpec(wl.CONV, wl.ACT_NONE, 64, 64, 112, 112, 1, ksize=1, pad=0), wl.LayerSpec(wl.GAP, wl.ACT_NONE, 64, 64, 112, 112), wl.LayerSpec(wl.FC, wl.ACT_NONE, 64, 7)]
+    x = wl.round_to_bf16(np.random.default_rng(362).standard_normal((44, layers[0].in_len())).astype(np.float32))
+    w = wl.Workload("through", "bf16", {0: wl.make_model(layers, "bf16", 362, 0)}, np.zeros(44, np.int32), x)
+    ctx = make_context(w)
+    whole = gpu_run(ctx, w, poison=True)
+    for a, b in ((0, 22), (22, 44)):
+        part = gpu_run(ctx, w, ids=w.tenant_ids[a:b], inputs=w.inputs[a:b], poison=True)
+        assert all(np.array_equal(p, q[a:b]) for p, q in zip(part, whole))
+    rows = np.array([0, 21, 43])
+    compare(w, tuple(v[rows] for v in whole), oracle_rows(w, rows), rows=rows, what="through", deep=True)
