@@ -808,8 +808,9 @@ mt_status plan_model(mt_ctx* c, const mt_layer_spec* specs, uint32_t n_layers, H
 // rows and columns as padding), the order in which a wavefront consumes MFMA operands.  The
 // reduction index k is the fan-in for FC; for conv the filters [Co][Ci][kh][kw] are read as
 // k = (kh*ksize + kw) * ci_padded + ci, so that a GEMM k index walks the NHWC input contiguously.
+// (On a line of the instruction cache: registration is this loop, 10 % slower where it happened to straddle two.)
 template <typename T>
-void pack_weights(const HostLayer& hl, const void* w_src, uint8_t* dst)
+__attribute__((aligned(64))) void pack_weights(const HostLayer& hl, const void* w_src, uint8_t* dst)
 {
     const LayerDev& d = hl.dev;
     const T* src = (const T*)w_src;
