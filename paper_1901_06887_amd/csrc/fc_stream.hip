@@ -157,38 +157,41 @@ __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Ti
         row_ok = row >= 0;
         rowp = (gptr_t)a.row_src[row_ok ? row : a.perm[p0]];  // padding rows read a real row and discard it
     }
+    // (a submitted row's chunk is masked where it is used, not where it is asked for: that would wait for it)
+    auto chunk_of = [&](uint32_t kk) { return (kb0 + kk) * KB + (lane >> 5) * EPC; };
+    auto in_row = [&](uint32_t k) { return row_ok && k < L.k_valid; };
     auto load_x = [&](uint32_t kk) -> u32x4 {
-        if (GATHER) {
-            const uint32_t k = (kb0 + kk) * KB + (lane >> 5) * EPC;
-            const bool ok = row_ok && k < L.k_valid;
-            const u32x4 v = rowp[(ok ? k : 0) / EPC];
-            return ok ? v : u32x4{0, 0, 0, 0};
-        }
-        return xp[(size_t)kk * 64];
+        if (!GATHER) return xp[(size_t)kk * 64];
+        const uint32_t k = chunk_of(kk);
+        return rowp[(in_row(k) ? k : 0) / EPC];
     };
+    auto masked = [&](const u32x4& v, uint32_t kk) -> u32x4 { return !GATHER || in_row(chunk_of(kk)) ? v : u32x4{0, 0, 0, 0}; };
     u32x4 bq[P], aq[P];
 #pragma unroll
     for (int j = 0; j < P; ++j) {
         const uint32_t kk = min((uint32_t)j, cnt - 1);
         bq[j] = wp[(size_t)kk * 64];
         aq[j] = load_x(kk);
+        __builtin_amdgcn_sched_barrier(0);
     }
     // steady state: straight-line groups of P bricks, each slot refilled right after use; the
-    // clamped refill index re-reads the last brick instead of branching
+    // clamped refill index re-reads the last brick instead of branching.  The fences keep the loads in the order of their
+    // use, one step's behind the other's: left to itself the compiler gathers a group's MFMAs behind a wait for all its loads
     const uint32_t full = cnt / P;
     for (uint32_t g = 0; g < full; ++g) {
 #pragma unroll
         for (int j = 0; j < P; ++j) {
-            Mma<T>::run(acc, aq[j], bq[j]);
+            Mma<T>::run(acc, masked(aq[j], g * P + j), bq[j]);
             const uint32_t kk = min(g * P + j + P, cnt - 1);
             bq[j] = wp[(size_t)kk * 64];
             aq[j] = load_x(kk);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     const uint32_t rem = cnt - full * P;                      // the slots already hold the remaining bricks
 #pragma unroll
     for (int j = 0; j < P; ++j)
-        if ((uint32_t)j < rem) Mma<T>::run(acc, aq[j], bq[j]);
+        if ((uint32_t)j < rem) Mma<T>::run(acc, masked(aq[j], full * P + j), bq[j]);
 }
 
 // End of a tile whose waves split K (split < 4; ks = 4 / split waves share a column block): the partial sums meet in LDS and are
