@@ -15,25 +15,29 @@
 
   python profile_summary.py split <..._kernel_trace.csv> --kernel fc_kernel
       average duration of one kernel in the benchmark's warm steps and in its cache-flushed steps
+
+  python profile_summary.py launches <..._kernel_trace.csv>
+      median duration of every launch of a run, in order, over the runs of the trace that have the most usual number of launches
 """
 import argparse
 import csv
 import os
 import re
 import sys
+from collections import Counter
 
 from bench import kernel_source_sha256      # the fingerprint bench.py checks stored counter summaries against
 
 
 def short_name(name: str) -> str:
     """'_ZN2mt9fc_kernelIDF16bEEvNS_8GemmArgsE' or 'mt::fc_kernel<__bf16>(...)' -> a readable name."""
-    m = re.match(r"_ZN2mt\d+([a-z_]+)I(DF16b|f)((?:L[ib]\d+E)*)", name)
+    m = re.match(r"_ZN2mt\d+([a-z_]+)I(DF16b|f)((?:L[ijb]\d+E)*)", name)
     if m:
-        args = ["bf16" if m.group(2) == "DF16b" else "float"] + re.findall(r"L[ib](\d+)E", m.group(3))
+        args = ["bf16" if m.group(2) == "DF16b" else "float"] + re.findall(r"L[ijb](\d+)E", m.group(3))
         return "mt::%s<%s>" % (m.group(1), ",".join(args))
-    m = re.match(r"_ZN2mt\d+([a-z_]+)ILb([01])", name)
+    m = re.match(r"_ZN2mt\d+([a-z_]+)I((?:L[ijb]\d+E)+)", name)
     if m:
-        return "mt::%s<%s>" % (m.group(1), m.group(2))
+        return "mt::%s<%s>" % (m.group(1), ",".join(re.findall(r"L[ijb](\d+)E", m.group(2))))
     m = re.match(r"_ZN2mt\d+([a-z_]+)E", name)
     if m:
         return "mt::%s" % m.group(1)
@@ -73,6 +77,26 @@ def split_warm_cold(trace_csv: str, kernel: str) -> str:
         if v:
             out.append("%s %s: %d dispatches, avg %.2f us, min %.2f us, max %.2f us" % (
                 kernel, "after a cache flush" if cold else "warm (steps back to back)", len(v), sum(v) / len(v), min(v), max(v)))
+    return "\n".join(out)
+
+
+def launches(trace_csv: str) -> str:
+    """Median duration of every launch of a run: from one segmentation kernel to the next."""
+    rows = sorted(csv.DictReader(open(trace_csv)), key=lambda r: int(r["Start_Timestamp"]))
+    runs = []
+    for r in rows:
+        name = short_name(r["Kernel_Name"])
+        if "rank_kernel" in name or ("batcher_kernel" in name and not (runs and "rank_kernel" in runs[-1][-1][0])):
+            runs.append([])
+        if runs and "mt::" in name:
+            runs[-1].append((name, (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3, r))
+    usual = Counter(len(x) for x in runs).most_common(1)[0][0]
+    runs = [x for x in runs if len(x) == usual]
+    out = ["%-44s %10s %10s   (%d runs)" % ("launch", "median_us", "workgroups", len(runs))]
+    for step in zip(*runs):
+        r = step[0][2]
+        size = [int(r["Grid_Size_" + d]) // int(r["Workgroup_Size_" + d]) for d in "XYZ"]
+        out.append("%-44s %10.2f %10d" % (step[0][0][:44], sorted(s[1] for s in step)[len(step) // 2], size[0] * size[1] * size[2]))
     return "\n".join(out)
 
 
@@ -135,6 +159,8 @@ def main(argv=None):
     w = sub.add_parser("split")
     w.add_argument("csv")
     w.add_argument("--kernel", required=True)
+    l = sub.add_parser("launches")
+    l.add_argument("csv")
     c = sub.add_parser("counters")
     c.add_argument("csv")
     c.add_argument("--kernel", required=True)
@@ -144,6 +170,8 @@ def main(argv=None):
         print(stats(a.csv, a.top))
     elif a.cmd == "split":
         print(split_warm_cold(a.csv, a.kernel))
+    elif a.cmd == "launches":
+        print(launches(a.csv))
     elif a.cmd == "traffic":
         print(traffic(a.fetch, a.write, a.kernel, a.copy_bytes))
     else:
