@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmt.so")
-SOURCES = ["mt_api.cpp", "batcher.hip", "fc_stream.hip", "fc_big.hip", "conv.hip", "small.hip"]
+SOURCES = ["mt_api.cpp", "batcher.hip", "fc_stream.hip", "fc_big.hip", "conv.hip", "conv_first.hip", "small.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
          # keep the compiler from forming packed-fp32 VALU ops
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -28,7 +28,7 @@ def compile_one(src: str, verbose: bool) -> str:
 
 def build(verbose: bool = False) -> str:
     from concurrent.futures import ThreadPoolExecutor
-    with ThreadPoolExecutor(max_workers=min(6, os.cpu_count() or 1)) as pool:       # one hipcc per source
+    with ThreadPoolExecutor(max_workers=min(7, os.cpu_count() or 1)) as pool:       # one hipcc per source
         objs = list(pool.map(lambda src: compile_one(src, verbose), SOURCES))
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.check_call(cmd)

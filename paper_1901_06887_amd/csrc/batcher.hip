@@ -357,7 +357,7 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
             const bool rem_sk = big && big_remainder_split_k(y);
             const uint32_t sh = sk || rem_sk || ((x >> 30) & 1) ? 5 : 6, gq = rem_sk ? y / kBrickRows : groups;
             n_fc[j] = !conv && groups && M ? ((M - Mb + (1u << sh) - 1) >> sh) * gq : 0;
-            n_conv[j] = conv && M ? (split ? ceil_div(M * f[j].z, kBrickRows) * blocks : ceil_div(M * y, kConvTileRows) * ceil_div(blocks, kTileCols / kBrickRows)) : 0;
+            n_conv[j] = conv && M ? (a.first_cap && l == 0 ? M * first_strips(f[j].w & 0xffffu, f[j].w >> 16, a.first_cap) * ceil_div(blocks, kFirstBlocks) : split ? ceil_div(M * f[j].z, kBrickRows) * blocks : ceil_div(M * y, kConvTileRows) * ceil_div(blocks, kTileCols / kBrickRows)) : 0;
             n_big[j] = ceil_div(Mb, kBigTile) * ceil_div(y, kBigTile);
         }
         auto emit = [&](uint32_t kind, const uint32_t (&n)[J], uint32_t& run) {

@@ -103,6 +103,14 @@ struct mt_ctx {
     bool pool_fused[MT_MAX_LAYERS]{};
     double sum_macs = 0.0;                           // multiply-accumulates of one request, summed over the registered tenants
     uint32_t max_conv_cb[MT_MAX_LAYERS]{};
+    // Every registered model that starts with a convolution has one that can read the submitted images (LayerDev::first_rows): layer
+    // index 0 is launched that way and nothing stages images.  Over those models: whether some max-pool is done with them, some
+    // layer's rows are stored themselves; largest window; most rows of a tile, and tiles of one row of an image.
+    bool first_on = false, first_pool = false, first_plain = false;
+    uint32_t first_max_ks = 0, first_max_rows = 0;
+    uint64_t first_max_tiles = 0;
+    uint32_t no_conv_first = 0;                      // tuning/testing: images are always staged
+    uint32_t first_cap = 0;                          // testing: MT_FIRST_ROWS in place of first_tile_rows()'s choice
     uint32_t conv_img_lds[MT_MAX_LAYERS]{};          // every conv of a layer index can keep its tiles' input in LDS: the largest frame in bytes, else 0
     int conv_img_two[MT_MAX_LAYERS]{};               // ... and their pixels are one 16-byte chunk: 1, none is: 0 (-1: no convolution seen yet)
     uint32_t no_conv_img = 0;                        // tuning: never use that kernel
@@ -302,6 +310,23 @@ uint32_t choose_row_tiling(const LayerDev& L, uint32_t es)
     return 0;
 }
 
+// LDS of a tile of conv_first_kernel: the input rows of `rows` rows of the layer's output, or of the max-pool's behind it (else null).
+uint64_t first_frame_bytes(const LayerDev& L, const LayerDev* pool, uint32_t es, uint32_t rows)
+{
+    const uint64_t conv_rows = pool ? std::min((rows - 1) * pool->stride + pool->ksize, L.rows_per_req / L.out_w) : rows;
+    return ((conv_rows - 1) * L.stride + L.ksize) * first_frame_cols(L) * kFirstMaxCin * es;
+}
+
+// Most rows of such a tile (0: not even one row's input fits LDS, or the image has too many).
+uint32_t choose_first_rows(const LayerDev& L, const LayerDev* pool, uint32_t es)
+{
+    const uint32_t H = pool ? pool->rows_per_req / pool->out_w : L.rows_per_req / L.out_w;
+    if (H > 0xffffu || L.in_w > 0xffffu) return 0;
+    uint32_t rows = pool ? H : std::min(H, std::max(1u, kFirstTilePixels / L.out_w));
+    while (rows > 1 && first_frame_bytes(L, pool, es, rows) > (pool ? kFirstPoolFrameBytes : kFirstFrameBytes)) --rows;
+    return first_frame_bytes(L, pool, es, rows) + first_scratch_bytes(es) + 16 <= kFirstMaxBytes ? rows : 0;
+}
+
 // The batcher's words per layer of one tenant (see BatchArgs::facts).
 void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[kFactWords])
 {
@@ -315,6 +340,7 @@ void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[kFactWords]
             w[l][0] = L.N_pad / kBrickRows | 1u << 31;
             w[l][1] = conv_tile_rows(L.rows_per_req, L.row_tiles);
             w[l][2] = L.rows_per_req;
+            if (L.first_rows) w[l][3] = L.first_h | L.first_rows << 16;
         }
     }
 }
@@ -455,6 +481,18 @@ void recompute_bounds(mt_ctx* c)
     c->fc_first_chunked = true; c->any_conv_first = c->any_fc_first = false;
     for (uint32_t& m : c->list_mask) m = 0;
     c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
+    c->first_on = !c->no_conv_first; c->first_pool = c->first_plain = false;
+    c->first_max_ks = c->first_max_rows = 0; c->first_max_tiles = 0;
+    for (const HostTenant& t : c->tenants) {         // (ahead of the others: it says which max-pools have a launch)
+        if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
+        const LayerDev& L = t.layers[0].dev;
+        c->any_conv_first = true;
+        if (!L.first_rows) { c->first_on = false; continue; }
+        (L.first_pool ? c->first_pool : c->first_plain) = true;
+        c->first_max_ks = std::max(c->first_max_ks, L.ksize); c->first_max_rows = std::max(c->first_max_rows, L.first_rows);
+        c->first_max_tiles = std::max<uint64_t>(c->first_max_tiles, (uint64_t)L.first_h * ((L.N_pad / kBrickRows + kFirstBlocks - 1) / kFirstBlocks));
+    }
+    c->first_on = c->first_on && c->any_conv_first;
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
         c->has_gap[l] = 0; c->gap_chunks[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
         for (int k = 0; k < kListKinds; ++k) { c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
@@ -470,13 +508,13 @@ void recompute_bounds(mt_ctx* c)
             c->any_fc_first = true;
             if ((t.dev.in_len * c->elem_size) % 16) c->fc_first_chunked = false;
         } else {
-            c->any_conv_first = true;
             c->max_image_pixels = std::max(c->max_image_pixels, t.dev.in_len / (t.dev.in_cin ? t.dev.in_cin : (uint32_t)kChanPad));
         }
         for (uint32_t l = 0; l < t.n_layers; ++l) {
             const LayerDev& L = t.layers[l].dev;
             if (L.kind == kKindNone) continue;
             if (L.kind == MT_GAP) { c->has_gap[l] = 1; c->gap_chunks[l] = std::max(c->gap_chunks[l], std::min<uint64_t>((uint64_t)L.in_h * L.in_w, kGapSweepPixels) * L.cin * c->elem_size / 16); continue; }
+            if (l == 1 && c->first_on && t.layers[0].dev.first_pool) continue;          // done with the convolution in front of it
             if (L.kind == MT_MAXPOOL || L.kind == MT_ADD) { c->has_image_ops[l] = 1; c->image_op_fill[l] = std::max(c->image_op_fill[l], L.out_fill); continue; }
             const int k = L.kind == MT_FC ? 0 : 1;
             c->sum_macs += (double)L.k_valid * L.N * L.rows_per_req;
@@ -560,6 +598,8 @@ bool run_split_k(const mt_ctx* c, uint64_t R)
 struct ConvPlan {
     bool frames;        // tiles read their input from LDS frames
     bool split;         // tiles of 32 pixels and one channel block whose waves split K
+    uint32_t first_cap; // > 0: the submitted images are read (layer index 0), in tiles of at most so many rows ...
+    uint32_t first_frame; // ... whose input takes at most so many bytes of LDS
     uint64_t tiles;     // upper bound of the launch's tiles
 };
 
@@ -584,11 +624,36 @@ uint64_t conv_split_line(const mt_ctx* c, uint32_t l, bool frames)
 // such limit 128 requests to the first 1306 instead of 237); MLPs, CNNs and small residual nets by turns, 600 requests 246 / 214 / 206.
 constexpr uint64_t kConvSplitSkew = 2;
 
+// Most rows of a tile of the first convolutions in a run of R rows: the whole batch in about two workgroups to a compute unit.  A workgroup takes 4-9 us
+// to find its tenant, its filters and its pixels, and more of them do not hide that from each other.  Launches in us at 512 / 1024 / 2048 / 4096
+// workgroups (as far as tiles go): 64 images 224x224 through 7x7x64 and its max-pool 48 / 56 / 60 / 92, 2048 images 32x32 (3x3x32) 33.5 / 33.8 / 33.2 /
+// 35.1, 500 of them 11.4 / 11.9 / 14.3 / 18.9, 150 fp32 29x35 (3x3x24) 14.5 / 14.2 / 17.7 / 24.6, MLPs, CNNs and residual nets by turns, 600 requests
+// 13.3 / 16.4 / 19.9 / 28.4.
+uint32_t first_tile_rows(const mt_ctx* c, uint64_t R)
+{
+    if (c->first_cap) return c->first_cap;
+    const uint64_t wanted = 2 * c->n_cus;
+    return (uint32_t)std::min<uint64_t>((R * c->first_max_tiles + wanted - 1) / wanted, c->first_max_rows);
+}
+
 // `named`: the requests of every tenant that has any, where each submission named its tenant; null where some stand in a
 // device-resident id array
 ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<NamedRows>* named)
 {
     ConvPlan p{};
+    if (l == 0 && c->first_on) {
+        p.first_cap = first_tile_rows(c, R);
+        uint64_t most = 0;
+        for (const HostTenant& t : c->tenants) {
+            if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
+            const LayerDev& L = t.layers[0].dev;
+            const uint32_t strips = first_strips(L.first_h, L.first_rows, p.first_cap), rows = (L.first_h + strips - 1) / strips;
+            p.first_frame = std::max<uint32_t>(p.first_frame, (uint32_t)first_frame_bytes(L, L.first_pool ? &t.layers[1].dev : nullptr, c->elem_size, rows));
+            most = std::max<uint64_t>(most, strips * ((L.N_pad / kBrickRows + kFirstBlocks - 1) / kFirstBlocks));
+        }
+        p.tiles = R * most;
+        return p;
+    }
     p.frames = c->conv_img_lds[l] > 1 && !c->pool_fused[l] && !c->no_conv_img;
     p.tiles = tile_bound(c, 1, l, R);
     if (c->max_nt[1][l] == 0 || c->pool_fused[l]) return p;
@@ -801,6 +866,16 @@ mt_status plan_model(mt_ctx* c, const mt_layer_spec* specs, uint32_t n_layers, H
         LayerDev& d = out->layers[l].dev;
         if (d.kind == MT_CONV2D && !d.pool_fill) d.row_tiles = choose_row_tiling(d, es);
     }
+    // A first convolution of images with few channels can read them as submitted, and take a max-pool that is its only reader with it.
+    if (LayerDev& d = out->layers[0].dev; d.kind == MT_CONV2D && specs[0].in_features <= kFirstMaxCin && !d.pool_fill && !d.fuse_add) {
+        const LayerDev* pool = n_layers > 1 && out->layers[1].dev.kind == MT_MAXPOOL && src_of[1] == 1 && last_use[1] == 1 ? &out->layers[1].dev : nullptr;
+        d.first_rows = pool ? choose_first_rows(d, pool, es) : 0;
+        d.first_pool = d.first_rows != 0;
+        if (!d.first_pool) { pool = nullptr; d.first_rows = choose_first_rows(d, nullptr, es); }
+        const LayerDev& last = pool ? *pool : d;
+        d.first_cin = specs[0].in_features;
+        d.first_h = last.rows_per_req / last.out_w;
+    }
     return MT_OK;
 }
 
@@ -861,6 +936,13 @@ uint16_t bf16_bits_from_double(double x)
         return (uint16_t)(sign | (uint16_t)(be << 7) | (uint16_t)(kept - 128));
     }
     return (uint16_t)(sign | (uint16_t)kept);                        // subnormal; kept == 128 is the smallest normal number
+}
+
+bool all_finite_bf16(const uint16_t* w, size_t n)
+{
+    for (size_t i = 0; i < n; ++i)
+        if ((w[i] & 0x7f80) == 0x7f80) return false;
+    return true;
 }
 
 // W' = round(W * s), b' = float((b - mean) * s + beta) with s = gamma / sqrt(var + eps), per output
@@ -937,6 +1019,8 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
     if (const char* e = getenv("MT_NO_FUSED_HEAD")) c->no_fused_head = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_FUSED_POOL")) c->no_fused_pool = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_IMG")) c->no_conv_img = atoi(e) != 0;
+    if (const char* e = getenv("MT_NO_CONV_FIRST")) c->no_conv_first = atoi(e) != 0;
+    if (const char* e = getenv("MT_FIRST_ROWS")) c->first_cap = (uint32_t)std::max(0, atoi(e));
     if (const char* e = getenv("MT_NO_FUSED_ADD")) c->no_fused_add = atoi(e) != 0;
     if (const char* e = getenv("MT_CONV_SPLIT_TILES")) c->conv_split_tiles = std::max(0, atoi(e));
     if (const char* e = getenv("MT_BIG_WALK")) c->big_walk = atoi(e) != 0;
@@ -959,6 +1043,7 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
         c->n_cus = (uint32_t)std::max(cus, 8) / 8 * 8;
     }
     CREATE_TRY(prepare_conv(cfg->dtype));
+    CREATE_TRY(prepare_conv_first(cfg->dtype));
     const uint64_t R = cfg->max_requests, T = cfg->max_tenants;
     CREATE_TRY(hipMalloc((void**)&c->d_arena, c->cfg.arena_bytes));
     CREATE_TRY(hipMalloc((void**)&c->d_tenants, T * sizeof(TenantDev)));
@@ -1115,6 +1200,9 @@ mt_status mt_register_model_bn(mt_ctx* c, uint32_t tenant, const mt_layer_spec* 
                 w_src = folded.data();
             }
             if (c->elem_size == 2) pack_weights<uint16_t>(hl, w_src, w_dst); else pack_weights<float>(hl, w_src, w_dst);
+            // conv_first_kernel's bf16 form multiplies a step's zeros with another step's filters: not with infinite ones
+            if (LayerDev& d = ht.layers[l].dev; d.first_rows && c->elem_size == 2 && !all_finite_bf16((const uint16_t*)w_src, (size_t)d.N * hl.spec.in_features * d.ksize * d.ksize))
+                d.first_rows = d.first_pool = 0;
         }
     }
     auto drop_stage = [&]() { if (c->cache && stage) (void)hipHostFree(stage); };
@@ -1470,6 +1558,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     for (uint32_t g = 0; g < MT_MAX_LAYERS / kLayerGroup; ++g)
         b.list_mask[g] = big_enabled ? c->list_mask[g] : c->list_mask[g] & ((1u << (2 * kLayerGroup)) - 1);   // no big-tile lists to build
     b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles;
+    b.first_cap = plan_conv(c, 0, R, named).first_cap;
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) {
         if (plan_conv(c, l, R, named).split) b.conv_split[l / 32] |= 1u << l % 32;
     }
@@ -1521,7 +1610,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
         // workgroups per block of 32 rows: each takes ~64 KiB of it, so that long rows have enough loads in flight
         const uint32_t gs = row_slices((uint64_t)c->max_in_len * c->elem_size * kBrickRows, 65536);      // c5: 146 -> 133 us with four
         if (c->any_fc_first && !fuse_gather) TIMED(kProfGather, launch_gather(g, gs, s));
-        if (c->any_conv_first) TIMED(kProfGatherImg, launch_gather_image(g, image_slices(c->max_image_pixels / 2, R), s));       // in pairs of pixels
+        if (c->any_conv_first && !c->first_on) TIMED(kProfGatherImg, launch_gather_image(g, image_slices(c->max_image_pixels / 2, R), s));       // in pairs of pixels
     }
 
     ActBufs bufs{};                        // every layer names the buffers it reads and writes (LayerDev::in_buf ...)
@@ -1543,10 +1632,12 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             ga.layers = c->d_layers; ga.off = c->d_off; ga.M = c->d_M; ga.act = bufs; ga.arena = c->d_arena;
             ga.logits = c->d_logits; ga.S = c->S; ga.C_pad = c->C_pad; ga.zeros = c->d_zeros;
             // a launch holds fewer than 2^32 work items; cannot be exceeded by activations that fit the device's memory
-            if (grid > kMaxLaunchItems / (conv.split ? 1024 : kind == 2 ? 512 : 256))
+            if (grid > kMaxLaunchItems / (conv.split ? 1024 : kind == 2 || conv.first_cap ? 512 : 256))
                 return fail(c, MT_EUNSUPPORTED, "layer %u: %llu tiles exceed one launch", l, (unsigned long long)grid);
             const uint32_t g32 = (uint32_t)grid;
+            ga.first_cap = conv.first_cap;
             if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, split_k || c->max_fc_cols[l] <= 2 * (uint32_t)kBrickRows, g32, s));
+            else if (conv.first_cap) TIMED(kProfConv + l, launch_conv_first(ga, c->cfg.dtype, c->first_max_ks, c->first_pool, c->first_plain, conv.first_frame, g32, s));
             else if (conv.split) TIMED(kProfConv + l, launch_conv_split(ga, c->cfg.dtype, (c->max_conv_k[l] * c->elem_size + 31) / 32, g32, s));
             else if (kind == 1) TIMED(kProfConv + l, launch_conv(ga, c->cfg.dtype, c->max_conv_cb[l], c->conv_quad[l],
                                                                     conv.frames ? c->conv_img_lds[l] : 0, c->conv_img_two[l] == 1,
@@ -1565,7 +1656,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             GapArgs pa{};
             pa.layer = l; pa.P = P; pa.layers = c->d_layers; pa.tenants = c->d_tenants;
             pa.off = c->d_off; pa.M = c->d_M; pa.T = T; pa.act = bufs; pa.S = c->S;
-            pa.elem_size = c->elem_size;
+            pa.elem_size = c->elem_size; pa.first_pooled = l == 1 && c->first_on;
             TIMED(kProfImageOps + l, launch_image_ops(pa, image_slices(c->image_op_fill[l] * c->elem_size / 16, R), s));   // in 16-byte chunks
         }
     }
@@ -1651,12 +1742,13 @@ void request_cost(const mt_ctx* c, const HostTenant& ht, uint64_t* flops, uint64
 // than the chain of dependent loads through K of one tile.
 // Weights that fit the 256 MB memory-side cache and are read by every run stream faster than
 // weights that come from HBM every time (steady serving of the same tenants is assumed).
-constexpr double kUsLaunchGap = 4.0;
+constexpr double kUsLaunchGap = 3.0;
 constexpr double kUsFcFixed = 3.7, kUsPerMbCached = 0.132, kUsPerMbHbm = 0.18, kCachedMb = 240.0;
 constexpr double kUsPerMbL2 = 0.056, kUsFcChainFixed = 4.0, kUsPerKStep = 0.12;
-constexpr double kUsBigFixed = 4.0, kUsBigTileFixed = 7.0, kUsBigTilePer4096 = 116.0;
+constexpr double kUsBigFixed = 4.0, kUsBigTileFixed = 7.0, kUsBigTilePer4096 = 108.0;
 constexpr double kUsConvFixed = 5.0, kConvMbPerUs = 4.0, kConvMflopPerUs = 0.5e3;      // 4.0 TB/s, 0.5 PFLOP/s
-constexpr double kUsConvFramePerKStep = 0.13, kConvFrameMflopPerUs = 0.6e3;   // the same for layer indices served from LDS frames: filter bricks are the only loads in the K loop
+constexpr double kUsConvFramePerKStep = 0.095, kConvFrameMflopPerUs = 0.6e3;   // the same for layer indices served from LDS frames: filter bricks are the only loads in the K loop
+constexpr double kUsConvFirstFixed = 8.0, kConvFirstMbPerUs = 5.2, kConvFirstMflopPerUs = 0.38e3;     // first convolutions on the submitted images, by the multiplications that they need
 constexpr double kUsConvSplitFixed = 1.0, kUsConvSplitPerKStep = 0.034;     // launches whose tiles split K among their waves: per k-step of a tile, one tile per compute unit at a time
 constexpr double kUsConvPerKStep = 0.21;     // a convolution tile's walk through K, per k-step of 32 bytes per pixel: a launch lasts at least as long as its longest tile
 constexpr double kUsSmallFixed = 3.0, kCopyMbPerUs = 3.7, kHeadMbPerUs = 5.7, kUsHeadPerRow = 0.0008;
@@ -1739,7 +1831,7 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
         else { img_in_mb += counts[t] * (double)ht.dev.in_len * es / MB; img_out_mb += counts[t] * (double)ht.dev.in_fill * es / MB; }
     }
     if (c->any_fc_first && !fuse_gather) launch(kUsSmallFixed + 2.0 * fc_in_mb / kCopyMbPerUs);
-    if (c->any_conv_first) launch(kUsSmallFixed + (img_in_mb + img_out_mb) / kCopyMbPerUs);
+    if (c->any_conv_first && !c->first_on) launch(kUsSmallFixed + (img_in_mb + img_out_mb) / kCopyMbPerUs);
 
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) {
         if (l > 0 && c->pool_fused[l - 1]) continue;           // pooled by the convolutions of the index before
@@ -1754,7 +1846,7 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
             }
         const bool big_layer = big_tiles >= c->big_min_tiles;
         double w_mb = 0.0, l2_mb = 0.0, chain = 0.0, big_us = 0.0, conv_mb = 0.0, conv_mflop = 0.0, gap_mb = 0.0, ops_mb = 0.0;
-        double big_rounds_k = 0.0, conv_chain = 0.0;
+        double big_rounds_k = 0.0, conv_chain = 0.0, first_mb = 0.0, first_mflop = 0.0;
         const ConvPlan conv_plan = plan_conv(c, l, R, nullptr);                                      // the launch decision of run_impl where the tenants stand in an id array
         const bool conv_frames = conv_plan.frames;
         double split_steps = 0.0, split_longest = 0.0;
@@ -1781,18 +1873,26 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
                 const double out_elems = (c->pool_fused[l] ? d.N : d.out_len) + (d.fuse_add ? d.out_len : 0);      // pooled on the way out; the other operand of an addition done here
                 conv_mb += (M * ((double)d.in_h * d.in_w * d.cin + out_elems) * es + (double)d.N_pad * d.K * es) / MB;
                 conv_mflop += 2.0 * M * d.rows_per_req * d.k_valid * d.N / 1e6;
+                if (conv_plan.first_cap) {
+                    const LayerDev& last = d.first_pool ? c->tenants[t].layers[1].dev : d;
+                    first_mb += (M * ((double)d.in_h * d.in_w * d.first_cin + last.out_len) * es + (double)d.N_pad * d.K * es) / MB;
+                    first_mflop += 2.0 * M * d.rows_per_req * d.ksize * d.ksize * d.first_cin * d.N / 1e6;
+                }
                 const double k_steps = std::ceil(d.k_valid * es / 32.0);
                 split_longest = std::max(split_longest, k_steps);
                 split_steps += std::ceil(M * d.rows_per_req / kBrickRows) * (d.N_pad / kBrickRows) * k_steps;
                 conv_chain = std::max(conv_chain, (conv_frames ? kUsConvFramePerKStep : kUsConvPerKStep) * d.k_valid * es / 32.0);
             } else if (d.kind == MT_GAP) {
                 gap_mb += M * ((double)d.in_h * d.in_w * d.cin + d.out_len) * es / MB;
+            } else if (l == 1 && c->first_on && c->tenants[t].layers[0].dev.first_pool) {
+                // done with the convolution in front of it
             } else if (d.kind == MT_MAXPOOL || d.kind == MT_ADD) {    // an addition has two inputs
                 ops_mb += M * ((double)d.in_h * d.in_w * d.cin * (d.kind == MT_ADD ? 2.0 : 1.0) + d.out_len) * es / MB;
             }
         }
         if (c->max_nt[0][l] > 0) launch(std::max(chain, kUsFcFixed + us_per_mb * w_mb + kUsPerMbL2 * l2_mb));
-        if (conv_plan.split) launch(kUsConvSplitFixed + kUsConvSplitPerKStep * std::max(split_longest, split_steps / kComputeUnits));
+        if (conv_plan.first_cap) launch(kUsConvFirstFixed + std::max(first_mb / kConvFirstMbPerUs, first_mflop / kConvFirstMflopPerUs));
+        else if (conv_plan.split) launch(kUsConvSplitFixed + kUsConvSplitPerKStep * std::max(split_longest, split_steps / kComputeUnits));
         else if (c->max_nt[1][l] > 0) launch(kUsConvFixed + std::max(conv_chain, std::max(conv_mb / kConvMbPerUs, conv_mflop / (conv_frames ? kConvFrameMflopPerUs : kConvMflopPerUs))));
         if (big_enabled && c->max_nt[2][l] > 0 && tile_bound(c, 2, l, R) >= c->big_min_tiles) {
             // tiles share the chip in rounds of one per compute unit; a tile's time grows with K

@@ -20,6 +20,8 @@
 //                   copied to LDS once and every tap is read from there) and conv_split_kernel
 //                   (launches of few tiles: 32 pixels and 32 channels to a tile, whose 4 to 16 waves
 //                   share K): implicit-GEMM convolution for all tenants
+//   conv_first.hip  conv_first_kernel: first convolutions of images with at most four channels, from the
+//                   submitted images themselves; takes the max-pool behind the layer with it
 //   small.hip       gather_kernel / gather_image_kernel (submitted rows -> bricks / padded NHWC),
 //                   gap_kernel (global average pooling), head_kernel (softmax + argmax in
 //                   submission order), copy_kernel (the yardstick for byte counters)
@@ -211,6 +213,57 @@ __device__ __forceinline__ void add_residual(f32x4 (&y)[4], const T* skip, uint3
         }
     }
     activate_block<4>(y, act);
+}
+
+// Quotient and remainder by a wave-uniform divisor; image sizes are mostly powers of two, and a
+// general 32-bit division costs some thirty vector instructions per lane.
+__device__ __forceinline__ void divmod_uniform(uint32_t x, uint32_t d, uint32_t* q, uint32_t* r)
+{
+    if ((d & (d - 1)) == 0) { *q = x >> __builtin_ctz(d); *r = x & (d - 1); }
+    else { *q = x / d; *r = x - *q * d; }
+}
+
+// ---- NHWC store of one 32-pixel x 32-channel unit held in the transposed accumulator layout ----
+// After an MFMA with the filter brick as row operand, lane (li, lh) holds channels 8g + 4 lh +
+// {0..3} of pixel li: stored from there, a wave instruction writes 64 separate 8- or 16-byte
+// pieces, and the texture path counts (and takes time for) every one of them; the counters
+// showed the convolution kernels bound by exactly that rate.  So the unit goes through a
+// wave-private LDS scratch as [pixel][channel] rows and is read back so that consecutive
+// lanes hold consecutive 16-byte chunks of a pixel's row: a pixel's 64 (bf16) or 128 (fp32)
+// bytes leave in one piece.  Each pixel's destination travels through the scratch as well
+// (null for pixels past the end), so the storing lane needs no index arithmetic.
+template <typename T> constexpr uint32_t unit_row_stride() { return kBrickRows * sizeof(T) + 16; }
+template <typename T> constexpr uint32_t unit_scratch_bytes() { return kBrickRows * unit_row_stride<T>() + kBrickRows * 8; }
+
+template <typename T>
+__device__ __forceinline__ void store_unit_nhwc(const f32x4 (&y)[4], T* my_pixel_out, uint32_t n_valid, uint32_t through, uint8_t* scratch)
+{
+    constexpr uint32_t EPC = 16 / sizeof(T), RS = unit_row_stride<T>();
+    constexpr uint32_t CP = kBrickRows / EPC;                       // 16-byte chunks per pixel row: 4 (bf16) or 8 (fp32)
+    const uint32_t lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    T** dests = (T**)(scratch + kBrickRows * RS);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        T o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (T)y[g][e];
+        uint8_t* p = scratch + li * RS + (8 * g + 4 * lh) * sizeof(T);
+        if constexpr (sizeof(T) == 2) *(uint64_t*)p = __builtin_bit_cast(uint64_t, o);
+        else *(u32x4*)p = __builtin_bit_cast(u32x4, o);
+    }
+    if (lh == 0) dests[li] = my_pixel_out;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // the wave's own LDS writes have landed
+#pragma unroll
+    for (uint32_t pass = 0; pass < CP / 2; ++pass) {
+        const uint32_t px = pass * (64 / CP) + lane / CP, ch = lane % CP;
+        T* dst = dests[px];
+        const u32x4 v = *(const u32x4*)(scratch + px * RS + ch * 16);
+        if (dst != nullptr && ch * EPC < n_valid) {
+            if (through) store_through((u32x4*)(dst + ch * EPC), v);      // the same for the whole launch
+            else *(u32x4*)(dst + ch * EPC) = v;
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // reads done before the next unit overwrites the scratch
 }
 
 // The label of a row whose classes were compared in parts with `>` from -inf on: best is the first class with the largest logit, 0x7fffffff

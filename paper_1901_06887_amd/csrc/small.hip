@@ -288,6 +288,7 @@ __global__ __launch_bounds__(kImageOpThreads) void image_ops_kernel(GapArgs a)
     if (!packed_row_tenant<kImageOpThreads>(a.off, a.M, a.T, p, &t)) return;
     const LayerDev L = a.layers[t * MT_MAX_LAYERS + a.layer];
     if (a.tenants[t].n_layers <= a.layer) return;
+    if (a.first_pooled && a.layers[t * MT_MAX_LAYERS].first_pool) return;      // done with the convolution in front of it
     if (L.kind == MT_MAXPOOL) {
         if (a.elem_size == 2) { if (L.ksize == 3) maxpool_row<__bf16, 3>(a, L, p); else maxpool_row<__bf16, 2>(a, L, p); }
         else { if (L.ksize == 3) maxpool_row<float, 3>(a, L, p); else maxpool_row<float, 2>(a, L, p); }

@@ -310,3 +310,103 @@ def test_convolution_outputs_on_both_sides_of_the_line_for_stores_through_l2():
         assert all(np.array_equal(p, q[a:b]) for p, q in zip(part, whole))
     rows = np.array([0, 21, 43])
     compare(w, tuple(v[rows] for v in whole), oracle_rows(w, rows), rows=rows, what="through", deep=True)
+
+
+def first_conv_workload(dtype, rows, hw, ci, convs, pool=None, act=wl.ACT_RELU, seed=370):
+    """Models that start with a convolution (k, stride, channels) of the same images, a max-pool (k, stride, pad) behind it or not, and a
+    convolution behind that to which places matter."""
+    tenants = {}
+    for t, (k, stride, co) in enumerate(convs):
+        h, w_ = hw
+        layers = [wl.LayerSpec(wl.CONV, act, ci, co, h, w_, stride, ksize=k, pad=(k - 1) // 2)]
+        h, w_ = layers[-1].out_hw()
+        if pool:
+            layers.append(wl.LayerSpec(wl.MAXPOOL, wl.ACT_NONE, co, co, h, w_, pool[1], ksize=pool[0], pad=pool[2]))
+            h, w_ = layers[-1].out_hw()
+        layers.append(wl.LayerSpec(wl.CONV, wl.ACT_RELU, co, 16, h, w_, 2, ksize=3, pad=1))
+        h, w_ = layers[-1].out_hw()
+        layers += [wl.LayerSpec(wl.GAP, wl.ACT_NONE, 16, 16, h, w_), wl.LayerSpec(wl.FC, wl.ACT_NONE, 16, 7)]
+        tenants[t] = wl.make_model(layers, dtype, seed, t)
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((rows, ci * hw[0] * hw[1])).astype(np.float32)
+    return wl.Workload("first", dtype, tenants, rng.integers(0, len(convs), rows).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
+
+
+# first convolutions on the submitted images: one to four channels, every window and stride (several in a launch), images of a pixel and
+# of rows that are not whole groups of pixels, one to five channel blocks, every pool, tiles of one row, of a few and of whatever fits
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("hw,ci,convs,pool,rows", [
+    ((1, 1), 3, [(3, 1, 8)], None, 9), ((1, 3), 3, [(7, 2, 40), (1, 1, 8)], None, 1), ((5, 7), 1, [(3, 1, 72), (1, 2, 16)], None, 2), ((9, 6), 2, [(7, 1, 24)], None, 9),
+    ((11, 13), 4, [(3, 2, 32), (7, 1, 136)], None, 4), ((40, 66), 3, [(3, 1, 40), (3, 1, 96)], None, 99), ((70, 33), 3, [(3, 2, 8), (1, 1, 64), (7, 2, 32)], None, 3),
+    ((2, 2), 3, [(3, 1, 8)], (2, 2, 0), 1), ((8, 8), 3, [(7, 2, 32), (3, 1, 160)], (3, 2, 1), 9), ((13, 10), 1, [(3, 1, 72)], (2, 1, 1), 5), ((15, 22), 4, [(3, 2, 24), (1, 1, 64)], (3, 1, 1), 99),
+    ((90, 61), 3, [(7, 2, 64), (3, 1, 40)], (3, 2, 1), 5), ((64, 150), 3, [(3, 1, 64)], (3, 2, 0), 99), ((33, 120), 2, [(3, 1, 96)], (2, 2, 1), 1), ((61, 57), 3, [(7, 1, 128)], (3, 1, 0), 7)])
+def test_first_convolutions_on_the_submitted_images(monkeypatch, dtype, hw, ci, convs, pool, rows):
+    monkeypatch.setenv("MT_FIRST_ROWS", str(rows))
+    monkeypatch.setenv("MT_CONV_SPLIT_TILES", "0")
+    w = first_conv_workload(dtype, 11, hw, ci, convs, pool, act={1: wl.ACT_GELU, 2: wl.ACT_NONE}.get(ci, wl.ACT_RELU))
+    what = "%s %s x%d %s %s tiles of %d rows" % (dtype, hw, ci, convs, pool, rows)
+    print(what, flush=True)
+    ctx = make_context(w)
+    one = check(w, what, ctx)
+    # rows that start and lie at odd addresses: the same bits
+    n_in, es = w.inputs.shape[1], 2 if dtype == "bf16" else 4
+    x = torch_io.to_device(np.concatenate([w.inputs, np.zeros((11, 1), np.float32)], axis=1), dtype).reshape(-1)
+    flat = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")
+    flat[1:] = x
+    ids, out = torch.from_numpy(w.tenant_ids).cuda(), torch_io.alloc_outputs(11, ctx.cfg.max_classes)
+    ctx.submit_batch(ids.data_ptr(), flat.data_ptr() + es, 11, n_in + 1)
+    ctx.run(torch.cuda.current_stream().cuda_stream, out.labels.data_ptr(), out.probs.data_ptr(), out.logits.data_ptr(), out.n_classes.data_ptr(), 11, ctx.cfg.max_classes)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.logits.cpu().numpy().astype(np.float64), one[0])
+    ctx.close()
+    # staged images and a max-pool of its own: the same bits in bf16, the same products in another order in fp32
+    monkeypatch.setenv("MT_NO_CONV_FIRST", "1")
+    ctx = make_context(w)
+    staged = gpu_run(ctx, w, poison=True)
+    if dtype == "bf16":
+        assert np.array_equal(staged[0], one[0])
+    else:
+        assert np.linalg.norm(staged[0] - one[0]) <= 5e-6 * np.linalg.norm(one[0])
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("k,stride,pool", [(1, 1, None), (3, 1, None), (7, 2, None), (3, 1, (3, 2, 1))])
+def test_infinite_pixels_stay_inside_their_windows(dtype, k, stride, pool):
+    """Linear layers of ones over an image with one infinite pixel: the mean over the outputs is infinite if some window holds the pixel, and never NaN."""
+    h, w_ = 12, 14
+    layers = [wl.LayerSpec(wl.CONV, wl.ACT_NONE, 3, 8, h, w_, stride, ksize=k, pad=(k - 1) // 2)]
+    h, w_ = layers[-1].out_hw()
+    if pool:
+        layers.append(wl.LayerSpec(wl.MAXPOOL, wl.ACT_NONE, 8, 8, h, w_, pool[1], ksize=pool[0], pad=pool[2]))
+        h, w_ = layers[-1].out_hw()
+    layers += [wl.LayerSpec(wl.GAP, wl.ACT_NONE, 8, 8, h, w_), wl.LayerSpec(wl.FC, wl.ACT_NONE, 8, 3)]
+    m = wl.make_model(layers, dtype, 371, 0)
+    for l, s in enumerate(layers):
+        if s.kind in (wl.CONV, wl.FC):
+            m.weights[l][:] = 1
+            m.biases[l][:] = 0
+    x = np.ones((12 * 14 + 1, 12 * 14 * 3), np.float32)
+    x[np.arange(12 * 14), np.arange(12 * 14) * 3 + 1] = -np.inf      # request p: pixel p; the last one: none
+    w = wl.Workload("inf", dtype, {0: m}, np.zeros(len(x), np.int32), x)
+    lg = gpu_run(make_context(w), w, poison=True)[0][:, :3]
+    assert np.isfinite(lg[-1]).all() and not np.isnan(lg).any()
+    ch, cw = layers[0].out_hw()
+    for p, row in enumerate(lg[:-1]):
+        y, xx = divmod(p, 14)
+        holds = np.outer(np.abs(np.arange(ch) * stride - y) <= k // 2, np.abs(np.arange(cw) * stride - xx) <= k // 2)      # convolution outputs whose window holds the pixel
+        if pool:                                                     # a maximum is infinite where all of its window is
+            cut = lambda v, o: v[max(o * pool[1] - pool[2], 0):o * pool[1] - pool[2] + pool[0]]  # noqa: E731
+            holds = np.array([[cut(cut(holds, oy).T, ox).all() for ox in range(w_)] for oy in range(h)])
+        assert np.array_equal(row, np.full(3, -np.inf)) == holds.any() and np.isinf(row).all() == holds.any(), p
+
+
+def test_first_convolutions_with_infinite_filters(monkeypatch):
+    """Filters that are not finite take the staged path: the same bits, undefined and infinite logits among them."""
+    w = first_conv_workload("bf16", 7, (9, 10), 3, [(3, 1, 16), (7, 2, 40)], (3, 2, 1))
+    w.tenants[0].weights[0][3, 1, 0, 2] = np.inf
+    got = []
+    for off in ("0", "1"):
+        monkeypatch.setenv("MT_NO_CONV_FIRST", off)
+        got.append(gpu_run(make_context(w), w, poison=True)[0])
+    assert np.array_equal(got[0], got[1], equal_nan=True) and np.isfinite(got[0][w.tenant_ids == 1]).all() and not np.isfinite(got[0][w.tenant_ids == 0]).all()
