@@ -206,6 +206,7 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
     uint4 fq[kPre];
 #pragma unroll
     for (uint32_t i = 0; i < kPre; ++i) fq[i] = one_wave ? load_fact(w + i * kWaves, lane) : load_fact(w, lane * kPre + i);
+    const uint32_t second = a.first_pair && one_wave && w == 0 ? load_fact(1, lane).w : 0;       // (second convolutions that are done with the first)
     for (uint32_t t = tid; t < Tp; t += kBatchThreads) regl[t] = t < T && a.tenants[t].registered;
     for (uint32_t i = tid; i < nw * Tp; i += kBatchThreads) hist[i] = PRE ? a.hist_g[i] : 0;
     if (tid == 0) big_l = 0;
@@ -357,7 +358,8 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
             const bool rem_sk = big && big_remainder_split_k(y);
             const uint32_t sh = sk || rem_sk || ((x >> 30) & 1) ? 5 : 6, gq = rem_sk ? y / kBrickRows : groups;
             n_fc[j] = !conv && groups && M ? ((M - Mb + (1u << sh) - 1) >> sh) * gq : 0;
-            n_conv[j] = conv && M ? (a.first_cap && l == 0 ? M * first_strips(f[j].w & 0xffffu, f[j].w >> 16, a.first_cap) * ceil_div(blocks, kFirstBlocks) : split ? ceil_div(M * f[j].z, kBrickRows) * blocks : ceil_div(M * y, kConvTileRows) * ceil_div(blocks, kTileCols / kBrickRows)) : 0;
+            const uint32_t rows = a.first_pair && l == 0 ? (J == 1 ? second : load_fact(1, t0 + j).w) : f[j].w;     // first convolutions on the submitted images
+            n_conv[j] = conv && M && !(a.first_pair && l == 1) ? (a.first_cap && l == 0 ? M * first_strips(rows & 0xffffu, rows >> 16, a.first_cap) * ceil_div(blocks, kFirstBlocks) : split ? ceil_div(M * f[j].z, kBrickRows) * blocks : ceil_div(M * y, kConvTileRows) * ceil_div(blocks, kTileCols / kBrickRows)) : 0;
             n_big[j] = ceil_div(Mb, kBigTile) * ceil_div(y, kBigTile);
         }
         auto emit = [&](uint32_t kind, const uint32_t (&n)[J], uint32_t& run) {

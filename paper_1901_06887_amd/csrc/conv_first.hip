@@ -161,11 +161,11 @@ __device__ __forceinline__ void first_rows_out(const FirstTile<T>& f, const u32x
     const float inv = 1.0f / (float)f.out_w;
     for (uint32_t u = u0; u * kBrickRows < px; u += du) {
         const uint32_t p = u * kBrickRows + li, q = p < px ? p : 0;  // empty slots multiply the first pixel; nothing becomes of them
-        const uint32_t oh = (uint32_t)(((float)q + 0.5f) * inv), ow = q - oh * f.out_w;      // (exact: fewer than 2^20 pixels)
+        const uint32_t oh = (uint32_t)(((float)q + 0.5f) * inv), ow = q - __umul24(oh, f.out_w);      // (exact: fewer than 2^20 pixels)
         f32x16 acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-        first_window<T, KS>(acc, filters, f.frame + (oh * f.stride * f.row_bytes + ow * f.stride * 4 * (uint32_t)sizeof(T)), f.row_bytes);
+        first_window<T, KS>(acc, filters, f.frame + (__umul24(oh, f.stride * f.row_bytes) + __umul24(ow, f.stride * 4 * (uint32_t)sizeof(T))), f.row_bytes);
         f32x4 y[4];
         first_activate<T>(y, acc, f);
         store_unit_nhwc<T>(y, p < px ? f.out + (size_t)(f.c0 * f.out_w + p) * f.N + f.nbase : nullptr, nvalid, through, scratch);
@@ -425,6 +425,170 @@ void conv_first_kernel(GemmArgs a)
     else compute(std::integral_constant<uint32_t, 1>{});
 }
 
+// ---- a first convolution and the 3x3 convolution behind it ----------------------------------------
+// Where that convolution is the first one's only reader, in every model that starts with one (LayerDev::pair_rows): a workgroup computes the rows of the first layer that a
+// tile of whole rows of the second one needs into a frame in LDS, rounded as they would have been stored and with a zero border, and
+// the second layer from there as conv_img_kernel does: four waves side by side over NCB blocks of channels and the pixel blocks,
+// filters through a register ring.  The first layer's output is never written; its rows on a tile's edge are computed twice.  Sums in the
+// order of the other kernels: the same bits.
+// 2048 images of 32x32x3 through 3x3x32 and 3x3x64 at stride 2: 33 + 55 -> 65 us, and 134 MB neither written nor read (the pass 162 -> 115); 150 fp32 images of
+// 29x35x3 through 3x3x24 and 3x3x40 14.5 + 54 -> 64.5.  Of the 11 us of a tile (three to a compute unit) 4 pass before the first MFMA, 3 are the first
+// layer, 2.3 the second, 1.4 its stores.  Tiles in 26 / 32 / 40 / 52 KiB of LDS: 103 / 78 / 70 / 65.5 us.  Beside models that cannot take
+// it (a launch of theirs besides) it gains nothing: MLPs, CNNs and residual nets by turns, 600 requests 12.6 + 12.7 against 12.7 + 13.8, 6000 requests 78 + 36 against 98 + 70.
+template <typename T, uint32_t NCB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void conv_pair_kernel(GemmArgs a)
+{
+    constexpr uint32_t THREADS = 256, WAVES = 4, EPC = 16 / sizeof(T), KB = 2 * EPC, P = 8, WR = WAVES / NCB, RBW = kConvTileRows / kBrickRows / WR;
+    typedef const __attribute__((address_space(1))) u32x4* gptr_t;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    __shared__ uint32_t owner_part[WAVES];
+    __shared__ __attribute__((aligned(16))) float bias[kFirstBlocks * kBrickRows];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
+    TileOwner<THREADS> lookup;
+    lookup.fetch(a.tile_base, a.T);
+    const uint32_t n_tiles = a.tile_base[a.T];
+    uint8_t* const mid = lds + a.img_lds;                            // the first layer's rows
+    for (uint32_t q = tid * 16; q < a.img_lds + a.mid_lds; q += THREADS * 16) *(u32x4*)(lds + q) = u32x4{0, 0, 0, 0};
+    uint32_t idx;
+    if (!logical_tile(n_tiles, &idx)) return;
+    const uint32_t t = lookup.owner(a.T, idx, owner_part);           // uniform: the tenant's facts come through scalar loads
+    const LayerDev L = a.layers[t * MT_MAX_LAYERS], M = a.layers[t * MT_MAX_LAYERS + 1];
+    const uint32_t seg0 = a.off[t], strips = first_strips(M.pair_h, M.pair_rows, a.first_cap), step = ceil_div(M.pair_h, strips);
+    const uint32_t local = idx - a.tile_base[t], req = local / strips, strip = local - req * strips;
+    const T* const src = (const T*)a.row_src[a.perm[seg0 + req]];
+    const uint32_t p0 = strip * step, p1 = min(p0 + step, M.pair_h);
+    const uint32_t w0 = L.out_w, h0 = L.rows_per_req / w0, ncb0 = L.N_pad / kBrickRows, cb0 = wave % ncb0;
+
+    // ---- the first layer's rows under rows p0 .. p1 - 1 of the second one's
+    const uint32_t st = M.stride, cin = M.cin, PB = cin * (uint32_t)sizeof(T) + 16, RSB = (w0 + 2) * PB;     // bytes per pixel and row of `mid`
+    const int32_t m0 = (int32_t)(p0 * st) - 1;                       // the first layer's row in row 0 of `mid`
+    FirstTile<T> f;
+    f.row_bytes = first_frame_cols(L) * 4 * (uint32_t)sizeof(T);
+    f.c0 = (uint32_t)max(m0, 0);
+    f.rows = (uint32_t)min((int32_t)((p1 - 1) * st) + 2, (int32_t)h0) - f.c0;
+    f.frame = lds; f.stride = L.stride; f.out_w = w0; f.N = L.N; f.nbase = cb0 * kBrickRows; f.act = L.act;
+    f.bias = bias + cb0 * kBrickRows; f.out = nullptr;
+    constexpr uint32_t KSMAX = 3;
+    u32x4 filters[first_quads<T, KSMAX>()];
+    {
+        const uint8_t* wp = a.arena + L.w_off + (size_t)cb0 * L.K * kBrickRows * sizeof(T);
+        if (L.ksize == 3) load_filters<T, 3>(filters, wp); else load_filters<T, 1>(filters, wp);
+    }
+    if (tid < ncb0 * kBrickRows) bias[tid] = ((const float*)(a.arena + L.b_off))[tid];      // padded to N_pad
+    {
+        const int32_t ih0 = (int32_t)(f.c0 * L.stride) - (int32_t)L.pad, n_ih = (int32_t)((f.rows - 1) * L.stride + L.ksize);
+        const int32_t lo = max(ih0, 0), hi = min(ih0 + n_ih, (int32_t)L.in_h);
+        fill_frame<T, THREADS>(lds + (uint32_t)(lo - ih0) * f.row_bytes, src, (uint32_t)lo, (uint32_t)max(hi - lo, 0), L.in_w, L.first_cin, f.row_bytes, L.pad);
+    }
+    lds_barrier();
+    {
+        const uint32_t px = f.rows * w0, du = WAVES / ncb0, top = (uint32_t)((int32_t)f.c0 - m0);
+        const float inv = 1.0f / (float)w0;
+        for (uint32_t u = wave / ncb0; u * kBrickRows < px; u += du) {
+            const uint32_t p = u * kBrickRows + li, q = p < px ? p : 0;
+            const uint32_t oh = (uint32_t)(((float)q + 0.5f) * inv), ow = q - __umul24(oh, w0);      // (exact: fewer than 2^20 pixels)
+            const uint8_t* at = lds + (__umul24(oh, f.stride * f.row_bytes) + __umul24(ow, f.stride * 4 * (uint32_t)sizeof(T)));
+            f32x16 acc;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+            if (L.ksize == 3) first_window<T, 3>(acc, filters, at, f.row_bytes); else first_window<T, 1>(acc, filters, at, f.row_bytes);
+            f32x4 y[4];
+            first_activate<T>(y, acc, f);
+            uint8_t* dst = mid + __umul24(oh + top, RSB) + __umul24(ow + 1, PB) + (f.nbase + 4 * lh) * (uint32_t)sizeof(T);
+#pragma unroll
+            for (uint32_t g = 0; g < 4; ++g) {
+                if (p < px && f.nbase + 8 * g + 4 * lh < L.N) put4<T>(dst + 8 * g * (uint32_t)sizeof(T), y[g]);      // channels are a multiple of 8: a run of four exists whole or not at all
+            }
+        }
+    }
+
+    // ---- the second layer; its first filters are asked for in front of the barrier
+    const uint32_t nKB = M.K / KB, nKBv = M.k_valid / KB;            // cin is whole k steps
+    const uint32_t wc = wave % NCB, wr = wave / NCB, out_w = M.out_w, px = (p1 - p0) * out_w;
+    const bool active = wc < M.N_pad / kBrickRows && wr * RBW * kBrickRows < px;
+    gptr_t wp = (gptr_t)((const u32x4*)(a.arena + M.w_off) + (size_t)(active ? wc : 0) * nKB * 64 + lane);
+    u32x4 wq[P];
+#pragma unroll
+    for (uint32_t j = 0; j < P; ++j) wq[j] = wp[(size_t)min(j, nKBv - 1) * 64];
+    lds_barrier();
+    f32x16 acc[RBW];
+#pragma unroll
+    for (uint32_t r = 0; r < RBW; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[r][v] = 0.0f;
+    if (active) {
+        const uint8_t* base[RBW];
+        const float inv = 1.0f / (float)out_w;
+#pragma unroll
+        for (uint32_t r = 0; r < RBW; ++r) {
+            const uint32_t p = (wr * RBW + r) * kBrickRows + li, q = p < px ? p : 0;         // an empty slot multiplies the first pixel; nothing is stored for it
+            const uint32_t oh = (uint32_t)(((float)q + 0.5f) * inv), ow = q - __umul24(oh, out_w);
+            base[r] = mid + (__umul24(oh, st * RSB) + __umul24(ow, st * PB) + lh * 16);
+        }
+        const uint32_t last = 2 * RSB + 2 * PB + (cin - KB) * (uint32_t)sizeof(T);
+        auto k_loop = [&](auto NR_) {
+            constexpr uint32_t NR = decltype(NR_)::value;
+            uint32_t ch = 0, kw = 0, row_off = 0, off = 0;           // scalar: channel inside the tap, kernel column, byte offset of the tap's row, of the k step
+            auto advance = [&] {
+                ch += KB; off += KB * (uint32_t)sizeof(T);
+                if (ch == cin) {
+                    ch = 0; ++kw;
+                    if (kw == 3) { kw = 0; row_off += RSB; }
+                    off = row_off + kw * PB;
+                }
+            };
+            u32x4 av[NR];
+#pragma unroll
+            for (uint32_t r = 0; r < NR; ++r) av[r] = *(const u32x4*)(base[r]);
+            auto one = [&](const u32x4& wv) {                        // operands a step ahead (past the last one: the frame's last, unused)
+                advance();
+                const uint32_t next = min(off, last);
+                u32x4 an[NR];
+#pragma unroll
+                for (uint32_t r = 0; r < NR; ++r) an[r] = *(const u32x4*)(base[r] + next);
+#pragma unroll
+                for (uint32_t r = 0; r < NR; ++r) Mma<T>::run(acc[r], wv, av[r]);           // rows = channels, columns = pixels
+#pragma unroll
+                for (uint32_t r = 0; r < NR; ++r) av[r] = an[r];
+            };
+            const uint32_t full = nKBv / P;
+            for (uint32_t g = 0; g < full; ++g) {
+#pragma unroll
+                for (uint32_t j = 0; j < P; ++j) {
+                    one(wq[j]);
+                    wq[j] = wp[(size_t)min(g * P + j + P, nKBv - 1) * 64];
+                }
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < P; ++j)
+                if (full * P + j < nKBv) one(wq[j]);
+        };
+        if (RBW > 1 && px <= (wr * RBW + RBW / 2) * kBrickRows) k_loop(std::integral_constant<uint32_t, (RBW > 1 ? RBW / 2 : 1)>{});
+        else k_loop(std::integral_constant<uint32_t, RBW>{});
+    }
+    const uint32_t nbase = (active ? wc : 0) * kBrickRows;
+    const float* bias2 = (const float*)(a.arena + M.b_off);
+    f32x4 bias_q[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias2 + nbase + 8 * g + 4 * lh);
+    lds_barrier();                                                   // every wave is done with the rows: they now serve as store scratch
+    if (!active) return;
+    uint8_t* scratch = lds + wave * unit_scratch_bytes<T>();
+    T* const out = (T*)act_of(a.act, M.out_buf) + (size_t)(seg0 + req) * a.S + (size_t)p0 * out_w * M.N + nbase;
+#pragma unroll
+    for (uint32_t r = 0; r < RBW; ++r) {
+        const uint32_t p = (wr * RBW + r) * kBrickRows + li;
+        f32x4 y[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[g][e] = acc[r][4 * g + e] + bias_q[g][e];
+        __builtin_amdgcn_sched_barrier(0);
+        activate_block<4>(y, M.act);
+        store_unit_nhwc<T>(y, p < px ? out + (size_t)p * M.N : nullptr, min((uint32_t)kBrickRows, M.N - nbase), a.store_through, scratch);
+    }
+}
+
 // ---- launcher ------------------------------------------------------------
 // scratch: some model's rows leave through the waves' store scratch (none does where every model's max-pool is done here)
 template <typename T, uint32_t KSMAX, bool POOL>
@@ -447,8 +611,28 @@ static hipError_t prepare_first_t()
         if (e == hipSuccess) e = x;
     };
     allow(conv_first_kernel<T, 3, false>); allow(conv_first_kernel<T, 3, true>); allow(conv_first_kernel<T, 7, false>); allow(conv_first_kernel<T, 7, true>);
+    allow(conv_pair_kernel<T, 2>); allow(conv_pair_kernel<T, 4>);
     return e;
 }
+template <typename T>
+static hipError_t launch_pair_t(const GemmArgs& a, uint32_t blocks, uint32_t frame_bytes, uint32_t mid_bytes, uint32_t grid, hipStream_t s)
+{
+    GemmArgs b = a;
+    b.img_lds = (frame_bytes + 15) / 16 * 16;
+    b.mid_lds = mid_bytes;                                           // (pixels are multiples of 16 bytes)
+    const uint32_t lds = std::max<uint32_t>(b.img_lds + b.mid_lds, 4 * unit_scratch_bytes<T>());
+    if (blocks <= 2) hipLaunchKernelGGL((conv_pair_kernel<T, 2>), dim3(grid), dim3(256), lds, s, b);
+    else hipLaunchKernelGGL((conv_pair_kernel<T, 4>), dim3(grid), dim3(256), lds, s, b);
+    return hipGetLastError();
+}
+// blocks: the widest second layer in blocks of 32 channels
+hipError_t launch_conv_pair(const GemmArgs& a, uint32_t dtype, uint32_t blocks, uint32_t frame_bytes, uint32_t mid_bytes, uint32_t grid, hipStream_t s)
+{
+    if (grid == 0) return hipSuccess;
+    grid = (grid + 7) / 8 * 8;
+    return dtype == MT_BF16 ? launch_pair_t<__bf16>(a, blocks, frame_bytes, mid_bytes, grid, s) : launch_pair_t<float>(a, blocks, frame_bytes, mid_bytes, grid, s);
+}
+
 hipError_t prepare_conv_first(uint32_t dtype) { return dtype == MT_BF16 ? prepare_first_t<__bf16>() : prepare_first_t<float>(); }
 
 template <typename T>

@@ -109,6 +109,11 @@ struct mt_ctx {
     bool first_on = false, first_pool = false, first_plain = false;
     uint32_t first_max_ks = 0, first_max_rows = 0;
     uint64_t first_max_tiles = 0;
+    // In every one of those models the second layer is a 3x3 convolution that can be done with the first (LayerDev::pair_rows); the widest in
+    // blocks; no other model has a convolution at layer index 1 then.
+    bool pair_on = false;
+    uint32_t pair_blocks = 0;
+    uint32_t no_conv_pair = 0;                       // tuning/testing: every convolution has a launch
     uint32_t no_conv_first = 0;                      // tuning/testing: images are always staged
     uint32_t first_cap = 0;                          // testing: MT_FIRST_ROWS in place of first_tile_rows()'s choice
     uint32_t conv_img_lds[MT_MAX_LAYERS]{};          // every conv of a layer index can keep its tiles' input in LDS: the largest frame in bytes, else 0
@@ -317,6 +322,28 @@ uint64_t first_frame_bytes(const LayerDev& L, const LayerDev* pool, uint32_t es,
     return ((conv_rows - 1) * L.stride + L.ksize) * first_frame_cols(L) * kFirstMaxCin * es;
 }
 
+// The same of conv_pair_kernel: the first layer's rows under `rows` rows of the second one's output, and their input.
+void pair_lds(const LayerDev& L, const LayerDev& second, uint32_t es, uint32_t rows, uint64_t* frame, uint64_t* mid)
+{
+    const uint32_t need = (rows - 1) * second.stride + 3;
+    *frame = first_frame_bytes(L, nullptr, es, std::min(need, L.rows_per_req / L.out_w));
+    *mid = (uint64_t)need * (L.out_w + 2) * (second.cin * es + 16);
+}
+
+// Most rows of such a tile: up to 128 pixels; 0: its rows are too long or too wide.  A tile computes the row above and below it once more than
+// needed, so it takes at least half as many rows as that.
+uint32_t choose_pair_rows(const LayerDev& L, const LayerDev& second, uint32_t es)
+{
+    const uint32_t H = second.rows_per_req / second.out_w;
+    if (L.N_pad > kFirstBlocks * kBrickRows || second.N_pad > kPairMaxBlocks * kBrickRows || second.cin % (32 / es) || second.out_w > (uint32_t)kConvTileRows || H > 0xffffu || L.in_w > 0xffffu) return 0;
+    for (uint32_t rows = std::min<uint32_t>(H, (uint32_t)kConvTileRows / second.out_w); rows >= 1; --rows) {
+        uint64_t frame, mid;
+        pair_lds(L, second, es, rows, &frame, &mid);
+        if (frame + 16 + mid <= kPairLdsBytes) return rows;
+    }
+    return 0;
+}
+
 // Most rows of such a tile (0: not even one row's input fits LDS, or the image has too many).
 uint32_t choose_first_rows(const LayerDev& L, const LayerDev* pool, uint32_t es)
 {
@@ -340,7 +367,7 @@ void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[kFactWords]
             w[l][0] = L.N_pad / kBrickRows | 1u << 31;
             w[l][1] = conv_tile_rows(L.rows_per_req, L.row_tiles);
             w[l][2] = L.rows_per_req;
-            if (L.first_rows) w[l][3] = L.first_h | L.first_rows << 16;
+            w[l][3] = L.first_rows ? L.first_h | L.first_rows << 16 : L.pair_h | L.pair_rows << 16;
         }
     }
 }
@@ -481,18 +508,31 @@ void recompute_bounds(mt_ctx* c)
     c->fc_first_chunked = true; c->any_conv_first = c->any_fc_first = false;
     for (uint32_t& m : c->list_mask) m = 0;
     c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
-    c->first_on = !c->no_conv_first; c->first_pool = c->first_plain = false;
-    c->first_max_ks = c->first_max_rows = 0; c->first_max_tiles = 0;
+    c->first_on = !c->no_conv_first; c->first_pool = c->first_plain = false; c->pair_on = !c->no_conv_pair;
+    c->first_max_ks = c->first_max_rows = c->pair_blocks = 0; c->first_max_tiles = 0;
     for (const HostTenant& t : c->tenants) {         // (ahead of the others: it says which max-pools have a launch)
         if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
         const LayerDev& L = t.layers[0].dev;
         c->any_conv_first = true;
         if (!L.first_rows) { c->first_on = false; continue; }
         (L.first_pool ? c->first_pool : c->first_plain) = true;
-        c->first_max_ks = std::max(c->first_max_ks, L.ksize); c->first_max_rows = std::max(c->first_max_rows, L.first_rows);
+        c->first_max_ks = std::max(c->first_max_ks, L.ksize);
         c->first_max_tiles = std::max<uint64_t>(c->first_max_tiles, (uint64_t)L.first_h * ((L.N_pad / kBrickRows + kFirstBlocks - 1) / kFirstBlocks));
+        const LayerDev& second = t.layers[t.n_layers > 1 ? 1 : 0].dev;
+        if (!second.pair_rows) c->pair_on = false;
+        c->pair_blocks = std::max(c->pair_blocks, second.N_pad / kBrickRows);
+        c->first_max_rows = std::max(c->first_max_rows, L.first_rows);
     }
     c->first_on = c->first_on && c->any_conv_first;
+    c->pair_on = c->pair_on && c->first_on;
+    if (c->pair_on) {                                // tiles are rows of the second layer's output then
+        c->first_max_rows = 0; c->first_max_tiles = 0;
+        for (const HostTenant& t : c->tenants) {
+            if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
+            c->first_max_rows = std::max(c->first_max_rows, t.layers[1].dev.pair_rows);
+            c->first_max_tiles = std::max<uint64_t>(c->first_max_tiles, t.layers[1].dev.pair_h);
+        }
+    }
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
         c->has_gap[l] = 0; c->gap_chunks[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
         for (int k = 0; k < kListKinds; ++k) { c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
@@ -515,6 +555,7 @@ void recompute_bounds(mt_ctx* c)
             if (L.kind == kKindNone) continue;
             if (L.kind == MT_GAP) { c->has_gap[l] = 1; c->gap_chunks[l] = std::max(c->gap_chunks[l], std::min<uint64_t>((uint64_t)L.in_h * L.in_w, kGapSweepPixels) * L.cin * c->elem_size / 16); continue; }
             if (l == 1 && c->first_on && t.layers[0].dev.first_pool) continue;          // done with the convolution in front of it
+            if (l == 1 && c->pair_on && L.pair_rows) { c->sum_macs += (double)L.k_valid * L.N * L.rows_per_req; continue; }
             if (L.kind == MT_MAXPOOL || L.kind == MT_ADD) { c->has_image_ops[l] = 1; c->image_op_fill[l] = std::max(c->image_op_fill[l], L.out_fill); continue; }
             const int k = L.kind == MT_FC ? 0 : 1;
             c->sum_macs += (double)L.k_valid * L.N * L.rows_per_req;
@@ -600,6 +641,7 @@ struct ConvPlan {
     bool split;         // tiles of 32 pixels and one channel block whose waves split K
     uint32_t first_cap; // > 0: the submitted images are read (layer index 0), in tiles of at most so many rows ...
     uint32_t first_frame; // ... whose input takes at most so many bytes of LDS
+    uint32_t pair_mid;  // > 0: ... and the convolutions behind them with them: the tiles are rows of those; bytes of LDS for the first layer's rows
     uint64_t tiles;     // upper bound of the launch's tiles
 };
 
@@ -647,8 +689,12 @@ ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<Na
         for (const HostTenant& t : c->tenants) {
             if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
             const LayerDev& L = t.layers[0].dev;
-            const uint32_t strips = first_strips(L.first_h, L.first_rows, p.first_cap), rows = (L.first_h + strips - 1) / strips;
-            p.first_frame = std::max<uint32_t>(p.first_frame, (uint32_t)first_frame_bytes(L, L.first_pool ? &t.layers[1].dev : nullptr, c->elem_size, rows));
+            const LayerDev& last = c->pair_on ? t.layers[1].dev : L;
+            const uint32_t h = c->pair_on ? last.pair_h : L.first_h, strips = first_strips(h, c->pair_on ? last.pair_rows : L.first_rows, p.first_cap), rows = (h + strips - 1) / strips;
+            uint64_t frame, mid = 0;
+            if (c->pair_on) pair_lds(L, last, c->elem_size, rows, &frame, &mid);
+            else frame = first_frame_bytes(L, L.first_pool ? &t.layers[1].dev : nullptr, c->elem_size, rows);
+            p.first_frame = std::max(p.first_frame, (uint32_t)frame); p.pair_mid = std::max(p.pair_mid, (uint32_t)mid);
             most = std::max<uint64_t>(most, strips * ((L.N_pad / kBrickRows + kFirstBlocks - 1) / kFirstBlocks));
         }
         p.tiles = R * most;
@@ -872,6 +918,11 @@ mt_status plan_model(mt_ctx* c, const mt_layer_spec* specs, uint32_t n_layers, H
         d.first_rows = pool ? choose_first_rows(d, pool, es) : 0;
         d.first_pool = d.first_rows != 0;
         if (!d.first_pool) { pool = nullptr; d.first_rows = choose_first_rows(d, nullptr, es); }
+        if (d.first_rows && !pool && n_layers > 2 && d.ksize <= 3 && src_of[1] == 1 && last_use[1] == 1) {
+            LayerDev& second = out->layers[1].dev;
+            const uint32_t rows = second.kind == MT_CONV2D && second.ksize == 3 && !second.pool_fill && !second.fuse_add ? choose_pair_rows(d, second, es) : 0;
+            if (rows) { second.pair_rows = rows; second.pair_h = second.rows_per_req / second.out_w; }
+        }
         const LayerDev& last = pool ? *pool : d;
         d.first_cin = specs[0].in_features;
         d.first_h = last.rows_per_req / last.out_w;
@@ -1019,6 +1070,7 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
     if (const char* e = getenv("MT_NO_FUSED_HEAD")) c->no_fused_head = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_FUSED_POOL")) c->no_fused_pool = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_IMG")) c->no_conv_img = atoi(e) != 0;
+    if (const char* e = getenv("MT_NO_CONV_PAIR")) c->no_conv_pair = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_FIRST")) c->no_conv_first = atoi(e) != 0;
     if (const char* e = getenv("MT_FIRST_ROWS")) c->first_cap = (uint32_t)std::max(0, atoi(e));
     if (const char* e = getenv("MT_NO_FUSED_ADD")) c->no_fused_add = atoi(e) != 0;
@@ -1202,7 +1254,7 @@ mt_status mt_register_model_bn(mt_ctx* c, uint32_t tenant, const mt_layer_spec* 
             if (c->elem_size == 2) pack_weights<uint16_t>(hl, w_src, w_dst); else pack_weights<float>(hl, w_src, w_dst);
             // conv_first_kernel's bf16 form multiplies a step's zeros with another step's filters: not with infinite ones
             if (LayerDev& d = ht.layers[l].dev; d.first_rows && c->elem_size == 2 && !all_finite_bf16((const uint16_t*)w_src, (size_t)d.N * hl.spec.in_features * d.ksize * d.ksize))
-                d.first_rows = d.first_pool = 0;
+                d.first_rows = d.first_pool = 0, ht.layers[n_layers > 1 ? 1 : 0].dev.pair_rows = 0;
         }
     }
     auto drop_stage = [&]() { if (c->cache && stage) (void)hipHostFree(stage); };
@@ -1558,7 +1610,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     for (uint32_t g = 0; g < MT_MAX_LAYERS / kLayerGroup; ++g)
         b.list_mask[g] = big_enabled ? c->list_mask[g] : c->list_mask[g] & ((1u << (2 * kLayerGroup)) - 1);   // no big-tile lists to build
     b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles;
-    b.first_cap = plan_conv(c, 0, R, named).first_cap;
+    { const ConvPlan first = plan_conv(c, 0, R, named); b.first_cap = first.first_cap; b.first_pair = first.pair_mid != 0; }
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) {
         if (plan_conv(c, l, R, named).split) b.conv_split[l / 32] |= 1u << l % 32;
     }
@@ -1637,6 +1689,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             const uint32_t g32 = (uint32_t)grid;
             ga.first_cap = conv.first_cap;
             if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, split_k || c->max_fc_cols[l] <= 2 * (uint32_t)kBrickRows, g32, s));
+            else if (conv.pair_mid) TIMED(kProfConv + l, launch_conv_pair(ga, c->cfg.dtype, c->pair_blocks, conv.first_frame, conv.pair_mid, g32, s));
             else if (conv.first_cap) TIMED(kProfConv + l, launch_conv_first(ga, c->cfg.dtype, c->first_max_ks, c->first_pool, c->first_plain, conv.first_frame, g32, s));
             else if (conv.split) TIMED(kProfConv + l, launch_conv_split(ga, c->cfg.dtype, (c->max_conv_k[l] * c->elem_size + 31) / 32, g32, s));
             else if (kind == 1) TIMED(kProfConv + l, launch_conv(ga, c->cfg.dtype, c->max_conv_cb[l], c->conv_quad[l],
@@ -1869,13 +1922,16 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
                     const double k_steps = d.K * es / 32.0 / (4 / split);       // bricks one wave walks (the waves split K when split < 4)
                     chain = std::max(chain, kUsFcChainFixed + kUsPerKStep * k_steps);
                 }
+            } else if (l == 1 && c->pair_on && d.pair_rows) {
+                // done with the convolution in front of it
             } else if (d.kind == MT_CONV2D) {
                 const double out_elems = (c->pool_fused[l] ? d.N : d.out_len) + (d.fuse_add ? d.out_len : 0);      // pooled on the way out; the other operand of an addition done here
                 conv_mb += (M * ((double)d.in_h * d.in_w * d.cin + out_elems) * es + (double)d.N_pad * d.K * es) / MB;
                 conv_mflop += 2.0 * M * d.rows_per_req * d.k_valid * d.N / 1e6;
                 if (conv_plan.first_cap) {
-                    const LayerDev& last = d.first_pool ? c->tenants[t].layers[1].dev : d;
+                    const LayerDev& last = d.first_pool || c->pair_on ? c->tenants[t].layers[1].dev : d;
                     first_mb += (M * ((double)d.in_h * d.in_w * d.first_cin + last.out_len) * es + (double)d.N_pad * d.K * es) / MB;
+                    if (c->pair_on) first_mflop += 2.0 * M * last.rows_per_req * last.k_valid * last.N / 1e6;
                     first_mflop += 2.0 * M * d.rows_per_req * d.ksize * d.ksize * d.first_cin * d.N / 1e6;
                 }
                 const double k_steps = std::ceil(d.k_valid * es / 32.0);
@@ -1893,7 +1949,7 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
         if (c->max_nt[0][l] > 0) launch(std::max(chain, kUsFcFixed + us_per_mb * w_mb + kUsPerMbL2 * l2_mb));
         if (conv_plan.first_cap) launch(kUsConvFirstFixed + std::max(first_mb / kConvFirstMbPerUs, first_mflop / kConvFirstMflopPerUs));
         else if (conv_plan.split) launch(kUsConvSplitFixed + kUsConvSplitPerKStep * std::max(split_longest, split_steps / kComputeUnits));
-        else if (c->max_nt[1][l] > 0) launch(kUsConvFixed + std::max(conv_chain, std::max(conv_mb / kConvMbPerUs, conv_mflop / (conv_frames ? kConvFrameMflopPerUs : kConvMflopPerUs))));
+        else if (conv_plan.tiles > 0) launch(kUsConvFixed + std::max(conv_chain, std::max(conv_mb / kConvMbPerUs, conv_mflop / (conv_frames ? kConvFrameMflopPerUs : kConvMflopPerUs))));
         if (big_enabled && c->max_nt[2][l] > 0 && tile_bound(c, 2, l, R) >= c->big_min_tiles) {
             // tiles share the chip in rounds of one per compute unit; a tile's time grows with K
             if (big_layer) big_us = std::ceil(big_tiles / kComputeUnits) * kUsBigTileFixed + big_rounds_k / kComputeUnits / 4096.0 * kUsBigTilePer4096;

@@ -21,7 +21,8 @@
 //                   (launches of few tiles: 32 pixels and 32 channels to a tile, whose 4 to 16 waves
 //                   share K): implicit-GEMM convolution for all tenants
 //   conv_first.hip  conv_first_kernel: first convolutions of images with at most four channels, from the
-//                   submitted images themselves; takes the max-pool behind the layer with it
+//                   submitted images themselves; takes the max-pool behind the layer with it; conv_pair_kernel: those and
+//                   the 3x3 convolution behind them
 //   small.hip       gather_kernel / gather_image_kernel (submitted rows -> bricks / padded NHWC),
 //                   gap_kernel (global average pooling), head_kernel (softmax + argmax in
 //                   submission order), copy_kernel (the yardstick for byte counters)
@@ -235,6 +236,22 @@ __device__ __forceinline__ void divmod_uniform(uint32_t x, uint32_t d, uint32_t*
 template <typename T> constexpr uint32_t unit_row_stride() { return kBrickRows * sizeof(T) + 16; }
 template <typename T> constexpr uint32_t unit_scratch_bytes() { return kBrickRows * unit_row_stride<T>() + kBrickRows * 8; }
 
+// Four values rounded to the element type, as they lie in memory.  (Converted as a vector: two instructions for bf16.  Element by element the compiler
+// converts each for itself and puts the pairs together again.)
+template <typename T> struct Packed4;
+template <> struct Packed4<__bf16> {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ uint64_t of(const f32x4& y) { return __builtin_bit_cast(uint64_t, __builtin_convertvector(y, bf16x4)); }
+};
+template <> struct Packed4<float> {
+    static __device__ __forceinline__ f32x4 of(const f32x4& y) { return y; }
+};
+template <typename T> __device__ __forceinline__ void put4(void* p, const f32x4& y)
+{
+    auto v = Packed4<T>::of(y);
+    *(decltype(v)*)p = v;
+}
+
 template <typename T>
 __device__ __forceinline__ void store_unit_nhwc(const f32x4 (&y)[4], T* my_pixel_out, uint32_t n_valid, uint32_t through, uint8_t* scratch)
 {
@@ -244,12 +261,7 @@ __device__ __forceinline__ void store_unit_nhwc(const f32x4 (&y)[4], T* my_pixel
     T** dests = (T**)(scratch + kBrickRows * RS);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-        T o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (T)y[g][e];
-        uint8_t* p = scratch + li * RS + (8 * g + 4 * lh) * sizeof(T);
-        if constexpr (sizeof(T) == 2) *(uint64_t*)p = __builtin_bit_cast(uint64_t, o);
-        else *(u32x4*)p = __builtin_bit_cast(u32x4, o);
+        put4<T>(scratch + li * RS + (8 * g + 4 * lh) * sizeof(T), y[g]);
     }
     if (lh == 0) dests[li] = my_pixel_out;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // the wave's own LDS writes have landed

@@ -84,6 +84,7 @@ constexpr uint32_t kConvFrameMaxBytes = 96 * 1024;   // most LDS that the input 
 // make 1024 pixels and a frame of 32 KiB; with a max-pool as many as leave room for a second workgroup on the compute unit.
 // Single rows may take more, up to what is left beside the store scratch of eight waves.
 constexpr uint32_t kFirstMaxCin = 4, kFirstBlocks = 2;                        // ... and channel blocks of a workgroup
+constexpr uint32_t kPairMaxBlocks = 4, kPairLdsBytes = 52 * 1024;               // second convolutions done with the first: channel blocks; LDS of a tile (three to a compute unit)
 constexpr uint32_t kFirstTilePixels = 1024, kFirstFrameBytes = 32 * 1024, kFirstPoolFrameBytes = 78 * 1024, kFirstMaxBytes = 152 * 1024;
 inline __host__ __device__ constexpr uint32_t first_scratch_bytes(uint32_t es) { return 8 * kBrickRows * (kBrickRows * es + 16 + 8); }
 
@@ -122,8 +123,9 @@ struct LayerDev {
     uint32_t row_tiles;
     // First layer CONV of images with at most four channels that conv_first_kernel can take (first_rows > 0): submitted channels; most
     // rows of a tile (of the layer's output, or, first_pool, of the max-pool's behind it) and rows of an image; whether that
-    // max-pool, the layer's only reader, is done with the convolution.
-    uint32_t first_cin, first_rows, first_h, first_pool;
+    // max-pool, the layer's only reader, is done with the convolution; in the row of a
+    // 3x3 convolution behind it, its only reader, that can be done with it: the same rows of that one's output.
+    uint32_t first_cin, first_rows, first_h, first_pool, pair_rows, pair_h;
     uint64_t w_off;      // byte offset of the packed weights in the arena
     uint64_t b_off;      // byte offset of the fp32 bias in the arena (N_pad entries for FC)
 };
@@ -181,6 +183,7 @@ struct BatchArgs {
     uint32_t fc_split_k;   // 1: FC tiles take one column block each and split K four ways
     uint32_t conv_split[(MT_MAX_LAYERS + 31) / 32];   // layer indices (bit l % 32 of word l / 32) whose convolution launch takes tiles of 32 pixels and one channel block
     uint32_t first_cap;    // > 0: layer 0's convolutions read the submitted images, in tiles of at most so many rows
+    uint32_t first_pair;   // ... and the 3x3 convolutions behind them with them
     uint32_t big_enabled;  // 0: no tenant-layer is given big tiles in this run (small batches)
     uint32_t big_min_tiles; // a layer index uses big tiles only when its qualifying tenants make at least this many
     const TenantDev* tenants;
@@ -189,7 +192,8 @@ struct BatchArgs {
     // Word 0, FC: column groups of the layer's tiles, bit 30: tiles of 32 rows instead of 64; convolution: bit 31 and the
     // channel blocks of 32 (a tile takes four of them, or one where the launch splits K); 0: no tiles (pooling, or no such layer).
     // Word 1: padded outputs (FC), rows per request by which the tiles are counted (convolution: conv_tile_rows).  Word 2: a convolution's output pixels.
-    // Word 3, a first convolution that can read the submitted images: rows of an image, and above 16 bits most rows of a tile.
+    // Word 3, a first convolution that can read the submitted images: rows of an image, and above 16 bits most rows of a tile; the same of a second
+    // convolution that can be done with the first one.
     const uint32_t* facts;
     unsigned long long* served;   // [T][2]: requests served and runs with requests, per tenant, over all runs (atomic adds: runs may overlap)
     int32_t* row_tenant;   // [R] tenant of each submitted row, -1 if rejected
@@ -229,6 +233,7 @@ struct GemmArgs {
     uint32_t pool;                // conv launch: the layers with pool_fill write the pooled activation instead of their own
     uint32_t store_through;       // conv launch: outputs go through L2 to memory (see store_through)
     uint32_t img_lds;             // conv launch with LDS-resident input: bytes of dynamic LDS (the largest frame)
+    uint32_t mid_lds;             // launch of first convolutions with the ones behind them: bytes of LDS for the first layer's rows
     uint32_t first_cap;           // launch of first convolutions on the submitted images: most rows of a tile
     // FC layer 0 can read the submitted rows itself (16-byte aligned rows whose length is a
     // whole number of 16-byte chunks), which saves the staging pass:
@@ -274,6 +279,7 @@ hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps
 // first convolutions on the submitted images: the largest window, whether some model's max-pool is done with it and some model's rows
 // are stored themselves, and the largest frame in bytes
 hipError_t launch_conv_first(const GemmArgs& a, uint32_t dtype, uint32_t max_ks, bool pool, bool scratch, uint32_t frame_bytes, uint32_t grid, hipStream_t s);
+hipError_t launch_conv_pair(const GemmArgs& a, uint32_t dtype, uint32_t blocks, uint32_t frame_bytes, uint32_t mid_bytes, uint32_t grid, hipStream_t s);
 hipError_t prepare_conv_first(uint32_t dtype);
 constexpr uint32_t kGapSweepPixels = 512;        // pixels of a row that the pooling kernel reads at once (64 groups of eight)
 // chunks: the most 16-byte pieces of that many pixels (or of all, if fewer) among the models of the layer index

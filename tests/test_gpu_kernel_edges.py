@@ -370,6 +370,42 @@ def test_first_convolutions_on_the_submitted_images(monkeypatch, dtype, hw, ci, 
     ctx.close()
 
 
+# a first convolution and the 3x3 convolution behind it in one launch: one to four blocks of second channels, both strides of both, images of a pixel, of
+# several tiles and of rows that fill a tile badly; beside models that do not take it, which leaves both layers a launch
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("hw,models,rows", [
+    ((1, 1), [(3, 1, 16, 1, 8)], 9), ((2, 9), [(1, 1, 32, 2, 40), (3, 2, 48, 1, 128)], 9), ((16, 16), [(3, 1, 32, 2, 64), (3, 1, 64, 1, 96), (3, 1, 16, 1, 128)], 3),
+    ((35, 29), [(3, 1, 24, 1, 40), (3, 2, 64, 2, 32)], 99), ((21, 100), [(3, 1, 16, 1, 16), (1, 2, 16, 1, 8)], 1), ((9, 11), [(3, 1, 32, 1, 40), (3, 1, 16, 1, 136), (7, 2, 16, 1, 8)], 9), ((33, 130), [(3, 1, 32, 2, 72)], 99)])
+def test_first_convolutions_with_the_ones_behind_them(monkeypatch, dtype, hw, models, rows):
+    monkeypatch.setenv("MT_FIRST_ROWS", str(rows))
+    monkeypatch.setenv("MT_CONV_SPLIT_TILES", "0")
+    tenants = {}
+    for t, (k, s0, c0, s1, c1) in enumerate(models):
+        layers = [wl.LayerSpec(wl.CONV, wl.ACT_GELU if t else wl.ACT_RELU, 3, c0, *hw, s0, ksize=k, pad=(k - 1) // 2)]
+        layers.append(wl.LayerSpec(wl.CONV, wl.ACT_RELU, c0, c1, *layers[-1].out_hw(), s1, ksize=3, pad=1))
+        layers.append(wl.LayerSpec(wl.CONV, wl.ACT_RELU, c1, 8, *layers[-1].out_hw(), 2, ksize=3, pad=1))
+        layers += [wl.LayerSpec(wl.GAP, wl.ACT_NONE, 8, 8, *layers[-1].out_hw()), wl.LayerSpec(wl.FC, wl.ACT_NONE, 8, 5)]
+        tenants[t] = wl.make_model(layers, dtype, 372, t)
+    h, w_ = (hw[0] - 1) // 2 + 1, (hw[1] - 1) // 2 + 1
+    tenants[len(models)] = wl.make_model([wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, 16, *hw, 1, ksize=3, pad=1), wl.LayerSpec(wl.MAXPOOL, wl.ACT_NONE, 16, 16, *hw, 2, ksize=3, pad=1),
+                                          wl.LayerSpec(wl.CONV, wl.ACT_RELU, 16, 8, h, w_, 1, ksize=3, pad=1), wl.LayerSpec(wl.GAP, wl.ACT_NONE, 8, 8, h, w_),
+                                          wl.LayerSpec(wl.FC, wl.ACT_NONE, 8, 5)], dtype, 372, 9)
+    x = np.random.default_rng(372).standard_normal((23, 3 * hw[0] * hw[1])).astype(np.float32)
+    ids = np.random.default_rng(373).integers(0, len(tenants), 23).astype(np.int32)
+    for apart in (True, False):                                      # with and without the model that is served apart
+        if not apart:
+            del tenants[len(models)]
+        ids_ = ids if apart else ids % len(models)
+        w = wl.Workload("pair", dtype, tenants, ids_, wl.round_to_bf16(x) if dtype == "bf16" else x)
+        what = "%s %s %s tiles of %d rows" % (dtype, hw, models, rows)
+        print(what, flush=True)
+        one = check(w, what)
+        monkeypatch.setenv("MT_NO_CONV_PAIR", "1")                   # two launches: the same bits in both types
+        got = gpu_run(make_context(w), w, poison=True)
+        monkeypatch.delenv("MT_NO_CONV_PAIR")
+        assert np.array_equal(got[0], one[0]), what
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("k,stride,pool", [(1, 1, None), (3, 1, None), (7, 2, None), (3, 1, (3, 2, 1))])
 def test_infinite_pixels_stay_inside_their_windows(dtype, k, stride, pool):
