@@ -206,7 +206,6 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
     uint4 fq[kPre];
 #pragma unroll
     for (uint32_t i = 0; i < kPre; ++i) fq[i] = one_wave ? load_fact(w + i * kWaves, lane) : load_fact(w, lane * kPre + i);
-    const uint32_t second = a.first_pair && one_wave && w == 0 ? load_fact(1, lane).w : 0;       // (second convolutions that are done with the first)
     for (uint32_t t = tid; t < Tp; t += kBatchThreads) regl[t] = t < T && a.tenants[t].registered;
     for (uint32_t i = tid; i < nw * Tp; i += kBatchThreads) hist[i] = PRE ? a.hist_g[i] : 0;
     if (tid == 0) big_l = 0;
@@ -358,8 +357,7 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
             const bool rem_sk = big && big_remainder_split_k(y);
             const uint32_t sh = sk || rem_sk || ((x >> 30) & 1) ? 5 : 6, gq = rem_sk ? y / kBrickRows : groups;
             n_fc[j] = !conv && groups && M ? ((M - Mb + (1u << sh) - 1) >> sh) * gq : 0;
-            const uint32_t rows = a.first_pair && l == 0 ? (J == 1 ? second : load_fact(1, t0 + j).w) : f[j].w;     // first convolutions on the submitted images
-            n_conv[j] = conv && M && !(a.first_pair && l == 1) ? (a.first_cap && l == 0 ? M * first_strips(rows & 0xffffu, rows >> 16, a.first_cap) * ceil_div(blocks, kFirstBlocks) : split ? ceil_div(M * f[j].z, kBrickRows) * blocks : ceil_div(M * y, kConvTileRows) * ceil_div(blocks, kTileCols / kBrickRows)) : 0;
+            n_conv[j] = conv && M ? (split ? ceil_div(M * f[j].z, kBrickRows) * blocks : ceil_div(M * y, kConvTileRows) * ceil_div(blocks, kTileCols / kBrickRows)) : 0;
             n_big[j] = ceil_div(Mb, kBigTile) * ceil_div(y, kBigTile);
         }
         auto emit = [&](uint32_t kind, const uint32_t (&n)[J], uint32_t& run) {
@@ -438,6 +436,23 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
                 for (uint32_t j = 0; j < kPre; ++j) fq[j] = ahead[j];
             }
         }
+    }
+    // First convolutions on the submitted images, alone or with the ones behind them: a list of rows of tiles, which the code above does not make
+    // (list_mask).  Apart from it, by the wave that has the fewest lists: every instruction in its unrolled steps costs each run its fetch (1.4 us
+    // with this in them, of a batcher of 4.2).
+    if (a.first_cap && w == kWaves - 1) {
+        uint32_t* base = a.tile_base + (size_t)MT_MAX_LAYERS * (T + 1);
+        uint32_t run = 0;
+        for (uint32_t t0 = 0; t0 < T; t0 += 64) {
+            const uint32_t t = t0 + lane, M = one_wave ? Mt1 : t < T ? Ml[t] : 0;
+            const uint4 f = load_fact(0, t);
+            const uint32_t rows = a.first_pair ? load_fact(1, t).w : f.w;
+            const uint32_t n = f.x >> 31 && M ? M * first_strips(rows & 0xffffu, rows >> 16, a.first_cap) * ceil_div(f.x & 0x7fffffffu, kFirstBlocks) : 0;
+            const uint32_t incl = wave_inclusive_scan(n);
+            if (t < T) base[t] = run + incl - n;
+            run += __builtin_amdgcn_readlane(incl, 63);
+        }
+        if (lane == 0) base[T] = run;
     }
     if (a.big_enabled) __syncthreads();
     if (tid == 0) *a.big_layers = big_l;               // the FC kernels split a qualifying tenant's rows by it

@@ -368,7 +368,7 @@ void conv_first_kernel(GemmArgs a)
     const bool pooled = POOL && L.first_pool;
     const LayerDev& G = a.layers[t * MT_MAX_LAYERS + (POOL ? 1 : 0)];   // the max-pool, if it is done here
     const uint32_t pk = pooled ? G.ksize : 1, ps = pooled ? G.stride : 1, pp = pooled ? G.pad : 0, pw = pooled ? G.out_w : 1;
-    const uint32_t out_w = L.out_w, out_h = L.rows_per_req / out_w, end_rows = L.first_h;
+    const uint32_t out_w = L.out_w, out_h = L.rows_per_req / out_w, end_rows = pooled ? G.rows_per_req / pw : out_h;
     const uint32_t strips = first_strips(end_rows, L.first_rows, a.first_cap), step = ceil_div(end_rows, strips);
     uint32_t local = idx - a.tile_base[t];
     const uint32_t strip = local % strips;
@@ -453,10 +453,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
     if (!logical_tile(n_tiles, &idx)) return;
     const uint32_t t = lookup.owner(a.T, idx, owner_part);           // uniform: the tenant's facts come through scalar loads
     const LayerDev L = a.layers[t * MT_MAX_LAYERS], M = a.layers[t * MT_MAX_LAYERS + 1];
-    const uint32_t seg0 = a.off[t], strips = first_strips(M.pair_h, M.pair_rows, a.first_cap), step = ceil_div(M.pair_h, strips);
+    const uint32_t seg0 = a.off[t], h1 = M.rows_per_req / M.out_w, strips = first_strips(h1, M.pair_rows, a.first_cap), step = ceil_div(h1, strips);
     const uint32_t local = idx - a.tile_base[t], req = local / strips, strip = local - req * strips;
     const T* const src = (const T*)a.row_src[a.perm[seg0 + req]];
-    const uint32_t p0 = strip * step, p1 = min(p0 + step, M.pair_h);
+    const uint32_t p0 = strip * step, p1 = min(p0 + step, h1);
     const uint32_t w0 = L.out_w, h0 = L.rows_per_req / w0, ncb0 = L.N_pad / kBrickRows, cb0 = wave % ncb0;
 
     // ---- the first layer's rows under rows p0 .. p1 - 1 of the second one's

@@ -354,6 +354,13 @@ uint32_t choose_first_rows(const LayerDev& L, const LayerDev* pool, uint32_t es)
     return first_frame_bytes(L, pool, es, rows) + first_scratch_bytes(es) + 16 <= kFirstMaxBytes ? rows : 0;
 }
 
+// Rows of an image that the tiles of such a layer deal out: of its output, or of the max-pool's that is done with it.
+uint32_t first_out_rows(const HostTenant& t)
+{
+    const LayerDev& last = t.layers[t.layers[0].dev.first_pool ? 1 : 0].dev;
+    return last.rows_per_req / last.out_w;
+}
+
 // The batcher's words per layer of one tenant (see BatchArgs::facts).
 void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[kFactWords])
 {
@@ -367,7 +374,8 @@ void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[kFactWords]
             w[l][0] = L.N_pad / kBrickRows | 1u << 31;
             w[l][1] = conv_tile_rows(L.rows_per_req, L.row_tiles);
             w[l][2] = L.rows_per_req;
-            w[l][3] = L.first_rows ? L.first_h | L.first_rows << 16 : L.pair_h | L.pair_rows << 16;
+            if (L.first_rows) w[l][3] = first_out_rows(ht) | L.first_rows << 16;
+            else if (L.pair_rows) w[l][3] = L.rows_per_req / L.out_w | L.pair_rows << 16;
         }
     }
 }
@@ -517,7 +525,7 @@ void recompute_bounds(mt_ctx* c)
         if (!L.first_rows) { c->first_on = false; continue; }
         (L.first_pool ? c->first_pool : c->first_plain) = true;
         c->first_max_ks = std::max(c->first_max_ks, L.ksize);
-        c->first_max_tiles = std::max<uint64_t>(c->first_max_tiles, (uint64_t)L.first_h * ((L.N_pad / kBrickRows + kFirstBlocks - 1) / kFirstBlocks));
+        c->first_max_tiles = std::max<uint64_t>(c->first_max_tiles, (uint64_t)first_out_rows(t) * ((L.N_pad / kBrickRows + kFirstBlocks - 1) / kFirstBlocks));
         const LayerDev& second = t.layers[t.n_layers > 1 ? 1 : 0].dev;
         if (!second.pair_rows) c->pair_on = false;
         c->pair_blocks = std::max(c->pair_blocks, second.N_pad / kBrickRows);
@@ -530,7 +538,7 @@ void recompute_bounds(mt_ctx* c)
         for (const HostTenant& t : c->tenants) {
             if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
             c->first_max_rows = std::max(c->first_max_rows, t.layers[1].dev.pair_rows);
-            c->first_max_tiles = std::max<uint64_t>(c->first_max_tiles, t.layers[1].dev.pair_h);
+            c->first_max_tiles = std::max<uint64_t>(c->first_max_tiles, t.layers[1].dev.rows_per_req / t.layers[1].dev.out_w);
         }
     }
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
@@ -690,7 +698,7 @@ ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<Na
             if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
             const LayerDev& L = t.layers[0].dev;
             const LayerDev& last = c->pair_on ? t.layers[1].dev : L;
-            const uint32_t h = c->pair_on ? last.pair_h : L.first_h, strips = first_strips(h, c->pair_on ? last.pair_rows : L.first_rows, p.first_cap), rows = (h + strips - 1) / strips;
+            const uint32_t h = c->pair_on ? last.rows_per_req / last.out_w : first_out_rows(t), strips = first_strips(h, c->pair_on ? last.pair_rows : L.first_rows, p.first_cap), rows = (h + strips - 1) / strips;
             uint64_t frame, mid = 0;
             if (c->pair_on) pair_lds(L, last, c->elem_size, rows, &frame, &mid);
             else frame = first_frame_bytes(L, L.first_pool ? &t.layers[1].dev : nullptr, c->elem_size, rows);
@@ -921,11 +929,9 @@ mt_status plan_model(mt_ctx* c, const mt_layer_spec* specs, uint32_t n_layers, H
         if (d.first_rows && !pool && n_layers > 2 && d.ksize <= 3 && src_of[1] == 1 && last_use[1] == 1) {
             LayerDev& second = out->layers[1].dev;
             const uint32_t rows = second.kind == MT_CONV2D && second.ksize == 3 && !second.pool_fill && !second.fuse_add ? choose_pair_rows(d, second, es) : 0;
-            if (rows) { second.pair_rows = rows; second.pair_h = second.rows_per_req / second.out_w; }
+            second.pair_rows = rows;
         }
-        const LayerDev& last = pool ? *pool : d;
         d.first_cin = specs[0].in_features;
-        d.first_h = last.rows_per_req / last.out_w;
     }
     return MT_OK;
 }
@@ -1610,7 +1616,10 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     for (uint32_t g = 0; g < MT_MAX_LAYERS / kLayerGroup; ++g)
         b.list_mask[g] = big_enabled ? c->list_mask[g] : c->list_mask[g] & ((1u << (2 * kLayerGroup)) - 1);   // no big-tile lists to build
     b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles;
-    { const ConvPlan first = plan_conv(c, 0, R, named); b.first_cap = first.first_cap; b.first_pair = first.pair_mid != 0; }
+    if (const ConvPlan first = plan_conv(c, 0, R, named); first.first_cap) {     // its list is made apart from the others; a second convolution done with it has none
+        b.first_cap = first.first_cap; b.first_pair = first.pair_mid != 0;
+        b.list_mask[0] &= ~((first.pair_mid ? 3u : 1u) << kLayerGroup);
+    }
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) {
         if (plan_conv(c, l, R, named).split) b.conv_split[l / 32] |= 1u << l % 32;
     }

@@ -91,28 +91,30 @@ inline __host__ __device__ constexpr uint32_t first_scratch_bytes(uint32_t es) {
 enum : uint32_t { kLayoutRows = 0, kLayoutBricks = 1 };
 constexpr uint32_t kKindNone = 0xffu;     // a layer index at which this tenant has nothing to run (its work was taken over by the layer before)
 
-// One layer of one tenant, as the kernels see it (lives in device memory).
+// One layer of one tenant, as the kernels see it (lives in device memory).  Two cache lines: what every kernel needs stands in the first one.
 struct LayerDev {
+    uint64_t w_off;      // byte offset of the packed weights in the arena
+    uint64_t b_off;      // byte offset of the fp32 bias in the arena (N_pad entries for FC)
     uint32_t kind, act;
     uint32_t K;          // reduction length as stored (padded to kWidthAlign), elements
     uint32_t k_valid;    // FC: true fan-in; CONV: 9 * cin (the rest of K is zero padding)
     uint32_t N;          // output features (FC) / output channels (CONV)
     uint32_t N_pad;      // FC: weight rows as stored (multiple of 32; of 64 for hidden layers)
+    uint32_t is_last;    // outputs are the logits
+    uint32_t out_fill;   // out_len rounded up to kWidthAlign (zero-filled tail)
+    // which of the run's activation buffers the layer reads (in2_buf: the second operand of ADD) and writes;
+    // pool_buf: where a convolution that pools by itself writes (the out_buf of the pooling layer behind it)
+    uint32_t in_buf, in2_buf, out_buf, pool_buf;
     uint32_t in_h, in_w; // CONV / GAP input geometry
     uint32_t cin;        // CONV: padded input channels (multiple of kChanPad); GAP: channels
     uint32_t stride;     // CONV
     uint32_t out_w;      // CONV output width
     uint32_t rows_per_req;  // GEMM rows one request contributes: 1 (FC) or out_h*out_w (CONV)
     uint32_t out_len;    // elements one request's output occupies
-    uint32_t out_fill;   // out_len rounded up to kWidthAlign (zero-filled tail)
-    uint32_t is_last;    // outputs are the logits
     uint32_t pool_fill;  // CONV whose next layer is a global average pool that the convolution can do itself (whole images
                          // per wave: 32 or 64 output pixels per image, channels a multiple of 64): the pool's out_fill, else 0
     uint32_t ksize;      // CONV / MAXPOOL: window (ksize x ksize)
     uint32_t pad;        // CONV / MAXPOOL
-    // which of the run's activation buffers the layer reads (in2_buf: the second operand of ADD) and writes;
-    // pool_buf: where a convolution that pools by itself writes (the out_buf of the pooling layer behind it)
-    uint32_t in_buf, in2_buf, out_buf, pool_buf;
     // CONV whose output goes to a residual addition and nowhere else: the convolution adds the other operand
     // (buffer in2_buf, same pixel and channel) to its rounded output itself and applies the addition's
     // activation; 1 + that activation, else 0.  The addition's own row then has kind kKindNone.
@@ -122,13 +124,12 @@ struct LayerDev {
     // tiles by conv_tile_rows() whichever kernel serves the layer index.
     uint32_t row_tiles;
     // First layer CONV of images with at most four channels that conv_first_kernel can take (first_rows > 0): submitted channels; most
-    // rows of a tile (of the layer's output, or, first_pool, of the max-pool's behind it) and rows of an image; whether that
-    // max-pool, the layer's only reader, is done with the convolution; in the row of a
-    // 3x3 convolution behind it, its only reader, that can be done with it: the same rows of that one's output.
-    uint32_t first_cin, first_rows, first_h, first_pool, pair_rows, pair_h;
-    uint64_t w_off;      // byte offset of the packed weights in the arena
-    uint64_t b_off;      // byte offset of the fp32 bias in the arena (N_pad entries for FC)
+    // rows of a tile (of the layer's output, or, first_pool, of the max-pool's behind it); whether that max-pool, the layer's only reader,
+    // is done with the convolution.  pair_rows, in the row of a 3x3 convolution behind it, its only reader, that can be done with
+    // it: most rows of that one's output.
+    uint32_t first_cin, first_rows, first_pool, pair_rows;
 };
+static_assert(sizeof(LayerDev) == 128, "two cache lines");
 
 // tiles of an image of h rows, at most `rows` and at most `cap` of them to a tile (dealt out evenly)
 inline __host__ __device__ uint32_t first_strips(uint32_t h, uint32_t rows, uint32_t cap)
