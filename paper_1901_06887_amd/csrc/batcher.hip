@@ -42,25 +42,6 @@ __device__ uint32_t block_exclusive_scan(uint32_t* data, uint32_t n, uint32_t* t
     return total;
 }
 
-// A row's packed position is known: note it both ways; a rejected row (t < 0: unknown tenant or
-// no model) is answered at once with label -1 and zero rows.
-__device__ __forceinline__ void place_row(const BatchArgs& a, uint32_t r, int32_t t, uint32_t position)
-{
-    int32_t pos = -1;
-    if (t >= 0) {
-        pos = (int32_t)position;
-        a.perm[pos] = (int32_t)r;
-    } else {
-        a.out.labels[r] = -1;
-        if (a.out.n_classes) a.out.n_classes[r] = 0;
-        for (uint32_t c = 0; c < a.out.row_stride; ++c) {
-            if (a.out.probs) a.out.probs[(size_t)r * a.out.row_stride + c] = 0.0f;
-            if (a.out.logits) a.out.logits[(size_t)r * a.out.row_stride + c] = 0.0f;
-        }
-    }
-    a.pos_of[r] = pos;
-}
-
 // Placement pass for large batches (after rank_kernel and the batcher): one row per thread;
 // position = the tenant's first row + rows of the tenant in earlier ranking workgroups + rank.
 __global__ __launch_bounds__(kBatchThreads) void place_kernel(BatchArgs a)

@@ -134,6 +134,8 @@ struct mt_ctx {
     uint32_t list_mask[MT_MAX_LAYERS / kLayerGroup] = {};   // per group of layer indices, bit kind*kLayerGroup + l%kLayerGroup: some registered model has that kind at layer l
     uint32_t has_image_ops[MT_MAX_LAYERS]{};   // some registered model has a max-pool or an addition at this layer index
     uint32_t image_op_fill[MT_MAX_LAYERS]{};   // ... and the longest output row (elements) among them
+    uint32_t min_layers = 0;                   // layers of the registered model with the fewest
+    uint32_t no_entry = 0;                     // tuning/testing: the batcher always has a launch
     uint32_t max_image_pixels = 0;             // most pixels in a submitted image (models whose first layer is a convolution)
     uint32_t act_buffers = 2;      // activation buffers every run slot holds (grows when a model with skip connections needs more)
     uint32_t max_reg_classes = 0, min_reg_classes = 0;
@@ -512,7 +514,7 @@ void recompute_pool_fusion(mt_ctx* c)
 void recompute_bounds(mt_ctx* c)
 {
     c->n_layer_slots = 0;
-    c->max_in_len = 0; c->max_image_pixels = 0;
+    c->max_in_len = 0; c->max_image_pixels = 0; c->min_layers = 0xffffffffu;
     c->fc_first_chunked = true; c->any_conv_first = c->any_fc_first = false;
     for (uint32_t& m : c->list_mask) m = 0;
     c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
@@ -549,6 +551,7 @@ void recompute_bounds(mt_ctx* c)
     for (const HostTenant& t : c->tenants) {
         if (!t.registered) continue;
         c->n_layer_slots = std::max(c->n_layer_slots, t.n_layers);
+        c->min_layers = std::min(c->min_layers, t.n_layers);
         c->max_in_len = std::max(c->max_in_len, t.dev.in_len);
         c->max_reg_classes = std::max(c->max_reg_classes, t.dev.n_classes);
         c->min_reg_classes = std::min(c->min_reg_classes, t.dev.n_classes);
@@ -733,6 +736,14 @@ ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<Na
     }
     if (split) { p.split = true; p.frames = false; p.tiles = tiles; }
     return p;
+}
+
+// Whether layer 0 does the batcher's work in a run of one submission of R rows that it reads itself: few rows and tenants, nothing but streaming FC
+// tiles that split K, and no model that is finished there.
+bool run_entry(const mt_ctx* c, uint64_t R, bool split_k)
+{
+    return R <= kEntryMaxRows && c->cfg.max_tenants <= kEntryMaxTenants && !c->no_entry && !c->any_conv_first && c->any_fc_first && c->min_layers >= 2 &&
+           (split_k || c->max_fc_cols[0] <= 2 * (uint32_t)kBrickRows);
 }
 
 // Most classes a last layer may have for its FC tiles to finish their rows themselves (softmax,
@@ -1076,6 +1087,7 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
     if (const char* e = getenv("MT_NO_FUSED_HEAD")) c->no_fused_head = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_FUSED_POOL")) c->no_fused_pool = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_IMG")) c->no_conv_img = atoi(e) != 0;
+    if (const char* e = getenv("MT_NO_ENTRY")) c->no_entry = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_PAIR")) c->no_conv_pair = atoi(e) != 0;
     if (const char* e = getenv("MT_NO_CONV_FIRST")) c->no_conv_first = atoi(e) != 0;
     if (const char* e = getenv("MT_FIRST_ROWS")) c->first_cap = (uint32_t)std::max(0, atoi(e));
@@ -1649,9 +1661,6 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
         hipLaunchKernelGGL(fill_zero_kernel, dim3((static_descr_words + 255) / 256), dim3(256), 0, s, rs.d_M, static_descr_words);
         HIP_TRY(c, hipGetLastError()); ++launches;
     }
-    TIMED(kProfBatcher, launch_batcher(b, s));
-    if (b.n_rank_groups) launches += 2;
-
     // The FC kernel of layer 0 reads the submitted rows itself when every row is 16-byte aligned
     // and a whole number of 16-byte chunks long; otherwise (and for CNN models, whose images are
     // channel-padded) a gather pass stages the inputs first.
@@ -1662,6 +1671,13 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     bool fuse_gather = c->any_fc_first && c->fc_first_chunked && !c->no_fused_gather && !big_possible;
     for (const Segment& sg : c->pending)
         if (((uintptr_t)sg.src & 15) || ((uint64_t)sg.row_stride * c->elem_size) % 16) fuse_gather = false;
+    const bool entry = n_segs == 1 && fuse_gather && run_entry(c, R, split_k);
+    if (entry) {                           // (the time of the whole run starts where the batcher's would)
+        if (c->profiling) HIP_TRY(c, hipEventRecord(c->prof_events[2 * kProfBatcher], s));
+    } else {
+        TIMED(kProfBatcher, launch_batcher(b, s));
+        if (b.n_rank_groups) launches += 2;
+    }
     // packed rows: every tenant with traffic pads its segment to a multiple of 32
     const uint32_t P = packed_rows_bound(c, R);
     {
@@ -1697,7 +1713,8 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
                 return fail(c, MT_EUNSUPPORTED, "layer %u: %llu tiles exceed one launch", l, (unsigned long long)grid);
             const uint32_t g32 = (uint32_t)grid;
             ga.first_cap = conv.first_cap;
-            if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, split_k || c->max_fc_cols[l] <= 2 * (uint32_t)kBrickRows, g32, s));
+            if (kind == 0 && l == 0 && entry) TIMED(kProfFc + l, launch_fc_entry(ga, b, c->cfg.dtype, g32, s));
+            else if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, split_k || c->max_fc_cols[l] <= 2 * (uint32_t)kBrickRows, g32, s));
             else if (conv.pair_mid) TIMED(kProfConv + l, launch_conv_pair(ga, c->cfg.dtype, c->pair_blocks, conv.first_frame, conv.pair_mid, g32, s));
             else if (conv.first_cap) TIMED(kProfConv + l, launch_conv_first(ga, c->cfg.dtype, c->first_max_ks, c->first_pool, c->first_plain, conv.first_frame, g32, s));
             else if (conv.split) TIMED(kProfConv + l, launch_conv_split(ga, c->cfg.dtype, (c->max_conv_k[l] * c->elem_size + 31) / 32, g32, s));
@@ -1813,6 +1830,7 @@ constexpr double kUsConvFramePerKStep = 0.095, kConvFrameMflopPerUs = 0.6e3;   /
 constexpr double kUsConvFirstFixed = 8.0, kConvFirstMbPerUs = 5.2, kConvFirstMflopPerUs = 0.38e3;     // first convolutions on the submitted images, by the multiplications that they need
 constexpr double kUsConvSplitFixed = 1.0, kUsConvSplitPerKStep = 0.034;     // launches whose tiles split K among their waves: per k-step of a tile, one tile per compute unit at a time
 constexpr double kUsConvPerKStep = 0.21;     // a convolution tile's walk through K, per k-step of 32 bytes per pixel: a launch lasts at least as long as its longest tile
+constexpr double kUsEntry = 3.0;             // what the segmentation costs a small run's first layer
 constexpr double kUsSmallFixed = 3.0, kCopyMbPerUs = 3.7, kHeadMbPerUs = 5.7, kUsHeadPerRow = 0.0008;
 constexpr double kComputeUnits = 256.0;
 constexpr double kUploadBytesPerMs = 55e6, kUsUploadFixed = 20.0;     // pinned host memory to HBM over the host link: 55 GB/s measured
@@ -1882,7 +1900,8 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
     double us = 0.0;
     uint32_t launches = 0;
     auto launch = [&](double t) { us += t + (launches ? kUsLaunchGap : 0.0); ++launches; };
-    if (spread) { launch(20.0 + 0.15 * R / 1024.0); launches += 2; }       // ranking, scan, placement
+    if (fuse_gather && run_entry(c, R, split_k)) us += kUsEntry;           // done by the first layer's launch
+    else if (spread) { launch(20.0 + 0.15 * R / 1024.0); launches += 2; }       // ranking, scan, placement
     else launch(7.0 + 1.1 * R / 1024.0);                                   // kernel trace: 7.0 us at 64 rows, 9.2 at 2048, 11.3 at 4096
 
     double fc_in_mb = 0.0, img_in_mb = 0.0, img_out_mb = 0.0;

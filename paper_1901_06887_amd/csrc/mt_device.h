@@ -8,7 +8,8 @@
 //                   bricks go from memory into MFMA operands through a register ring, activation
 //                   bricks are shared through LDS; fused bias + activation (+ rounding), brick
 //                   output, fp32 logits, or softmax/argmax where one tile holds all classes (at most
-//                   128).  Narrow layers and small runs take tiles of 32 rows whose waves split K
+//                   128).  Narrow layers and small runs take tiles of 32 rows whose waves split K;
+//                   fc_entry_kernel: layer 0 of a small run with the segmentation in it
 //   fc_big.hip      fc_big_walk_kernel / fc_big_kernel: the same layer index, compute-bound tenant-layers:
 //                   256x256 tiles, both operands through an LDS ring filled by direct global->LDS loads;
 //                   one workgroup per compute unit walks the tiles (or, for short K, one workgroup per tile)
@@ -302,6 +303,25 @@ template <> struct Mma<float> {
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[3], bf[3], acc, 0, 0, 0);
     }
 };
+
+// A row's packed position is known: note it both ways; a rejected row (t < 0: unknown tenant or
+// no model) is answered at once with label -1 and zero rows.
+__device__ __forceinline__ void place_row(const BatchArgs& a, uint32_t r, int32_t t, uint32_t position)
+{
+    int32_t pos = -1;
+    if (t >= 0) {
+        pos = (int32_t)position;
+        a.perm[pos] = (int32_t)r;
+    } else {
+        a.out.labels[r] = -1;
+        if (a.out.n_classes) a.out.n_classes[r] = 0;
+        for (uint32_t c = 0; c < a.out.row_stride; ++c) {
+            if (a.out.probs) a.out.probs[(size_t)r * a.out.row_stride + c] = 0.0f;
+            if (a.out.logits) a.out.logits[(size_t)r * a.out.row_stride + c] = 0.0f;
+        }
+    }
+    a.pos_of[r] = pos;
+}
 
 // What a workgroup works on, derived from its block index and the list's tile_base array.
 struct Tile {

@@ -51,6 +51,7 @@ inline __host__ __device__ uint32_t big_rows(uint32_t rows)
 // (c5's last layer: 35 -> 19 us; the hidden layers would go from 39 to 44 us, their weights read once more).
 constexpr int kBigRemSplitMaxCols = 1024;
 inline __host__ __device__ bool big_remainder_split_k(uint32_t n_pad) { return n_pad <= (uint32_t)kBigRemSplitMaxCols; }
+constexpr uint32_t kEntryMaxRows = 256, kEntryMaxTenants = 64;   // runs whose first launch may do the batcher's work: a few rows and one tenant to a lane
 constexpr int kRankRows = 1024;     // rows per workgroup of the ranking kernel
 constexpr int kRankMinRows = 8192;  // smaller batches are ranked by the batcher's single workgroup (one launch less)
 constexpr int kRankMaxTenants = 512;
@@ -269,6 +270,7 @@ hipError_t launch_batcher(const BatchArgs& a, hipStream_t s);   // three launche
 hipError_t launch_gather(const GatherArgs& a, uint32_t slices, hipStream_t s);   // `slices` workgroups share a block of 32 rows
 hipError_t launch_gather_image(const GatherArgs& a, uint32_t slices, hipStream_t s);   // `slices` workgroups share a row
 hipError_t launch_fc(const GemmArgs& a, uint32_t dtype, bool narrow, uint32_t grid, hipStream_t s);
+hipError_t launch_fc_entry(const GemmArgs& a, const BatchArgs& b, uint32_t dtype, uint32_t grid, hipStream_t s);   // layer 0 of a small run, the batcher's work in it
 hipError_t launch_fc_big(const GemmArgs& a, uint32_t dtype, uint32_t grid, uint32_t walk_grid, hipStream_t s);   // walk_grid > 0: that many workgroups walk the tiles (a multiple of 8)
 hipError_t launch_copy(void* dst, const void* src, uint64_t bytes, hipStream_t s);
 hipError_t launch_mfma_rate(float* out, uint32_t iters, uint32_t grid, hipStream_t s);   // out: grid * 512 floats

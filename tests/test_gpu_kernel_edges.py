@@ -446,3 +446,39 @@ def test_first_convolutions_with_infinite_filters(monkeypatch):
         monkeypatch.setenv("MT_NO_CONV_FIRST", off)
         got.append(gpu_run(make_context(w), w, poison=True)[0])
     assert np.array_equal(got[0], got[1], equal_nan=True) and np.isfinite(got[0][w.tenant_ids == 1]).all() and not np.isfinite(got[0][w.tenant_ids == 0]).all()
+
+
+# runs whose first launch does the batcher's work: rows at the edges of a wave's 64 and of what it takes, one tenant and all 64, models of two to four
+# layers and of few and many classes, rows of unknown tenants and of tenants without a model; the same bits and counts as with the batcher
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_tenants", [1, 9, 64])
+@pytest.mark.parametrize("rows", [1, 33, 64, 65, 200, 256, 257])
+def test_small_runs_without_a_batcher(monkeypatch, dtype, n_tenants, rows):
+    shapes = ([48, 24, 5], [48, 64, 40, 130], [48, 200, 33, 7, 64])
+    tenants = {t: wl.make_model(wl.mlp_layers(shapes[t % 3], wl.ACT_RELU), dtype, 380, t) for t in range(n_tenants) if t != 7}
+    rng = np.random.default_rng(380)
+    x = rng.standard_normal((rows, 48)).astype(np.float32)
+    ids = rng.integers(0, n_tenants, rows).astype(np.int32)
+    ids[ids == 7] = 3
+    w = wl.Workload("entry", dtype, tenants, ids, wl.round_to_bf16(x) if dtype == "bf16" else x)
+    odd = ids.copy()
+    odd[rng.random(rows) < 0.2] = rng.choice([-1, n_tenants, 1 << 30, min(7, n_tenants)])
+    got = {}
+    for off in ("0", "1"):
+        monkeypatch.setenv("MT_NO_ENTRY", off)
+        ctx = make_context(w, max_tenants=n_tenants)
+        got[off] = [check(w, "%s, %d tenants, %d rows" % (dtype, n_tenants, rows), ctx) if off == "0" else gpu_run(ctx, w, poison=True)]
+        launches = ctx.stats()["last_run_launches"]
+        got[off].append(gpu_run(ctx, w, ids=odd, poison=True))
+        got[off].append((ctx.last_counts(), [ctx.tenant_account(t)["requests"] for t in tenants]))
+        one = torch_io.to_device(w.inputs, dtype)                    # all of them one tenant's, named by the submission
+        out = torch_io.alloc_outputs(rows, ctx.cfg.max_classes)
+        ctx.submit(0, one.data_ptr(), rows)
+        ctx.run(torch.cuda.current_stream().cuda_stream, out.labels.data_ptr(), out.probs.data_ptr(), out.logits.data_ptr(), out.n_classes.data_ptr(), rows, ctx.cfg.max_classes)
+        torch.cuda.synchronize()
+        got[off].append((out.logits.cpu().numpy(), out.labels.cpu().numpy(), ctx.last_counts()))
+        got[off + "n"] = launches
+        ctx.close()
+    for a, b in zip(got["0"], got["1"]):
+        assert all(np.array_equal(u, v) for u, v in zip(a, b))
+    assert got["0n"] in (got["1n"], got["1n"] - 1) and (got["0n"] < got["1n"] or rows > 60)
