@@ -864,8 +864,14 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(KS == 
 // 16.8-19.2 -> 8.8, 14x14x256 24.7 -> 11, 7x7x512 27.3 -> 13.9, the stride-2 layers 12.2 / 18.2 / 23.2 -> 6.3 / 8.5 / 10.3, the
 // 1x1 projections 11-12 -> 4.6.  (Tiles of 128 pixels with their input in LDS frames and sixteen waves were slower up to
 // 144 k steps, 10-12 us each, and 12 us at 288: eight barriers, the frame's zeroing and one workgroup per CU.)
-template <typename T, uint32_t WAVES>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 16 ? 4 : 6, WAVES == 16 ? 4 : 6))) void conv_split_kernel(GemmArgs a)
+// CS > 0: every tenant's taps are whole chunks of CS k steps.  What bounds such a tile is then the rate at which its unit takes lane
+// addresses: 64 clocks for a brick gathered 32 bytes a pixel, as many for the two lanes of a pixel as for one (80 with its filters: 288 steps of one tile are 10 us).
+// So a wave's share of K is chunks, a load takes 16 bytes of a pixel in each of 2 CS neighbouring lanes, and the pieces change places in the
+// wave's part of the LDS (behind the K loop that of its sums).  One residual-net request, us: 7x7x512 13.9 -> 10.1, 14x14x256 10.4 -> 7.7,
+// 28x28x128 8.6 -> 7.1, 56x56x64 6.4 -> 5.8, the stride-2 layers 10.0 -> 8.2 / 8.4 -> 6.8 / 6.1 -> 5.9; with 4 waves (at most 24 steps) 4.6 -> 5.1, which keep the gathers.
+// (Chunks of four steps, one in flight: 11.6, 9.6, 9.0, 7.3 of the first four; eight gathered steps in flight instead of four: 15.3, 12.2, 8.7, 6.1.)
+template <typename T, uint32_t WAVES, uint32_t CS>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 16 || CS ? 4 : 6, WAVES == 16 || CS ? 4 : 6))) void conv_split_kernel(GemmArgs a)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC, P = 4, THREADS = 64 * WAVES;
     typedef const __attribute__((address_space(1))) u32x4* gptr_t;
@@ -895,7 +901,94 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     f32x16 acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-    if (cnt) {
+    if constexpr (CS > 0) {
+        constexpr uint32_t PCS = 2 * CS, PXL = 64 / PCS, D = P / CS;      // pieces of a pixel, pixels of a load, chunks in flight
+        static_assert(P % CS == 0 && CS * 1024 <= 4096, "a ring of whole chunks; a chunk lies in a wave's part of the LDS");
+        const uint32_t ks = L.ksize, tap_chunks = L.cin / (CS * KB), n_chunks = ks * ks * tap_chunks;
+        const uint32_t c0 = wave * n_chunks / WAVES, n = (wave + 1) * n_chunks / WAVES - c0;
+        if (n) {
+            const uint32_t piece = lane % PCS;
+            gptr_t zeros = (gptr_t)a.zeros;
+            // every lane works out where the window of pixel li begins (it may be outside the image) and which of its taps lie inside; the
+            // lanes that load pieces of it are told
+            const int32_t ih = (int32_t)(oh * L.stride) - (int32_t)L.pad, iw = (int32_t)(ow * L.stride) - (int32_t)L.pad;
+            const uint64_t window = (uint64_t)((const T*)act_of(a.act, L.in_buf) + at + ((int64_t)ih * L.in_w + iw) * L.cin);
+            const uint32_t lo = (uint32_t)max(0, -iw), hi = (uint32_t)max(0, min((int32_t)ks, (int32_t)L.in_w - iw));
+            const uint64_t row = row_ok && lo < hi ? (1ull << hi) - (1ull << lo) : 0;
+            uint64_t taps = 0;
+            for (uint32_t th = 0; th < ks; ++th) taps |= (uint32_t)(ih + (int32_t)th) < L.in_h ? row << (th * ks) : 0;
+            uint64_t px[CS], inside[CS];
+#pragma unroll
+            for (uint32_t j = 0; j < CS; ++j) {
+                const int from = (int)(j * PXL + lane / PCS);
+                px[j] = __shfl(window, from) + piece * 16;
+                inside[j] = __shfl(taps, from);
+            }
+            uint32_t tap = c0 / tap_chunks, in_tap = c0 - tap * tap_chunks, left = n - 1;      // scalar: the chunk that is loaded next, those behind it
+            uint32_t tw = tap % ks;
+            uint64_t off = ((uint64_t)(tap / ks * L.in_w + tw) * L.cin + in_tap * (CS * KB)) * sizeof(T);        // bytes
+            auto advance = [&] {                                   // (behind the last chunk: that one again)
+                if (left == 0) return;
+                --left; off += CS * kBrickBytes / kBrickRows;
+                if (++in_tap == tap_chunks) {
+                    in_tap = 0; ++tap;
+                    if (++tw == ks) { tw = 0; off += ((uint64_t)L.in_w - ks) * L.cin * sizeof(T); }        // (less than nothing where the image is narrower than the window)
+                }
+            };
+            auto load = [&](u32x4 (&v)[CS]) {
+                const uint64_t tap_bit = 1ull << tap;
+#pragma unroll
+                for (uint32_t j = 0; j < CS; ++j) {
+                    gptr_t p = inside[j] & tap_bit ? (gptr_t)(px[j] + off) : zeros;
+                    v[j] = *p;
+                }
+                advance();
+            };
+            const uint64_t wbase = (uint64_t)(a.arena + L.w_off) + ((uint64_t)nb * nKB + c0 * CS) * kBrickBytes;
+            auto load_w = [&](uint32_t c, u32x4 (&v)[CS]) {
+                uint64_t src = uniform64(wbase + (uint64_t)min(c, n - 1) * (CS * kBrickBytes));
+                uint32_t lo = lane * 16;
+                asm("" : "+s"(src));
+                asm("" : "+v"(lo));
+#pragma unroll
+                for (uint32_t q = 0; q < CS; ++q) v[q] = *(gptr_t)(src + lo + q * kBrickBytes);
+            };
+            // piece c of pixel p lies where lane p + 32 (c % 2) of brick c / 2 reads, pixels of unlike pieces in another order: the lanes
+            // of a pixel write, and a brick's lanes read, all banks
+            constexpr uint32_t SWZ = 8 / PCS;
+            uint8_t* stage = red + wave * 4096;
+            auto place = [&](const u32x4 (&v)[CS]) {
+#pragma unroll
+                for (uint32_t j = 0; j < CS; ++j)
+                    *(u32x4*)(stage + piece * 512 + (((j * PXL + lane / PCS) ^ (piece * SWZ)) * 16)) = v[j];
+            };
+            auto brick = [&](uint32_t q) -> u32x4 { return *(const u32x4*)(stage + (2 * q + lh) * 512 + ((li ^ ((2 * q + lh) * SWZ)) * 16)); };
+            u32x4 aq[D][CS], wq[D][CS];
+#pragma unroll
+            for (uint32_t d = 0; d < D; ++d) { load_w(d, wq[d]); load(aq[d]); }
+            auto chunk = [&](uint32_t c, uint32_t d) {
+                place(aq[d]);
+                load(aq[d]);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the wave's own pieces are there
+                u32x4 av[CS];
+#pragma unroll
+                for (uint32_t q = 0; q < CS; ++q) av[q] = brick(q);
+#pragma unroll
+                for (uint32_t q = 0; q < CS; ++q) Mma<T>::run(acc, wq[d][q], av[q]);       // rows = channels, columns = pixels
+                load_w(c + D, wq[d]);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read before the next chunk overwrites them
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            uint32_t s = 0;
+            for (; s + D <= n; s += D) {
+#pragma unroll
+                for (uint32_t d = 0; d < D; ++d) chunk(s + d, d);
+            }
+#pragma unroll
+            for (uint32_t d = 0; d < D; ++d)
+                if (s + d < n) chunk(s + d, d);
+        }
+    } else if (cnt) {
         gptr_t wp = (gptr_t)((const u32x4*)(a.arena + L.w_off) + ((size_t)nb * nKB + k0) * 64 + lane);
         gptr_t src = (gptr_t)((const T*)act_of(a.act, L.in_buf) + at), zeros = (gptr_t)a.zeros;
         TapWalk<T> walk;
@@ -1016,19 +1109,21 @@ static hipError_t prepare_conv_t()
 hipError_t prepare_conv(uint32_t dtype) { return dtype == MT_BF16 ? prepare_conv_t<__bf16>() : prepare_conv_t<float>(); }
 
 template <typename T>
-static void launch_conv_split_t(const GemmArgs& a, uint32_t k_steps, uint32_t grid, hipStream_t s)
+static void launch_conv_split_t(const GemmArgs& a, uint32_t k_steps, bool chunks, uint32_t grid, hipStream_t s)
 {
-    if (k_steps <= kSplitFewSteps) hipLaunchKernelGGL((conv_split_kernel<T, 4>), dim3(grid), dim3(256), 0, s, a);
-    else if (k_steps <= kSplitSomeSteps) hipLaunchKernelGGL((conv_split_kernel<T, 8>), dim3(grid), dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((conv_split_kernel<T, 16>), dim3(grid), dim3(1024), 0, s, a);
+    if (k_steps <= kSplitFewSteps) hipLaunchKernelGGL((conv_split_kernel<T, 4, 0>), dim3(grid), dim3(256), 0, s, a);
+    else if (k_steps <= kSplitSomeSteps && chunks) hipLaunchKernelGGL((conv_split_kernel<T, 8, 2>), dim3(grid), dim3(512), 0, s, a);
+    else if (k_steps <= kSplitSomeSteps) hipLaunchKernelGGL((conv_split_kernel<T, 8, 0>), dim3(grid), dim3(512), 0, s, a);
+    else if (chunks) hipLaunchKernelGGL((conv_split_kernel<T, 16, 2>), dim3(grid), dim3(1024), 0, s, a);
+    else hipLaunchKernelGGL((conv_split_kernel<T, 16, 0>), dim3(grid), dim3(1024), 0, s, a);
 }
 
-// k_steps: the longest reduction of the layer index in bricks
-hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, uint32_t grid, hipStream_t s)
+// k_steps: the longest reduction of the layer index in bricks; chunks: every tenant's taps are whole pairs of k steps
+hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, bool chunks, uint32_t grid, hipStream_t s)
 {
     if (grid == 0) return hipSuccess;
     grid = (grid + 7) / 8 * 8;
-    if (dtype == MT_BF16) launch_conv_split_t<__bf16>(a, k_steps, grid, s); else launch_conv_split_t<float>(a, k_steps, grid, s);
+    if (dtype == MT_BF16) launch_conv_split_t<__bf16>(a, k_steps, chunks, grid, s); else launch_conv_split_t<float>(a, k_steps, chunks, grid, s);
     return hipGetLastError();
 }
 

@@ -1723,7 +1723,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             else if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, split_k || c->max_fc_cols[l] <= 2 * (uint32_t)kBrickRows, g32, s));
             else if (conv.pair_mid) TIMED(kProfConv + l, launch_conv_pair(ga, c->cfg.dtype, c->pair_blocks, conv.first_frame, conv.pair_mid, g32, s));
             else if (conv.first_cap) TIMED(kProfConv + l, launch_conv_first(ga, c->cfg.dtype, c->first_max_ks, c->first_pool, c->first_plain, conv.first_frame, g32, s));
-            else if (conv.split) TIMED(kProfConv + l, launch_conv_split(ga, c->cfg.dtype, (c->max_conv_k[l] * c->elem_size + 31) / 32, g32, s));
+            else if (conv.split) TIMED(kProfConv + l, launch_conv_split(ga, c->cfg.dtype, (c->max_conv_k[l] * c->elem_size + 31) / 32, c->conv_quad[l], g32, s));
             else if (kind == 1) TIMED(kProfConv + l, launch_conv(ga, c->cfg.dtype, c->max_conv_cb[l], c->conv_quad[l],
                                                                     conv.frames ? c->conv_img_lds[l] : 0, c->conv_img_two[l] == 1, conv.frame_sets,
                                                                     !c->no_conv_loaders && c->min_conv_k[l] >= kConvLongK,

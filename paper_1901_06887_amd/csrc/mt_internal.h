@@ -278,7 +278,7 @@ hipError_t prepare_conv(uint32_t dtype);   // once per device, before the first 
 // max_cb: the widest tile of this layer index over the registered tenants, in 32-channel blocks (1..4)
 // quad: every tenant's input channels at this layer index are a multiple of four 16-byte chunks
 hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool img_sets, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s);
-hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, uint32_t grid, hipStream_t s);
+hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, bool chunks, uint32_t grid, hipStream_t s);
 // first convolutions on the submitted images: the largest window, whether some model's max-pool is done with it and some model's rows
 // are stored themselves, and the largest frame in bytes
 hipError_t launch_conv_first(const GemmArgs& a, uint32_t dtype, uint32_t max_ks, bool pool, bool scratch, uint32_t frame_bytes, uint32_t grid, hipStream_t s);

@@ -110,7 +110,9 @@ def test_average_pooling_of_any_channel_count(hw, channels, dtype):
 # with 8 of 32 channels, pixel tiles with a single pixel; against the oracle, and against the launches that do not split K
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("k,stride,ci,co,hw", [(1, 1, 8, 8, (1, 1)), (1, 2, 16, 40, (5, 7)), (3, 1, 8, 72, (11, 3)), (3, 2, 24, 32, (9, 6)), (3, 1, 64, 96, (4, 8)),
-                                               (3, 1, 200, 128, (7, 7)), (7, 2, 8, 64, (17, 13)), (7, 1, 40, 8, (6, 6))])
+                                               (3, 1, 200, 128, (7, 7)), (7, 2, 8, 64, (17, 13)), (7, 1, 40, 8, (6, 6)),
+                                               # taps of whole chunks, images narrower than the window among them
+                                               (3, 1, 128, 64, (1, 1)), (3, 1, 192, 40, (5, 2)), (3, 2, 160, 96, (9, 6)), (7, 1, 32, 72, (3, 4)), (3, 1, 288, 32, (7, 11))])
 def test_convolutions_that_split_their_reduction(monkeypatch, dtype, k, stride, ci, co, hw):
     h, w_ = hw
     first = wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, ci, h, w_, 1, ksize=3, pad=1)
