@@ -32,7 +32,11 @@ constexpr int kBigMinRows = 2048;
 // those rows go to the streaming kernel, which reads the tenant's weights once more instead.
 constexpr int kBigRemRows = 128;
 constexpr int kBigMinCols = 192;
-constexpr int kBigMinTiles = 512;   // a layer index is served with big tiles only when it has at least two per compute unit
+// A layer index is served with big tiles only when its qualifying tenants make at least so many.  bf16: a round of one per compute unit takes
+// less than the streaming tiles of as many rows and columns do, and so do two with the second nearly empty (models of 2048-2048-classes, whole passes with
+// big tiles from 256 / from 512 on: 4 tenants, 16384 rows, 1000 classes 377 / 447 us, 500 classes 295 / 363, 200 classes 261 / 317; 3 tenants, 8192 rows, 264 hidden tiles
+// 252 / 260; from 64 on 312; 8 tenants, 32768 rows through 4096-1024-4096-1000 1022 / 1451).  fp32 tiles of both kinds run at the MFMA rate: a nearly empty round loses (264 tiles: 846 -> 1199 us).
+constexpr int kBigMinTiles = 256, kBigMinTilesF32 = 512;
 constexpr double kRidgeFlopsPerByte = 312.0;   // dense bf16 MFMA peak over HBM bandwidth (2.5 PFLOP/s / 8 TB/s)
 constexpr int kBigMinBatch = 8192;  // runs with fewer rows are latency/HBM bound as a whole: no big tiles
 inline __host__ __device__ bool fc_is_big(uint32_t rows, uint32_t n_pad) { return rows >= (uint32_t)kBigMinRows && n_pad >= (uint32_t)kBigMinCols; }
