@@ -566,30 +566,24 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
 // multiple of 32 bytes, which spreads the lanes of a stride-2 read over half the banks (2-way
 // conflict; stride 1: none).  Filters stream through a register ring per wave as in conv_kernel.
 // Sub-images: a tile holds `ni` of them, each `n_oh` output rows of one image.
-// KS: sets of four waves, each with a share of K and the whole of the tile; two where a launch has at most a tile to a compute unit, whose
-// walk through K a single wave to a SIMD leaves idle most of the time.  The sets hand each other the sums of
-// every second pixel block through LDS, and finish the others.  64 images: 14x14x256 25.6/28.4 -> 24/25.2 us (without and with a residual
-// addition), 7x7x512 27.1/28.8 -> 24.3/25.4.  Not for launches of more tiles: two workgroups of one set share a unit at least as well.
-template <typename T, int NCB, bool TWO, int KS = 1>
-__global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(KS == 2 ? 2 : NCB == 1 ? 8 : NCB == 2 ? 4 : 3, KS == 2 ? 2 : NCB == 1 ? 8 : NCB == 2 ? 4 : 3))) void conv_img_kernel(GemmArgs a)
+template <typename T, int NCB, bool TWO>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 8 : NCB == 2 ? 4 : 3, NCB == 1 ? 8 : NCB == 2 ? 4 : 3))) void conv_img_kernel(GemmArgs a)
 {
-    static_assert(KS == 1 || (KS == 2 && NCB == 4 && !TWO), "two sets: four channel blocks, whole taps");
-    constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC, THREADS = 256 * KS;
+    constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC;
     constexpr uint32_t NB = NCB == 1 ? 2 : NCB == 2 ? 5 : 9;        // frame loads in flight per lane
     constexpr uint32_t P = NCB == 1 ? 4 : 8;                        // filter bricks in flight per wave (one channel block: small tiles, many resident waves)
     static_assert(NCB == 1 || NCB == 2 || NCB == 4, "channel blocks side by side");
     constexpr uint32_t WR = 4 / NCB, RBW = 4 / WR;                  // wave rows; pixel blocks per wave
     typedef const __attribute__((address_space(1))) u32x4* gptr_t;
     extern __shared__ __attribute__((aligned(16))) uint8_t img[];
-    __shared__ uint32_t owner_part[4 * KS];
-    const uint32_t tid = threadIdx.x, lane = tid & 63, set_wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
-    const uint32_t wave = KS == 1 ? set_wave : set_wave & 3, kset = KS == 1 ? 0 : set_wave >> 2;
-    TileOwner<THREADS> lookup;
+    __shared__ uint32_t owner_part[4];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
+    TileOwner<256> lookup;
     lookup.fetch(a.tile_base, a.T);
     const uint32_t n_tiles = a.tile_base[a.T];
     // the frame starts as zeros (its border, rows past the image, sub-images past the tenant's last request);
     // written while the tile list is on its way, published by the barrier of the lookup
-    for (uint32_t q = tid * 16; q < a.img_lds; q += THREADS * 16) *(u32x4*)(img + q) = u32x4{0, 0, 0, 0};
+    for (uint32_t q = tid * 16; q < a.img_lds; q += 256 * 16) *(u32x4*)(img + q) = u32x4{0, 0, 0, 0};
     uint32_t idx;
     if (!logical_tile(n_tiles, &idx)) return;
     const uint32_t t = lookup.owner(a.T, idx, owner_part);   // uniform: the tenant's facts come through scalar loads
@@ -620,12 +614,10 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(KS == 
     const uint32_t px_t = min(n_oh * ow_n, rpr - oh_first * ow_n);                // pixels of a sub-image in this tile (an image's last tile may be short)
 
     // the first filter bricks travel while the frame is filled (idle waves stream block 0 and drop it)
-    constexpr uint32_t G = 4, GP = P / G;                          // k steps of a group (k_loop_groups), groups in flight
-    const uint32_t g_first = KS == 1 ? 0 : kset * (nKBv / G) / KS, g_end = KS == 1 ? nKBv / G : (kset + 1) * (nKBv / G) / KS;      // this set's groups
-    gptr_t wp = (gptr_t)((const u32x4*)(a.arena + L.w_off) + ((size_t)(nb0 + (active ? wc : 0)) * nKB + g_first * G) * 64 + lane);
+    gptr_t wp = (gptr_t)((const u32x4*)(a.arena + L.w_off) + (size_t)(nb0 + (active ? wc : 0)) * nKB * 64 + lane);
     u32x4 wq[P];
 #pragma unroll
-    for (uint32_t j = 0; j < P; ++j) wq[j] = wp[(size_t)min(j, nKBv - 1 - g_first * G) * 64];
+    for (uint32_t j = 0; j < P; ++j) wq[j] = wp[(size_t)min(j, nKBv - 1) * 64];
 
     const uint32_t cpp = cin * (uint32_t)sizeof(T) / 16, cpr = iw_n * cpp;       // 16-byte chunks per pixel, per image row
     for (uint32_t i = 0; i < ni; ++i) {
@@ -637,16 +629,16 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(KS == 
         gptr_t src = (gptr_t)((const T*)act_of(a.act, L.in_buf) + (size_t)(seg0 + req) * a.S) + (size_t)(ih_first + r_lo) * cpr;
         const uint32_t n_chunks = (uint32_t)(r_hi - r_lo) * cpr;                 // contiguous in memory
         uint8_t* dst = img + i * SUB + (uint32_t)r_lo * RSB + PB;                // first pixel slot after the left border
-        for (uint32_t q0 = 0; q0 < n_chunks; q0 += NB * THREADS) {                   // NB loads in flight per lane
+        for (uint32_t q0 = 0; q0 < n_chunks; q0 += NB * 256) {                   // NB loads in flight per lane
             u32x4 v[NB];
 #pragma unroll
             for (uint32_t j = 0; j < NB; ++j) {
-                const uint32_t q = q0 + j * THREADS + tid;
+                const uint32_t q = q0 + j * 256 + tid;
                 v[j] = src[q < n_chunks ? q : 0];
             }
 #pragma unroll
             for (uint32_t j = 0; j < NB; ++j) {
-                const uint32_t q = q0 + j * THREADS + tid;
+                const uint32_t q = q0 + j * 256 + tid;
                 uint32_t r, x, col, c16;
                 divmod_uniform(q, cpr, &r, &x);
                 divmod_uniform(x, cpp, &col, &c16);
@@ -727,12 +719,11 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(KS == 
         // 64 images, 56x56x64: 31.7/36.4 -> 29.6/31.1 us (without and with a residual addition), 28x28x128 29.5/32.0 -> 25.5/28.1,
         // 14x14x256 29.2/32.3 -> 26.1/28.9, 7x7x512 33.2/34.6 -> 30.3/32.2.
         auto k_loop_groups = [&](auto NR_) {
-            constexpr uint32_t NR = decltype(NR_)::value;
+            constexpr uint32_t NR = decltype(NR_)::value, G = 4, GP = P / G;      // k steps of a group, groups in flight
             static_assert(P % G == 0 && (kBrickBytes * (int)(G - 1)) < 4096, "a ring of whole groups; offsets of a load are below 4 KiB");
-            const uint32_t n_groups = KS == 1 ? nKBv / G : g_end - g_first, tap_groups = cin / (G * KB);
+            const uint32_t n_groups = nKBv / G, tap_groups = cin / (G * KB);
             const uint64_t wbase = uniform64((uint64_t)wp - lane * 16);
-            const uint32_t tap = KS == 1 ? 0 : g_first / tap_groups, in_tap = KS == 1 ? 0 : g_first - tap * tap_groups;
-            uint32_t kw = tap % 3, left = tap_groups - in_tap, row_off = tap / 3 * RSB, off = row_off + kw * PB + in_tap * (G * KB * (uint32_t)sizeof(T));             // scalar: kernel column, groups left in the tap, byte offset of the tap's row, of the group
+            uint32_t kw = 0, left = tap_groups, row_off = 0, off = 0;             // scalar: kernel column, groups left in the tap, byte offset of the tap's row, of the group
             auto advance = [&] {
                 off += G * KB * (uint32_t)sizeof(T);
                 if (--left == 0) {
@@ -790,8 +781,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(KS == 
         const bool half = RBW > 1 && blocks_used <= wr * RBW + RBW / 2;
         constexpr std::integral_constant<uint32_t, RBW> all_blocks{};
         constexpr std::integral_constant<uint32_t, (RBW > 1 ? RBW / 2 : 1)> half_blocks{};
-        if constexpr (KS > 1) { if (half) k_loop_groups(half_blocks); else k_loop_groups(all_blocks); }        // the launcher's rule: cin % (4 * KB) == 0
-        else if (!two && cin % (4 * KB) == 0) { if (half) k_loop_groups(half_blocks); else k_loop_groups(all_blocks); }
+        if (!two && cin % (4 * KB) == 0) { if (half) k_loop_groups(half_blocks); else k_loop_groups(all_blocks); }
         else if (half) k_loop(half_blocks);
         else k_loop(all_blocks);
     }
@@ -801,36 +791,10 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(KS == 
 #pragma unroll
     for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias + nbase + 8 * g + 4 * lh);   // bias is padded to N_pad
     __syncthreads();                                               // every wave is done with the frame: it now serves as store scratch
-    if (KS == 1 && !active) return;
+    if (!active) return;
     uint8_t* scratch = img + wave * unit_scratch_bytes<T>();
-    if constexpr (KS > 1) {                                        // set s finishes the pixel blocks r with r % 2 == s
-        static_assert(RBW / 2 * 4096 >= unit_scratch_bytes<T>(), "a wave's share of the exchange is its store scratch afterwards");
-        auto sums_of = [&](uint32_t set) { return img + (set * 4 + wave) * (RBW / 2 * 4096) + lane * 16; };
-#pragma unroll
-        for (uint32_t r = 0; r < RBW; ++r) {
-            if ((r & 1) == kset) continue;
-            uint8_t* to = sums_of(kset) + r / 2 * 4096;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) *(f32x4*)(to + q * 1024) = f32x4{acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]};
-        }
-        __syncthreads();
-        const uint8_t* from = sums_of(1 - kset);
-#pragma unroll
-        for (uint32_t r = 0; r < RBW; ++r) {
-            if ((r & 1) != kset) continue;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 v = *(const f32x4*)(from + r / 2 * 4096 + q * 1024);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[r][4 * q + e] += v[e];
-            }
-        }
-        scratch = img + ((1 - kset) * 4 + wave) * (RBW / 2 * 4096);
-        if (!active) return;
-    }
 #pragma unroll
     for (uint32_t r = 0; r < RBW; ++r) {
-        if (KS > 1 && (r & 1) != kset) continue;
         uint32_t i, pl;
         divmod_uniform((wr * RBW + r) * kBrickRows + li, spi, &i, &pl);
         T* out = nullptr;
@@ -1074,17 +1038,13 @@ static hipError_t allow_frame(K kernel)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kConvFrameMaxBytes);
 }
 
-constexpr uint32_t kConvSetsExchangeBytes = 64 * 1024;             // eight waves' sums of two pixel blocks each
-static_assert(kConvSetsExchangeBytes <= kConvFrameMaxBytes, "allow_frame");
-
 template <typename T>
-static hipError_t launch_conv_img_t(const GemmArgs& a, uint32_t max_cb, bool two, bool two_sets, uint32_t lds_bytes, uint32_t grid, hipStream_t s)
+static hipError_t launch_conv_img_t(const GemmArgs& a, uint32_t max_cb, bool two, uint32_t lds_bytes, uint32_t grid, hipStream_t s)
 {
-    lds_bytes = std::max<uint32_t>(lds_bytes, two_sets ? kConvSetsExchangeBytes : 4 * unit_scratch_bytes<T>());       // the frame also serves as exchange and store scratch
+    lds_bytes = std::max<uint32_t>(lds_bytes, 4 * unit_scratch_bytes<T>());       // the frame also serves as store scratch
     GemmArgs b = a;
     b.img_lds = lds_bytes;
-    if (two_sets) hipLaunchKernelGGL((conv_img_kernel<T, 4, false, 2>), dim3(grid), dim3(512), lds_bytes, s, b);
-    else if (two && sizeof(T) == 2) {
+    if (two && sizeof(T) == 2) {
         if (max_cb <= 1) hipLaunchKernelGGL((conv_img_kernel<T, 1, sizeof(T) == 2>), dim3(grid), dim3(256), lds_bytes, s, b);
         else if (max_cb <= 2) hipLaunchKernelGGL((conv_img_kernel<T, 2, sizeof(T) == 2>), dim3(grid), dim3(256), lds_bytes, s, b);
         else hipLaunchKernelGGL((conv_img_kernel<T, 4, sizeof(T) == 2>), dim3(grid), dim3(256), lds_bytes, s, b);
@@ -1103,7 +1063,6 @@ static hipError_t prepare_conv_t()
     auto also = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     also(allow_frame(conv_img_kernel<T, 1, false>)); also(allow_frame(conv_img_kernel<T, 2, false>)); also(allow_frame(conv_img_kernel<T, 4, false>));
     also(allow_frame(conv_img_kernel<T, 1, sizeof(T) == 2>)); also(allow_frame(conv_img_kernel<T, 2, sizeof(T) == 2>)); also(allow_frame(conv_img_kernel<T, 4, sizeof(T) == 2>));
-    also(allow_frame(conv_img_kernel<T, 4, false, 2>));
     return e;
 }
 hipError_t prepare_conv(uint32_t dtype) { return dtype == MT_BF16 ? prepare_conv_t<__bf16>() : prepare_conv_t<float>(); }
@@ -1128,15 +1087,15 @@ hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps
 }
 
 // img_lds_bytes > 0: every convolution of the layer index qualifies for the LDS-resident-input kernel, whose largest frame is that
-// size; img_two: their pixels are one 16-byte chunk (else none is); img_sets: at most a tile to a compute unit, every one's taps groups of four k steps
-hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool img_sets, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s)
+// size; img_two: their pixels are one 16-byte chunk (else none is)
+hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s)
 {
     if (grid == 0) return hipSuccess;
     grid = (grid + 7) / 8 * 8;
     const bool loaders = long_k && grid <= 256;                      // at most one tile per CU, every tenant's K long: waves of their own for the loads
     if (img_lds_bytes) {
-        return dtype == MT_BF16 ? launch_conv_img_t<__bf16>(a, max_cb, img_two, img_sets && max_cb > 2 && !img_two, img_lds_bytes, grid, s)
-                                : launch_conv_img_t<float>(a, max_cb, img_two, img_sets && max_cb > 2 && !img_two, img_lds_bytes, grid, s);
+        return dtype == MT_BF16 ? launch_conv_img_t<__bf16>(a, max_cb, img_two, img_lds_bytes, grid, s)
+                                : launch_conv_img_t<float>(a, max_cb, img_two, img_lds_bytes, grid, s);
     }
     if (dtype == MT_BF16) launch_conv_t<__bf16>(a, max_cb, quad, loaders, uniform_walk, grid, s);
     else launch_conv_t<float>(a, max_cb, quad, loaders, uniform_walk, grid, s);

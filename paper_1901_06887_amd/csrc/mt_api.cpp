@@ -117,8 +117,6 @@ struct mt_ctx {
     uint32_t no_conv_first = 0;                      // tuning/testing: images are always staged
     uint32_t first_cap = 0;                          // testing: MT_FIRST_ROWS in place of first_tile_rows()'s choice
     uint32_t conv_img_lds[MT_MAX_LAYERS]{};          // every conv of a layer index can keep its tiles' input in LDS: the largest frame in bytes, else 0
-    uint64_t conv_ragged[MT_MAX_LAYERS]{};           // channel tiles of its layers whose tiles hold several images (a tenant's last one may be partly filled)
-    bool conv_groups[MT_MAX_LAYERS]{};               // every conv of a layer index has whole groups of four k steps to a tap
     int conv_img_two[MT_MAX_LAYERS]{};               // ... and their pixels are one 16-byte chunk: 1, none is: 0 (-1: no convolution seen yet)
     uint32_t no_conv_img = 0;                        // tuning: never use that kernel
     bool conv_uniform[MT_MAX_LAYERS]{};              // every conv of a layer index has input channels in multiples of a k step, and a window of at most 64 taps
@@ -546,7 +544,7 @@ void recompute_bounds(mt_ctx* c)
         }
     }
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
-        c->has_gap[l] = 0; c->gap_chunks[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1; c->conv_ragged[l] = 0; c->conv_groups[l] = true;
+        c->has_gap[l] = 0; c->gap_chunks[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
         for (int k = 0; k < kListKinds; ++k) { c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
         c->max_fc_per64[l] = 0; c->max_fc_per64_sk[l] = 0; c->sum_nt_sk[l] = 0; c->max_big_blocks[l] = 0;
     }
@@ -601,8 +599,6 @@ void recompute_bounds(mt_ctx* c)
                 const bool chunk_pixel = L.cin * c->elem_size == 16;            // a pixel is one 16-byte chunk: two taps per k step, no padding
                 const uint64_t frame = L.row_tiles ? row_tile_frame_bytes(L, c->elem_size, unpack_row_tiling(L.row_tiles)) : 0;
                 if (c->conv_img_two[l] < 0) c->conv_img_two[l] = chunk_pixel;
-                if (L.row_tiles && unpack_row_tiling(L.row_tiles).ni > 1) c->conv_ragged[l] += nt;
-                if (L.cin % (4 * 32 / c->elem_size)) c->conv_groups[l] = false;
                 if (frame == 0 || c->conv_img_lds[l] == 0 || c->conv_img_two[l] != (int)chunk_pixel) c->conv_img_lds[l] = 0;
                 else c->conv_img_lds[l] = std::max<uint32_t>(c->conv_img_lds[l], (uint32_t)frame);
             }
@@ -653,7 +649,6 @@ bool run_split_k(const mt_ctx* c, uint64_t R)
 // How the convolutions of a layer index are launched in a run of R rows.
 struct ConvPlan {
     bool frames;        // tiles read their input from LDS frames
-    bool frame_sets;    // ... with two sets of waves to a tile, each with half of K (conv_img_kernel)
     bool split;         // tiles of 32 pixels and one channel block whose waves split K
     uint32_t first_cap; // > 0: the submitted images are read (layer index 0), in tiles of at most so many rows ...
     uint32_t first_frame; // ... whose input takes at most so many bytes of LDS
@@ -740,7 +735,6 @@ ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<Na
         split = even <= line && tiles <= kConvSplitSkew * line;
     }
     if (split) { p.split = true; p.frames = false; p.tiles = tiles; }
-    p.frame_sets = p.frames && c->conv_groups[l] && R * c->max_conv_tile_rows[l] / kConvTileRows + c->conv_ragged[l] <= c->n_cus;
     return p;
 }
 
@@ -1726,7 +1720,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             else if (conv.first_cap) TIMED(kProfConv + l, launch_conv_first(ga, c->cfg.dtype, c->first_max_ks, c->first_pool, c->first_plain, conv.first_frame, g32, s));
             else if (conv.split) TIMED(kProfConv + l, launch_conv_split(ga, c->cfg.dtype, (c->max_conv_k[l] * c->elem_size + 31) / 32, c->conv_quad[l], g32, s));
             else if (kind == 1) TIMED(kProfConv + l, launch_conv(ga, c->cfg.dtype, c->max_conv_cb[l], c->conv_quad[l],
-                                                                    conv.frames ? c->conv_img_lds[l] : 0, c->conv_img_two[l] == 1, conv.frame_sets,
+                                                                    conv.frames ? c->conv_img_lds[l] : 0, c->conv_img_two[l] == 1,
                                                                     !c->no_conv_loaders && c->min_conv_k[l] >= kConvLongK,
                                                                     c->conv_uniform[l] && !c->no_conv_uniform && (uint64_t)c->cfg.max_requests * c->S * c->elem_size < (1ull << 31), g32, s));
             else TIMED(kProfBig + l, launch_fc_big(ga, c->cfg.dtype, g32, (c->big_walk && c->min_fc_k[l] >= kBigWalkMinK) ? c->n_cus : 0, s));

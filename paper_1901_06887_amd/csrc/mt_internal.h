@@ -281,7 +281,7 @@ hipError_t launch_mfma_rate(float* out, uint32_t iters, uint32_t grid, hipStream
 hipError_t prepare_conv(uint32_t dtype);   // once per device, before the first launch_conv: lets the frame kernels ask for more than 64 KiB of LDS
 // max_cb: the widest tile of this layer index over the registered tenants, in 32-channel blocks (1..4)
 // quad: every tenant's input channels at this layer index are a multiple of four 16-byte chunks
-hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool img_sets, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s);
+hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s);
 hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, bool chunks, uint32_t grid, hipStream_t s);
 // first convolutions on the submitted images: the largest window, whether some model's max-pool is done with it and some model's rows
 // are stored themselves, and the largest frame in bytes

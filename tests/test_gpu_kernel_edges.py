@@ -185,25 +185,6 @@ def test_frame_convolutions_in_groups_of_k_steps(monkeypatch, dtype, ci, co, hw)
     check(w, "%dx%d %d->%d %s" % (h, w_, ci, co, dtype))
 
 
-# frames of at most a tile to a compute unit, two sets of waves each with half of K: an odd and an even number of groups, three and more
-# channel blocks, half-filled and full tiles, several images to a tile, a skip; and as many requests as take one set to a tile
-@pytest.mark.parametrize("rows", [1, 13, 300])
-@pytest.mark.parametrize("hw", [(7, 7), (14, 14), (3, 5), (5, 9)])
-@pytest.mark.parametrize("dtype,ci,co", [("bf16", 64, 96), ("bf16", 128, 136), ("bf16", 192, 256), ("f32", 32, 72), ("f32", 96, 128)])
-def test_frame_convolutions_with_two_sets_of_waves(monkeypatch, dtype, ci, co, hw, rows):
-    monkeypatch.setenv("MT_CONV_SPLIT_TILES", "0")
-    h, w_ = hw
-    conv = lambda a, i, o, src=0: wl.LayerSpec(wl.CONV, a, i, o, h, w_, 1, ksize=3, pad=1, src=src)  # noqa: E731
-    layers = [conv(wl.ACT_RELU, 3, ci), conv(wl.ACT_GELU, ci, co), wl.LayerSpec(wl.CONV, wl.ACT_NONE, co, co, h, w_, 1, ksize=1, pad=0),
-              conv(wl.ACT_NONE, ci, co, src=1), wl.LayerSpec(wl.ADD, wl.ACT_RELU, co, co, h, w_, src=4, src2=3),
-              wl.LayerSpec(wl.GAP, wl.ACT_NONE, co, co, h, w_), wl.LayerSpec(wl.FC, wl.ACT_NONE, co, 9)]
-    tenants = {t: wl.make_model(layers, dtype, 345, t) for t in range(3)}
-    rng = np.random.default_rng(345)
-    x = rng.standard_normal((rows, 3 * h * w_)).astype(np.float32)
-    w = wl.Workload("sets", dtype, tenants, rng.integers(0, 3, rows).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
-    check(w, "%dx%d %d->%d %s, %d rows" % (h, w_, ci, co, dtype, rows))
-
-
 # tiles whose waves split K finish on all their waves: one and two column blocks (64 hidden outputs), class counts at the edges of a
 # block and of the two, row counts at the edges of a tile, output rows that do not take 16-byte stores
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
