@@ -830,8 +830,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
 // 144 k steps, 10-12 us each, and 12 us at 288: eight barriers, the frame's zeroing and one workgroup per CU.)
 // CS > 0: every tenant's taps are whole chunks of CS k steps.  What bounds such a tile is then the rate at which its unit takes lane
 // addresses: 64 clocks for a brick gathered 32 bytes a pixel, as many for the two lanes of a pixel as for one (80 with its filters: 288 steps of one tile are 10 us).
-// So a wave's share of K is chunks, a load takes 16 bytes of a pixel in each of 2 CS neighbouring lanes, and the pieces change places in the
-// wave's part of the LDS (behind the K loop that of its sums).  One residual-net request, us: 7x7x512 13.9 -> 10.1, 14x14x256 10.4 -> 7.7,
+// So a load takes 16 bytes of a pixel in each of 2 CS neighbouring lanes, and the pieces change places in the
+// wave's part of the LDS (behind the K loop that of its sums).  Same shares of K and same sums as gathered: another order turns labels of deep nets.  One residual-net request, us: 7x7x512 13.9 -> 10.1, 14x14x256 10.4 -> 7.7,
 // 28x28x128 8.6 -> 7.1, 56x56x64 6.4 -> 5.8, the stride-2 layers 10.0 -> 8.2 / 8.4 -> 6.8 / 6.1 -> 5.9; with 4 waves (at most 24 steps) 4.6 -> 5.1, which keep the gathers.
 // (Chunks of four steps, one in flight: 11.6, 9.6, 9.0, 7.3 of the first four; eight gathered steps in flight instead of four: 15.3, 12.2, 8.7, 6.1.)
 template <typename T, uint32_t WAVES, uint32_t CS>
@@ -868,9 +868,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     if constexpr (CS > 0) {
         constexpr uint32_t PCS = 2 * CS, PXL = 64 / PCS, D = P / CS;      // pieces of a pixel, pixels of a load, chunks in flight
         static_assert(P % CS == 0 && CS * 1024 <= 4096, "a ring of whole chunks; a chunk lies in a wave's part of the LDS");
-        const uint32_t ks = L.ksize, tap_chunks = L.cin / (CS * KB), n_chunks = ks * ks * tap_chunks;
-        const uint32_t c0 = wave * n_chunks / WAVES, n = (wave + 1) * n_chunks / WAVES - c0;
-        if (n) {
+        const uint32_t ks = L.ksize, tap_chunks = L.cin / (CS * KB);
+        const uint32_t c0 = k0 / CS, n = ceil_div(k0 + cnt, CS) - c0;      // chunks with a step of the wave's share: the first and last may hold one of a neighbour's, which is left out
+        if (cnt) {
             const uint32_t piece = lane % PCS;
             gptr_t zeros = (gptr_t)a.zeros;
             // every lane works out where the window of pixel li begins (it may be outside the image) and which of its taps lie inside; the
@@ -938,7 +938,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 #pragma unroll
                 for (uint32_t q = 0; q < CS; ++q) av[q] = brick(q);
 #pragma unroll
-                for (uint32_t q = 0; q < CS; ++q) Mma<T>::run(acc, wq[d][q], av[q]);       // rows = channels, columns = pixels
+                for (uint32_t q = 0; q < CS; ++q)
+                    if ((c0 + c) * CS + q - k0 < cnt) Mma<T>::run(acc, wq[d][q], av[q]);       // rows = channels, columns = pixels
                 load_w(c + D, wq[d]);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read before the next chunk overwrites them
                 __builtin_amdgcn_sched_barrier(0);
