@@ -117,6 +117,7 @@ struct mt_ctx {
     uint32_t no_conv_first = 0;                      // tuning/testing: images are always staged
     uint32_t first_cap = 0;                          // testing: MT_FIRST_ROWS in place of first_tile_rows()'s choice
     uint32_t conv_img_lds[MT_MAX_LAYERS]{};          // every conv of a layer index can keep its tiles' input in LDS: the largest frame in bytes, else 0
+    double conv_frame_share[MT_MAX_LAYERS]{};        // largest share of a row-tiled layer's MFMAs that is neither empty pixel slots nor missing channel blocks
     int conv_img_two[MT_MAX_LAYERS]{};               // ... and their pixels are one 16-byte chunk: 1, none is: 0 (-1: no convolution seen yet)
     uint32_t no_conv_img = 0;                        // tuning: never use that kernel
     bool conv_uniform[MT_MAX_LAYERS]{};              // every conv of a layer index has input channels in multiples of a k step, and a window of at most 64 taps
@@ -290,6 +291,17 @@ uint64_t row_tile_frame_bytes(const LayerDev& L, uint32_t es, RowTiling r)
     const bool chunk_pixel = L.cin * es == 16;
     const uint32_t n_ih = (r.n_oh - 1) * L.stride + 3;
     return (uint64_t)r.ni * n_ih * (L.in_w + 2) * (L.cin * es + (chunk_pixel ? 0 : 16));
+}
+
+// Of the pixel slots and channel blocks that row tiles multiply, the share that holds some (a tile of at most half the slots multiplies half).
+double row_tile_share(const LayerDev& L)
+{
+    const RowTiling r = unpack_row_tiling(L.row_tiles);
+    const uint32_t blocks = L.N_pad / kBrickRows, wide = kTileCols / kBrickRows;
+    const uint32_t full = r.n_oh * L.out_w, px = L.rows_per_req;
+    auto slots = [](uint32_t n) { return n <= (uint32_t)kConvTileRows / 2 ? (uint32_t)kConvTileRows / 2 : (uint32_t)kConvTileRows; };
+    const double pixels = r.ni > 1 ? (double)px * r.ni / kConvTileRows : (double)px / ((r.tpi - 1) * slots(full) + slots(px - (r.tpi - 1) * full));
+    return pixels * blocks / (blocks <= 2 ? blocks : (blocks + wide - 1) / wide * wide);
 }
 
 // Row tiling of a 3x3 convolution (0: none): the most output rows per tile, or the most whole small images (a power
@@ -544,7 +556,7 @@ void recompute_bounds(mt_ctx* c)
         }
     }
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
-        c->has_gap[l] = 0; c->gap_chunks[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1;
+        c->has_gap[l] = 0; c->gap_chunks[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1; c->conv_frame_share[l] = 0.0;
         for (int k = 0; k < kListKinds; ++k) { c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
         c->max_fc_per64[l] = 0; c->max_fc_per64_sk[l] = 0; c->sum_nt_sk[l] = 0; c->max_big_blocks[l] = 0;
     }
@@ -599,6 +611,7 @@ void recompute_bounds(mt_ctx* c)
                 const bool chunk_pixel = L.cin * c->elem_size == 16;            // a pixel is one 16-byte chunk: two taps per k step, no padding
                 const uint64_t frame = L.row_tiles ? row_tile_frame_bytes(L, c->elem_size, unpack_row_tiling(L.row_tiles)) : 0;
                 if (c->conv_img_two[l] < 0) c->conv_img_two[l] = chunk_pixel;
+                if (L.row_tiles) c->conv_frame_share[l] = std::max(c->conv_frame_share[l], row_tile_share(L));
                 if (frame == 0 || c->conv_img_lds[l] == 0 || c->conv_img_two[l] != (int)chunk_pixel) c->conv_img_lds[l] = 0;
                 else c->conv_img_lds[l] = std::max<uint32_t>(c->conv_img_lds[l], (uint32_t)frame);
             }
@@ -657,18 +670,27 @@ struct ConvPlan {
 };
 
 // Convolution launches of at most so many tiles of 32 pixels and one channel block take such tiles, K split among their waves.
-// Chains of eight equal layers, split over unsplit time at 512 / 640 / 800 tiles (one tenant; the tiles of 16 waves come in rounds
-// of 256): LDS frames in bf16, 18 k steps (16x16x32) 0.94 / 1.00 / 1.08, 36 (8x8x64) 0.97 / 1.14 / 1.32, 72 (28x28x128) 1.03 / 1.38 /
-// 1.64, 144 (14x14x256) 0.96 / 1.29 / 1.58, 288 (7x7x512) 1.45 / 1.64 / 2.00, and at 256 / 320 tiles 0.73 / 1.17; in fp32 0.88 / 1.05 /
-// 1.21 (16x16x32), 0.73 / 0.93 / 1.14 (8x8x64), 0.35 / 0.47 / 0.58 (28x28x128); gathers in bf16 0.68 / 0.75 / 0.79 (9x9x40), 0.86 / 0.97 / 1.08
-// (1x1 over 14x14x256), 0.87 / 0.91 / 1.13 (7x7 over 14x14x64), in fp32 0.49 .. 0.91.
+// Chains of eight equal layers, split over unsplit time (one tenant; the tiles of 16 waves come in rounds of 256).  LDS frames in bf16 at 256 / 512 / 640
+// tiles: 18 k steps (16x16x32) 0.81 / 0.88 / 1.00, 36 (8x8x64) 0.81 / 0.91 / 1.06, 72 (28x28x128) 0.63 / 0.96 / 1.25, 144 (14x14x256) 0.52 / 0.81 / 1.06,
+// 288 (7x7x512) 0.64 / 1.29 / 1.29, and 0.94 at 320.  In fp32 at 512 / 768 / 1536 / 2048: 36 (16x16x32) 0.89 / 1.12, 27 (32x32x24, 1024) 1.14, 72 (8x8x64)
+// 0.78 / 0.97 / 1.52, 144 (28x28x128) 0.33 / 0.54 / 0.85 / 1.06.  Gathers, whole passes of three convolutions the last of which has stride 2, split and unsplit, us: bf16,
+// 36 steps 39 / 40 us at 640 tiles, 72 steps 43 / 46 at 496, 47 / 46 at 640, 144 steps 43 / 59 at 256, 58 / 60 at 400, 68 / 60 at 528; fp32, 45 steps 59 / 71 at
+// 1029, 72 steps 103 / 108 at 1032, 116 / 109 at 1544, 144 steps 127 / 151 at 1520, 221 / 186 at 3088, 288 steps 240 / 264 at 1552.  (The bf16 lines of long
+// gathers and of frames stay above the crossing: another order of the sums turns roundings, and with them close labels, of deep bf16 nets.)
+// fp32 frames are long in bytes: images of many channels leave most of a frame's tile empty.  A k step of a split tile then takes less than its share of a frame's
+// tile does where it can load whole chunks, however many tiles there are: nanoseconds of a compute unit, fitted to 8192 tiles, measured 41 against 122 (7x7x512, a share of 0.26), 47 / 57
+// (14x14x256, 0.58), 55 / 89 (9x9x160, 0.4), 58 / 65 (12x12x40, 0.75), and where the frames stay 63 / 50 (28x28x128, 0.88), 80 / 61 (20x20x72, 0.6), 80 / 40 (8x8x64, 1), 76 / 49 (16x16x32, 1).
 uint64_t conv_split_line(const mt_ctx* c, uint32_t l, bool frames)
 {
-    constexpr uint32_t kFewSteps = 24, kManySteps = 192;
+    constexpr uint32_t kFewSteps = 24, kManySteps = 192, kMostTiles = 1u << 20;        // (a launch of 16 waves a tile stays below 2^32 work items)
+    constexpr double kSplitStepNs = 35.0, kSplitTileNs = 3200.0, kFrameStepNs = 40.0;
     if (c->conv_split_tiles >= 0) return (uint64_t)c->conv_split_tiles;
     const uint32_t k_steps = (c->max_conv_k[l] * c->elem_size + 31) / 32;
-    if (!frames) return 768;
-    if (c->elem_size == 4) return 640;
+    if (!frames) return c->elem_size == 2 ? 768 : k_steps > 128 ? 1536 : 1024;
+    if (c->elem_size == 4) {
+        if (c->conv_quad[l] && k_steps > 64 && kSplitStepNs + kSplitTileNs / k_steps < kFrameStepNs / c->conv_frame_share[l]) return kMostTiles;
+        return k_steps >= 128 || (k_steps <= 64 && c->conv_frame_share[l] < 0.8) ? 1536 : k_steps > 64 ? 768 : 640;        // (12x12x40 at 1638: 0.83)
+    }
     return k_steps <= kFewSteps ? 768 : k_steps <= kManySteps ? 512 : 256;
 }
 // Where the host does not know whose the requests are, it takes them to be spread evenly, unless their all being the

@@ -492,3 +492,20 @@ def test_where_the_line_lies_for_split_convolutions():
     assert most_rows(B.MT_BF16, 8, 4, 512, 32) == 256
     assert most_rows(B.MT_BF16, 8, 4, 40, 32) == 768       # gathered: 40 channels are not whole k steps
     assert most_rows(B.MT_F32, 8, 4, 32, 32) == 640
+
+
+def test_the_line_for_long_reductions_and_frames_that_are_mostly_empty():
+    """Gathered windows by their k steps, and fp32 frames: by their k steps too, and without a line where images of many channels leave most
+    pixel slots or channel blocks of a frame's tile empty, up to what a launch holds."""
+    def split(dtype, h, w, ci, co, rows):
+        return conv_fleet(0, [(h, w, ci, co)], dtype).debug_conv_launch(0, rows, [rows])
+
+    for dtype, shape, line in ((B.MT_BF16, (8, 4, 136, 32), 768), (B.MT_BF16, (8, 4, 264, 32), 768),       # 77 and 149 steps of gathers
+                               (B.MT_F32, (8, 4, 64, 32), 768), (B.MT_F32, (8, 16, 128, 32), 384)):        # 72 and 144 steps from frames without an empty slot, one and four tiles a request
+        assert split(dtype, *shape, line)[0] and not split(dtype, *shape, line + 1)[0]
+    for h, ci in ((7, 512), (14, 256), (9, 160)):
+        on, n = split(B.MT_F32, h, h, ci, ci, 1024)
+        assert on and 0 <= n - 1024 * h * h // 32 * (ci // 32) <= ci // 32
+    rows = (1 << 20) * 32 // (49 * 16)
+    assert split(B.MT_F32, 7, 7, 512, 512, rows - 1)[0] and not split(B.MT_F32, 7, 7, 512, 512, rows + 100)[0]
+    assert split(B.MT_F32, 28, 28, 128, 128, 15)[0] and not split(B.MT_F32, 28, 28, 128, 128, 16)[0]
