@@ -1010,11 +1010,6 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 }
 
 // ---- launcher ------------------------------------------------------------
-// Waves of a tile that splits K: a wave should have a few steps to itself (a 7x7x8 window is 25 steps: 784 tiles of 16 waves,
-// one workgroup per CU, took 14.6 us, of 8 waves 8.5), a long walk is worth all 16 (1x1 over 64 channels: 4.9 us with
-// 16 waves, 4.6 with 4).
-constexpr uint32_t kSplitFewSteps = 24, kSplitSomeSteps = 64;
-
 template <typename T, bool FAST>
 static void launch_conv_lds_t(const GemmArgs& a, uint32_t max_cb, bool quad, bool loaders, uint32_t grid, hipStream_t s)
 {

@@ -63,6 +63,32 @@ struct HostTenant {
 
 struct FreeBlock { uint64_t off, len; };
 
+// What the tiles of a first convolution on the submitted images take: LDS for the images' rows and for the first layer's (with the second layer), and
+// tiles of a request.
+struct FirstNeed {
+    uint64_t frame, mid, tiles;
+    bool operator==(const FirstNeed& o) const { return frame == o.frame && mid == o.mid && tiles == o.tiles; }
+};
+
+// What the launches of the runs enqueued between two registrations assume of every model they serve.  Such a run may execute after a
+// later registration (it is queued, or was captured and is replayed): that model is served by it only if this holds for it too.
+struct PlanUse {
+    uint32_t plan = 0;
+    bool entry = false;               // layer 0 did the batcher's work
+    bool first = false;               // first convolutions read the submitted images: ...
+    bool pair = false, pool = false, plain = false, ops1 = false;      // with the convolutions behind them; some max-pool done with them; some rows stored themselves; max-pools or additions at layer index 1 have a launch
+    uint32_t max_ks = 0, pair_blocks = 0;
+    uint64_t chunk_layers = 0;        // layer indices whose split convolutions loaded whole chunks
+    std::vector<FirstNeed> most;      // the most that the models then registered take, by the rows of a tile less one ...
+    uint32_t cap = 0;                 // ... or of tiles of so many rows
+    bool same_as(const PlanUse& o) const
+    {
+        return entry == o.entry && first == o.first && pair == o.pair && pool == o.pool && plain == o.plain && ops1 == o.ops1 && max_ks == o.max_ks &&
+               pair_blocks == o.pair_blocks && chunk_layers == o.chunk_layers && most == o.most && cap == o.cap;
+    }
+};
+constexpr size_t kPlansKept = 64;
+
 struct NamedRows { uint32_t tenant, rows; };   // requests of a tenant in the submissions that named it
 
 // Device scratch of one run in flight: batch descriptors, activation buffers, logits.  A run owns
@@ -196,6 +222,11 @@ struct mt_ctx {
     hipStream_t cache_stream = nullptr;
     bool cache_pending = false;
     uint64_t n_uploads = 0, upload_bytes = 0, n_evictions = 0;
+
+    uint32_t plan = 1;                      // registrations and removals so far, and one (BatchArgs::plan)
+    PlanUse used;                           // by the runs enqueued since the last of them (`entry`, `first` and `chunk_layers`; the rest is noted by close_plan)
+    std::vector<PlanUse> plans_used;        // by those enqueued before, oldest first, each kind once (the newest of it); at most kPlansKept
+    uint32_t plans_dropped = 0;             // the newest of those no longer known
 
     // pending submissions
     std::vector<Segment> pending;
@@ -375,6 +406,18 @@ uint32_t first_out_rows(const HostTenant& t)
     return last.rows_per_req / last.out_w;
 }
 
+// The same of one model in a run whose tiles have at most `cap` rows; pair: with the second layer.
+FirstNeed first_need(const LayerDev& conv, const LayerDev& next, bool pair, uint32_t es, uint32_t cap)
+{
+    const LayerDev& out = pair || conv.first_pool ? next : conv;
+    const uint32_t h = out.rows_per_req / out.out_w, strips = first_strips(h, pair ? next.pair_rows : conv.first_rows, cap), rows = (h + strips - 1) / strips;
+    FirstNeed n{};
+    if (pair) pair_lds(conv, next, es, rows, &n.frame, &n.mid);
+    else n.frame = first_frame_bytes(conv, conv.first_pool ? &next : nullptr, es, rows);
+    n.tiles = (uint64_t)strips * ((conv.N_pad / kBrickRows + kFirstBlocks - 1) / kFirstBlocks);
+    return n;
+}
+
 // The batcher's words per layer of one tenant (see BatchArgs::facts).
 void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[kFactWords])
 {
@@ -442,7 +485,7 @@ void place_tenant(const mt_ctx* c, HostTenant& ht, uint64_t off, uint8_t* stage)
         ht.layers[l].dev.b_off = off + ht.layers[l].b_rel;
         tail->rows[l] = ht.layers[l].dev;
     }
-    tail->td = ht.dev; tail->td.registered = 1;
+    tail->td = ht.dev;
     fill_facts(c, ht, tail->facts);
 }
 
@@ -624,6 +667,60 @@ void recompute_bounds(mt_ctx* c)
     }
 }
 
+// Whether a run that was planned like `u` can serve a model registered since.
+bool covers(const mt_ctx* c, const PlanUse& u, const HostTenant& m)
+{
+    const bool images = m.dev.in_layout != kLayoutBricks;
+    if (u.entry && (images || m.n_layers < 2)) return false;
+    for (uint32_t l = 0; l < m.n_layers; ++l)
+        if (m.layers[l].dev.kind == MT_CONV2D && ((u.chunk_layers >> l) & 1) && m.layers[l].dev.cin % (4 * (16 / c->elem_size))) return false;
+    if (!u.first || !images) return true;
+    const LayerDev &conv = m.layers[0].dev, &next = m.layers[1].dev;
+    if (!conv.first_rows || !(conv.first_pool ? u.pool : u.plain) || (conv.ksize > 3 && u.max_ks <= 3)) return false;
+    if (u.pair && (!next.pair_rows || (u.pair_blocks <= 2 && next.N_pad / kBrickRows > 2))) return false;
+    if (!u.ops1 && !conv.first_pool && (next.kind == MT_MAXPOOL || next.kind == MT_ADD)) return false;
+    for (uint32_t i = 0; i < u.most.size(); ++i) {                   // any of these a run may have had
+        const FirstNeed n = first_need(conv, next, u.pair, c->elem_size, u.cap ? u.cap : i + 1), &most = u.most[i];
+        if (n.frame > most.frame || n.mid > most.mid || n.tiles > most.tiles) return false;
+    }
+    return true;
+}
+
+// A registration or a removal follows: the runs enqueued from now on are another plan's.
+void close_plan(mt_ctx* c)
+{
+    PlanUse& u = c->used;
+    if (u.entry || u.first || u.chunk_layers) {
+        u.plan = c->plan;
+        if (u.first) {
+            u.pair = c->pair_on; u.pool = c->first_pool; u.plain = c->first_plain; u.ops1 = c->has_image_ops[1];
+            u.max_ks = c->first_max_ks; u.pair_blocks = c->pair_blocks; u.cap = c->first_cap;
+            u.most.resize(u.cap ? 1 : c->first_max_rows);
+        }
+        for (const HostTenant& t : c->tenants) {
+            if (!u.first || !t.registered || t.dev.in_layout == kLayoutBricks) continue;
+            for (uint32_t i = 0; i < u.most.size(); ++i) {
+                const FirstNeed n = first_need(t.layers[0].dev, t.layers[1].dev, u.pair, c->elem_size, u.cap ? u.cap : i + 1);
+                FirstNeed& m = u.most[i];
+                m.frame = std::max(m.frame, n.frame); m.mid = std::max(m.mid, n.mid); m.tiles = std::max(m.tiles, n.tiles);
+            }
+        }
+        c->plans_used.erase(std::remove_if(c->plans_used.begin(), c->plans_used.end(), [&](const PlanUse& o) { return o.same_as(u); }), c->plans_used.end());
+        if (c->plans_used.size() == kPlansKept) { c->plans_dropped = c->plans_used.front().plan; c->plans_used.erase(c->plans_used.begin()); }
+        c->plans_used.push_back(std::move(u));
+    }
+    u = PlanUse{};
+    c->plan++;
+}
+
+// The first plan from which on every run enqueued covers a model that is about to be registered.
+uint32_t first_plan_for(const mt_ctx* c, const HostTenant& m)
+{
+    for (size_t i = c->plans_used.size(); i-- > 0;)
+        if (!covers(c, c->plans_used[i], m)) return c->plans_used[i].plan + 1;
+    return c->plans_dropped + 1;
+}
+
 // Upper bound of the number of tiles of one list over any split of R rows among tenants.
 uint64_t tile_bound(const mt_ctx* c, int kind, uint32_t l, uint64_t R, bool split_k = false, bool big_enabled = false)
 {
@@ -721,14 +818,9 @@ ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<Na
         uint64_t most = 0;
         for (const HostTenant& t : c->tenants) {
             if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
-            const LayerDev& L = t.layers[0].dev;
-            const LayerDev& last = c->pair_on ? t.layers[1].dev : L;
-            const uint32_t h = c->pair_on ? last.rows_per_req / last.out_w : first_out_rows(t), strips = first_strips(h, c->pair_on ? last.pair_rows : L.first_rows, p.first_cap), rows = (h + strips - 1) / strips;
-            uint64_t frame, mid = 0;
-            if (c->pair_on) pair_lds(L, last, c->elem_size, rows, &frame, &mid);
-            else frame = first_frame_bytes(L, L.first_pool ? &t.layers[1].dev : nullptr, c->elem_size, rows);
-            p.first_frame = std::max(p.first_frame, (uint32_t)frame); p.pair_mid = std::max(p.pair_mid, (uint32_t)mid);
-            most = std::max<uint64_t>(most, strips * ((L.N_pad / kBrickRows + kFirstBlocks - 1) / kFirstBlocks));
+            const FirstNeed n = first_need(t.layers[0].dev, t.layers[1].dev, c->pair_on, c->elem_size, p.first_cap);
+            p.first_frame = std::max(p.first_frame, (uint32_t)n.frame); p.pair_mid = std::max(p.pair_mid, (uint32_t)n.mid);
+            most = std::max(most, n.tiles);
         }
         p.tiles = R * most;
         return p;
@@ -1329,6 +1421,8 @@ mt_status mt_register_model_bn(mt_ctx* c, uint32_t tenant, const mt_layer_spec* 
         return fail(c, MT_ENOMEM, "weight arena exhausted: model needs %llu bytes, %llu of %llu in use",
                     (unsigned long long)total, (unsigned long long)c->arena_used, (unsigned long long)c->cfg.arena_bytes);
     }
+    close_plan(c);
+    ht.dev.registered = first_plan_for(c, ht); ht.dev.number = c->plan;
     ht.arena_off = off;
     for (uint32_t l = 0; l < n_layers; ++l) { ht.layers[l].dev.w_off = off + ht.layers[l].w_rel; ht.layers[l].dev.b_off = off + ht.layers[l].b_rel; }
     if (!c->host_only) {
@@ -1340,7 +1434,7 @@ mt_status mt_register_model_bn(mt_ctx* c, uint32_t tenant, const mt_layer_spec* 
             return fail(c, MT_EDEVICE, "upload of tenant %u failed: %s", tenant, hipGetErrorString(e));
         }
     }
-    ht.registered = true; ht.dev.registered = 1; ht.resident = true; ht.last_use = stamp;
+    ht.registered = true; ht.resident = true; ht.last_use = stamp;
     ht.stage = c->cache ? stage : nullptr;
     c->tenants[tenant] = ht;
     c->n_registered++;
@@ -1413,6 +1507,7 @@ mt_status mt_unregister_model(mt_ctx* c, uint32_t tenant)
         HIP_TRY(c, hide_tenant(c, tenant, nullptr, false));
         if (c->tenants[tenant].stage) (void)hipHostFree(c->tenants[tenant].stage);
     }
+    close_plan(c);
     if (c->tenants[tenant].resident) arena_free(c, c->tenants[tenant].arena_off, c->tenants[tenant].arena_len);
     c->tenants[tenant] = HostTenant{};
     c->n_registered--;
@@ -1650,13 +1745,16 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     b.M = c->d_M; b.off = c->d_off; b.tile_base = c->d_tile_base; b.big_layers = c->d_tile_base + (size_t)kListKinds * MT_MAX_LAYERS * (T + 1); b.fc_split_k = split_k;
     for (uint32_t g = 0; g < MT_MAX_LAYERS / kLayerGroup; ++g)
         b.list_mask[g] = big_enabled ? c->list_mask[g] : c->list_mask[g] & ((1u << (2 * kLayerGroup)) - 1);   // no big-tile lists to build
-    b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles;
+    b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles; b.plan = c->plan;
     if (const ConvPlan first = plan_conv(c, 0, R, named); first.first_cap) {     // its list is made apart from the others; a second convolution done with it has none
         b.first_cap = first.first_cap; b.first_pair = first.pair_mid != 0;
         b.list_mask[0] &= ~((first.pair_mid ? 3u : 1u) << kLayerGroup);
+        c->used.first = true;
     }
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) {
-        if (plan_conv(c, l, R, named).split) b.conv_split[l / 32] |= 1u << l % 32;
+        if (!plan_conv(c, l, R, named).split) continue;
+        b.conv_split[l / 32] |= 1u << l % 32;
+        if (c->conv_quad[l] && (c->max_conv_k[l] * c->elem_size + 31) / 32 > kSplitFewSteps) c->used.chunk_layers |= 1ull << l;
     }
     const OutPtrs outp{out->labels, out->probs, out->logits, out->n_classes, out->row_stride};
     b.out = outp;
@@ -1694,7 +1792,15 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     bool fuse_gather = c->any_fc_first && c->fc_first_chunked && !c->no_fused_gather && !big_possible;
     for (const Segment& sg : c->pending)
         if (((uintptr_t)sg.src & 15) || ((uint64_t)sg.row_stride * c->elem_size) % 16) fuse_gather = false;
-    const bool entry = n_segs == 1 && fuse_gather && run_entry(c, R, split_k);
+    bool entry = n_segs == 1 && fuse_gather && run_entry(c, R, split_k);
+    if (entry) {
+        // Every workgroup of fc_entry_kernel looks up for itself which tenants there are, so it goes by those registered now.  What is
+        // captured goes on to serve models registered later, which the one workgroup of the batcher can look up.
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &status) != hipSuccess) { (void)hipGetLastError(); status = hipStreamCaptureStatusNone; }
+        entry = status == hipStreamCaptureStatusNone;
+    }
+    if (entry) c->used.entry = true;
     if (entry) {                           // (the time of the whole run starts where the batcher's would)
         if (c->profiling) HIP_TRY(c, hipEventRecord(c->prof_events[2 * kProfBatcher], s));
     } else {

@@ -150,7 +150,8 @@ inline __host__ __device__ uint32_t first_frame_cols(const LayerDev& L)
 }
 
 struct TenantDev {
-    uint32_t registered;
+    uint32_t registered; // 0: no model; else the first plan that covers the model (BatchArgs::plan): a run planned before answers its rows like those of no model
+    uint32_t number;     // ... and the plan that counts it: runs planned before it was registered have a smaller one
     uint32_t n_layers;
     uint32_t in_len;     // elements of one request's input as submitted
     uint32_t n_classes;
@@ -159,6 +160,9 @@ struct TenantDev {
     uint32_t in_fill;    // elements of the staged input row incl. zero tail
     uint32_t in_layout;  // kLayoutBricks if the first layer is FC, else kLayoutRows
 };
+
+// Whether a run that was planned as `plan` serves a tenant.
+inline __host__ __device__ bool serves(uint32_t plan, uint32_t registered) { return registered - 1u < plan; }
 
 // One run of submitted rows (lives in pinned host memory, read by the batcher kernel).
 struct Segment {
@@ -188,6 +192,7 @@ struct BatchArgs {
     uint32_t elem_size;
     uint32_t fc_split_k;   // 1: FC tiles take one column block each and split K four ways
     uint32_t conv_split[(MT_MAX_LAYERS + 31) / 32];   // layer indices (bit l % 32 of word l / 32) whose convolution launch takes tiles of 32 pixels and one channel block
+    uint32_t plan;         // registrations and removals before the run was enqueued, and one: which tenants it serves (TenantDev::registered)
     uint32_t first_cap;    // > 0: layer 0's convolutions read the submitted images, in tiles of at most so many rows
     uint32_t first_pair;   // ... and the 3x3 convolutions behind them with them
     uint32_t big_enabled;  // 0: no tenant-layer is given big tiles in this run (small batches)
@@ -282,6 +287,10 @@ hipError_t prepare_conv(uint32_t dtype);   // once per device, before the first 
 // max_cb: the widest tile of this layer index over the registered tenants, in 32-channel blocks (1..4)
 // quad: every tenant's input channels at this layer index are a multiple of four 16-byte chunks
 hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s);
+// Waves of a tile that splits K: a wave should have a few steps to itself (a 7x7x8 window is 25 steps: 784 tiles of 16 waves,
+// one workgroup per CU, took 14.6 us, of 8 waves 8.5), a long walk is worth all 16 (1x1 over 64 channels: 4.9 us with
+// 16 waves, 4.6 with 4).
+constexpr uint32_t kSplitFewSteps = 24, kSplitSomeSteps = 64;
 hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps, bool chunks, uint32_t grid, hipStream_t s);
 // first convolutions on the submitted images: the largest window, whether some model's max-pool is done with it and some model's rows
 // are stored themselves, and the largest frame in bytes

@@ -388,3 +388,111 @@ def test_a_run_captured_in_a_graph_replays_to_the_same_answers(static):
         assert torch.equal(half.labels, eager.labels[: w.n_requests // 2])
     assert np.array_equal(eager.labels.cpu().numpy(), oracle_rows(w)[2])
     ctx.close()
+
+
+def _image_model(hw, ci, convs, pool=None, seed=0):
+    """convs: (window, stride, channels); pool: (window, stride, pad) behind the first of them."""
+    (h, w), layers = hw, []
+    for i, (k, stride, co) in enumerate(convs):
+        layers.append(wl.LayerSpec(wl.CONV, wl.ACT_RELU, ci, co, h, w, stride, ksize=k, pad=(k - 1) // 2))
+        (h, w), ci = layers[-1].out_hw(), co
+        if pool and i == 0:
+            layers.append(wl.LayerSpec(wl.MAXPOOL, wl.ACT_NONE, co, co, h, w, pool[1], ksize=pool[0], pad=pool[2]))
+            h, w = layers[-1].out_hw()
+    return wl.make_model(layers + [wl.LayerSpec(wl.GAP, wl.ACT_NONE, ci, ci, h, w), wl.LayerSpec(wl.FC, wl.ACT_NONE, ci, 10)], "bf16", 401, seed)
+
+
+# What is registered for the first two tenants when a run is captured, and what comes for the third one afterwards: with the same layers, which the run
+# goes on to serve, and models that it was not planned for.
+LATE = {
+    "first": ({"MT_FIRST_ROWS": "9"}, [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)]), _image_model((11, 13), 3, [(1, 1, 8), (3, 2, 16)])],
+              [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)], seed=1)],
+              [_image_model((9, 9), 5, [(3, 1, 16), (3, 2, 24)]), _image_model((4, 40), 3, [(3, 1, 16), (3, 2, 24)]), _image_model((11, 13), 3, [(7, 1, 16), (3, 2, 24)]),
+               _image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)], (3, 2, 1))]),
+    "pooled": ({"MT_FIRST_ROWS": "9"}, [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)], (3, 2, 1))] * 2,
+               [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)], (3, 2, 1), seed=1)],
+               [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)]), _image_model((11, 13), 3, [(3, 1, 136), (3, 2, 24)], (3, 2, 1)), _image_model((9, 9), 5, [(3, 1, 16)])]),
+    "pair": ({"MT_FIRST_ROWS": "9"}, [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24), (3, 2, 8)])] * 2,
+             [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24), (3, 2, 8)], seed=1)],
+             [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 128), (3, 2, 8)]), _image_model((11, 13), 3, [(3, 1, 16), (1, 1, 24), (3, 2, 8)]), _image_model((4, 40), 3, [(3, 1, 16), (3, 1, 24), (3, 2, 8)]),
+              _image_model((9, 9), 5, [(3, 1, 16), (3, 1, 24)])]),
+    "chunks": ({"MT_NO_CONV_FIRST": "1"}, [_image_model((9, 9), 3, [(1, 1, 64), (3, 1, 32)])] * 2, [_image_model((9, 9), 3, [(1, 1, 64), (3, 1, 32)], seed=1)],
+               [_image_model((9, 9), 3, [(1, 1, 8), (3, 1, 32)])]),
+    "small": ({}, [wl.make_model(wl.mlp_layers([48, 64, 10], wl.ACT_RELU), "bf16", 402, 0)] * 2, [wl.make_model(wl.mlp_layers([48, 64, 10], wl.ACT_RELU), "bf16", 402, 1)], []),
+}
+
+
+def _late_context(monkeypatch, form):
+    env, models, same, others = LATE[form]
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    ctx = mt.context_for(dict(enumerate(models + same + others)), "bf16", 64, max_tenants=3)
+    mt.register_tenants(ctx, dict(enumerate(models)))
+    rng = np.random.default_rng(403)
+    width = max(m.layers[0].in_features * max(1, m.layers[0].in_h * m.layers[0].in_w) for m in models + same + others)
+    ids = torch.from_numpy(rng.integers(0, 3, 40).astype(np.int32)).cuda()
+    return ctx, ids, torch_io.to_device(rng.standard_normal((40, -(-width // 8) * 8)).astype(np.float32), "bf16"), same, others
+
+
+def _register(ctx, m):
+    ctx.register_model(2, torch_io.specs_of(m.layers), m.weights, m.biases)
+
+
+@pytest.mark.parametrize("form", sorted(LATE))
+def test_a_captured_run_and_models_registered_after_it(monkeypatch, form):
+    """A replay serves a model registered since the capture if it has the layers of one that was there; rows of a model that the captured
+    launches were not planned for are answered like those of no model, and nobody else's answers change."""
+    ctx, ids, x, same, others = _late_context(monkeypatch, form)
+    out = torch_io.alloc_outputs(40, ctx.cfg.max_classes)
+    mt.serve(ctx, ids, x, out=out)
+    torch.cuda.synchronize()
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=s):
+        mt.serve(ctx, ids, x, out=out, stream=s)
+
+    def replay():
+        out.logits.fill_(-7); out.labels.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        return out.logits.clone(), out.labels.clone()
+
+    third = ids == 2
+    before = replay()
+    assert (before[1][third] == -1).all() and (before[0][third] == 0).all() and (before[1][~third] >= 0).all()
+    for m in others + same + others + same:
+        _register(ctx, m)
+        print(form, [(l.ksize, l.out_features) for l in m.layers], flush=True)
+        got = replay()
+        assert torch.equal(got[0][~third], before[0][~third]) and torch.equal(got[1][~third], before[1][~third])
+        eager = mt.serve(ctx, ids, x)
+        torch.cuda.synchronize()
+        assert (eager.labels >= 0).all()
+        if any(m is k for k in same):
+            assert torch.equal(got[0], eager.logits) and torch.equal(got[1], eager.labels)
+        else:
+            assert (got[1][third] == -1).all() and (got[0][third] == 0).all()
+        ctx.unregister_model(2)
+    assert all(torch.equal(a, b) for a, b in zip(replay(), before))
+    ctx.close()
+
+
+@pytest.mark.parametrize("form", sorted(LATE))
+def test_a_queued_run_and_a_model_registered_behind_it(monkeypatch, form):
+    """The same of a run that is still queued when the model is registered; of a small run, whose workgroups each look up the tenants for themselves, no model
+    registered behind it is served."""
+    ctx, ids, x, _, others = _late_context(monkeypatch, form)
+    m = others[0] if others else wl.make_model(wl.mlp_layers([48, 10], wl.ACT_RELU), "bf16", 402, 2)
+    want = mt.serve(ctx, ids, x)
+    busy = torch.zeros(1 << 26, device="cuda")
+    torch.cuda.synchronize()
+    out = torch_io.alloc_outputs(40, ctx.cfg.max_classes)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        for _ in range(200):
+            busy.add_(1)                                               # milliseconds of queued work in front of the run
+    mt.serve(ctx, ids, x, out=out, stream=s)
+    _register(ctx, m)
+    torch.cuda.synchronize()
+    assert torch.equal(out.logits, want.logits) and torch.equal(out.labels, want.labels) and (out.labels[ids == 2] == -1).all()
+    ctx.close()
