@@ -141,7 +141,7 @@ struct mt_ctx {
     uint32_t pair_blocks = 0;
     uint32_t no_conv_pair = 0;                       // tuning/testing: every convolution has a launch
     uint32_t no_conv_first = 0;                      // tuning/testing: images are always staged
-    uint32_t first_cap = 0;                          // testing: MT_FIRST_ROWS in place of first_tile_rows()'s choice
+    uint32_t first_cap = 0;                          // testing: MT_FIRST_ROWS in place of first_tile_rows()'s choice, and whatever fits takes those tiles
     uint32_t conv_img_lds[MT_MAX_LAYERS]{};          // every conv of a layer index can keep its tiles' input in LDS: the largest frame in bytes, else 0
     double conv_frame_share[MT_MAX_LAYERS]{};        // largest share of a row-tiled layer's MFMAs that is neither empty pixel slots nor missing channel blocks
     int conv_img_two[MT_MAX_LAYERS]{};               // ... and their pixels are one 16-byte chunk: 1, none is: 0 (-1: no convolution seen yet)
@@ -387,6 +387,23 @@ uint32_t choose_pair_rows(const LayerDev& L, const LayerDev& second, uint32_t es
         if (frame + 16 + mid <= kPairLdsBytes) return rows;
     }
     return 0;
+}
+
+// MFMA steps of a window of 32 pixels and 32 channels in conv_first_kernel.
+uint32_t first_steps(uint32_t ksize, uint32_t es) { return es == 2 ? (ksize * ksize + 1) / 2 : ksize * ((ksize + 1) / 2); }
+
+// Whether such a layer is at least as fast that way as on staged images, from one request to thousands.  A tile holds pixels of one image, where the tiles
+// of the staged kernels run on over the images, and a row of pixels is walked by one workgroup.  Passes over the staged ones, most requests (8192, or 2^18
+// pixels) and 64 channels unless noted: 3x3, 1x1 to 6x6 images 1.19 / 0.87 / 0.82 / 0.81 / 0.80 / 0.78 bf16 and 1.54 / 0.96 / 0.93 / 0.95 / 0.84 / 0.75 fp32, at
+// stride 2 1.18 / 1.17 / 1.10 / 1.12 / 1.03 / 1.04 and 1.54 / 1.52 / 1.30 / 1.28 / 1.20 / 1.20, 512 channels 1.44 / 1.41 / 1.21 / 1.35 / 1.04 / 0.90; from 8x8 on 0.7-1.0 all.
+// 7x7 at stride 2, 8x8 / 10x10 / 12x12 1.11 / 1.00 / 0.91 and 1.18 / 1.03 / 0.82.  Long rows and few of them, one request (and many): fp32 7x7 and 32 channels,
+// 30x260 1.16 (0.73), 20x150 1.06 (0.66), 40x130 1.05 (0.63), 48x200 0.97 (0.67), 12x120 0.94 (0.71); 3x3 and 64, 3x300 1.18 (0.90), 8x200 1.08 (0.80), 20x150 0.95; bf16
+// 7x7, 16x700 1.11 (0.79), 30x260 1.01 (0.76).
+bool first_pays(const LayerDev& L, uint32_t es)
+{
+    const uint32_t out_h = L.rows_per_req / L.out_w, row = (L.out_w + kBrickRows - 1) / kBrickRows * std::min<uint32_t>(L.N_pad / kBrickRows, kFirstBlocks) * first_steps(L.ksize, es);
+    if (L.in_h * L.in_w < 64 || (L.ksize == 7 && L.rows_per_req < (uint32_t)kBrickRows)) return false;
+    return out_h >= 48 || row <= (es == 2 ? 512u : out_h < 10 ? 59u : 112u);
 }
 
 // Most rows of such a tile (0: not even one row's input fits LDS, or the image has too many).
@@ -1046,7 +1063,7 @@ mt_status plan_model(mt_ctx* c, const mt_layer_spec* specs, uint32_t n_layers, H
         if (d.kind == MT_CONV2D && !d.pool_fill) d.row_tiles = choose_row_tiling(d, es);
     }
     // A first convolution of images with few channels can read them as submitted, and take a max-pool that is its only reader with it.
-    if (LayerDev& d = out->layers[0].dev; d.kind == MT_CONV2D && specs[0].in_features <= kFirstMaxCin && !d.pool_fill && !d.fuse_add) {
+    if (LayerDev& d = out->layers[0].dev; d.kind == MT_CONV2D && specs[0].in_features <= kFirstMaxCin && !d.pool_fill && !d.fuse_add && (c->first_cap || first_pays(d, es))) {
         const LayerDev* pool = n_layers > 1 && out->layers[1].dev.kind == MT_MAXPOOL && src_of[1] == 1 && last_use[1] == 1 ? &out->layers[1].dev : nullptr;
         d.first_rows = pool ? choose_first_rows(d, pool, es) : 0;
         d.first_pool = d.first_rows != 0;

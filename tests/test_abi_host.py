@@ -509,3 +509,32 @@ def test_the_line_for_long_reductions_and_frames_that_are_mostly_empty():
     rows = (1 << 20) * 32 // (49 * 16)
     assert split(B.MT_F32, 7, 7, 512, 512, rows - 1)[0] and not split(B.MT_F32, 7, 7, 512, 512, rows + 100)[0]
     assert split(B.MT_F32, 28, 28, 128, 128, 15)[0] and not split(B.MT_F32, 28, 28, 128, 128, 16)[0]
+
+
+def image_launches(dtype, hw, ci, convs, pool=None):
+    """Kernels of a run over one request to one model: convolutions (window, stride, channels), a max-pool (window, stride, pad) behind the first, mean, linear layer."""
+    (h, w), specs = hw, []
+    for i, (k, stride, co) in enumerate(convs):
+        specs.append(B.layer_spec(B.MT_CONV2D, B.MT_ACT_RELU, ci, co, h, w, stride, ksize=k, pad=(k - 1) // 2))
+        h, w, ci = (h - 1) // stride + 1, (w - 1) // stride + 1, co
+        if pool and i == 0:
+            specs.append(B.layer_spec(B.MT_MAXPOOL, B.MT_ACT_NONE, co, co, h, w, pool[1], ksize=pool[0], pad=pool[2]))
+            h, w = (h + 2 * pool[2] - pool[0]) // pool[1] + 1, (w + 2 * pool[2] - pool[0]) // pool[1] + 1
+    specs += [B.layer_spec(B.MT_GAP, B.MT_ACT_NONE, ci, ci, h, w), fc(ci, 10)]
+    c = host_ctx(dtype, arena=64 << 20, max_width=B.model_footprint(specs, dtype)["min_width"], max_tenants=1)
+    c.register_model(0, specs, *zeros_for(specs, dtype))
+    return c.estimate_run([1])["launches"]
+
+
+def test_which_first_convolutions_read_the_submitted_images():
+    """Where the tiles of one image waste most of what they multiply, or one request has too few of them, images are staged: one launch more."""
+    staged = lambda *a: {4: False, 5: True}[image_launches(*a)]  # noqa: E731  (batcher, convolution, mean, linear layer)
+    bf, f32 = B.MT_BF16, B.MT_F32
+    for dtype in (bf, f32):
+        for hw in ((1, 1), (7, 9), (1, 63)):
+            assert staged(dtype, hw, 3, [(3, 1, 64)]) and staged(dtype, hw, 3, [(1, 1, 8)])
+        assert not staged(dtype, (9, 9), 3, [(3, 2, 64)]) and not staged(dtype, (16, 4), 3, [(1, 1, 24)]) and not staged(dtype, (224, 224), 3, [(7, 2, 64)])
+        assert staged(dtype, (10, 12), 3, [(7, 2, 64)]) and not staged(dtype, (12, 12), 3, [(7, 2, 64)])
+    assert staged(f32, (30, 260), 3, [(7, 1, 32)]) and not staged(bf, (30, 260), 3, [(7, 1, 32)]) and not staged(f32, (48, 260), 3, [(7, 1, 32)])
+    assert staged(f32, (8, 200), 3, [(3, 1, 64)]) and not staged(f32, (20, 150), 3, [(3, 1, 64)])
+    assert staged(bf, (16, 700), 3, [(7, 1, 64)]) and not staged(bf, (16, 700), 3, [(3, 1, 64)])

@@ -443,6 +443,7 @@ def test_first_convolutions_with_infinite_filters(monkeypatch):
     """Filters that are not finite take the staged path: the same bits, undefined and infinite logits among them."""
     w = first_conv_workload("bf16", 7, (9, 10), 3, [(3, 1, 16), (7, 2, 40)], (3, 2, 1))
     w.tenants[0].weights[0][3, 1, 0, 2] = np.inf
+    monkeypatch.setenv("MT_FIRST_ROWS", "9")                         # (images as small as these are staged otherwise)
     got = []
     for off in ("0", "1"):
         monkeypatch.setenv("MT_NO_CONV_FIRST", off)
