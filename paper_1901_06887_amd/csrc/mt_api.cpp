@@ -416,6 +416,25 @@ uint32_t choose_first_rows(const LayerDev& L, const LayerDev* pool, uint32_t es)
     return first_frame_bytes(L, pool, es, rows) + first_scratch_bytes(es) + 16 <= kFirstMaxBytes ? rows : 0;
 }
 
+// Whether the max-pool behind such a layer is better done with it (in tiles of `rows` of its output) than by a launch of its own.  A wave's column of 32 outputs of the
+// convolution holds whole windows only, rows shared by two waves' windows are multiplied twice, and some waves of a tile may have no column: `more` is what
+// is multiplied over what is needed, less one.  Passes over the staged ones, 2^18 pixels and a 3x3 pool at stride 2, done with it / by itself:
+// bf16, where the columns decide, 3x3x64 images 3 / 8 / 10 / 12 / 16 / 24 / 32 / 64 / 224 wide 1.59 / 1.10 / 1.01 / 0.81 / 0.78 / 0.74 / 0.74 / 0.71 / 0.52 against 0.86 / 0.83 /
+// 0.85 / 0.80 / 0.88 / 0.86 / 0.85 / 0.87 / 0.77, 7x7x64 at stride 2, 12 / 16 / 24 / 64 wide 1.25 / 0.96 / 0.83 / 0.75 against 0.91 / 0.75 / 0.79 / 0.78.  fp32, whose multiplications take
+// eight times as long and weigh against the convolution's output that is neither written nor read: 7x7x64 at stride 2, 48 / 128 / 224 wide 1.06 / 1.18 / 0.68
+// against 0.74 / 0.80 / 0.71, 3x3x64 24 / 48 / 96 / 224 wide 0.91 / 0.73 / 0.70 / 0.42 against 0.76 / 0.78 / 0.77 / 0.85, 3x3x8 1.01 / 0.83 / 0.74 / 0.65 against 0.76 / 0.75 / 0.71 / 0.74.
+bool first_pool_pays(const LayerDev& L, const LayerDev& pool, uint32_t es, uint32_t rows)
+{
+    auto ceil_div = [](uint32_t a, uint32_t b) { return (a + b - 1) / b; };
+    const uint32_t h = pool.rows_per_req / pool.out_w, columns = ceil_div(pool.out_w, ((uint32_t)kBrickRows - pool.ksize) / pool.stride + 1);
+    if (columns * kBrickRows > 2 * L.out_w) return false;
+    if (es == 2) return true;
+    const uint32_t waves = 8 / std::min<uint32_t>(L.N_pad / kBrickRows, kFirstBlocks), parts = std::max(waves / columns, 1u);
+    const uint32_t per = ceil_div(ceil_div(h, ceil_div(h, rows)), parts), units = columns * parts;
+    const double more = (double)(columns * kBrickRows) / L.out_w * ((per - 1) * pool.stride + pool.ksize) / (per * pool.stride) * (ceil_div(units, waves) * waves) / units - 1.0;
+    return more * first_steps(L.ksize, es) <= (L.ksize == 7 ? 9.5 : 3.0) * L.N / L.N_pad;      // (the 7x7 at 224 and 48 above: 9.3 and 15.6; the 3x3x64 at 96 and 24: 2.3 and 3.3)
+}
+
 // Rows of an image that the tiles of such a layer deal out: of its output, or of the max-pool's that is done with it.
 uint32_t first_out_rows(const HostTenant& t)
 {
@@ -1066,6 +1085,7 @@ mt_status plan_model(mt_ctx* c, const mt_layer_spec* specs, uint32_t n_layers, H
     if (LayerDev& d = out->layers[0].dev; d.kind == MT_CONV2D && specs[0].in_features <= kFirstMaxCin && !d.pool_fill && !d.fuse_add && (c->first_cap || first_pays(d, es))) {
         const LayerDev* pool = n_layers > 1 && out->layers[1].dev.kind == MT_MAXPOOL && src_of[1] == 1 && last_use[1] == 1 ? &out->layers[1].dev : nullptr;
         d.first_rows = pool ? choose_first_rows(d, pool, es) : 0;
+        if (d.first_rows && !c->first_cap && !first_pool_pays(d, *pool, es, d.first_rows)) d.first_rows = 0;
         d.first_pool = d.first_rows != 0;
         if (!d.first_pool) { pool = nullptr; d.first_rows = choose_first_rows(d, nullptr, es); }
         if (d.first_rows && !pool && n_layers > 2 && d.ksize <= 3 && src_of[1] == 1 && last_use[1] == 1) {

@@ -538,3 +538,16 @@ def test_which_first_convolutions_read_the_submitted_images():
     assert staged(f32, (30, 260), 3, [(7, 1, 32)]) and not staged(bf, (30, 260), 3, [(7, 1, 32)]) and not staged(f32, (48, 260), 3, [(7, 1, 32)])
     assert staged(f32, (8, 200), 3, [(3, 1, 64)]) and not staged(f32, (20, 150), 3, [(3, 1, 64)])
     assert staged(bf, (16, 700), 3, [(7, 1, 64)]) and not staged(bf, (16, 700), 3, [(3, 1, 64)])
+
+
+def test_which_max_pools_are_done_with_the_first_convolution():
+    """Where the columns of 32 outputs are mostly empty or (fp32) the rows that two waves multiply cost more than the convolution's output takes, the pool has a launch."""
+    apart = lambda *a: {4: False, 5: True}[image_launches(*a)]  # noqa: E731
+    bf, f32 = B.MT_BF16, B.MT_F32
+    for dtype in (bf, f32):
+        for hw in ((9, 8), (300, 3), (12, 12)):
+            assert apart(dtype, hw, 3, [(3, 1, 64)], (3, 2, 1)) and apart(dtype, hw, 3, [(3, 1, 8)], (2, 2, 0))
+        assert not apart(dtype, (224, 224), 3, [(7, 2, 64)], (3, 2, 1)) and not apart(dtype, (32, 32), 3, [(3, 1, 64)], (2, 2, 0)) and not apart(dtype, (9, 32), 3, [(3, 1, 24)], (2, 2, 0))
+    for hw, conv, pool in (((16, 16), (3, 1, 64), (3, 2, 1)), ((48, 48), (7, 2, 64), (3, 2, 1)), ((128, 128), (7, 2, 64), (3, 2, 1)), ((24, 24), (3, 1, 8), (3, 1, 1))):
+        assert apart(f32, hw, 3, [conv], pool) and not apart(bf, hw, 3, [conv], pool), (hw, conv, pool)
+    assert not apart(f32, (96, 96), 3, [(3, 1, 64)], (3, 2, 1))
