@@ -375,8 +375,7 @@ void pair_lds(const LayerDev& L, const LayerDev& second, uint32_t es, uint32_t r
     *mid = (uint64_t)need * (L.out_w + 2) * (second.cin * es + 16);
 }
 
-// Most rows of such a tile: up to 128 pixels; 0: its rows are too long or too wide.  A tile computes the row above and below it once more than
-// needed, so it takes at least half as many rows as that.
+// Most rows of such a tile: up to 128 pixels; 0: its rows are too long or too wide.
 uint32_t choose_pair_rows(const LayerDev& L, const LayerDev& second, uint32_t es)
 {
     const uint32_t H = second.rows_per_req / second.out_w;
@@ -391,6 +390,28 @@ uint32_t choose_pair_rows(const LayerDev& L, const LayerDev& second, uint32_t es
 
 // MFMA steps of a window of 32 pixels and 32 channels in conv_first_kernel.
 uint32_t first_steps(uint32_t ksize, uint32_t es) { return es == 2 ? (ksize * ksize + 1) / 2 : ksize * ((ksize + 1) / 2); }
+
+// Whether the two layers are at least as fast with each other as by a launch each, from one request to thousands.  A tile (at most `rows` rows) multiplies the first layer's
+// rows above and below it once more, and pixel slots that its rows do not fill; one request has its tiles' two walks through K one behind the other, in four waves.
+// Passes over those with staged images, with each other / by a launch each, most requests (4096, or 2^18 pixels): bf16, 32 -> 64 channels at stride 2, images 4 / 6 / 8 / 10 / 12 / 16 / 32 / 64
+// wide 1.06 / 1.03 / 0.98 / 0.89 / 0.75 / 0.74 / 0.73 / 0.74 against 0.92 / 0.93 / 0.91 / 0.89 / 0.80 / 0.89 / 0.87 / 0.89, 64 -> 128 1.32 / 1.11 / 1.01 / 0.91 / 0.72 / 0.73 / 0.75 / 0.76 against 0.88 /
+// 0.85 / 0.85 / 0.83 / 0.78 / 0.86 / 0.87 / 0.85.  fp32, where multiplications decide: the steps of a tile's longest wave against those of full tiles: 24 -> 40 over 29x35 1.12 (0.91 against
+// 0.94), 64 -> 64 over 28x28 1.05 (0.92 / 0.93), 24x24 1.26 (0.99 / 0.93), 32x32 1.43 (1.06 / 0.93), 32 -> 32 over 32x32 2.0 (1.01 / 0.91), one or two rows to a tile: 64 -> 32 over 48x48 1.68 / 0.92,
+// 64 -> 128 at stride 2 over 40x40 1.80 / 0.88.  One request in fp32: 66 steps (24 -> 40) 0.94-1.08, 162 (64 -> 64) 1.05-1.27, 270 (64 -> 128) 1.26.
+bool pair_pays(const LayerDev& L, const LayerDev& second, uint32_t es, uint32_t rows)
+{
+    constexpr uint32_t kMostSteps = 72;
+    constexpr double kMostMore = 1.25;
+    const uint32_t px0 = L.rows_per_req, px1 = second.rows_per_req, h1 = px1 / second.out_w, b0 = L.N_pad / kBrickRows, b1 = second.N_pad / kBrickRows;
+    if (px1 < (es == 2 ? 24u : 32u)) return false;
+    if (es == 2) return true;
+    auto ceil_div = [](uint32_t a, uint32_t b) { return (a + b - 1) / b; };
+    const uint32_t tiles = ceil_div(h1, rows), step = ceil_div(h1, tiles), need = std::min((step - 1) * second.stride + 3, px0 / L.out_w);
+    const uint32_t units = b1 <= 2 ? 2 : 4, unit = step * second.out_w <= units / 2 * kBrickRows ? units / 2 : units;      // pixel blocks of a wave (conv_pair_kernel)
+    const uint32_t s0 = first_steps(L.ksize, es), s1 = second.k_valid * es / 32, longest = ceil_div(ceil_div(need * L.out_w, kBrickRows), 4 / b0) * s0 + unit * s1;
+    const double full = ((double)px0 * b0 * s0 + (double)px1 * b1 * s1 / (second.row_tiles ? row_tile_share(second) : 1.0)) / kBrickRows / 4;
+    return longest <= kMostSteps && tiles * longest <= kMostMore * full;
+}
 
 // Whether such a layer is at least as fast that way as on staged images, from one request to thousands.  A tile holds pixels of one image, where the tiles
 // of the staged kernels run on over the images, and a row of pixels is walked by one workgroup.  Passes over the staged ones, most requests (8192, or 2^18
@@ -1091,7 +1112,7 @@ mt_status plan_model(mt_ctx* c, const mt_layer_spec* specs, uint32_t n_layers, H
         if (d.first_rows && !pool && n_layers > 2 && d.ksize <= 3 && src_of[1] == 1 && last_use[1] == 1) {
             LayerDev& second = out->layers[1].dev;
             const uint32_t rows = second.kind == MT_CONV2D && second.ksize == 3 && !second.pool_fill && !second.fuse_add ? choose_pair_rows(d, second, es) : 0;
-            second.pair_rows = rows;
+            second.pair_rows = rows && (c->first_cap || pair_pays(d, second, es, rows)) ? rows : 0;
         }
         d.first_cin = specs[0].in_features;
     }
