@@ -2087,7 +2087,9 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
     double us = 0.0;
     uint32_t launches = 0;
     auto launch = [&](double t) { us += t + (launches ? kUsLaunchGap : 0.0); ++launches; };
-    if (fuse_gather && run_entry(c, R, split_k)) us += kUsEntry;           // done by the first layer's launch
+    // one submission, unless these are the requests that are pending in several
+    const bool one_submission = c->pending.size() <= 1 || c->pending_rows != R;
+    if (one_submission && fuse_gather && run_entry(c, R, split_k)) us += kUsEntry;           // done by the first layer's launch
     else if (spread) { launch(20.0 + 0.15 * R / 1024.0); launches += 2; }       // ranking, scan, placement
     else launch(7.0 + 1.1 * R / 1024.0);                                   // kernel trace: 7.0 us at 64 rows, 9.2 at 2048, 11.3 at 4096
 

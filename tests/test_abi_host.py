@@ -564,3 +564,19 @@ def test_which_pairs_of_convolutions_share_a_launch():
     assert paired(f32, (29, 35), 3, chain(24, 1, 40))
     for hw, c0, s, c1 in (((40, 40), 64, 1, 32), ((20, 57), 64, 1, 32), ((32, 32), 64, 1, 64), ((40, 40), 64, 2, 128), ((32, 32), 32, 1, 32), ((48, 48), 32, 2, 64), ((128, 128), 16, 1, 16)):
         assert not paired(f32, hw, 3, chain(c0, s, c1)) and paired(bf, hw, 3, chain(c0, s, c1)), (hw, c0, s, c1)
+
+
+def test_small_runs_of_several_submissions_are_estimated_with_a_batcher():
+    """Layer 0 does the batcher's work in a small run of one submission; requests that are pending in several take the batcher's launch."""
+    c = host_ctx(max_tenants=4)
+    specs = [fc(64, 64, B.MT_ACT_RELU), fc(64, 10)]
+    for t in range(4):
+        c.register_model(t, specs, *zeros_for(specs))
+    one = c.estimate_run([3, 4, 0, 0])
+    assert one["launches"] == 2
+    c.submit(0, 1 << 20, 3)
+    assert c.estimate_run([3, 4, 0, 0])["launches"] == 2 and c.estimate_run([3, 0, 0, 0])["launches"] == 2
+    c.submit(1, 1 << 21, 4)
+    several = c.estimate_run([3, 4, 0, 0])
+    assert several["launches"] == 3 and several["device_ms"] > one["device_ms"]
+    assert c.estimate_run([3, 5, 0, 0])["launches"] == 2              # not the requests that are pending

@@ -496,3 +496,20 @@ def test_a_queued_run_and_a_model_registered_behind_it(monkeypatch, form):
     torch.cuda.synchronize()
     assert torch.equal(out.logits, want.logits) and torch.equal(out.labels, want.labels) and (out.labels[ids == 2] == -1).all()
     ctx.close()
+
+
+def test_the_estimate_counts_the_launches_of_pending_submissions():
+    w = wl.c1(n_tenants=4, n_requests=64, seed=404)
+    ctx = make_context(w)
+    x = torch_io.to_device(w.inputs, w.dtype)
+    out = torch_io.alloc_outputs(64, ctx.cfg.max_classes)
+    for parts in ([(0, 20), (1, 30)], [(2, 50)]):
+        counts = [0] * ctx.cfg.max_tenants
+        for t, n in parts:
+            ctx.submit(t, x.data_ptr(), n)
+            counts[t] += n
+        est = ctx.estimate_run(counts)
+        ctx.run(torch.cuda.current_stream().cuda_stream, out.labels.data_ptr(), out.probs.data_ptr(), out.logits.data_ptr(), out.n_classes.data_ptr(), 64, ctx.cfg.max_classes)
+        torch.cuda.synchronize()
+        assert est["launches"] == ctx.stats()["last_run_launches"], parts
+    ctx.close()
