@@ -70,6 +70,9 @@ struct FirstNeed {
     bool operator==(const FirstNeed& o) const { return frame == o.frame && mid == o.mid && tiles == o.tiles; }
 };
 
+// The first two layers of models that start with a convolution which can read the submitted images (without arena offsets), and how many have them.
+struct FirstShape { LayerDev conv, next; uint32_t models; };
+
 // What the launches of the runs enqueued between two registrations assume of every model they serve.  Such a run may execute after a
 // later registration (it is queued, or was captured and is replayed): that model is served by it only if this holds for it too.
 struct PlanUse {
@@ -135,6 +138,8 @@ struct mt_ctx {
     bool first_on = false, first_pool = false, first_plain = false;
     uint32_t first_max_ks = 0, first_max_rows = 0;
     uint64_t first_max_tiles = 0;
+    std::vector<FirstShape> first_shapes;
+    uint32_t n_conv_first = 0;                       // registered models that start with a convolution
     // In every one of those models the second layer is a 3x3 convolution that can be done with the first (LayerDev::pair_rows); the widest in
     // blocks; no other model has a convolution at layer index 1 then.
     bool pair_on = false;
@@ -631,11 +636,11 @@ void recompute_bounds(mt_ctx* c)
     for (uint32_t& m : c->list_mask) m = 0;
     c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
     c->first_on = !c->no_conv_first; c->first_pool = c->first_plain = false; c->pair_on = !c->no_conv_pair;
-    c->first_max_ks = c->first_max_rows = c->pair_blocks = 0; c->first_max_tiles = 0;
+    c->first_max_ks = c->first_max_rows = c->pair_blocks = c->n_conv_first = 0; c->first_max_tiles = 0;
     for (const HostTenant& t : c->tenants) {         // (ahead of the others: it says which max-pools have a launch)
         if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
         const LayerDev& L = t.layers[0].dev;
-        c->any_conv_first = true;
+        c->any_conv_first = true; ++c->n_conv_first;
         if (!L.first_rows) { c->first_on = false; continue; }
         (L.first_pool ? c->first_pool : c->first_plain) = true;
         c->first_max_ks = std::max(c->first_max_ks, L.ksize);
@@ -724,6 +729,30 @@ void recompute_bounds(mt_ctx* c)
     }
 }
 
+// The most that the registered models take.
+FirstNeed most_first_need(const mt_ctx* c, uint32_t cap)
+{
+    FirstNeed m{};
+    for (const FirstShape& s : c->first_shapes) {
+        const FirstNeed n = first_need(s.conv, s.next, c->pair_on, c->elem_size, cap);
+        m.frame = std::max(m.frame, n.frame); m.mid = std::max(m.mid, n.mid); m.tiles = std::max(m.tiles, n.tiles);
+    }
+    return m;
+}
+
+// Keeps mt_ctx::first_shapes: a model comes (+1) or goes (-1).
+void note_first_shape(mt_ctx* c, const HostTenant& t, int by)
+{
+    if (t.dev.in_layout == kLayoutBricks || !t.layers[0].dev.first_rows) return;
+    FirstShape s{t.layers[0].dev, t.layers[1].dev, 1};
+    s.conv.w_off = s.conv.b_off = s.next.w_off = s.next.b_off = 0;
+    auto it = std::find_if(c->first_shapes.begin(), c->first_shapes.end(), [&](const FirstShape& o) {
+        return std::memcmp(&o.conv, &s.conv, sizeof s.conv) == 0 && std::memcmp(&o.next, &s.next, sizeof s.next) == 0;
+    });
+    if (it == c->first_shapes.end()) c->first_shapes.push_back(s);
+    else if ((it->models += (uint32_t)by) == 0) c->first_shapes.erase(it);
+}
+
 // Whether a run that was planned like `u` can serve a model registered since.
 bool covers(const mt_ctx* c, const PlanUse& u, const HostTenant& m)
 {
@@ -754,14 +783,7 @@ void close_plan(mt_ctx* c)
             u.max_ks = c->first_max_ks; u.pair_blocks = c->pair_blocks; u.cap = c->first_cap;
             u.most.resize(u.cap ? 1 : c->first_max_rows);
         }
-        for (const HostTenant& t : c->tenants) {
-            if (!u.first || !t.registered || t.dev.in_layout == kLayoutBricks) continue;
-            for (uint32_t i = 0; i < u.most.size(); ++i) {
-                const FirstNeed n = first_need(t.layers[0].dev, t.layers[1].dev, u.pair, c->elem_size, u.cap ? u.cap : i + 1);
-                FirstNeed& m = u.most[i];
-                m.frame = std::max(m.frame, n.frame); m.mid = std::max(m.mid, n.mid); m.tiles = std::max(m.tiles, n.tiles);
-            }
-        }
+        for (uint32_t i = 0; i < u.most.size(); ++i) u.most[i] = most_first_need(c, u.cap ? u.cap : i + 1);
         c->plans_used.erase(std::remove_if(c->plans_used.begin(), c->plans_used.end(), [&](const PlanUse& o) { return o.same_as(u); }), c->plans_used.end());
         if (c->plans_used.size() == kPlansKept) { c->plans_dropped = c->plans_used.front().plan; c->plans_used.erase(c->plans_used.begin()); }
         c->plans_used.push_back(std::move(u));
@@ -853,7 +875,7 @@ uint64_t conv_split_line(const mt_ctx* c, uint32_t l, bool frames)
 // such limit 128 requests to the first 1306 instead of 237); MLPs, CNNs and small residual nets by turns, 600 requests 246 / 214 / 206.
 constexpr uint64_t kConvSplitSkew = 2;
 
-// Most rows of a tile of the first convolutions in a run of R rows: the whole batch in about two workgroups to a compute unit.  A workgroup takes 4-9 us
+// Most rows of a tile of the first convolutions in a run of R rows to models that start with one: the whole batch in about two workgroups to a compute unit.  A workgroup takes 4-9 us
 // to find its tenant, its filters and its pixels, and more of them do not hide that from each other.  Launches in us at 512 / 1024 / 2048 / 4096
 // workgroups (as far as tiles go): 64 images 224x224 through 7x7x64 and its max-pool 48 / 56 / 60 / 92, 2048 images 32x32 (3x3x32) 33.5 / 33.8 / 33.2 /
 // 35.1, 500 of them 11.4 / 11.9 / 14.3 / 18.9, 150 fp32 29x35 (3x3x24) 14.5 / 14.2 / 17.7 / 24.6, MLPs, CNNs and residual nets by turns, 600 requests
@@ -862,24 +884,36 @@ uint32_t first_tile_rows(const mt_ctx* c, uint64_t R)
 {
     if (c->first_cap) return c->first_cap;
     const uint64_t wanted = 2 * c->n_cus;
-    return (uint32_t)std::min<uint64_t>((R * c->first_max_tiles + wanted - 1) / wanted, c->first_max_rows);
+    return (uint32_t)std::min<uint64_t>((std::max<uint64_t>(R, 1) * c->first_max_tiles + wanted - 1) / wanted, c->first_max_rows);
 }
 
 // `named`: the requests of every tenant that has any, where each submission named its tenant; null where some stand in a
-// device-resident id array
-ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<NamedRows>* named)
+// device-resident id array; captured: replays may find other models of those tenants
+ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<NamedRows>* named, bool captured = false)
 {
     ConvPlan p{};
     if (l == 0 && c->first_on) {
-        p.first_cap = first_tile_rows(c, R);
-        uint64_t most = 0;
-        for (const HostTenant& t : c->tenants) {
-            if (!t.registered || t.dev.in_layout == kLayoutBricks) continue;
-            const FirstNeed n = first_need(t.layers[0].dev, t.layers[1].dev, c->pair_on, c->elem_size, p.first_cap);
-            p.first_frame = std::max(p.first_frame, (uint32_t)n.frame); p.pair_mid = std::max(p.pair_mid, (uint32_t)n.mid);
-            most = std::max(most, n.tiles);
+        // Where the host does not know whose the requests are: all of them, or, where at most half of the models start with a convolution, their
+        // share of an even spread and at least an eighth.  512 requests to 32x32x64 layers and MLPs, 10 of them to the former, us a pass with tiles for 512 and for the
+        // share: one model of 16 61.7 / 52.6, four of eight 59.2 / 54.2; 150 of them 60.0 / 53.3 and 57.9 / 53.1; MLPs, CNNs and residual nets by turns, 600 requests 194.1 / 196.6.
+        const uint64_t models = c->n_registered, share = 2 * c->n_conv_first > models ? 8 * models : std::max<uint64_t>(8 * (uint64_t)c->n_conv_first, models);
+        uint64_t images = (R * share + 8 * models - 1) / (8 * models);
+        if (named) {
+            images = 0;
+            for (const NamedRows& r : *named) if (c->tenants[r.tenant].dev.in_layout != kLayoutBricks) images += r.rows;
         }
-        p.tiles = R * most;
+        p.first_cap = first_tile_rows(c, images);
+        const FirstNeed most = most_first_need(c, p.first_cap);
+        p.first_frame = (uint32_t)most.frame; p.pair_mid = (uint32_t)most.mid;
+        p.tiles = R * most.tiles;
+        if (named && !captured) {
+            p.tiles = 0;
+            for (const NamedRows& r : *named) {
+                const HostTenant& t = c->tenants[r.tenant];
+                if (t.dev.in_layout != kLayoutBricks) p.tiles += r.rows * first_need(t.layers[0].dev, t.layers[1].dev, c->pair_on, c->elem_size, p.first_cap).tiles;
+            }
+            p.tiles = std::max<uint64_t>(p.tiles, 1);      // (none: an empty launch, as mt_estimate_run counts them)
+        }
         return p;
     }
     p.frames = c->conv_img_lds[l] > 1 && !c->pool_fused[l] && !c->no_conv_img;
@@ -1496,6 +1530,7 @@ mt_status mt_register_model_bn(mt_ctx* c, uint32_t tenant, const mt_layer_spec* 
     ht.stage = c->cache ? stage : nullptr;
     c->tenants[tenant] = ht;
     c->n_registered++;
+    note_first_shape(c, ht, 1);
     recompute_bounds(c);
     recompute_pool_fusion(c);
     return MT_OK;
@@ -1567,6 +1602,7 @@ mt_status mt_unregister_model(mt_ctx* c, uint32_t tenant)
     }
     close_plan(c);
     if (c->tenants[tenant].resident) arena_free(c, c->tenants[tenant].arena_off, c->tenants[tenant].arena_len);
+    note_first_shape(c, c->tenants[tenant], -1);
     c->tenants[tenant] = HostTenant{};
     c->n_registered--;
     recompute_bounds(c);
@@ -1804,13 +1840,18 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     for (uint32_t g = 0; g < MT_MAX_LAYERS / kLayerGroup; ++g)
         b.list_mask[g] = big_enabled ? c->list_mask[g] : c->list_mask[g] & ((1u << (2 * kLayerGroup)) - 1);   // no big-tile lists to build
     b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles; b.plan = c->plan;
-    if (const ConvPlan first = plan_conv(c, 0, R, named); first.first_cap) {     // its list is made apart from the others; a second convolution done with it has none
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusNone; }
+    const bool captured = capture != hipStreamCaptureStatusNone;
+    ConvPlan convs[MT_MAX_LAYERS]{};
+    for (uint32_t l = 0; l < c->n_layer_slots; ++l) convs[l] = plan_conv(c, l, R, named, captured);
+    if (const ConvPlan& first = convs[0]; first.first_cap) {     // its list is made apart from the others; a second convolution done with it has none
         b.first_cap = first.first_cap; b.first_pair = first.pair_mid != 0;
         b.list_mask[0] &= ~((first.pair_mid ? 3u : 1u) << kLayerGroup);
         c->used.first = true;
     }
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) {
-        if (!plan_conv(c, l, R, named).split) continue;
+        if (!convs[l].split) continue;
         b.conv_split[l / 32] |= 1u << l % 32;
         if (c->conv_quad[l] && (c->max_conv_k[l] * c->elem_size + 31) / 32 > kSplitFewSteps) c->used.chunk_layers |= 1ull << l;
     }
@@ -1850,14 +1891,9 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     bool fuse_gather = c->any_fc_first && c->fc_first_chunked && !c->no_fused_gather && !big_possible;
     for (const Segment& sg : c->pending)
         if (((uintptr_t)sg.src & 15) || ((uint64_t)sg.row_stride * c->elem_size) % 16) fuse_gather = false;
-    bool entry = n_segs == 1 && fuse_gather && run_entry(c, R, split_k);
-    if (entry) {
-        // Every workgroup of fc_entry_kernel looks up for itself which tenants there are, so it goes by those registered now.  What is
-        // captured goes on to serve models registered later, which the one workgroup of the batcher can look up.
-        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s, &status) != hipSuccess) { (void)hipGetLastError(); status = hipStreamCaptureStatusNone; }
-        entry = status == hipStreamCaptureStatusNone;
-    }
+    // Every workgroup of fc_entry_kernel looks up for itself which tenants there are, so it goes by those registered now.  What is
+    // captured goes on to serve models registered later, which the one workgroup of the batcher can look up.
+    const bool entry = n_segs == 1 && fuse_gather && !captured && run_entry(c, R, split_k);
     if (entry) c->used.entry = true;
     if (entry) {                           // (the time of the whole run starts where the batcher's would)
         if (c->profiling) HIP_TRY(c, hipEventRecord(c->prof_events[2 * kProfBatcher], s));
@@ -1884,7 +1920,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
         // pooled activation is where the pooling layer would have written it
         if (l > 0 && c->pool_fused[l - 1]) continue;
         for (int kind = 0; kind < kListKinds; ++kind) {
-            const ConvPlan conv = kind == 1 ? plan_conv(c, l, R, named) : ConvPlan{};
+            const ConvPlan conv = kind == 1 ? convs[l] : ConvPlan{};
             const uint64_t grid = kind == 1 ? conv.tiles : tile_bound(c, kind, l, R, split_k, big_enabled);
             if (grid == 0 || (kind == 2 && (!big_enabled || grid < c->big_min_tiles))) continue;   // no big tiles possible: the batcher made none
             GemmArgs ga{};
@@ -1896,7 +1932,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             ga.layers = c->d_layers; ga.off = c->d_off; ga.M = c->d_M; ga.act = bufs; ga.arena = c->d_arena;
             ga.logits = c->d_logits; ga.S = c->S; ga.C_pad = c->C_pad; ga.zeros = c->d_zeros;
             // a launch holds fewer than 2^32 work items; cannot be exceeded by activations that fit the device's memory
-            if (grid > kMaxLaunchItems / (conv.split ? 1024 : kind == 2 || conv.first_cap ? 512 : 256))
+            if (grid > kMaxLaunchItems / (conv.split ? 1024 : kind == 2 || (conv.first_cap && c->first_pool) ? 512 : 256))
                 return fail(c, MT_EUNSUPPORTED, "layer %u: %llu tiles exceed one launch", l, (unsigned long long)grid);
             const uint32_t g32 = (uint32_t)grid;
             ga.first_cap = conv.first_cap;

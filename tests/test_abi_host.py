@@ -580,3 +580,19 @@ def test_small_runs_of_several_submissions_are_estimated_with_a_batcher():
     several = c.estimate_run([3, 4, 0, 0])
     assert several["launches"] == 3 and several["device_ms"] > one["device_ms"]
     assert c.estimate_run([3, 5, 0, 0])["launches"] == 2              # not the requests that are pending
+
+
+def test_launches_of_first_convolutions_hold_the_requests_that_have_images():
+    """Where the submissions name their tenants the launch is as large as their images' tiles, in few rows to a tile where they are few; else as large as any split may need."""
+    c = conv_fleet(3, [(32, 32, 3, 64)])
+
+    def workgroups(rows, counts=None):
+        return c.debug_conv_launch(0, rows, counts)[1]
+
+    assert workgroups(2048, [0, 2048, 0, 0]) == 1                     # an empty launch
+    assert workgroups(2048, [512, 1536, 0, 0]) == 512                  # whole images
+    assert workgroups(2048, [16, 2032, 0, 0]) == 16 * 32               # rows of images
+    assert workgroups(2048) == 2048 and workgroups(16) == 16 * 32      # any of them may be images
+    assert workgroups(512) == 512 * 4                                  # ... a quarter of them by an even spread: tiles for 128
+    c.unregister_model(1), c.unregister_model(2), c.unregister_model(3)
+    assert workgroups(512) == 512
