@@ -495,8 +495,9 @@ def test_where_the_line_lies_for_split_convolutions():
 
 
 def test_the_line_for_long_reductions_and_frames_that_are_mostly_empty():
-    """Gathered windows by their k steps, and fp32 frames: by their k steps too, and without a line where images of many channels leave most
-    pixel slots or channel blocks of a frame's tile empty, up to what a launch holds."""
+    """Gathered windows, in fp32 by their k steps and in bf16 at one line, which for long reductions lies above where both forms take the same time (another
+    order of the sums turns close labels of deep nets); fp32 frames by their k steps too, and without a line where images of many channels
+    leave most pixel slots or channel blocks of a frame's tile empty, up to what a launch holds."""
     def split(dtype, h, w, ci, co, rows):
         return conv_fleet(0, [(h, w, ci, co)], dtype).debug_conv_launch(0, rows, [rows])
 

@@ -373,11 +373,11 @@ def test_first_convolutions_on_the_submitted_images(monkeypatch, dtype, hw, ci, 
 
 
 # a first convolution and the 3x3 convolution behind it in one launch: one to four blocks of second channels, both strides of both, images of a pixel, of
-# several tiles and of rows that fill a tile badly; beside models that do not take it, which leaves both layers a launch
+# several tiles and of rows that fill a tile badly; beside models that do not take it (too many channels, a large window, a max-pool), which leaves both layers a launch
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("hw,models,rows", [
     ((1, 1), [(3, 1, 16, 1, 8)], 9), ((2, 9), [(1, 1, 32, 2, 40), (3, 2, 48, 1, 128)], 9), ((16, 16), [(3, 1, 32, 2, 64), (3, 1, 64, 1, 96), (3, 1, 16, 1, 128)], 3),
-    ((35, 29), [(3, 1, 24, 1, 40), (3, 2, 64, 2, 32)], 99), ((21, 100), [(3, 1, 16, 1, 16), (1, 2, 16, 1, 8)], 1), ((9, 11), [(3, 1, 32, 1, 40), (3, 1, 16, 1, 136), (7, 2, 16, 1, 8)], 9), ((33, 130), [(3, 1, 32, 2, 72)], 99)])
+    ((35, 29), [(3, 1, 48, 1, 40), (3, 2, 64, 2, 32)], 99), ((21, 100), [(3, 1, 16, 1, 16), (1, 2, 16, 1, 8)], 1), ((9, 11), [(3, 1, 32, 1, 40), (3, 1, 16, 1, 136), (7, 2, 16, 1, 8)], 9), ((33, 130), [(3, 1, 16, 2, 72)], 99)])
 def test_first_convolutions_with_the_ones_behind_them(monkeypatch, dtype, hw, models, rows):
     monkeypatch.setenv("MT_FIRST_ROWS", str(rows))
     monkeypatch.setenv("MT_CONV_SPLIT_TILES", "0")
@@ -401,11 +401,17 @@ def test_first_convolutions_with_the_ones_behind_them(monkeypatch, dtype, hw, mo
         w = wl.Workload("pair", dtype, tenants, ids_, wl.round_to_bf16(x) if dtype == "bf16" else x)
         what = "%s %s %s tiles of %d rows" % (dtype, hw, models, rows)
         print(what, flush=True)
-        one = check(w, what)
+        ctx = make_context(w)
+        one, launches = check(w, what, ctx), ctx.stats()["last_run_launches"]
+        ctx.close()
         monkeypatch.setenv("MT_NO_CONV_PAIR", "1")                   # two launches: the same bits in both types
-        got = gpu_run(make_context(w), w, poison=True)
+        ctx = make_context(w)
+        got = gpu_run(ctx, w, poison=True)
         monkeypatch.delenv("MT_NO_CONV_PAIR")
         assert np.array_equal(got[0], one[0]), what
+        takes = not apart and all(k <= 3 and c1 <= 128 for k, _, _, _, c1 in models)
+        assert ctx.stats()["last_run_launches"] == launches + takes, what
+        ctx.close()
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
@@ -484,4 +490,38 @@ def test_small_runs_without_a_batcher(monkeypatch, dtype, n_tenants, rows):
         ctx.close()
     for a, b in zip(got["0"], got["1"]):
         assert all(np.array_equal(u, v) for u, v in zip(a, b))
-    assert got["0n"] in (got["1n"], got["1n"] - 1) and (got["0n"] < got["1n"] or rows > 60)
+    assert got["0n"] == got["1n"] - (rows <= 256 and (n_tenants < 64 or rows <= 64))      # (64 tenants and more rows: ordinary tiles)
+
+
+# the lists of first convolutions, alone and with the ones behind them: more tenants than a wave has lanes, several steps of a list, and batches that are
+# ranked by a kernel of their own; models of one and of two tiles a request, MLPs between them
+@pytest.mark.parametrize("n_tenants,rows", [(65, 300), (300, 900), (1025, 1500), (5, 8300), (300, 8300)])
+@pytest.mark.parametrize("pair", [True, False])
+def test_lists_of_first_convolutions_of_many_tenants_and_requests(monkeypatch, n_tenants, rows, pair):
+    monkeypatch.setenv("MT_FIRST_ROWS", "5")
+    monkeypatch.setenv("MT_CONV_SPLIT_TILES", "0")                   # (another order of the sums)
+    tenants = {}
+    for t in range(n_tenants):
+        if t % 5 == 2:
+            layers = wl.mlp_layers([192, 32, 6], wl.ACT_RELU)
+        else:
+            layers = [wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3, 16, 8, 8, 1 + t % 2, ksize=3, pad=1)]
+            layers.append(wl.LayerSpec(wl.CONV, wl.ACT_RELU, 16, 8, *layers[0].out_hw(), 1, ksize=3 if pair else 1, pad=int(pair)))
+            layers.append(wl.LayerSpec(wl.CONV, wl.ACT_RELU, 8, 8, *layers[1].out_hw(), 2, ksize=3, pad=1))
+            layers += [wl.LayerSpec(wl.GAP, wl.ACT_NONE, 8, 8, *layers[2].out_hw()), wl.LayerSpec(wl.FC, wl.ACT_NONE, 8, 6)]
+        tenants[t] = wl.make_model(layers, "bf16", 390, t)
+    rng = np.random.default_rng(390)
+    w = wl.Workload("lists", "bf16", tenants, rng.integers(0, n_tenants, rows).astype(np.int32), wl.round_to_bf16(rng.standard_normal((rows, 192)).astype(np.float32)))
+    got, launches = {}, {}
+    for off in ("", "MT_NO_CONV_PAIR", "MT_NO_CONV_FIRST"):
+        if off:
+            monkeypatch.setenv(off, "1")
+        ctx = make_context(w)
+        got[off], launches[off] = gpu_run(ctx, w, poison=True), ctx.stats()["last_run_launches"]
+        assert np.array_equal(ctx.last_counts(), np.bincount(w.tenant_ids, minlength=n_tenants))
+        ctx.close()
+    assert launches["MT_NO_CONV_PAIR"] == launches[""] + pair and launches["MT_NO_CONV_FIRST"] == launches["MT_NO_CONV_PAIR"] + 1
+    for off in ("MT_NO_CONV_PAIR", "MT_NO_CONV_FIRST"):
+        assert all(np.array_equal(a, b) for a, b in zip(got[""], got[off])), off
+    pick = np.sort(rng.choice(rows, 250, replace=False))
+    compare(w, tuple(v[pick] for v in got[""]), oracle_rows(w, pick), rows=pick, what="lists")
