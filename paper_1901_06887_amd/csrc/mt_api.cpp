@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -77,7 +78,6 @@ struct FirstShape { LayerDev conv, next; uint32_t models; };
 // later registration (it is queued, or was captured and is replayed): that model is served by it only if this holds for it too.
 struct PlanUse {
     uint32_t plan = 0;
-    bool entry = false;               // layer 0 did the batcher's work
     bool first = false;               // first convolutions read the submitted images: ...
     bool pair = false, pool = false, plain = false, ops1 = false;      // with the convolutions behind them; some max-pool done with them; some rows stored themselves; max-pools or additions at layer index 1 have a launch
     uint32_t max_ks = 0, pair_blocks = 0;
@@ -86,7 +86,7 @@ struct PlanUse {
     uint32_t cap = 0;                 // ... or of tiles of so many rows
     bool same_as(const PlanUse& o) const
     {
-        return entry == o.entry && first == o.first && pair == o.pair && pool == o.pool && plain == o.plain && ops1 == o.ops1 && max_ks == o.max_ks &&
+        return first == o.first && pair == o.pair && pool == o.pool && plain == o.plain && ops1 == o.ops1 && max_ks == o.max_ks &&
                pair_blocks == o.pair_blocks && chunk_layers == o.chunk_layers && most == o.most && cap == o.cap;
     }
 };
@@ -229,7 +229,7 @@ struct mt_ctx {
     uint64_t n_uploads = 0, upload_bytes = 0, n_evictions = 0;
 
     uint32_t plan = 1;                      // registrations and removals so far, and one (BatchArgs::plan)
-    PlanUse used;                           // by the runs enqueued since the last of them (`entry`, `first` and `chunk_layers`; the rest is noted by close_plan)
+    PlanUse used;                           // by the runs enqueued since the last of them (`first` and `chunk_layers`; the rest is noted by close_plan)
     std::vector<PlanUse> plans_used;        // by those enqueued before, oldest first, each kind once (the newest of it); at most kPlansKept
     uint32_t plans_dropped = 0;             // the newest of those no longer known
 
@@ -757,7 +757,6 @@ void note_first_shape(mt_ctx* c, const HostTenant& t, int by)
 bool covers(const mt_ctx* c, const PlanUse& u, const HostTenant& m)
 {
     const bool images = m.dev.in_layout != kLayoutBricks;
-    if (u.entry && (images || m.n_layers < 2)) return false;
     for (uint32_t l = 0; l < m.n_layers; ++l)
         if (m.layers[l].dev.kind == MT_CONV2D && ((u.chunk_layers >> l) & 1) && m.layers[l].dev.cin % (4 * (16 / c->elem_size))) return false;
     if (!u.first || !images) return true;
@@ -776,7 +775,7 @@ bool covers(const mt_ctx* c, const PlanUse& u, const HostTenant& m)
 void close_plan(mt_ctx* c)
 {
     PlanUse& u = c->used;
-    if (u.entry || u.first || u.chunk_layers) {
+    if (u.first || u.chunk_layers) try {
         u.plan = c->plan;
         if (u.first) {
             u.pair = c->pair_on; u.pool = c->first_pool; u.plain = c->first_plain; u.ops1 = c->has_image_ops[1];
@@ -787,6 +786,9 @@ void close_plan(mt_ctx* c)
         c->plans_used.erase(std::remove_if(c->plans_used.begin(), c->plans_used.end(), [&](const PlanUse& o) { return o.same_as(u); }), c->plans_used.end());
         if (c->plans_used.size() == kPlansKept) { c->plans_dropped = c->plans_used.front().plan; c->plans_used.erase(c->plans_used.begin()); }
         c->plans_used.push_back(std::move(u));
+    } catch (const std::bad_alloc&) {                // nothing registered from now on is served by an earlier run
+        c->plans_used.clear();
+        c->plans_dropped = c->plan;
     }
     u = PlanUse{};
     c->plan++;
@@ -1285,6 +1287,7 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
     c->S = round_up(cfg->max_width, kWidthAlign);
     c->C_pad = round_up(cfg->max_classes, 4);
     c->named.reserve(cfg->max_tenants);
+    c->first_shapes.reserve(cfg->max_tenants);
     c->named_at.assign(cfg->max_tenants, 0);
     c->P_cap = round_up(cfg->max_requests, kBrickRows) + kBrickRows * std::min(cfg->max_tenants, cfg->max_requests);
     if (const char* e = getenv("MT_FC_SPLIT_K")) c->fc_split_k = atoi(e) != 0;
@@ -1894,7 +1897,6 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     // Every workgroup of fc_entry_kernel looks up for itself which tenants there are, so it goes by those registered now.  What is
     // captured goes on to serve models registered later, which the one workgroup of the batcher can look up.
     const bool entry = n_segs == 1 && fuse_gather && !captured && run_entry(c, R, split_k);
-    if (entry) c->used.entry = true;
     if (entry) {                           // (the time of the whole run starts where the batcher's would)
         if (c->profiling) HIP_TRY(c, hipEventRecord(c->prof_events[2 * kProfBatcher], s));
     } else {
