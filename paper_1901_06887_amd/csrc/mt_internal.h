@@ -35,7 +35,8 @@ constexpr int kBigMinCols = 192;
 // A layer index is served with big tiles only when its qualifying tenants make at least so many.  bf16: a round of one per compute unit takes
 // less than the streaming tiles of as many rows and columns do, and so do two with the second nearly empty (models of 2048-2048-classes, whole passes with
 // big tiles from 256 / from 512 on: 4 tenants, 16384 rows, 1000 classes 377 / 447 us, 500 classes 295 / 363, 200 classes 261 / 317; 3 tenants, 8192 rows, 264 hidden tiles
-// 252 / 260; from 64 on 312; 8 tenants, 32768 rows through 4096-1024-4096-1000 1022 / 1451).  fp32 tiles of both kinds run at the MFMA rate: a nearly empty round loses (264 tiles: 846 -> 1199 us).
+// 252 / 260; from 64 on 312; 8 tenants, 32768 rows through 4096-1024-4096-1000 1022 / 1451; 16384 rows through 8192-1024-1024-200, whose layer 0 is staged for it, 1 / 2 / 4 tenants 629 / 597,
+// 660 / 676, 668 / 713).  fp32 tiles of both kinds run at the MFMA rate: a nearly empty round loses (264 tiles: 846 -> 1199 us).
 constexpr int kBigMinTiles = 256, kBigMinTilesF32 = 512;
 constexpr double kRidgeFlopsPerByte = 312.0;   // dense bf16 MFMA peak over HBM bandwidth (2.5 PFLOP/s / 8 TB/s)
 constexpr int kBigMinBatch = 8192;  // runs with fewer rows are latency/HBM bound as a whole: no big tiles

@@ -81,12 +81,12 @@ def split_warm_cold(trace_csv: str, kernel: str) -> str:
 
 
 def launches(trace_csv: str) -> str:
-    """Median duration of every launch of a run: from one segmentation kernel to the next."""
+    """Median duration of every launch of a run: from one segmentation kernel (or first layer with the segmentation in it) to the next."""
     rows = sorted(csv.DictReader(open(trace_csv)), key=lambda r: int(r["Start_Timestamp"]))
     runs = []
     for r in rows:
         name = short_name(r["Kernel_Name"])
-        if "rank_kernel" in name or ("batcher_kernel" in name and not (runs and "rank_kernel" in runs[-1][-1][0])):
+        if "rank_kernel" in name or "fc_entry_kernel" in name or ("batcher_kernel" in name and not (runs and "rank_kernel" in runs[-1][-1][0])):
             runs.append([])
         if runs and "mt::" in name:
             runs[-1].append((name, (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3, r))
