@@ -156,12 +156,11 @@ mt_status mt_destroy(mt_ctx* ctx);
  *   biases[l]:  HOST fp32 [N] or [C_out]; NULL means zeros.
  * Weights are copied and repacked into the arena before the call returns; the caller
  * keeps ownership of its buffers.  Nothing is allocated when the call fails.
- * A run is planned for the models registered when mt_run is called.  Where one executes later
- * (queued behind other work, or captured in a graph and replayed), rows of a model registered
- * since are answered like those of a tenant without a model (label -1) unless the run's plan
- * covers that model; a captured run's plan covers models with the layers of one that was
- * registered at the capture (and finite weights, like it), so a tenant's model can be replaced
- * by one with other weights.
+ * A run serves the models registered when mt_run is called; rows of one registered since, while
+ * the run is still queued, are answered like those of a tenant without a model (label -1).  A run
+ * that was captured in a graph goes on, when it is replayed, to serve models registered since that
+ * its launches cover: those with the layers of one that was registered at the capture (and finite
+ * weights, like it), so a tenant's model can be replaced by one with other weights.
  * Errors: MT_EINVAL, MT_EEXIST, MT_EUNSUPPORTED (kind/act/geometry outside the closed
  * set, dims that do not chain, more than MT_MAX_LAYERS layers, widths beyond
  * max_width / max_classes), MT_ENOMEM (arena full), MT_EDEVICE. */

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(kBatchThreads) void rank_kernel(BatchArgs a)
             a.row_src[r] = (const uint8_t*)sg.src + (size_t)(r - sg.row_begin) * sg.row_stride * a.elem_size;
             t = sg.ids ? sg.ids[r - sg.row_begin] : sg.tenant;
         }
-        if (t < 0 || (uint32_t)t >= T || !serves(a.plan, a.tenants[t].registered)) t = -1;
+        if (t < 0 || (uint32_t)t >= T || !serves(a, a.tenants[t])) t = -1;
         a.row_tenant[r] = t;
     }
     uint64_t peers = __ballot(t >= 0);
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
     uint4 fq[kPre];
 #pragma unroll
     for (uint32_t i = 0; i < kPre; ++i) fq[i] = one_wave ? load_fact(w + i * kWaves, lane) : load_fact(w, lane * kPre + i);
-    for (uint32_t t = tid; t < Tp; t += kBatchThreads) regl[t] = t < T && serves(a.plan, a.tenants[t].registered);
+    for (uint32_t t = tid; t < Tp; t += kBatchThreads) regl[t] = t < T && serves(a, a.tenants[t]);
     for (uint32_t i = tid; i < nw * Tp; i += kBatchThreads) hist[i] = PRE ? a.hist_g[i] : 0;
     if (tid == 0) big_l = 0;
     __syncthreads();
@@ -428,7 +428,8 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
             const uint32_t t = t0 + lane, M = one_wave ? Mt1 : t < T ? Ml[t] : 0;
             const uint4 f = load_fact(0, t);
             const uint32_t rows = a.first_pair ? load_fact(1, t).w : f.w;
-            const uint32_t n = f.x >> 31 && M ? M * first_strips(rows & 0xffffu, rows >> 16, a.first_cap) * ceil_div(f.x & 0x7fffffffu, kFirstBlocks) : 0;
+            // (a replay during a registration may find the tenant and not yet its facts)
+            const uint32_t n = f.x >> 31 && rows >> 16 && M ? M * first_strips(rows & 0xffffu, rows >> 16, a.first_cap) * ceil_div(f.x & 0x7fffffffu, kFirstBlocks) : 0;
             const uint32_t incl = wave_inclusive_scan(n);
             if (t < T) base[t] = run + incl - n;
             run += __builtin_amdgcn_readlane(incl, 63);

@@ -559,8 +559,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         return f.x >> 31 ? 0 : ((M + (1u << sh) - 1) >> sh) * groups;
     };
     const uint4 f0 = fact(0);
-    // (every workgroup looks for itself: only what was registered when the run was enqueued, which no registration since can change)
-    const uint64_t registered = __ballot(lane < n_tenants && serves(b.plan, b.tenants[lane].number));
+    // (every workgroup looks for itself: a run that is not captured serves what was registered when it was enqueued, which no registration since can change)
+    const uint64_t registered = __ballot(lane < n_tenants && serves(b, b.tenants[lane]));
     uint64_t has[NIT];                                        // the rows of this lane's tenant
     uint32_t M = 0;
 #pragma unroll

@@ -74,8 +74,8 @@ struct FirstNeed {
 // The first two layers of models that start with a convolution which can read the submitted images (without arena offsets), and how many have them.
 struct FirstShape { LayerDev conv, next; uint32_t models; };
 
-// What the launches of the runs enqueued between two registrations assume of every model they serve.  Such a run may execute after a
-// later registration (it is queued, or was captured and is replayed): that model is served by it only if this holds for it too.
+// What the launches of the runs captured between two registrations assume of every model they serve.  Replayed after a later registration,
+// such a run serves that model only if this holds for it too.
 struct PlanUse {
     uint32_t plan = 0;
     bool first = false;               // first convolutions read the submitted images: ...
@@ -229,8 +229,8 @@ struct mt_ctx {
     uint64_t n_uploads = 0, upload_bytes = 0, n_evictions = 0;
 
     uint32_t plan = 1;                      // registrations and removals so far, and one (BatchArgs::plan)
-    PlanUse used;                           // by the runs enqueued since the last of them (`first` and `chunk_layers`; the rest is noted by close_plan)
-    std::vector<PlanUse> plans_used;        // by those enqueued before, oldest first, each kind once (the newest of it); at most kPlansKept
+    PlanUse used;                           // by the runs captured since the last of them (`first` and `chunk_layers`; the rest is noted by close_plan)
+    std::vector<PlanUse> plans_used;        // by those captured before, oldest first, each kind once (the newest of it); at most kPlansKept
     uint32_t plans_dropped = 0;             // the newest of those no longer known
 
     // pending submissions
@@ -771,7 +771,7 @@ bool covers(const mt_ctx* c, const PlanUse& u, const HostTenant& m)
     return true;
 }
 
-// A registration or a removal follows: the runs enqueued from now on are another plan's.
+// A registration or a removal follows: the runs from now on are another plan's.
 void close_plan(mt_ctx* c)
 {
     PlanUse& u = c->used;
@@ -786,7 +786,7 @@ void close_plan(mt_ctx* c)
         c->plans_used.erase(std::remove_if(c->plans_used.begin(), c->plans_used.end(), [&](const PlanUse& o) { return o.same_as(u); }), c->plans_used.end());
         if (c->plans_used.size() == kPlansKept) { c->plans_dropped = c->plans_used.front().plan; c->plans_used.erase(c->plans_used.begin()); }
         c->plans_used.push_back(std::move(u));
-    } catch (const std::bad_alloc&) {                // nothing registered from now on is served by an earlier run
+    } catch (const std::bad_alloc&) {                // nothing registered from now on is served by a run captured before
         c->plans_used.clear();
         c->plans_dropped = c->plan;
     }
@@ -794,7 +794,7 @@ void close_plan(mt_ctx* c)
     c->plan++;
 }
 
-// The first plan from which on every run enqueued covers a model that is about to be registered.
+// The first plan from which on every captured run covers a model that is about to be registered.
 uint32_t first_plan_for(const mt_ctx* c, const HostTenant& m)
 {
     for (size_t i = c->plans_used.size(); i-- > 0;)
@@ -1517,7 +1517,7 @@ mt_status mt_register_model_bn(mt_ctx* c, uint32_t tenant, const mt_layer_spec* 
                     (unsigned long long)total, (unsigned long long)c->arena_used, (unsigned long long)c->cfg.arena_bytes);
     }
     close_plan(c);
-    ht.dev.registered = first_plan_for(c, ht); ht.dev.number = c->plan;
+    ht.dev.registered = c->plan; ht.dev.covered = first_plan_for(c, ht);
     ht.arena_off = off;
     for (uint32_t l = 0; l < n_layers; ++l) { ht.layers[l].dev.w_off = off + ht.layers[l].w_rel; ht.layers[l].dev.b_off = off + ht.layers[l].b_rel; }
     if (!c->host_only) {
@@ -1842,21 +1842,21 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     b.M = c->d_M; b.off = c->d_off; b.tile_base = c->d_tile_base; b.big_layers = c->d_tile_base + (size_t)kListKinds * MT_MAX_LAYERS * (T + 1); b.fc_split_k = split_k;
     for (uint32_t g = 0; g < MT_MAX_LAYERS / kLayerGroup; ++g)
         b.list_mask[g] = big_enabled ? c->list_mask[g] : c->list_mask[g] & ((1u << (2 * kLayerGroup)) - 1);   // no big-tile lists to build
-    b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles; b.plan = c->plan;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusNone; }
     const bool captured = capture != hipStreamCaptureStatusNone;
+    b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles; b.plan = c->plan; b.captured = captured;
     ConvPlan convs[MT_MAX_LAYERS]{};
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) convs[l] = plan_conv(c, l, R, named, captured);
     if (const ConvPlan& first = convs[0]; first.first_cap) {     // its list is made apart from the others; a second convolution done with it has none
         b.first_cap = first.first_cap; b.first_pair = first.pair_mid != 0;
         b.list_mask[0] &= ~((first.pair_mid ? 3u : 1u) << kLayerGroup);
-        c->used.first = true;
+        if (captured) c->used.first = true;
     }
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) {
         if (!convs[l].split) continue;
         b.conv_split[l / 32] |= 1u << l % 32;
-        if (c->conv_quad[l] && (c->max_conv_k[l] * c->elem_size + 31) / 32 > kSplitFewSteps) c->used.chunk_layers |= 1ull << l;
+        if (captured && c->conv_quad[l] && (c->max_conv_k[l] * c->elem_size + 31) / 32 > kSplitFewSteps) c->used.chunk_layers |= 1ull << l;
     }
     const OutPtrs outp{out->labels, out->probs, out->logits, out->n_classes, out->row_stride};
     b.out = outp;

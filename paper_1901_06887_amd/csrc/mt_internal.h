@@ -151,8 +151,9 @@ inline __host__ __device__ uint32_t first_frame_cols(const LayerDev& L)
 }
 
 struct TenantDev {
-    uint32_t registered; // 0: no model; else the first plan that covers the model (BatchArgs::plan): a run planned before answers its rows like those of no model
-    uint32_t number;     // ... and the plan that counts it: runs planned before it was registered have a smaller one
+    // 0: no model; else the first plan that the model was registered for (BatchArgs::plan), and the first one whose launches cover it: a run planned
+    // before answers its rows like those of no model, a captured one by `covered`
+    uint32_t registered, covered;
     uint32_t n_layers;
     uint32_t in_len;     // elements of one request's input as submitted
     uint32_t n_classes;
@@ -161,9 +162,6 @@ struct TenantDev {
     uint32_t in_fill;    // elements of the staged input row incl. zero tail
     uint32_t in_layout;  // kLayoutBricks if the first layer is FC, else kLayoutRows
 };
-
-// Whether a run that was planned as `plan` serves a tenant.
-inline __host__ __device__ bool serves(uint32_t plan, uint32_t registered) { return registered - 1u < plan; }
 
 // One run of submitted rows (lives in pinned host memory, read by the batcher kernel).
 struct Segment {
@@ -193,7 +191,8 @@ struct BatchArgs {
     uint32_t elem_size;
     uint32_t fc_split_k;   // 1: FC tiles take one column block each and split K four ways
     uint32_t conv_split[(MT_MAX_LAYERS + 31) / 32];   // layer indices (bit l % 32 of word l / 32) whose convolution launch takes tiles of 32 pixels and one channel block
-    uint32_t plan;         // registrations and removals before the run was enqueued, and one: which tenants it serves (TenantDev::registered)
+    uint32_t plan;         // registrations and removals before the run was enqueued, and one: which tenants it serves (`serves`)
+    uint32_t captured;     // ... by TenantDev::covered
     uint32_t first_cap;    // > 0: layer 0's convolutions read the submitted images, in tiles of at most so many rows
     uint32_t first_pair;   // ... and the 3x3 convolutions behind them with them
     uint32_t big_enabled;  // 0: no tenant-layer is given big tiles in this run (small batches)
@@ -226,6 +225,9 @@ struct BatchArgs {
     uint32_t list_mask[MT_MAX_LAYERS / kLayerGroup];   // per group of layer indices: bit kind*kLayerGroup + l%kLayerGroup set if any registered model can have such tiles at layer l
     OutPtrs out;           // rejected rows are answered here (label -1, zero rows)
 };
+
+// Whether the run serves a tenant.
+inline __host__ __device__ bool serves(const BatchArgs& a, const TenantDev& t) { return (a.captured ? t.covered : t.registered) - 1u < a.plan; }
 
 // The run's activation buffers; a layer names the ones it reads and writes (LayerDev::in_buf ...).
 struct ActBufs { void* p[kActBuffers]; };

@@ -479,10 +479,9 @@ def test_a_captured_run_and_models_registered_after_it(monkeypatch, form):
 
 @pytest.mark.parametrize("form", sorted(LATE))
 def test_a_queued_run_and_a_model_registered_behind_it(monkeypatch, form):
-    """The same of a run that is still queued when the model is registered; of a small run, whose workgroups each look up the tenants for themselves, no model
-    registered behind it is served."""
+    """A run that is still queued when a model is registered serves those that were there when it was enqueued."""
     ctx, ids, x, _, others = _late_context(monkeypatch, form)
-    m = others[0] if others else wl.make_model(wl.mlp_layers([48, 10], wl.ACT_RELU), "bf16", 402, 2)
+    m = others[0] if others else wl.make_model(wl.mlp_layers([48, 10], wl.ACT_RELU), "bf16", 402, 2)      # (one layer: finished in the first launch)
     want = mt.serve(ctx, ids, x)
     busy = torch.zeros(1 << 26, device="cuda")
     torch.cuda.synchronize()
