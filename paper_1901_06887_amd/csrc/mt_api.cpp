@@ -408,7 +408,7 @@ bool pair_pays(const LayerDev& L, const LayerDev& second, uint32_t es, uint32_t 
     constexpr uint32_t kMostSteps = 72;
     constexpr double kMostMore = 1.25;
     const uint32_t px0 = L.rows_per_req, px1 = second.rows_per_req, h1 = px1 / second.out_w, b0 = L.N_pad / kBrickRows, b1 = second.N_pad / kBrickRows;
-    if (px1 < (es == 2 ? 24u : 32u)) return false;
+    if (px1 < (es == 4 ? 32u : b0 > 1 ? 24u : 16u)) return false;      // (few requests gain by small tiles too: 16 -> 32 over 8x8, one and 24 of them 0.81 / 0.79 against 0.98 / 0.90)
     if (es == 2) return true;
     auto ceil_div = [](uint32_t a, uint32_t b) { return (a + b - 1) / b; };
     const uint32_t tiles = ceil_div(h1, rows), step = ceil_div(h1, tiles), need = std::min((step - 1) * second.stride + 3, px0 / L.out_w);

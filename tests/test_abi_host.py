@@ -555,13 +555,14 @@ def test_which_max_pools_are_done_with_the_first_convolution():
 
 
 def test_which_pairs_of_convolutions_share_a_launch():
-    """A tile of both takes at least 24 pixels of the second one; in fp32 the rows computed twice, the slots left empty and the walk of a single request limit it too."""
+    """A tile of both takes at least 16 pixels of the second one, of two blocks of first channels 24; in fp32 32, and there the
+    rows computed twice, the slots left empty and the walk of a single request limit it too."""
     paired = lambda *a: {5: True, 6: False}[image_launches(*a)]  # noqa: E731  (batcher, convolutions, mean, linear layer)
     chain = lambda c0, s, c1: [(3, 1, c0), (3, s, c1), (3, 2, 16)]  # noqa: E731
     bf, f32 = B.MT_BF16, B.MT_F32
     for c0, c1 in ((32, 64), (64, 128), (16, 16)):
         assert paired(bf, (32, 32), 3, chain(c0, 2, c1)) and paired(bf, (10, 10), 3, chain(c0, 2, c1)) and paired(bf, (9, 9), 3, chain(c0, 1, c1))
-        assert not paired(bf, (8, 9), 3, chain(c0, 2, c1))
+        assert paired(bf, (8, 9), 3, chain(c0, 2, c1)) == (c0 <= 32) and not paired(bf, (9, 9), 3, [(3, 2, c0), (3, 2, c1), (3, 1, 16)])
     assert paired(f32, (29, 35), 3, chain(24, 1, 40))
     for hw, c0, s, c1 in (((40, 40), 64, 1, 32), ((20, 57), 64, 1, 32), ((32, 32), 64, 1, 64), ((40, 40), 64, 2, 128), ((32, 32), 32, 1, 32), ((48, 48), 32, 2, 64), ((128, 128), 16, 1, 16)):
         assert not paired(f32, hw, 3, chain(c0, s, c1)) and paired(bf, hw, 3, chain(c0, s, c1)), (hw, c0, s, c1)
