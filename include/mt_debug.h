@@ -64,8 +64,8 @@ uint32_t mt_debug_big_tile_walk(uint32_t in_features);
  * rows are held in LDS: *rows_per_tile output rows of one image per tile, or, if *images_per_tile > 1, that many
  * whole images of *rows_per_tile rows each; *tiles_per_image tiles cover an image; *frame_bytes is the LDS the
  * input rows of a tile take.  Returns 0 (and writes zeros) if the layer's tiles are runs of 128 output pixels
- * gathered tap by tap.  (Where every model that starts with a convolution takes images of at most four channels, those first
- * layers are served from the submitted images instead, in tiles chosen per run: mt_debug_conv_launch.)  Pure function of its arguments; needs no context and no device; NULL outputs are skipped. */
+ * gathered tap by tap.  (First layers of images with at most four channels are mostly served from the submitted images instead, in
+ * tiles chosen per run: mt_debug_conv_launch.)  Pure function of its arguments; needs no context and no device; NULL outputs are skipped. */
 int mt_debug_conv_row_tiling(uint32_t in_h, uint32_t in_w, uint32_t in_channels, uint32_t ksize, uint32_t stride, uint32_t elem_size,
                              uint32_t* rows_per_tile, uint32_t* images_per_tile, uint32_t* tiles_per_image, uint64_t* frame_bytes);
 
