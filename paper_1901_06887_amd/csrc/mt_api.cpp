@@ -78,6 +78,8 @@ struct FirstShape { LayerDev conv, next; uint32_t models; };
 // such a run serves that model only if this holds for it too.
 struct PlanUse {
     uint32_t plan = 0;
+    bool any = false;                 // there was one
+    uint32_t act_buffers = 0, layer_slots = 0;      // activation buffers and layer indices that it has
     bool first = false;               // first convolutions read the submitted images: ...
     bool pair = false, pool = false, plain = false, ops1 = false;      // with the convolutions behind them; some max-pool done with them; some rows stored themselves; max-pools or additions at layer index 1 have a launch
     uint32_t max_ks = 0, pair_blocks = 0;
@@ -86,7 +88,7 @@ struct PlanUse {
     uint32_t cap = 0;                 // ... or of tiles of so many rows
     bool same_as(const PlanUse& o) const
     {
-        return first == o.first && pair == o.pair && pool == o.pool && plain == o.plain && ops1 == o.ops1 && max_ks == o.max_ks &&
+        return act_buffers == o.act_buffers && layer_slots == o.layer_slots && first == o.first && pair == o.pair && pool == o.pool && plain == o.plain && ops1 == o.ops1 && max_ks == o.max_ks &&
                pair_blocks == o.pair_blocks && chunk_layers == o.chunk_layers && most == o.most && cap == o.cap;
     }
 };
@@ -229,7 +231,7 @@ struct mt_ctx {
     uint64_t n_uploads = 0, upload_bytes = 0, n_evictions = 0;
 
     uint32_t plan = 1;                      // registrations and removals so far, and one (BatchArgs::plan)
-    PlanUse used;                           // by the runs captured since the last of them (`first` and `chunk_layers`; the rest is noted by close_plan)
+    PlanUse used;                           // by the runs captured since the last of them (`any`, `act_buffers`, `first` and `chunk_layers`; the rest is noted by close_plan)
     std::vector<PlanUse> plans_used;        // by those captured before, oldest first, each kind once (the newest of it); at most kPlansKept
     uint32_t plans_dropped = 0;             // the newest of those no longer known
 
@@ -757,6 +759,7 @@ void note_first_shape(mt_ctx* c, const HostTenant& t, int by)
 bool covers(const mt_ctx* c, const PlanUse& u, const HostTenant& m)
 {
     const bool images = m.dev.in_layout != kLayoutBricks;
+    if (m.act_buffers > u.act_buffers || m.n_layers > u.layer_slots) return false;
     for (uint32_t l = 0; l < m.n_layers; ++l)
         if (m.layers[l].dev.kind == MT_CONV2D && ((u.chunk_layers >> l) & 1) && m.layers[l].dev.cin % (4 * (16 / c->elem_size))) return false;
     if (!u.first || !images) return true;
@@ -775,8 +778,8 @@ bool covers(const mt_ctx* c, const PlanUse& u, const HostTenant& m)
 void close_plan(mt_ctx* c)
 {
     PlanUse& u = c->used;
-    if (u.first || u.chunk_layers) try {
-        u.plan = c->plan;
+    if (u.any) try {
+        u.plan = c->plan; u.layer_slots = c->n_layer_slots;
         if (u.first) {
             u.pair = c->pair_on; u.pool = c->first_pool; u.plain = c->first_plain; u.ops1 = c->has_image_ops[1];
             u.max_ks = c->first_max_ks; u.pair_blocks = c->pair_blocks; u.cap = c->first_cap;
@@ -1846,6 +1849,10 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusNone; }
     const bool captured = capture != hipStreamCaptureStatusNone;
     b.big_enabled = big_enabled; b.big_min_tiles = c->big_min_tiles; b.plan = c->plan; b.captured = captured;
+    if (captured) {
+        c->used.act_buffers = c->used.any ? std::min(c->used.act_buffers, c->act_buffers) : c->act_buffers;
+        c->used.any = true;
+    }
     ConvPlan convs[MT_MAX_LAYERS]{};
     for (uint32_t l = 0; l < c->n_layer_slots; ++l) convs[l] = plan_conv(c, l, R, named, captured);
     if (const ConvPlan& first = convs[0]; first.first_cap) {     // its list is made apart from the others; a second convolution done with it has none

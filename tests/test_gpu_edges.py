@@ -402,13 +402,19 @@ def _image_model(hw, ci, convs, pool=None, seed=0):
     return wl.make_model(layers + [wl.LayerSpec(wl.GAP, wl.ACT_NONE, ci, ci, h, w), wl.LayerSpec(wl.FC, wl.ACT_NONE, ci, 10)], "bf16", 401, seed)
 
 
+def _skip_model():
+    """Three convolutions and an addition of the first one's output: a third activation buffer."""
+    conv = [wl.LayerSpec(wl.CONV, wl.ACT_RELU, 3 if i == 0 else 16, 16, 11, 13, 1, ksize=3, pad=1) for i in range(3)]
+    return wl.make_model(conv + [wl.LayerSpec(wl.ADD, wl.ACT_RELU, 16, 16, 11, 13, src2=1), wl.LayerSpec(wl.GAP, wl.ACT_NONE, 16, 16, 11, 13), wl.LayerSpec(wl.FC, wl.ACT_NONE, 16, 10)], "bf16", 404, 0)
+
+
 # What is registered for the first two tenants when a run is captured, and what comes for the third one afterwards: with the same layers, which the run
 # goes on to serve, and models that it was not planned for.
 LATE = {
     "first": ({"MT_FIRST_ROWS": "9"}, [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)]), _image_model((11, 13), 3, [(1, 1, 8), (3, 2, 16)])],
               [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)], seed=1)],
               [_image_model((9, 9), 5, [(3, 1, 16), (3, 2, 24)]), _image_model((4, 40), 3, [(3, 1, 16), (3, 2, 24)]), _image_model((11, 13), 3, [(7, 1, 16), (3, 2, 24)]),
-               _image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)], (3, 2, 1))]),
+               _image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)], (3, 2, 1)), _image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24), (3, 1, 8)]), _skip_model()]),
     "pooled": ({"MT_FIRST_ROWS": "9"}, [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)], (3, 2, 1))] * 2,
                [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)], (3, 2, 1), seed=1)],
                [_image_model((11, 13), 3, [(3, 1, 16), (3, 2, 24)]), _image_model((11, 13), 3, [(3, 1, 136), (3, 2, 24)], (3, 2, 1)), _image_model((9, 9), 5, [(3, 1, 16)])]),
@@ -418,7 +424,8 @@ LATE = {
               _image_model((9, 9), 5, [(3, 1, 16), (3, 1, 24)])]),
     "chunks": ({"MT_NO_CONV_FIRST": "1"}, [_image_model((9, 9), 3, [(1, 1, 64), (3, 1, 32)])] * 2, [_image_model((9, 9), 3, [(1, 1, 64), (3, 1, 32)], seed=1)],
                [_image_model((9, 9), 3, [(1, 1, 8), (3, 1, 32)])]),
-    "small": ({}, [wl.make_model(wl.mlp_layers([48, 64, 10], wl.ACT_RELU), "bf16", 402, 0)] * 2, [wl.make_model(wl.mlp_layers([48, 64, 10], wl.ACT_RELU), "bf16", 402, 1)], []),
+    "small": ({}, [wl.make_model(wl.mlp_layers([48, 64, 10], wl.ACT_RELU), "bf16", 402, 0)] * 2, [wl.make_model(wl.mlp_layers([48, 64, 10], wl.ACT_RELU), "bf16", 402, 1)],
+              [wl.make_model(wl.mlp_layers([48, 64, 32, 10], wl.ACT_RELU), "bf16", 402, 2)]),
 }
 
 
@@ -481,7 +488,7 @@ def test_a_captured_run_and_models_registered_after_it(monkeypatch, form):
 def test_a_queued_run_and_a_model_registered_behind_it(monkeypatch, form):
     """A run that is still queued when a model is registered serves those that were there when it was enqueued."""
     ctx, ids, x, _, others = _late_context(monkeypatch, form)
-    m = others[0] if others else wl.make_model(wl.mlp_layers([48, 10], wl.ACT_RELU), "bf16", 402, 2)      # (one layer: finished in the first launch)
+    m = wl.make_model(wl.mlp_layers([48, 10], wl.ACT_RELU), "bf16", 402, 3) if form == "small" else others[0]      # (one layer: finished in the first launch)
     want = mt.serve(ctx, ids, x)
     busy = torch.zeros(1 << 26, device="cuda")
     torch.cuda.synchronize()
