@@ -188,6 +188,7 @@ __device__ __forceinline__ void conv_wave(const GemmArgs& a, const LayerDev& L, 
     }
 }
 
+constexpr uint32_t kFewTenants = 32;      // whose facts are fetched ahead of a tile's lookup where more would cost a workgroup per compute unit
 // MAXCB bounds the channel blocks of any tile in the launch: narrow layers get a kernel with
 // few registers and many resident waves, which is what hides the latency of their short K loops.
 template <typename T, int MAXCB>
@@ -197,17 +198,17 @@ __global__ __launch_bounds__(256) void conv_kernel(GemmArgs a)
     __shared__ __attribute__((aligned(16))) uint8_t unit_scratch[4 * unit_scratch_bytes<T>()];
     const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint8_t* scratch = unit_scratch + wave * unit_scratch_bytes<T>();
-    TileOwner<256> lookup;
-    lookup.fetch(a.tile_base, a.T);
+    __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes(1, kFewTenants)];
+    TileLookup<256, 1, kFewTenants> lookup;
+    lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     uint32_t idx;
     if (!logical_tile(n_tiles, &idx)) return;
-    const uint32_t t = lookup.owner(a.T, idx, owner_part);   // uniform: the tenant's facts come through scalar loads
-    const LayerDev L = a.layers[t * MT_MAX_LAYERS + a.layer];
-    const uint32_t seg0 = a.off[t];
-    const uint32_t local = idx - a.tile_base[t];
+    LayerDev L;
+    uint32_t t, Mt, seg0, local;
+    lookup.find(a, idx, owner_part, facts, &t, &L, &Mt, &seg0, &local);
     // (a row-tiled layer's list counts more tiles than its pixels fill: those beyond the last pixel have nothing to do)
-    const uint32_t rows_total = a.M[t] * L.rows_per_req, mt_ = ceil_div(a.M[t] * conv_tile_rows(L.rows_per_req, L.row_tiles), kConvTileRows);
+    const uint32_t rows_total = Mt * L.rows_per_req, mt_ = ceil_div(Mt * conv_tile_rows(L.rows_per_req, L.row_tiles), kConvTileRows);
     const uint32_t nb0 = (local / mt_) * (kTileCols / kBrickRows);
     const uint32_t ncb = min((uint32_t)(kTileCols / kBrickRows), L.N_pad / kBrickRows - nb0);
     // no barrier below: the waves are independent; wave w takes row blocks w, w+4, ... of the tile
@@ -274,17 +275,17 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
     const uint32_t tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
     const uint32_t wave_all = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave_all % 4;
     const bool loader = !PW || wave_all >= 4, worker = !PW || wave_all < 4;     // who issues the loads, who multiplies
-    TileOwner<256 * (1 + PW)> lookup;
-    lookup.fetch(a.tile_base, a.T);
+    TileLookup<256 * (1 + PW), 1, sizeof(T) == 2 ? 64 : 0> lookup;      // (fp32 tiles take several times as long: 328 of them 56.0 -> 57.3 us)
+    lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     uint32_t idx;
     if (!logical_tile(n_tiles, &idx)) return;
-    const uint32_t t = lookup.owner(a.T, idx, owner_part);   // uniform: the tenant's facts come through scalar loads
-    const LayerDev L = a.layers[t * MT_MAX_LAYERS + a.layer];
-    const uint32_t seg0 = a.off[t];
-    const uint32_t local = idx - a.tile_base[t];
+    LayerDev L;
+    uint32_t t, Mt, seg0, local;
+    static_assert(kStageBytes >= ahead_bytes(), "the last stage is first written behind a barrier");
+    lookup.find(a, idx, owner_part, lds + (NS - 1) * kStageBytes, &t, &L, &Mt, &seg0, &local);
     const uint32_t rpr = L.rows_per_req;
-    const uint32_t rows_total = a.M[t] * rpr, mt_ = ceil_div(a.M[t] * conv_tile_rows(rpr, L.row_tiles), kConvTileRows);
+    const uint32_t rows_total = Mt * rpr, mt_ = ceil_div(Mt * conv_tile_rows(rpr, L.row_tiles), kConvTileRows);
     const uint32_t m0 = (local % mt_) * kConvTileRows;
     if (m0 >= rows_total) return;                             // a row-tiled layer's list counts more tiles than its pixels fill
     const uint32_t nb0 = (local / mt_) * (kTileCols / kBrickRows);
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
     u32x4 in_desc{};
     int32_t lane_off[NPX];
     uint32_t taps_lo[NPX], taps_hi[NPX];
-    if constexpr (FAST) in_desc = buffer_descriptor((const T*)act_of(a.act, L.in_buf) + (size_t)seg0 * a.S, a.M[t] * a.S * (uint32_t)sizeof(T));
+    if constexpr (FAST) in_desc = buffer_descriptor((const T*)act_of(a.act, L.in_buf) + (size_t)seg0 * a.S, Mt * a.S * (uint32_t)sizeof(T));
 #pragma unroll
     for (uint32_t i = 0; i < NPX; ++i) {
         const uint32_t gm = m0 + wave * kBrickRows + (QUAD ? (lane >> 2) + 16 * i : (lane >> 1));
@@ -578,18 +579,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     extern __shared__ __attribute__((aligned(16))) uint8_t img[];
     __shared__ uint32_t owner_part[4];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
-    TileOwner<256> lookup;
-    lookup.fetch(a.tile_base, a.T);
+    __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes(1, kFewTenants)];
+    TileLookup<256, 1, kFewTenants> lookup;
+    lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     // the frame starts as zeros (its border, rows past the image, sub-images past the tenant's last request);
     // written while the tile list is on its way, published by the barrier of the lookup
     for (uint32_t q = tid * 16; q < a.img_lds; q += 256 * 16) *(u32x4*)(img + q) = u32x4{0, 0, 0, 0};
     uint32_t idx;
     if (!logical_tile(n_tiles, &idx)) return;
-    const uint32_t t = lookup.owner(a.T, idx, owner_part);   // uniform: the tenant's facts come through scalar loads
-    const LayerDev L = a.layers[t * MT_MAX_LAYERS + a.layer];
-    const uint32_t seg0 = a.off[t], Mt = a.M[t];
-    const uint32_t local = idx - a.tile_base[t];
+    LayerDev L;
+    uint32_t t, Mt, seg0, local;
+    lookup.find(a, idx, owner_part, facts, &t, &L, &Mt, &seg0, &local);
     const uint32_t rpr = L.rows_per_req;
     const RowTiling rt = unpack_row_tiling(L.row_tiles);     // every tenant of such a launch has one
     const uint32_t mt_ = ceil_div(Mt * conv_tile_rows(rpr, L.row_tiles), kConvTileRows);
@@ -842,15 +843,15 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     __shared__ __attribute__((aligned(16))) uint8_t red[WAVES * 4096];
     __shared__ uint32_t owner_part[WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
-    TileOwner<THREADS> lookup;
-    lookup.fetch(a.tile_base, a.T);
+    __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes()];
+    TileLookup<THREADS> lookup;
+    lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     uint32_t idx;
     if (!logical_tile(n_tiles, &idx)) return;
-    const uint32_t t = lookup.owner(a.T, idx, owner_part);   // uniform: the tenant's facts come through scalar loads
-    const LayerDev L = a.layers[t * MT_MAX_LAYERS + a.layer];
-    const uint32_t seg0 = a.off[t], Mt = a.M[t];
-    const uint32_t local = idx - a.tile_base[t];
+    LayerDev L;
+    uint32_t t, Mt, seg0, local;
+    lookup.find(a, idx, owner_part, facts, &t, &L, &Mt, &seg0, &local);
     const uint32_t rpr = L.rows_per_req, rows_total = Mt * rpr;
     const uint32_t mt_ = ceil_div(rows_total, kBrickRows), nb = local / mt_, m0 = (local - nb * mt_) * kBrickRows;
     const uint32_t nKB = L.K / KB, nKBv = ceil_div(L.k_valid, KB);

@@ -216,6 +216,7 @@ struct BatchArgs {
     // The batcher turns hist_g into prefixes over the groups, and a third kernel places the rows.
     uint32_t n_rank_groups; uint32_t* hist_g;
     const void** row_src;  // [R] device address of each submitted row's input
+    const void** packed_src;   // [P] ... of each packed row's (real rows only); null in runs whose scratch has no room for it
     int32_t* pos_of;       // [R] packed position of each submitted row, -1 if rejected
     int32_t* perm;         // [P] packed position -> submission index, -1 for padding rows
     uint32_t* M;           // [T]
@@ -233,7 +234,7 @@ inline __host__ __device__ bool serves(const BatchArgs& a, const TenantDev& t) {
 struct ActBufs { void* p[kActBuffers]; };
 
 struct GatherArgs {
-    const void* const* row_src; uint32_t P;      // P = upper bound of packed rows (multiple of 32)
+    const void* const* row_src; const void* const* packed_src; uint32_t P;      // P = upper bound of packed rows (multiple of 32)
     const TenantDev* tenants; const LayerDev* layers; const int32_t* perm;
     const uint32_t* off; const uint32_t* M; uint32_t T;
     void* act; uint32_t S; uint32_t elem_size;
@@ -251,7 +252,7 @@ struct GemmArgs {
     uint32_t first_cap;           // launch of first convolutions on the submitted images: most rows of a tile
     // FC layer 0 can read the submitted rows itself (16-byte aligned rows whose length is a
     // whole number of 16-byte chunks), which saves the staging pass:
-    uint32_t gather; const int32_t* perm; const void* const* row_src;
+    uint32_t gather; const int32_t* perm; const void* const* row_src; const void* const* packed_src;
     // a last layer whose classes all lie inside one tile finishes its rows itself (softmax, argmax,
     // outputs): at most fuse_head_max classes (32: one column block; 128: a whole tile of four, not
     // in runs whose tiles are single column blocks); out_vec_ok: output rows take 16-byte stores

@@ -525,3 +525,26 @@ def test_lists_of_first_convolutions_of_many_tenants_and_requests(monkeypatch, n
         assert all(np.array_equal(a, b) for a, b in zip(got[""], got[off])), off
     pick = np.sort(rng.choice(rows, 250, replace=False))
     compare(w, tuple(v[pick] for v in got[""]), oracle_rows(w, pick), rows=pick, what="lists")
+
+
+# a tile finds its tenant's facts in LDS with up to 32 or 64 tenants, by loads of its own beyond: the first, the last and a middle one of them, few requests
+# (tiles that split K) and many, against the oracle and, to the bit, against a context of so many tenants that every kernel takes the other way
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_tenants", [3, 32, 33, 64, 65])
+@pytest.mark.parametrize("rows", [5, 300])
+def test_facts_of_few_and_many_tenants(dtype, n_tenants, rows):
+    hosts = [0, n_tenants // 2, n_tenants - 1]
+    layers = [wl.resnet18_layers(hw=24, widths=(16, 32, 64, 72), classes=10), wl.cnn_layers(hw=24, chans=(3, 32, 64, 128), strides=(1, 1, 2)),
+              wl.mlp_layers([24 * 24 * 3, 200, 72, 7], wl.ACT_RELU)]
+    models = [wl.make_model(m, dtype, 380, i) for i, m in enumerate(layers)]
+    rng = np.random.default_rng(380)
+    x = rng.standard_normal((rows, 24 * 24 * 3)).astype(np.float32)
+    at = rng.integers(0, 3, rows)
+    at[:3] = [0, 1, 2]
+    gpu = []
+    for ids, n in ((hosts, n_tenants), ([5, 100, 299], 300)):
+        w = wl.Workload("facts", dtype, {t: models[i] for i, t in enumerate(ids)}, np.asarray(ids, np.int32)[at], wl.round_to_bf16(x) if dtype == "bf16" else x)
+        ctx = make_context(w, max_tenants=n)
+        gpu.append(gpu_run(ctx, w, poison=True))
+    compare(w, gpu[1], oracle_rows(w), what="%d tenants, %d rows" % (n_tenants, rows), deep=dtype == "bf16")
+    assert all(np.array_equal(a, b) for a, b in zip(*gpu))
