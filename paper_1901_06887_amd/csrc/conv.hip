@@ -474,6 +474,23 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
     f32x4 bias_q[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias + nbase + 8 * g + 4 * lh);   // bias is padded to N_pad
+    // (what an addition done here adds likewise; fp32 tiles with four pixel blocks to a wave have no registers for it)
+    constexpr bool EARLY = sizeof(T) == 2 || RBW == 2;
+    const uint32_t nvalid = min((uint32_t)kBrickRows, L.N - min(L.N, nbase));
+    T* out[RBW];
+    Residual<T> residual[RBW];
+#pragma unroll
+    for (uint32_t r = 0; r < RBW; ++r) {
+        const uint32_t m = m0 + (wr * RBW + r) * kBrickRows + li;
+        uint32_t req, pix;
+        divmod_uniform(m, rpr, &req, &pix);
+        const size_t at = (size_t)(seg0 + req) * a.S + (size_t)pix * L.N + nbase;
+        out[r] = m < rows_total ? (T*)act_of(a.act, L.out_buf) + at : nullptr;
+        if (EARLY && L.fuse_add) {
+            const T* other = (const T*)act_of(a.act, L.in2_buf);
+            residual[r].fetch(m < rows_total ? other + at : nullptr, other + (size_t)seg0 * a.S, lh, nvalid);
+        }
+    }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     static_assert(NS * kStageBytes >= 4 * unit_scratch_bytes<T>(), "store scratch aliases the ring");
     if (!worker) return;
@@ -532,13 +549,6 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
     }
 #pragma unroll
     for (uint32_t r = 0; r < RBW; ++r) {
-        const uint32_t m = m0 + (wr * RBW + r) * kBrickRows + li;
-        T* out = nullptr;
-        if (m < rows_total) {
-            uint32_t req, pix;
-            divmod_uniform(m, rpr, &req, &pix);
-            out = (T*)act_of(a.act, L.out_buf) + (size_t)(seg0 + req) * a.S + (size_t)pix * L.N + nbase;
-        }
         f32x4 y[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -547,10 +557,11 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
         }
         __builtin_amdgcn_sched_barrier(0);
         activate_block<4>(y, L.act);
-        const uint32_t nvalid = min((uint32_t)kBrickRows, L.N - nbase);
-        if (L.fuse_add)
-            add_residual<T>(y, out ? (const T*)act_of(a.act, L.in2_buf) + (out - (T*)act_of(a.act, L.out_buf)) : nullptr, lh, nvalid, L.fuse_add - 1);
-        store_unit_nhwc<T>(y, out, nvalid, a.store_through, scratch);
+        if (L.fuse_add) {
+            if constexpr (EARLY) residual[r].add(y, L.fuse_add - 1);
+            else add_residual<T>(y, out[r] ? (const T*)act_of(a.act, L.in2_buf) + (out[r] - (T*)act_of(a.act, L.out_buf)) : nullptr, lh, nvalid, L.fuse_add - 1);
+        }
+        store_unit_nhwc<T>(y, out[r], nvalid, a.store_through, scratch);
     }
 }
 
@@ -580,7 +591,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     __shared__ uint32_t owner_part[4];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
     __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes(1, kFewTenants)];
-    TileLookup<256, 1, kFewTenants> lookup;
+    TileLookup<256, 1, NCB == 1 ? 0 : kFewTenants> lookup;       // (64 registers)
     lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     // the frame starts as zeros (its border, rows past the image, sub-images past the tenant's last request);
@@ -786,8 +797,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
         else if (half) k_loop(half_blocks);
         else k_loop(all_blocks);
     }
+    // Where this lane's pixels go.  What an addition done here adds to them is asked for together with the bias, in front of the barrier, not unit by unit
+    // behind it (fp32 tiles of four pixel blocks have no registers for that; asked for while the frame is filled, bf16 ones have none either).  64 images, 56x56x64 with an addition 31.7 -> 29.4 us, 28x28x128 26.5 -> 25.4, 14x14x256 27.2 -> 26.2,
+    // 7x7x512 27.4 -> 27.5, the 1x1 projections (conv_lds_kernel) 12.4 / 11.6 / 12.5 -> 11.6 / 10.4 / 11.4; one image, K split: 13 launches 0.2-0.6 us each.
+    constexpr bool EARLY = RBW == 2 || (sizeof(T) == 2 && RBW == 4);
+    const uint32_t nbase = (nb0 + (active ? wc : 0)) * kBrickRows, nvalid = min((uint32_t)kBrickRows, L.N - min(L.N, nbase));
+    T* out[RBW];
+    Residual<T> residual[RBW];
+    auto locate = [&](uint32_t r) -> const T* {                    // (the other operand's place)
+        uint32_t i, pl;
+        divmod_uniform((wr * RBW + r) * kBrickRows + li, spi, &i, &pl);
+        const size_t at = (size_t)(seg0 + req0 + i) * a.S + (size_t)(oh_first * ow_n + pl) * L.N + nbase;
+        const bool there = pl < px_t && req0 + i < Mt;
+        out[r] = there ? (T*)act_of(a.act, L.out_buf) + at : nullptr;
+        return there ? (const T*)act_of(a.act, L.in2_buf) + at : nullptr;
+    };
+    if constexpr (EARLY) {
+#pragma unroll
+        for (uint32_t r = 0; r < RBW; ++r) {
+            const T* other = locate(r);
+            if (L.fuse_add) residual[r].fetch(other, (const T*)act_of(a.act, L.in2_buf) + (size_t)seg0 * a.S, lh, nvalid);
+        }
+    }
     const float* bias = (const float*)(a.arena + L.b_off);
-    const uint32_t nbase = (nb0 + (active ? wc : 0)) * kBrickRows;
     f32x4 bias_q[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias + nbase + 8 * g + 4 * lh);   // bias is padded to N_pad
@@ -796,11 +828,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     uint8_t* scratch = img + wave * unit_scratch_bytes<T>();
 #pragma unroll
     for (uint32_t r = 0; r < RBW; ++r) {
-        uint32_t i, pl;
-        divmod_uniform((wr * RBW + r) * kBrickRows + li, spi, &i, &pl);
-        T* out = nullptr;
-        if (pl < px_t && req0 + i < Mt)
-            out = (T*)act_of(a.act, L.out_buf) + (size_t)(seg0 + req0 + i) * a.S + (size_t)(oh_first * ow_n + pl) * L.N + nbase;
         f32x4 y[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -809,10 +836,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
         }
         __builtin_amdgcn_sched_barrier(0);
         activate_block<4>(y, L.act);
-        const uint32_t nvalid = min((uint32_t)kBrickRows, L.N - nbase);
-        if (L.fuse_add)
-            add_residual<T>(y, out ? (const T*)act_of(a.act, L.in2_buf) + (out - (T*)act_of(a.act, L.out_buf)) : nullptr, lh, nvalid, L.fuse_add - 1);
-        store_unit_nhwc<T>(y, out, nvalid, a.store_through, scratch);
+        const T* other = EARLY ? nullptr : locate(r);
+        if (L.fuse_add) {
+            if constexpr (EARLY) residual[r].add(y, L.fuse_add - 1);
+            else add_residual<T>(y, other, lh, nvalid, L.fuse_add - 1);
+        }
+        store_unit_nhwc<T>(y, out[r], nvalid, a.store_through, scratch);
     }
 }
 
@@ -985,22 +1014,22 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     // thread (g = wave, lane) of the first four waves: channels 8g + 4 lh + {0..3} of pixel li
     const uint32_t g = wave & 3, nbase = nb * kBrickRows, ch0 = 8 * g + 4 * lh;
     const f32x4 bias = *(const f32x4*)((const float*)(a.arena + L.b_off) + nbase + ch0);   // bias is padded to N_pad
+    const size_t to = at + (size_t)pix * L.N + nbase + ch0;
+    typename Residual<T>::vec skip{};                              // asked for in front of the barrier, not behind it
+    const bool mine = wave < 4 && row_ok && ch0 < L.N - nbase;     // channel counts are multiples of 8: a run of four exists whole or not at all
+    if (L.fuse_add && mine) skip = *(const typename Residual<T>::vec*)((const T*)act_of(a.act, L.in2_buf) + to);
 #pragma unroll
     for (uint32_t q = 0; q < 4; ++q)
         *(f32x4*)(red + wave * 4096 + q * 1024 + lane * 16) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
     __syncthreads();
-    if (wave >= 4 || !row_ok || ch0 >= L.N - nbase) return;        // channel counts are multiples of 8: a run of four exists whole or not at all
+    if (!mine) return;
     f32x4 y[1] = {bias};
 #pragma unroll
     for (uint32_t w = 0; w < WAVES; ++w) y[0] += *(const f32x4*)(red + w * 4096 + g * 1024 + lane * 16);
-    const size_t to = at + (size_t)pix * L.N + nbase + ch0;
     activate_block<1>(y, L.act);
     if (L.fuse_add) {                                              // see add_residual: rounded first, as the addition would have read it
-        T sv[4];
-        const T* skip = (const T*)act_of(a.act, L.in2_buf) + to;
-        if constexpr (sizeof(T) == 2) *(uint64_t*)sv = *(const uint64_t*)skip; else *(u32x4*)sv = *(const u32x4*)skip;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[0][e] = (float)(T)y[0][e] + (float)sv[e];
+        for (int e = 0; e < 4; ++e) y[0][e] = (float)(T)y[0][e] + (float)skip[e];
         activate_block<1>(y, L.fuse_add - 1);
     }
     T o[4];

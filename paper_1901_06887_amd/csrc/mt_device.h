@@ -217,6 +217,30 @@ __device__ __forceinline__ void add_residual(f32x4 (&y)[4], const T* skip, uint3
     activate_block<4>(y, act);
 }
 
+// The same in two parts: the other operand is asked for long before the sums are there, as a memory trip per unit (1.5-2 thousand clocks) at the end of a tile
+// has nothing to hide behind.  Lanes and channels that do not exist read some that do (`any`: the tenant's first row).
+template <typename T> struct Residual {
+    typedef T vec __attribute__((ext_vector_type(4)));
+    vec v[4];
+    __device__ __forceinline__ void fetch(const T* skip, const T* any, uint32_t lh, uint32_t nvalid)
+    {
+        typedef const __attribute__((address_space(1))) vec* vptr_t;
+#pragma unroll
+        for (uint32_t g = 0; g < 4; ++g) {
+            const uint32_t c = 8 * g + 4 * lh;
+            v[g] = *(vptr_t)(skip ? skip + (c < nvalid ? c : 0) : any);
+        }
+    }
+    __device__ __forceinline__ void add(f32x4 (&y)[4], uint32_t act) const
+    {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[g][e] = (float)(T)y[g][e] + (float)v[g][e];
+        activate_block<4>(y, act);
+    }
+};
+
 // Quotient and remainder by a wave-uniform divisor; image sizes are mostly powers of two, and a
 // general 32-bit division costs some thirty vector instructions per lane.
 __device__ __forceinline__ void divmod_uniform(uint32_t x, uint32_t d, uint32_t* q, uint32_t* r)
