@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kBatchThreads) void place_kernel(BatchArgs a)
     uint32_t Tp = 64;
     while (Tp < a.T) Tp <<= 1;
     const int32_t t = a.row_tenant[r];
-    place_row(a, r, t, t >= 0 ? a.off[t] + a.hist_g[blockIdx.x * Tp + t] + a.row_rank[r] : 0, a.row_src[r]);
+    place_row(a, r, t, t >= 0 ? a.off[t] + a.hist_g[blockIdx.x * Tp + t] + a.row_rank[r] : 0);
 }
 
 // Ranking pass for large batches, spread over the chip: workgroup g takes rows
@@ -290,12 +290,10 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
 
     // pass 3: packed position of every row (pre-ranked batches: place_kernel, from the prefixes
     // over the ranking workgroups that were handed back above); a wave places the rows it ranked
-    // where its input lies (noted above: by this lane, or in front of a barrier)
-    auto source = [&](uint32_t r) -> const void* { return ONE_SEG ? (const uint8_t*)a.first.src + (size_t)r * a.first.row_stride * a.elem_size : a.row_src[r]; };
     auto place = [&](uint32_t r, int32_t t, uint32_t rank) {
         const uint32_t tl = t >= 0 ? (uint32_t)t : 0;
         const uint32_t base = one_wave ? (uint32_t)__shfl((int)base1, (int)(tl & 63)) : offl[tl] + hist[w * Tp + tl];
-        if (r < end) place_row(a, r, t, base + rank, source(r));
+        if (r < end) place_row(a, r, t, base + rank);
     };
     // (unless most waves ranked none: with more than 512 tenants the histograms leave room for eight or four of the sixteen)
     if (in_regs) {
@@ -306,7 +304,7 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
 #pragma unroll 4
         for (uint32_t r = tid; r < R; r += kBatchThreads) {
             const int32_t t = a.row_tenant[r];
-            place_row(a, r, t, t >= 0 ? offl[t] + hist[r / chunk * Tp + t] + a.row_rank[r] : 0, source(r));
+            place_row(a, r, t, t >= 0 ? offl[t] + hist[r / chunk * Tp + t] + a.row_rank[r] : 0);
         }
     } else if (!PRE) {
         for (uint32_t r0 = begin; r0 < end; r0 += 64) {

@@ -191,15 +191,15 @@ __device__ __forceinline__ void conv_wave(const GemmArgs& a, const LayerDev& L, 
 constexpr uint32_t kFewTenants = 32;      // whose facts are fetched ahead of a tile's lookup where more would cost a workgroup per compute unit
 // MAXCB bounds the channel blocks of any tile in the launch: narrow layers get a kernel with
 // few registers and many resident waves, which is what hides the latency of their short K loops.
-template <typename T, int MAXCB>
+template <typename T, int MAXCB, bool FEW>
 __global__ __launch_bounds__(256) void conv_kernel(GemmArgs a)
 {
     __shared__ uint32_t owner_part[4];
     __shared__ __attribute__((aligned(16))) uint8_t unit_scratch[4 * unit_scratch_bytes<T>()];
     const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint8_t* scratch = unit_scratch + wave * unit_scratch_bytes<T>();
-    __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes(1, kFewTenants)];
-    TileLookup<256, 1, kFewTenants> lookup;
+    __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes(kFewTenants)];
+    TileLookup<256, FEW ? kFewTenants : 0> lookup;
     lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     uint32_t idx;
@@ -259,9 +259,10 @@ constexpr uint32_t kConvDeepKC = 4, kConvDeepNS = 4;   // chunks and ring of a w
 // block w, the bricks of filter block w) and do nothing else, waves 0..3 read and multiply.  For launches of few
 // tiles with a long K (deep layers of small batches): their workgroups sit alone on their CUs, one wave per SIMD,
 // and a wave that issues its own loads stands at every one of them for ~100 clocks with no MFMA in the pipe.
+// FEW: at most 64 tenants (bf16; fp32 tiles take several times as long and gain nothing: 328 of them 56.0 -> 57.3 us).
 // FAST: the gather's walk through the window is shared by the wave (UniformTapWalk): every tenant's cin is a
 // multiple of the elements a lane group takes per step, and a tenant's activations are less than 2 GiB.
-template <typename T, int NCB, bool QUAD, int PW, bool FAST>
+template <typename T, int NCB, bool QUAD, int PW, bool FAST, bool FEW>
 __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(PW ? 2 : NCB == 2 ? 4 : 3, NCB == 2 && !PW ? 4 : 3))) void conv_lds_kernel(GemmArgs a)     // PW = 0: as many workgroups per CU as the LDS ring allows: three (48 KiB), four with two filter blocks (36 KiB)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC;
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
     const uint32_t tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
     const uint32_t wave_all = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave_all % 4;
     const bool loader = !PW || wave_all >= 4, worker = !PW || wave_all < 4;     // who issues the loads, who multiplies
-    TileLookup<256 * (1 + PW), 1, sizeof(T) == 2 ? 64 : 0> lookup;      // (fp32 tiles take several times as long: 328 of them 56.0 -> 57.3 us)
+    TileLookup<256 * (1 + PW), FEW ? 64 : 0> lookup;
     lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     uint32_t idx;
@@ -476,7 +477,7 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
     for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias + nbase + 8 * g + 4 * lh);   // bias is padded to N_pad
     // (what an addition done here adds likewise; fp32 tiles with four pixel blocks to a wave have no registers for it)
     constexpr bool EARLY = sizeof(T) == 2 || RBW == 2;
-    const uint32_t nvalid = min((uint32_t)kBrickRows, L.N - min(L.N, nbase));
+    const uint32_t nvalid = min((uint32_t)kBrickRows, L.N - nbase);
     T* out[RBW];
     Residual<T> residual[RBW];
 #pragma unroll
@@ -578,7 +579,7 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
 // multiple of 32 bytes, which spreads the lanes of a stride-2 read over half the banks (2-way
 // conflict; stride 1: none).  Filters stream through a register ring per wave as in conv_kernel.
 // Sub-images: a tile holds `ni` of them, each `n_oh` output rows of one image.
-template <typename T, int NCB, bool TWO>
+template <typename T, int NCB, bool TWO, bool FEW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 8 : NCB == 2 ? 4 : 3, NCB == 1 ? 8 : NCB == 2 ? 4 : 3))) void conv_img_kernel(GemmArgs a)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC;
@@ -590,8 +591,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     extern __shared__ __attribute__((aligned(16))) uint8_t img[];
     __shared__ uint32_t owner_part[4];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
-    __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes(1, kFewTenants)];
-    TileLookup<256, 1, NCB == 1 ? 0 : kFewTenants> lookup;       // (64 registers)
+    __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes(kFewTenants)];
+    TileLookup<256, FEW ? kFewTenants : 0> lookup;            // (not with one channel block: 64 registers)
     lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     // the frame starts as zeros (its border, rows past the image, sub-images past the tenant's last request);
@@ -801,22 +802,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     // behind it (fp32 tiles of four pixel blocks have no registers for that; asked for while the frame is filled, bf16 ones have none either).  64 images, 56x56x64 with an addition 31.7 -> 29.4 us, 28x28x128 26.5 -> 25.4, 14x14x256 27.2 -> 26.2,
     // 7x7x512 27.4 -> 27.5, the 1x1 projections (conv_lds_kernel) 12.4 / 11.6 / 12.5 -> 11.6 / 10.4 / 11.4; one image, K split: 13 launches 0.2-0.6 us each.
     constexpr bool EARLY = RBW == 2 || (sizeof(T) == 2 && RBW == 4);
-    const uint32_t nbase = (nb0 + (active ? wc : 0)) * kBrickRows, nvalid = min((uint32_t)kBrickRows, L.N - min(L.N, nbase));
+    const uint32_t nbase = (nb0 + (active ? wc : 0)) * kBrickRows, nvalid = min((uint32_t)kBrickRows, L.N - nbase);
     T* out[RBW];
     Residual<T> residual[RBW];
-    auto locate = [&](uint32_t r) -> const T* {                    // (the other operand's place)
+    auto locate = [&](uint32_t r) -> T* {
         uint32_t i, pl;
         divmod_uniform((wr * RBW + r) * kBrickRows + li, spi, &i, &pl);
-        const size_t at = (size_t)(seg0 + req0 + i) * a.S + (size_t)(oh_first * ow_n + pl) * L.N + nbase;
-        const bool there = pl < px_t && req0 + i < Mt;
-        out[r] = there ? (T*)act_of(a.act, L.out_buf) + at : nullptr;
-        return there ? (const T*)act_of(a.act, L.in2_buf) + at : nullptr;
+        T* at = nullptr;
+        if (pl < px_t && req0 + i < Mt)
+            at = (T*)act_of(a.act, L.out_buf) + (size_t)(seg0 + req0 + i) * a.S + (size_t)(oh_first * ow_n + pl) * L.N + nbase;
+        return at;
     };
+    auto other = [&](const T* at) { return at ? (const T*)act_of(a.act, L.in2_buf) + (at - (T*)act_of(a.act, L.out_buf)) : nullptr; };
     if constexpr (EARLY) {
 #pragma unroll
         for (uint32_t r = 0; r < RBW; ++r) {
-            const T* other = locate(r);
-            if (L.fuse_add) residual[r].fetch(other, (const T*)act_of(a.act, L.in2_buf) + (size_t)seg0 * a.S, lh, nvalid);
+            out[r] = locate(r);
+            if (L.fuse_add) residual[r].fetch(other(out[r]), (const T*)act_of(a.act, L.in2_buf) + (size_t)seg0 * a.S, lh, nvalid);
         }
     }
     const float* bias = (const float*)(a.arena + L.b_off);
@@ -828,6 +830,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     uint8_t* scratch = img + wave * unit_scratch_bytes<T>();
 #pragma unroll
     for (uint32_t r = 0; r < RBW; ++r) {
+        T* const to = EARLY ? out[r] : locate(r);
         f32x4 y[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -836,12 +839,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
         }
         __builtin_amdgcn_sched_barrier(0);
         activate_block<4>(y, L.act);
-        const T* other = EARLY ? nullptr : locate(r);
         if (L.fuse_add) {
             if constexpr (EARLY) residual[r].add(y, L.fuse_add - 1);
-            else add_residual<T>(y, other, lh, nvalid, L.fuse_add - 1);
+            else add_residual<T>(y, other(to), lh, nvalid, L.fuse_add - 1);
         }
-        store_unit_nhwc<T>(y, out[r], nvalid, a.store_through, scratch);
+        store_unit_nhwc<T>(y, to, nvalid, a.store_through, scratch);
     }
 }
 
@@ -864,7 +866,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
 // wave's part of the LDS (behind the K loop that of its sums).  Same shares of K and same sums as gathered: another order turns labels of deep nets.  One residual-net request, us: 7x7x512 13.9 -> 10.1, 14x14x256 10.4 -> 7.7,
 // 28x28x128 8.6 -> 7.1, 56x56x64 6.4 -> 5.8, the stride-2 layers 10.0 -> 8.2 / 8.4 -> 6.8 / 6.1 -> 5.9; with 4 waves (at most 24 steps) 4.6 -> 5.1, which keep the gathers.
 // (Chunks of four steps, one in flight: 11.6, 9.6, 9.0, 7.3 of the first four; eight gathered steps in flight instead of four: 15.3, 12.2, 8.7, 6.1.)
-template <typename T, uint32_t WAVES, uint32_t CS>
+template <typename T, uint32_t WAVES, uint32_t CS, bool FEW>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 16 || CS ? 4 : 6, WAVES == 16 || CS ? 4 : 6))) void conv_split_kernel(GemmArgs a)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC, P = 4, THREADS = 64 * WAVES;
@@ -873,7 +875,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     __shared__ uint32_t owner_part[WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
     __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes()];
-    TileLookup<THREADS> lookup;
+    TileLookup<THREADS, FEW ? 64 : 0> lookup;
     lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     uint32_t idx;
@@ -1040,21 +1042,24 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 }
 
 // ---- launcher ------------------------------------------------------------
-template <typename T, bool FAST>
+template <typename T, bool FAST, bool FEW>
 static void launch_conv_lds_t(const GemmArgs& a, uint32_t max_cb, bool quad, bool loaders, uint32_t grid, hipStream_t s)
 {
-    if (max_cb == 2 && quad) hipLaunchKernelGGL((conv_lds_kernel<T, 2, true, 0, FAST>), dim3(grid), dim3(256), 0, s, a);
-    else if (max_cb == 2) hipLaunchKernelGGL((conv_lds_kernel<T, 2, false, 0, FAST>), dim3(grid), dim3(256), 0, s, a);
-    else if (loaders) hipLaunchKernelGGL((conv_lds_kernel<T, 4, false, 1, FAST>), dim3(grid), dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((conv_lds_kernel<T, 4, false, 0, FAST>), dim3(grid), dim3(256), 0, s, a);
+    if (max_cb == 2 && quad) hipLaunchKernelGGL((conv_lds_kernel<T, 2, true, 0, FAST, FEW>), dim3(grid), dim3(256), 0, s, a);
+    else if (max_cb == 2) hipLaunchKernelGGL((conv_lds_kernel<T, 2, false, 0, FAST, FEW>), dim3(grid), dim3(256), 0, s, a);
+    else if (loaders) hipLaunchKernelGGL((conv_lds_kernel<T, 4, false, 1, FAST, FEW>), dim3(grid), dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((conv_lds_kernel<T, 4, false, 0, FAST, FEW>), dim3(grid), dim3(256), 0, s, a);
 }
 
 template <typename T>
 static void launch_conv_t(const GemmArgs& a, uint32_t max_cb, bool quad, bool loaders, bool fast, uint32_t grid, hipStream_t s)
 {
-    if (max_cb <= 1) hipLaunchKernelGGL((conv_kernel<T, 1>), dim3(grid), dim3(256), 0, s, a);
-    else if (fast) launch_conv_lds_t<T, true>(a, max_cb, quad, loaders, grid, s);
-    else launch_conv_lds_t<T, false>(a, max_cb, quad, loaders, grid, s);
+    constexpr bool few = sizeof(T) == 2;
+    if (max_cb <= 1 && a.T <= kFewTenants) hipLaunchKernelGGL((conv_kernel<T, 1, true>), dim3(grid), dim3(256), 0, s, a);
+    else if (max_cb <= 1) hipLaunchKernelGGL((conv_kernel<T, 1, false>), dim3(grid), dim3(256), 0, s, a);
+    else if (few && a.T <= 64) { if (fast) launch_conv_lds_t<T, true, few>(a, max_cb, quad, loaders, grid, s); else launch_conv_lds_t<T, false, few>(a, max_cb, quad, loaders, grid, s); }
+    else if (fast) launch_conv_lds_t<T, true, false>(a, max_cb, quad, loaders, grid, s);
+    else launch_conv_lds_t<T, false, false>(a, max_cb, quad, loaders, grid, s);
 }
 
 // A launch may ask for more dynamic LDS than the 64 KiB a kernel gets without saying so; said once per kernel.
@@ -1070,15 +1075,16 @@ static hipError_t launch_conv_img_t(const GemmArgs& a, uint32_t max_cb, bool two
     lds_bytes = std::max<uint32_t>(lds_bytes, 4 * unit_scratch_bytes<T>());       // the frame also serves as store scratch
     GemmArgs b = a;
     b.img_lds = lds_bytes;
-    if (two && sizeof(T) == 2) {
-        if (max_cb <= 1) hipLaunchKernelGGL((conv_img_kernel<T, 1, sizeof(T) == 2>), dim3(grid), dim3(256), lds_bytes, s, b);
-        else if (max_cb <= 2) hipLaunchKernelGGL((conv_img_kernel<T, 2, sizeof(T) == 2>), dim3(grid), dim3(256), lds_bytes, s, b);
-        else hipLaunchKernelGGL((conv_img_kernel<T, 4, sizeof(T) == 2>), dim3(grid), dim3(256), lds_bytes, s, b);
-    } else {
-        if (max_cb <= 1) hipLaunchKernelGGL((conv_img_kernel<T, 1, false>), dim3(grid), dim3(256), lds_bytes, s, b);
-        else if (max_cb <= 2) hipLaunchKernelGGL((conv_img_kernel<T, 2, false>), dim3(grid), dim3(256), lds_bytes, s, b);
-        else hipLaunchKernelGGL((conv_img_kernel<T, 4, false>), dim3(grid), dim3(256), lds_bytes, s, b);
-    }
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds_bytes, s, b); };
+    auto wide = [&](auto few_) {
+        constexpr bool few = decltype(few_)::value, pair = sizeof(T) == 2;      // (two taps a step: bf16 only)
+        if (two && pair) { if (max_cb <= 2) launch(conv_img_kernel<T, 2, pair, few>); else launch(conv_img_kernel<T, 4, pair, few>); }
+        else if (max_cb <= 2) launch(conv_img_kernel<T, 2, false, few>);
+        else launch(conv_img_kernel<T, 4, false, few>);
+    };
+    if (max_cb <= 1) { if (two && sizeof(T) == 2) launch(conv_img_kernel<T, 1, sizeof(T) == 2, false>); else launch(conv_img_kernel<T, 1, false, false>); }
+    else if (a.T <= kFewTenants) wide(std::true_type{});
+    else wide(std::false_type{});
     return hipGetLastError();
 }
 
@@ -1087,20 +1093,24 @@ static hipError_t prepare_conv_t()
 {
     hipError_t e = hipSuccess;
     auto also = [&](hipError_t x) { if (e == hipSuccess) e = x; };
-    also(allow_frame(conv_img_kernel<T, 1, false>)); also(allow_frame(conv_img_kernel<T, 2, false>)); also(allow_frame(conv_img_kernel<T, 4, false>));
-    also(allow_frame(conv_img_kernel<T, 1, sizeof(T) == 2>)); also(allow_frame(conv_img_kernel<T, 2, sizeof(T) == 2>)); also(allow_frame(conv_img_kernel<T, 4, sizeof(T) == 2>));
+    constexpr bool pair = sizeof(T) == 2;
+    also(allow_frame(conv_img_kernel<T, 1, false, false>)); also(allow_frame(conv_img_kernel<T, 1, pair, false>));
+    also(allow_frame(conv_img_kernel<T, 2, false, false>)); also(allow_frame(conv_img_kernel<T, 4, false, false>));
+    also(allow_frame(conv_img_kernel<T, 2, false, true>)); also(allow_frame(conv_img_kernel<T, 4, false, true>));
+    also(allow_frame(conv_img_kernel<T, 2, pair, false>)); also(allow_frame(conv_img_kernel<T, 4, pair, false>));
+    also(allow_frame(conv_img_kernel<T, 2, pair, true>)); also(allow_frame(conv_img_kernel<T, 4, pair, true>));
     return e;
 }
 hipError_t prepare_conv(uint32_t dtype) { return dtype == MT_BF16 ? prepare_conv_t<__bf16>() : prepare_conv_t<float>(); }
 
-template <typename T>
+template <typename T, bool FEW>
 static void launch_conv_split_t(const GemmArgs& a, uint32_t k_steps, bool chunks, uint32_t grid, hipStream_t s)
 {
-    if (k_steps <= kSplitFewSteps) hipLaunchKernelGGL((conv_split_kernel<T, 4, 0>), dim3(grid), dim3(256), 0, s, a);
-    else if (k_steps <= kSplitSomeSteps && chunks) hipLaunchKernelGGL((conv_split_kernel<T, 8, 2>), dim3(grid), dim3(512), 0, s, a);
-    else if (k_steps <= kSplitSomeSteps) hipLaunchKernelGGL((conv_split_kernel<T, 8, 0>), dim3(grid), dim3(512), 0, s, a);
-    else if (chunks) hipLaunchKernelGGL((conv_split_kernel<T, 16, 2>), dim3(grid), dim3(1024), 0, s, a);
-    else hipLaunchKernelGGL((conv_split_kernel<T, 16, 0>), dim3(grid), dim3(1024), 0, s, a);
+    if (k_steps <= kSplitFewSteps) hipLaunchKernelGGL((conv_split_kernel<T, 4, 0, FEW>), dim3(grid), dim3(256), 0, s, a);
+    else if (k_steps <= kSplitSomeSteps && chunks) hipLaunchKernelGGL((conv_split_kernel<T, 8, 2, FEW>), dim3(grid), dim3(512), 0, s, a);
+    else if (k_steps <= kSplitSomeSteps) hipLaunchKernelGGL((conv_split_kernel<T, 8, 0, FEW>), dim3(grid), dim3(512), 0, s, a);
+    else if (chunks) hipLaunchKernelGGL((conv_split_kernel<T, 16, 2, FEW>), dim3(grid), dim3(1024), 0, s, a);
+    else hipLaunchKernelGGL((conv_split_kernel<T, 16, 0, FEW>), dim3(grid), dim3(1024), 0, s, a);
 }
 
 // k_steps: the longest reduction of the layer index in bricks; chunks: every tenant's taps are whole pairs of k steps
@@ -1108,7 +1118,9 @@ hipError_t launch_conv_split(const GemmArgs& a, uint32_t dtype, uint32_t k_steps
 {
     if (grid == 0) return hipSuccess;
     grid = (grid + 7) / 8 * 8;
-    if (dtype == MT_BF16) launch_conv_split_t<__bf16>(a, k_steps, chunks, grid, s); else launch_conv_split_t<float>(a, k_steps, chunks, grid, s);
+    if (a.T <= 64) { if (dtype == MT_BF16) launch_conv_split_t<__bf16, true>(a, k_steps, chunks, grid, s); else launch_conv_split_t<float, true>(a, k_steps, chunks, grid, s); }
+    else if (dtype == MT_BF16) launch_conv_split_t<__bf16, false>(a, k_steps, chunks, grid, s);
+    else launch_conv_split_t<float, false>(a, k_steps, chunks, grid, s);
     return hipGetLastError();
 }
 

@@ -355,28 +355,26 @@ void conv_first_kernel(GemmArgs a)
     __shared__ uint32_t owner_part[WAVES];
     __shared__ __attribute__((aligned(16))) float bias[kFirstBlocks * kBrickRows];
     const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    TileLookup<THREADS, 2> lookup;
-    lookup.fetch(a);
+    TileOwner<THREADS> lookup;
+    lookup.fetch(a.tile_base, a.T);
     const uint32_t n_tiles = a.tile_base[a.T];
-    // the frame starts as zeros; written while the tile list is on its way, where the lookup keeps the tenants' facts behind it
-    for (uint32_t q = ahead_bytes(2) + tid * 16; q < a.img_lds; q += THREADS * 16) *(u32x4*)(lds + q) = u32x4{0, 0, 0, 0};
+    // the frame starts as zeros; written while the tile list is on its way, published by the barrier of the lookup
+    for (uint32_t q = tid * 16; q < a.img_lds; q += THREADS * 16) *(u32x4*)(lds + q) = u32x4{0, 0, 0, 0};
     uint32_t idx;
     if (!logical_tile(n_tiles, &idx)) return;
-    uint32_t t, Mt, seg0, local;
-    LayerDev rows[2];
-    lookup.find_rows(a, idx, owner_part, lds, &t, rows, &Mt, &seg0, &local);
-    lds_barrier();
-    for (uint32_t q = tid * 16; q < min(a.img_lds, ahead_bytes(2)); q += THREADS * 16) *(u32x4*)(lds + q) = u32x4{0, 0, 0, 0};
-    lds_barrier();
-    const LayerDev &L = rows[0], &G = rows[1];                       // G: the max-pool, if it is done here
+    const uint32_t t = lookup.owner(a.T, idx, owner_part);           // uniform: the tenant's facts come through scalar loads
+    const LayerDev L = a.layers[t * MT_MAX_LAYERS];
+    const uint32_t seg0 = a.off[t], Mt = a.M[t];
     const bool pooled = POOL && L.first_pool;
+    const LayerDev& G = a.layers[t * MT_MAX_LAYERS + (POOL ? 1 : 0)];   // the max-pool, if it is done here
     const uint32_t pk = pooled ? G.ksize : 1, ps = pooled ? G.stride : 1, pp = pooled ? G.pad : 0, pw = pooled ? G.out_w : 1;
     const uint32_t out_w = L.out_w, out_h = L.rows_per_req / out_w, end_rows = pooled ? G.rows_per_req / pw : out_h;
     const uint32_t strips = first_strips(end_rows, L.first_rows, a.first_cap), step = ceil_div(end_rows, strips);
+    uint32_t local = idx - a.tile_base[t];
     const uint32_t strip = local % strips;
     local /= strips;
     const uint32_t pass = local / Mt, req = local - pass * Mt;
-    const T* const src = (const T*)(a.packed_src ? a.packed_src[seg0 + req] : a.row_src[a.perm[seg0 + req]]);
+    const T* const src = (const T*)a.row_src[a.perm[seg0 + req]];
     const uint32_t nb0 = pass * kFirstBlocks, ncb = min(kFirstBlocks, L.N_pad / kBrickRows - nb0);
 
     // ---- this wave's filters, the workgroup's bias
@@ -446,20 +444,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
     __shared__ uint32_t owner_part[WAVES];
     __shared__ __attribute__((aligned(16))) float bias[kFirstBlocks * kBrickRows];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
-    TileLookup<THREADS, 2, 0> lookup;
-    lookup.fetch(a);
+    TileOwner<THREADS> lookup;
+    lookup.fetch(a.tile_base, a.T);
     const uint32_t n_tiles = a.tile_base[a.T];
     uint8_t* const mid = lds + a.img_lds;                            // the first layer's rows
     for (uint32_t q = tid * 16; q < a.img_lds + a.mid_lds; q += THREADS * 16) *(u32x4*)(lds + q) = u32x4{0, 0, 0, 0};
     uint32_t idx;
     if (!logical_tile(n_tiles, &idx)) return;
-    uint32_t t, Mt, seg0, local;
-    LayerDev rows[2];
-    lookup.find_rows(a, idx, owner_part, nullptr, &t, rows, &Mt, &seg0, &local);
-    const LayerDev &L = rows[0], &M = rows[1];
-    const uint32_t h1 = M.rows_per_req / M.out_w, strips = first_strips(h1, M.pair_rows, a.first_cap), step = ceil_div(h1, strips);
-    const uint32_t req = local / strips, strip = local - req * strips;
-    const T* const src = (const T*)(a.packed_src ? a.packed_src[seg0 + req] : a.row_src[a.perm[seg0 + req]]);
+    const uint32_t t = lookup.owner(a.T, idx, owner_part);           // uniform: the tenant's facts come through scalar loads
+    const LayerDev L = a.layers[t * MT_MAX_LAYERS], M = a.layers[t * MT_MAX_LAYERS + 1];
+    const uint32_t seg0 = a.off[t], h1 = M.rows_per_req / M.out_w, strips = first_strips(h1, M.pair_rows, a.first_cap), step = ceil_div(h1, strips);
+    const uint32_t local = idx - a.tile_base[t], req = local / strips, strip = local - req * strips;
+    const T* const src = (const T*)a.row_src[a.perm[seg0 + req]];
     const uint32_t p0 = strip * step, p1 = min(p0 + step, h1);
     const uint32_t w0 = L.out_w, h0 = L.rows_per_req / w0, ncb0 = L.N_pad / kBrickRows, cb0 = wave % ncb0;
 
@@ -602,8 +598,7 @@ static hipError_t launch_first_t(const GemmArgs& a, bool scratch, uint32_t frame
     static_assert(8 * unit_scratch_bytes<T>() == first_scratch_bytes(sizeof(T)), "what the layers' limits were checked with");
     GemmArgs b = a;
     b.img_lds = (frame_bytes + 15) / 16 * 16;
-    const uint32_t lds = std::max(b.img_lds + (scratch ? threads / 64 * unit_scratch_bytes<T>() : 0), ahead_bytes(2));
-    hipLaunchKernelGGL((conv_first_kernel<T, KSMAX, POOL>), dim3(grid), dim3(threads), lds, s, b);
+    hipLaunchKernelGGL((conv_first_kernel<T, KSMAX, POOL>), dim3(grid), dim3(threads), b.img_lds + (scratch ? threads / 64 * unit_scratch_bytes<T>() : 0), s, b);
     return hipGetLastError();
 }
 

@@ -27,9 +27,10 @@ constexpr uint32_t kFcLdsBytes = kTrOffset + 4 * kTrBytes;
 static_assert(kFcLdsBytes >= 2 * kStageBytes, "the two activation stages must fit");
 
 // split == 4: activations through LDS, weights through the register ring.
-template <typename T, int RB, bool GATHER>
+// row_of(block of 32 rows of the tile, lane, real): the submitted row of a lane (GATHER).
+template <typename T, int RB, bool GATHER, typename ROWS>
 __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t seg0,
-                                                     uint32_t nb, bool active, uint8_t* stages, f32x16 (&acc)[RB])
+                                                     uint32_t nb, bool active, const ROWS& row_of, uint8_t* stages, f32x16 (&acc)[RB])
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC;
     constexpr uint32_t KC = kChunkBricks / RB;               // k steps per chunk: 16 or 8
@@ -58,8 +59,7 @@ __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Ti
     gptr_t rowp = nullptr;
     bool row_ok = false;
     if (GATHER) {
-        const uint32_t p0 = seg0 + (tl.m0 / kBrickRows + min(wave * 4 / KC, nrb - 1)) * kBrickRows;
-        rowp = (gptr_t)submitted_row(a.row_src, a.packed_src, a.perm, p0, lane & 31, &row_ok);
+        rowp = (gptr_t)row_of(min(wave * 4 / KC, nrb - 1), lane & 31, &row_ok);
     }
     auto load_chunk = [&](uint32_t c, u32x4 (&xr)[4]) {
 #pragma unroll
@@ -333,8 +333,8 @@ __device__ __forceinline__ void fc_split_tile(const GemmArgs& a, const Tile& tl,
     fc_finish_split<T>(a, tl, L, Mt, seg0, nb, kq, ks, active, xout, acc, smem);
 }
 
-template <typename T, int RB, bool GATHER>
-__device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t Mt, uint32_t seg0, T* xout, uint8_t* smem)     // xout: the tenant's first output row
+template <typename T, int RB, bool GATHER, typename ROWS>
+__device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t Mt, uint32_t seg0, const ROWS& row_of, T* xout, uint8_t* smem)     // xout: the tenant's first output row
 {
     const uint32_t split = tl.split;
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC;
@@ -351,7 +351,7 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[r][v] = 0.0f;
 
-    fc_accumulate_shared<T, RB, GATHER>(a, tl, L, seg0, nb, active, smem, acc);
+    fc_accumulate_shared<T, RB, GATHER>(a, tl, L, seg0, nb, active, row_of, smem, acc);
 
     const uint32_t n = nb * kBrickRows + li;
     const float* bias = (const float*)(a.arena + L.b_off);
@@ -476,16 +476,16 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
     }
 }
 
-// NARROW: every tile of the launch splits K (small runs, layer indices with at most 64 outputs): a kernel a third the size, with registers
+// FEW: at most 64 tenants (for launches of nothing but K-split tiles; those of many tiles gain nothing: 1024 tiles of 64 tenants 99.3 -> 100.0 us a pass).  NARROW: every tile of the launch splits K (small runs, layer indices with at most 64 outputs): a kernel a third the size, with registers
 // for four workgroups per CU.  GATHER: layer 0 reads the submitted rows itself.  In the general kernel the wide tiles stand first
 // and the two kinds of layer 0 in kernels of their own: with both and the K-split tiles in front, 40 scalar registers were
 // spilled and layer 0 of 256 models of mixed depths took 175.9 us instead of 171.3.
-template <typename T, bool NARROW, bool GATHER>
+template <typename T, bool NARROW, bool GATHER, bool FEW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 : 3, NARROW ? 4 : 3))) void fc_kernel(GemmArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint8_t smem[kFcLdsBytes];
     __shared__ uint32_t owner_part[4];
-    TileLookup<256, 1, NARROW ? 64 : 0> lookup;                // (launches of many tiles gain nothing: 1024 tiles of 64 tenants 99.3 -> 100.0 us a pass)
+    TileLookup<256, FEW ? 64 : 0> lookup;
     lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     uint32_t idx;
@@ -508,17 +508,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 
     tl.n0 = (local / mt_) * tl.split * kBrickRows;
     const uint32_t nrb = (tl.rows + kBrickRows - 1) / kBrickRows;
     T* xout = (T*)act_of(a.act, L.out_buf) + (size_t)seg0 * a.S;
+    auto row_of = [&](uint32_t block, uint32_t i, bool* real) {
+        const uint32_t p0 = seg0 + tl.m0 + block * kBrickRows;
+        const int32_t r = a.perm[p0 + i];
+        *real = r >= 0;
+        return a.row_src[r >= 0 ? r : a.perm[p0]];            // padding rows read the block's first row (always a real request) and discard it: no branch around the loads
+    };
     if constexpr (!NARROW) {
         if (__builtin_expect(tl.split == 4, 1)) {
-            if (__builtin_expect(nrb > 1, 1)) fc_tile<T, 2, GATHER>(a, tl, L, Mt, seg0, xout, smem);
-            else fc_tile<T, 1, GATHER>(a, tl, L, Mt, seg0, xout, smem);
+            if (__builtin_expect(nrb > 1, 1)) fc_tile<T, 2, GATHER>(a, tl, L, Mt, seg0, row_of, xout, smem);
+            else fc_tile<T, 1, GATHER>(a, tl, L, Mt, seg0, row_of, xout, smem);
             return;
         }
     }
     const void* row = nullptr;
     bool row_ok = false;
     if (GATHER) {
-        row = submitted_row(a.row_src, a.packed_src, a.perm, seg0 + tl.m0, threadIdx.x & 31, &row_ok);
+        row = row_of(0, threadIdx.x & 31, &row_ok);
     }
     fc_split_tile<T, GATHER>(a, tl, L, Mt, seg0, row, row_ok, xout, smem);
 }
@@ -531,6 +537,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 
 // three.  The last workgroup has no tile and writes what the launches behind this one read, as the batcher leaves it: counts, offsets,
 // row order and the tile lists of layers 1 on (streaming FC tiles only: models with images are not served this way).
 // 1 request to 8 tenants' 784-1024-1024-10 models: 23.8 -> 20.2 us, 64 fp32 requests to four 256-512-512-10 models 26.5 -> 23.1.
+__device__ __forceinline__ uint32_t entry_tiles(const BatchArgs& b, const uint4& f, uint32_t M)      // streaming FC tiles of a tenant, as the batcher counts them
+{
+    const bool sk = b.fc_split_k && f.x;
+    const uint32_t groups = sk ? f.y / kBrickRows : f.x & 0x3fffffffu, sh = sk || ((f.x >> 30) & 1) ? 5 : 6;
+    return f.x >> 31 ? 0 : ((M + (1u << sh) - 1) >> sh) * groups;
+}
+// What the launches behind the first one read, by one wave: counts and offsets (a lane is a tenant), padding rows.
+__device__ __forceinline__ void entry_publish(const BatchArgs& b, uint32_t lane, uint32_t M, uint32_t off, uint32_t padded, uint32_t total)
+{
+    if (lane < b.T) {
+        b.M[lane] = M; b.off[lane] = off;
+        if (M) { atomicAdd(&b.served[2 * lane], (unsigned long long)M); atomicAdd(&b.served[2 * lane + 1], 1ull); }
+        for (uint32_t p = off + M; p < off + padded; ++p) b.perm[p] = -1;
+    }
+    if (lane == 63) b.off[b.T] = total;
+    if (lane == 0) *b.big_layers = 0;
+}
+// ... and the tile lists of layers first, first + step, ...
+__device__ __forceinline__ void entry_lists(const BatchArgs& b, uint32_t lane, uint32_t M, uint32_t first, uint32_t step)
+{
+    for (uint32_t l = first; l < b.n_layer_slots; l += step) {
+        if (!((b.list_mask[l / kLayerGroup] >> (l % kLayerGroup)) & 1)) continue;
+        const uint4 f = lane < b.T ? ((const uint4*)b.facts)[(size_t)l * b.T + lane] : uint4{0, 0, 0, 0};
+        const uint32_t n = entry_tiles(b, f, M), incl = wave_inclusive_scan(n);
+        uint32_t* base = b.tile_base + (size_t)l * (b.T + 1);
+        if (lane < b.T) base[lane] = incl - n;
+        if (lane == 63) base[b.T] = incl;
+    }
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void fc_entry_kernel(GemmArgs a, BatchArgs b)
 {
@@ -545,13 +581,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         const uint32_t r = i * 64 + lane;
         id[i] = r < R ? (b.first.ids ? b.first.ids[r] : b.first.tenant) : -1;
     }
-    auto fact = [&](uint32_t l) { return lane < n_tenants ? ((const uint4*)b.facts)[(size_t)l * n_tenants + lane] : uint4{0, 0, 0, 0}; };
-    auto tiles = [&](const uint4& f, uint32_t M) {            // streaming FC tiles of this lane's tenant, as the batcher counts them
-        const bool sk = b.fc_split_k && f.x;
-        const uint32_t groups = sk ? f.y / kBrickRows : f.x & 0x3fffffffu, sh = sk || ((f.x >> 30) & 1) ? 5 : 6;
-        return f.x >> 31 ? 0 : ((M + (1u << sh) - 1) >> sh) * groups;
-    };
-    const uint4 f0 = fact(0);
+    const uint4 f0 = lane < n_tenants ? ((const uint4*)b.facts)[lane] : uint4{0, 0, 0, 0};
     // (every workgroup looks for itself: a run that is not captured serves what was registered when it was enqueued, which no registration since can change)
     const uint64_t registered = __ballot(lane < n_tenants && serves(b, b.tenants[lane]));
     uint64_t has[NIT];                                        // the rows of this lane's tenant
@@ -576,13 +606,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 
     if (blockIdx.x == gridDim.x - 1) {
         if (wave == 0) {
-            if (lane < n_tenants) {
-                b.M[lane] = M; b.off[lane] = off;
-                if (M) { atomicAdd(&b.served[2 * lane], (unsigned long long)M); atomicAdd(&b.served[2 * lane + 1], 1ull); }
-                for (uint32_t p = off + M; p < off + padded; ++p) b.perm[p] = -1;
-            }
-            if (lane == 63) b.off[n_tenants] = off_incl;
-            if (lane == 0) *b.big_layers = 0;
+            entry_publish(b, lane, M, off, padded, off_incl);
         } else if (wave == 1) {
 #pragma unroll
             for (uint32_t i = 0; i < NIT; ++i) {
@@ -595,20 +619,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                     rank += (uint32_t)__popcll(j < i ? m : m & ((1ull << lane) - 1));
                 }
                 const uint32_t position = (uint32_t)__shfl((int)off, tl) + rank, r = i * 64 + lane;
-                if (r < R) { b.row_tenant[r] = t; place_row(b, r, t, position, nullptr); }      // (no launch behind this one reads submitted rows)
+                if (r < R) { b.row_tenant[r] = t; place_row(b, r, t, position); }
             }
         }
-        for (uint32_t l = 1 + (wave + 2) % 4; l < b.n_layer_slots; l += 4) {      // (waves 2 and 3, which have nothing else to do, first)
-            if (!((b.list_mask[l / kLayerGroup] >> (l % kLayerGroup)) & 1)) continue;
-            const uint32_t n = tiles(fact(l), M), incl = wave_inclusive_scan(n);
-            uint32_t* base = b.tile_base + (size_t)l * (n_tenants + 1);
-            if (lane < n_tenants) base[lane] = incl - n;
-            if (lane == 63) base[n_tenants] = incl;
-        }
+        entry_lists(b, lane, M, 1 + (wave + 2) % 4, 4);       // (waves 2 and 3, which have nothing else to do, first)
         return;
     }
 
-    const uint32_t n = tiles(f0, M), incl = wave_inclusive_scan(n);
+    const uint32_t n = entry_tiles(b, f0, M), incl = wave_inclusive_scan(n);
     uint32_t idx;
     if (!logical_tile(__builtin_amdgcn_readlane(incl, 63), &idx)) return;
     Tile tl;
@@ -636,21 +654,135 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     fc_split_tile<T, true>(a, tl, L, Mt, seg0, row, row_ok, (T*)act_of(a.act, L.out_buf) + (size_t)seg0 * a.S, smem);
 }
 
+// The same for one submission of at most 4096 rows and any tiles: the workgroup's waves take a quarter of the rows each, count them by tenant in LDS and, once the
+// tile's tenant is known, note those that are the tile's.  A tile waits for ids and facts, the layer's row and the submitted rows, in place of the tile list, that row,
+// the rows' addresses and the rows; the batcher's launch, alone on the chip for 5-7 us, is gone.  Passes and the line beside run_entry.  Bound as fc_kernel is: by the weight
+// stream, behind 2-3 us until the first weight load.  (With the ids in registers and masks from ballots, as above, 16 unrolled steps of them spilled 91 registers and the tiles took
+// half as long again; without the leader's addition 64 rows of one tenant added one by one, 4096 requests to one tenant 113 -> 123 us.)
+template <typename T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void fc_entry_wide_kernel(GemmArgs a, BatchArgs b)
+{
+    constexpr uint32_t NIT = kEntryWideRows / 256;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[kFcLdsBytes];
+    __shared__ uint32_t counts[4][65];                        // (the last one: rows of no tenant)
+    __shared__ int32_t rows_of[kTileRows];
+    uint8_t* const ids = smem + kStageBytes;                  // every row's tenant (0xff: none); until the second stage is written, behind a barrier
+    static_assert(kStageBytes + kEntryWideRows <= kFcLdsBytes && kEntryMaxTenants <= 64, "a byte per row");
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_tenants = b.T, R = b.R;
+    const uint32_t per = ceil_div(R, 256), begin = wave * per * 64, chunks = begin < R ? min(per, ceil_div(R - begin, 64)) : 0;      // this wave's rows, 64 at a time
+    int32_t id[NIT];
+    if (b.first.ids) {
+#pragma unroll
+        for (uint32_t i = 0; i < NIT; ++i) id[i] = b.first.ids[min(begin + min(i, per - 1) * 64 + lane, R - 1)];
+    } else {
+#pragma unroll
+        for (uint32_t i = 0; i < NIT; ++i) id[i] = b.first.tenant;
+    }
+    const uint4 f0 = lane < n_tenants ? ((const uint4*)b.facts)[lane] : uint4{0, 0, 0, 0};
+    const uint64_t registered = __ballot(lane < n_tenants && serves(b, b.tenants[lane]));
+    counts[wave][lane] = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < NIT; ++i) {
+        if (i >= chunks) break;                               // uniform
+        const uint32_t t = (uint32_t)id[i], r = begin + i * 64 + lane;
+        const bool ok = (r < R) & (t < n_tenants) & (((registered >> (t & 63)) & 1) != 0);
+        // (lanes of one tenant would add one after the other: those of the first lane's are added at once)
+        const uint32_t bin = ok ? t : 64, first = __builtin_amdgcn_readfirstlane(bin);
+        const uint32_t same = (uint32_t)__popcll(__ballot(bin == first));
+        if (bin != first || lane == 0) atomicAdd(&counts[wave][bin], lane == 0 ? same : 1u);
+        ids[r] = ok ? (uint8_t)t : (uint8_t)0xff;
+    }
+    lds_barrier();
+    uint32_t M = 0, before = 0;                               // this lane's tenant: its rows, and those of them in front of this wave's
+#pragma unroll
+    for (uint32_t w = 0; w < 4; ++w) {
+        before = w == wave ? M : before;
+        M += counts[w][lane];
+    }
+    const uint32_t padded = ceil_div(M, kBrickRows) * kBrickRows, off_incl = wave_inclusive_scan(padded), off = off_incl - padded;
+
+    if (blockIdx.x == gridDim.x - 1) {                        // the batcher's part
+        if (wave == 0) entry_publish(b, lane, M, off, padded, off_incl);
+        entry_lists(b, lane, M, 1 + (wave + 3) % 4, 4);
+        uint32_t at = off + before;                           // where the next row of this lane's tenant goes
+#pragma unroll 1
+        for (uint32_t i = 0; i < chunks; ++i) {
+            const uint32_t r = begin + i * 64 + lane;
+            const int32_t t = (int8_t)ids[r], tl = max(t, 0);
+            uint64_t has = __ballot(t >= 0);                  // the rows of this lane's tenant among these 64
+#pragma unroll
+            for (uint32_t bit = 0; bit < 6; ++bit) {
+                const uint64_t s = __ballot((t >> bit) & 1);
+                has &= (lane >> bit) & 1 ? s : ~s;
+            }
+            const uint64_t same = (uint64_t)(uint32_t)__shfl((int)(uint32_t)has, tl) | (uint64_t)(uint32_t)__shfl((int)(uint32_t)(has >> 32), tl) << 32;
+            const uint32_t position = (uint32_t)__shfl((int)at, tl) + (uint32_t)__popcll(same & ((1ull << lane) - 1));
+            at += (uint32_t)__popcll(has);
+            if (r < R) { b.row_tenant[r] = t; place_row(b, r, t, position); }
+        }
+        return;
+    }
+
+    const uint32_t n = entry_tiles(b, f0, M), incl = wave_inclusive_scan(n);
+    uint32_t idx;
+    if (!logical_tile(__builtin_amdgcn_readlane(incl, 63), &idx)) return;
+    Tile tl;
+    tl.tenant = (uint32_t)__popcll(__ballot(incl <= idx));    // (a lane without a tenant holds the total)
+    const LayerDev L = a.layers[tl.tenant * MT_MAX_LAYERS];
+    const uint32_t Mt = __builtin_amdgcn_readlane(M, tl.tenant), seg0 = __builtin_amdgcn_readlane(off, tl.tenant), local = idx - __builtin_amdgcn_readlane(incl - n, tl.tenant);
+    uint32_t groups, trows;
+    fc_shape(L.N_pad, a.fc_split_k, &tl.split, &groups, &trows);
+    const uint32_t mt_ = ceil_div(Mt, trows);
+    tl.m0 = (local % mt_) * trows;
+    tl.rows = min(trows, Mt - tl.m0);
+    tl.n0 = (local / mt_) * tl.split * kBrickRows;
+    uint32_t at = __builtin_amdgcn_readlane(before, tl.tenant);
+#pragma unroll 1
+    for (uint32_t i = 0; i < chunks; ++i) {
+        const uint64_t m = __ballot(ids[begin + i * 64 + lane] == tl.tenant);
+        const uint32_t p = at + (uint32_t)__popcll(m & ((1ull << lane) - 1)) - tl.m0;
+        if (((m >> lane) & 1) && p < tl.rows) rows_of[p] = (int32_t)(begin + i * 64 + lane);
+        at += (uint32_t)__popcll(m);
+    }
+    lds_barrier();
+    auto row_of = [&](uint32_t block, uint32_t i, bool* real) -> const void* {
+        const uint32_t p = block * kBrickRows + i;
+        *real = p < tl.rows;
+        const int32_t r = rows_of[*real ? p : block * kBrickRows];
+        return (const uint8_t*)b.first.src + (size_t)(uint32_t)r * b.first.row_stride * sizeof(T);
+    };
+    T* xout = (T*)act_of(a.act, L.out_buf) + (size_t)seg0 * a.S;
+    if (__builtin_expect(tl.split == 4, 1)) {
+        if (__builtin_expect(tl.rows > (uint32_t)kBrickRows, 1)) fc_tile<T, 2, true>(a, tl, L, Mt, seg0, row_of, xout, smem);
+        else fc_tile<T, 1, true>(a, tl, L, Mt, seg0, row_of, xout, smem);
+        return;
+    }
+    bool row_ok;
+    const void* row = row_of(0, lane & 31, &row_ok);
+    fc_split_tile<T, true>(a, tl, L, Mt, seg0, row, row_ok, xout, smem);
+}
+
 // ---- launcher ------------------------------------------------------------
 template <typename T>
 static void launch_fc_t(const GemmArgs& a, bool narrow, uint32_t grid, hipStream_t s)
 {
-    if (narrow && a.gather) hipLaunchKernelGGL((fc_kernel<T, true, true>), dim3(grid), dim3(256), 0, s, a);
-    else if (narrow) hipLaunchKernelGGL((fc_kernel<T, true, false>), dim3(grid), dim3(256), 0, s, a);
-    else if (a.gather) hipLaunchKernelGGL((fc_kernel<T, false, true>), dim3(grid), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((fc_kernel<T, false, false>), dim3(grid), dim3(256), 0, s, a);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, a); };
+    if (narrow && a.T <= 64) { if (a.gather) launch(fc_kernel<T, true, true, true>); else launch(fc_kernel<T, true, false, true>); }
+    else if (narrow) { if (a.gather) launch(fc_kernel<T, true, true, false>); else launch(fc_kernel<T, true, false, false>); }
+    else if (a.gather) launch(fc_kernel<T, false, true, false>);
+    else launch(fc_kernel<T, false, false, false>);
 }
 
 // grid: a bound of the tiles; eight workgroups more, of which the last does the batcher's part
-hipError_t launch_fc_entry(const GemmArgs& a, const BatchArgs& b, uint32_t dtype, uint32_t grid, hipStream_t s)
+hipError_t launch_fc_entry(const GemmArgs& a, const BatchArgs& b, uint32_t dtype, bool wide, uint32_t grid, hipStream_t s)
 {
-    if (b.R > kEntryMaxRows || b.T > kEntryMaxTenants) return hipErrorInvalidValue;
+    if (b.R > kEntryWideRows || b.T > kEntryMaxTenants || (!wide && b.R > kEntryMaxRows)) return hipErrorInvalidValue;
     grid = (grid + 7) / 8 * 8 + 8;
+    if (wide) {
+        if (dtype == MT_BF16) hipLaunchKernelGGL(fc_entry_wide_kernel<__bf16>, dim3(grid), dim3(256), 0, s, a, b);
+        else hipLaunchKernelGGL(fc_entry_wide_kernel<float>, dim3(grid), dim3(256), 0, s, a, b);
+        return hipGetLastError();
+    }
     if (dtype == MT_BF16) hipLaunchKernelGGL(fc_entry_kernel<__bf16>, dim3(grid), dim3(256), 0, s, a, b);
     else hipLaunchKernelGGL(fc_entry_kernel<float>, dim3(grid), dim3(256), 0, s, a, b);
     return hipGetLastError();

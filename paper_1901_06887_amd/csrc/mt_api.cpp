@@ -100,7 +100,7 @@ struct NamedRows { uint32_t tenant, rows; };   // requests of a tenant in the su
 // one slot from its batcher to its last kernel; the weights and model tables are shared.
 struct RunSlot {
     int32_t* d_row_tenant = nullptr; uint32_t* d_row_rank = nullptr; uint32_t* d_hist_g = nullptr;
-    const void** d_row_src = nullptr; const void** d_packed_src = nullptr; int32_t* d_pos_of = nullptr; int32_t* d_perm = nullptr;
+    const void** d_row_src = nullptr; int32_t* d_pos_of = nullptr; int32_t* d_perm = nullptr;
     uint32_t* d_M = nullptr; uint32_t* d_off = nullptr; uint32_t* d_tile_base = nullptr;
     void* d_act[kActBuffers] = {}; float* d_logits = nullptr;   // (only as many activation buffers as the registered models need)
     hipEvent_t done = nullptr;      // recorded behind the slot's last run
@@ -207,7 +207,7 @@ struct mt_ctx {
     uint32_t* d_row_rank = nullptr;
     uint32_t* d_hist_g = nullptr;      // [kHistEntries] per-workgroup tenant histograms of the ranking kernel
     const void** d_row_src = nullptr;
-    const void** d_packed_src = nullptr;
+   
     int32_t* d_pos_of = nullptr;
     int32_t* d_perm = nullptr;
     uint32_t* d_M = nullptr;
@@ -267,7 +267,7 @@ mt_status fail(mt_ctx* c, mt_status st, const char* fmt, ...)
 
 void bind_slot(mt_ctx* c, const RunSlot& r)
 {
-    c->d_row_tenant = r.d_row_tenant; c->d_row_rank = r.d_row_rank; c->d_hist_g = r.d_hist_g; c->d_row_src = r.d_row_src; c->d_packed_src = r.d_packed_src;
+    c->d_row_tenant = r.d_row_tenant; c->d_row_rank = r.d_row_rank; c->d_hist_g = r.d_hist_g; c->d_row_src = r.d_row_src;
     c->d_pos_of = r.d_pos_of; c->d_perm = r.d_perm; c->d_M = r.d_M; c->d_off = r.d_off; c->d_tile_base = r.d_tile_base;
     for (int i = 0; i < kActBuffers; ++i) c->d_act[i] = r.d_act[i];
     c->d_logits = r.d_logits;
@@ -949,12 +949,20 @@ ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<Na
     return p;
 }
 
-// Whether layer 0 does the batcher's work in a run of one submission of R rows that it reads itself: few rows and tenants, nothing but streaming FC
-// tiles that split K, and no model that is finished there.
-bool run_entry(const mt_ctx* c, uint64_t R, bool split_k)
+// Whether layer 0 does the batcher's work in a run of one submission of R rows that it reads itself: few tenants, nothing but FC layers, and no model that is
+// finished there.  kEntryNarrow: few rows and nothing but tiles that split K; kEntryWide: any tiles, as long as they start together (three workgroups to a compute unit):
+// every tile of a second round does the segmentation once more behind the first.  us a pass, with the batcher's launch and so, bf16: 64 tenants of 784-1024-1024-10,
+// 300 / 1024 / 2048 requests 55.6 / 72.2 / 73.8 -> 53.4 / 69.7 / 71.1, 16 of 512-512-512-10 26.2 / 31.3 / 35.4 -> 23.6 / 28.8 / 32.5, one of 1024-2048-2048-40, 2048 and 3000 (at most 766
+// tiles) 66.5 / 85.9 -> 65.2 / 84.1, 4096 (1040) 110.2 -> 112.7; at most 1024 tiles (4096 requests of the first) 100.9 -> 100.2, three runs in flight 215.0 -> 221.6.  (It gains as much from 65 rows on:
+// 54.6 -> 52.4 at 257.  Up to there runs of ordinary tiles keep the launches that they are known to have.)
+constexpr uint32_t kEntryWideMin = 288;
+constexpr uint64_t kEntryWideTiles = 768;
+enum : int { kEntryNone = 0, kEntryNarrow, kEntryWide };
+int run_entry(const mt_ctx* c, uint64_t R, bool split_k)
 {
-    return R <= kEntryMaxRows && c->cfg.max_tenants <= kEntryMaxTenants && !c->no_entry && !c->any_conv_first && c->any_fc_first && c->min_layers >= 2 &&
-           (split_k || c->max_fc_cols[0] <= 2 * (uint32_t)kBrickRows);
+    if (c->cfg.max_tenants > kEntryMaxTenants || c->no_entry || c->any_conv_first || !c->any_fc_first || c->min_layers < 2) return kEntryNone;
+    if (R <= kEntryMaxRows && (split_k || c->max_fc_cols[0] <= 2 * (uint32_t)kBrickRows)) return kEntryNarrow;
+    return R >= kEntryWideMin && R <= kEntryWideRows && tile_bound(c, 0, 0, R, split_k) <= kEntryWideTiles ? kEntryWide : kEntryNone;
 }
 
 // Most classes a last layer may have for its FC tiles to finish their rows themselves (softmax,
@@ -1346,7 +1354,6 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
         CREATE_TRY(hipMalloc((void**)&r.d_row_rank, R * 4));
         CREATE_TRY(hipMalloc((void**)&r.d_hist_g, kHistEntries * 4));
         CREATE_TRY(hipMalloc((void**)&r.d_row_src, R * sizeof(void*)));
-        CREATE_TRY(hipMalloc((void**)&r.d_packed_src, (uint64_t)c->P_cap * sizeof(void*)));
         CREATE_TRY(hipMalloc((void**)&r.d_pos_of, R * 4));
         CREATE_TRY(hipMalloc((void**)&r.d_perm, (uint64_t)c->P_cap * 4));
         CREATE_TRY(hipMalloc((void**)&r.d_M, T * 4));
@@ -1384,7 +1391,7 @@ mt_status mt_destroy(mt_ctx* c)
         void* bufs[] = {c->d_arena, c->d_tenants, c->d_layers, c->d_facts, c->d_served, c->d_zeros};
         for (void* p : bufs) if (p) (void)hipFree(p);
         for (RunSlot& r : c->slots) {
-            void* rb[] = {r.d_row_tenant, r.d_row_rank, r.d_hist_g, (void*)r.d_row_src, (void*)r.d_packed_src, r.d_pos_of, r.d_perm, r.d_M, r.d_off, r.d_tile_base,
+            void* rb[] = {r.d_row_tenant, r.d_row_rank, r.d_hist_g, (void*)r.d_row_src, r.d_pos_of, r.d_perm, r.d_M, r.d_off, r.d_tile_base,
                           r.d_act[0], r.d_act[1], r.d_act[2], r.d_act[3], r.d_logits};
             static_assert(kActBuffers == 4, "the list above names every activation buffer");
             for (void* p : rb) if (p) (void)hipFree(p);
@@ -1710,19 +1717,17 @@ uint64_t carve_static_slot(const mt_ctx* c, uint32_t R, RunSlot* rs, uint32_t* d
     const uint64_t o_src = take((uint64_t)R * sizeof(void*)), o_pos = take((uint64_t)R * 4), o_perm = take(P * 4);
     uint64_t o_act[kActBuffers] = {};
     for (uint32_t i = 0; i < c->act_buffers; ++i) o_act[i] = take(P * c->S * c->elem_size);
-    const uint64_t o_lg = take(P * c->C_pad * 4), need = at;
-    const uint64_t o_ps = take(P * sizeof(void*));           // (a run does without where this does not fit)
-    if (need <= MT_STATIC_SCRATCH_BYTES) {
+    const uint64_t o_lg = take(P * c->C_pad * 4);
+    if (at <= MT_STATIC_SCRATCH_BYTES) {
         uint8_t* b = c->static_scratch;
         rs->d_M = (uint32_t*)(b + o_M); rs->d_off = (uint32_t*)(b + o_off); rs->d_tile_base = (uint32_t*)(b + o_tb);
         rs->d_row_tenant = (int32_t*)(b + o_rt); rs->d_row_rank = (uint32_t*)(b + o_rr); rs->d_hist_g = (uint32_t*)(b + o_h);
         rs->d_row_src = (const void**)(b + o_src); rs->d_pos_of = (int32_t*)(b + o_pos); rs->d_perm = (int32_t*)(b + o_perm);
         for (uint32_t i = 0; i < (uint32_t)kActBuffers; ++i) rs->d_act[i] = i < c->act_buffers ? b + o_act[i] : nullptr;
         rs->d_logits = (float*)(b + o_lg);
-        rs->d_packed_src = at <= MT_STATIC_SCRATCH_BYTES ? (const void**)(b + o_ps) : nullptr;
         *descr_words = (uint32_t)(descr_end / 4);
     }
-    return need;
+    return at;
 }
 
 // The pending requests per tenant, if every submission named its tenant and some model has convolutions (which are
@@ -1836,7 +1841,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     const std::vector<NamedRows>* named = count_named(c);
     BatchArgs b{};
     b.segs = c->d_segs[slot]; b.n_segs = n_segs; b.R = R; b.T = T; b.n_layer_slots = c->n_layer_slots;
-    b.first = c->pending[0]; b.row_src = c->d_row_src; b.packed_src = c->d_packed_src; b.elem_size = c->elem_size;
+    b.first = c->pending[0]; b.row_src = c->d_row_src; b.elem_size = c->elem_size;
     b.tenants = c->d_tenants; b.facts = c->d_facts; b.served = (unsigned long long*)c->d_served;
     {   // large batches are ranked by a kernel of their own, where its per-workgroup histograms fit the batcher's LDS
         uint32_t Tp = 64;
@@ -1907,7 +1912,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
         if (((uintptr_t)sg.src & 15) || ((uint64_t)sg.row_stride * c->elem_size) % 16) fuse_gather = false;
     // Every workgroup of fc_entry_kernel looks up for itself which tenants there are, so it goes by those registered now.  What is
     // captured goes on to serve models registered later, which the one workgroup of the batcher can look up.
-    const bool entry = n_segs == 1 && fuse_gather && !captured && run_entry(c, R, split_k);
+    const int entry = n_segs == 1 && fuse_gather && !captured ? run_entry(c, R, split_k) : kEntryNone;
     if (entry) {                           // (the time of the whole run starts where the batcher's would)
         if (c->profiling) HIP_TRY(c, hipEventRecord(c->prof_events[2 * kProfBatcher], s));
     } else {
@@ -1918,7 +1923,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     const uint32_t P = packed_rows_bound(c, R);
     {
         GatherArgs g{};
-        g.row_src = c->d_row_src; g.packed_src = c->d_packed_src; g.P = P; g.tenants = c->d_tenants; g.layers = c->d_layers;
+        g.row_src = c->d_row_src; g.P = P; g.tenants = c->d_tenants; g.layers = c->d_layers;
         g.perm = c->d_perm; g.off = c->d_off; g.M = c->d_M; g.T = T; g.act = c->d_act[0]; g.S = c->S; g.elem_size = c->elem_size; g.zeros = c->d_zeros;
         // workgroups per block of 32 rows: each takes ~64 KiB of it, so that long rows have enough loads in flight
         const uint32_t gs = row_slices((uint64_t)c->max_in_len * c->elem_size * kBrickRows, 65536);      // c5: 146 -> 133 us with four
@@ -1939,7 +1944,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             GemmArgs ga{};
             ga.tile_base = c->d_tile_base + ((size_t)kind * MT_MAX_LAYERS + l) * (T + 1);
             ga.T = T; ga.layer = l; ga.fc_split_k = split_k; ga.big_layers = b.big_layers;
-            ga.gather = (kind == 0 && l == 0 && fuse_gather); ga.perm = c->d_perm; ga.row_src = c->d_row_src; ga.packed_src = c->d_packed_src;
+            ga.gather = (kind == 0 && l == 0 && fuse_gather); ga.perm = c->d_perm; ga.row_src = c->d_row_src;
             ga.fuse_head = fuse_head; ga.fuse_head_max = fuse_head_max; ga.out_vec_ok = out_vec_ok; ga.out = outp; ga.pool = kind == 1 && c->pool_fused[l];
             ga.store_through = kind == 1 && R * c->max_conv_work[l] * kBrickRows * c->elem_size <= kStoreThroughMaxBytes;
             ga.layers = c->d_layers; ga.off = c->d_off; ga.M = c->d_M; ga.act = bufs; ga.arena = c->d_arena;
@@ -1949,7 +1954,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
                 return fail(c, MT_EUNSUPPORTED, "layer %u: %llu tiles exceed one launch", l, (unsigned long long)grid);
             const uint32_t g32 = (uint32_t)grid;
             ga.first_cap = conv.first_cap;
-            if (kind == 0 && l == 0 && entry) TIMED(kProfFc + l, launch_fc_entry(ga, b, c->cfg.dtype, g32, s));
+            if (kind == 0 && l == 0 && entry) TIMED(kProfFc + l, launch_fc_entry(ga, b, c->cfg.dtype, entry == kEntryWide, g32, s));
             else if (kind == 0) TIMED(kProfFc + l, launch_fc(ga, c->cfg.dtype, split_k || c->max_fc_cols[l] <= 2 * (uint32_t)kBrickRows, g32, s));
             else if (conv.pair_mid) TIMED(kProfConv + l, launch_conv_pair(ga, c->cfg.dtype, c->pair_blocks, conv.first_frame, conv.pair_mid, g32, s));
             else if (conv.first_cap) TIMED(kProfConv + l, launch_conv_first(ga, c->cfg.dtype, c->first_max_ks, c->first_pool, c->first_plain, conv.first_frame, g32, s));

@@ -330,13 +330,12 @@ template <> struct Mma<float> {
 
 // A row's packed position is known: note it both ways; a rejected row (t < 0: unknown tenant or
 // no model) is answered at once with label -1 and zero rows.
-__device__ __forceinline__ void place_row(const BatchArgs& a, uint32_t r, int32_t t, uint32_t position, const void* src)
+__device__ __forceinline__ void place_row(const BatchArgs& a, uint32_t r, int32_t t, uint32_t position)
 {
     int32_t pos = -1;
     if (t >= 0) {
         pos = (int32_t)position;
         a.perm[pos] = (int32_t)r;
-        if (a.packed_src) a.packed_src[pos] = src;
     } else {
         a.out.labels[r] = -1;
         if (a.out.n_classes) a.out.n_classes[r] = 0;
@@ -346,16 +345,6 @@ __device__ __forceinline__ void place_row(const BatchArgs& a, uint32_t r, int32_
         }
     }
     a.pos_of[r] = pos;
-}
-
-// The submitted row of packed row p0 + i of a block of 32 whose first row is p0; a padding row gets that one's (always a real request), to be read and discarded:
-// no branch around the loads.
-__device__ __forceinline__ const void* submitted_row(const void* const* row_src, const void* const* packed_src, const int32_t* perm, uint32_t p0, uint32_t i, bool* real)
-{
-    const int32_t r = perm[p0 + i];
-    *real = r >= 0;
-    if (packed_src) return packed_src[r >= 0 ? p0 + i : p0];          // one trip to memory less
-    return row_src[r >= 0 ? r : perm[p0]];
 }
 
 // What a workgroup works on, derived from its block index and the list's tile_base array.
@@ -434,74 +423,64 @@ struct TileOwner {
     }
 };
 
-// The same, together with what a tile needs to know of its tenant: the rows of ROWS layers from a.layer on, the tenant's requests and first packed
-// row, and its first tile.  With up to TENANTS tenants the workgroup fetches those of all of them beside the tile list, a
+// The same, together with what a tile needs to know of its tenant: the layer's row, the tenant's requests and first packed row, and its first tile.  With at most TENANTS tenants (0: any number, by loads of its own) the workgroup fetches those of all of them beside the tile list, a
 // 16-byte piece or two per thread, and finds its own in LDS: one trip to memory at the head of a tile instead of two that depend on each other.
 // A launch of few tiles lasts as long as its chain of trips: residual nets of one request 161.9 -> 151.4 us a pass, MLPs, CNNs and residual nets side by side
 // 193.8 -> 182.0, residual nets of 64 images 531 -> 518, one request to an MLP 20.3 -> 19.7.  LDS: ahead_bytes(), not read behind the next barrier.
-constexpr uint32_t kRowWords = sizeof(LayerDev) / 4;
-constexpr uint32_t ahead_bytes(uint32_t rows = 1, uint32_t tenants = 64) { return tenants * (rows * kRowWords + 4) * 4; }
-template <uint32_t THREADS, uint32_t ROWS = 1, uint32_t TENANTS = 64>
+constexpr uint32_t kRowWords = sizeof(LayerDev) / 4, kFactsWords = kRowWords + 4;      // of a tenant's row; with three more, and padding
+constexpr uint32_t ahead_bytes(uint32_t tenants = 64) { return tenants * kFactsWords * 4; }
+template <uint32_t THREADS, uint32_t TENANTS = 64>
 struct TileLookup {
-    static constexpr uint32_t W = ROWS * kRowWords + 4, PER = ROWS * kRowWords / 4;      // words, and 16-byte pieces, of a tenant
-    static constexpr uint32_t PIECES = TENANTS ? (TENANTS * PER + THREADS - 1) / THREADS : 1;
-    static_assert(TENANTS <= 64 && ROWS * kRowWords <= 64, "a tenant and a word of its rows per lane");
+    static constexpr uint32_t PER = kRowWords / 4, PIECES = TENANTS ? (TENANTS * PER + THREADS - 1) / THREADS : 1;      // 16-byte pieces of a row; of a thread
+    static_assert(TENANTS <= 64 && kFactsWords <= 64, "a tenant, and a word, per lane");
     TileOwner<THREADS> list;
     u32x4 piece[PIECES];
     uint32_t first_tile, requests, off;
     __device__ __forceinline__ void fetch(const GemmArgs& a)
     {
-        if (TENANTS == 0 || a.T > TENANTS) { list.fetch(a.tile_base, a.T); return; }
-        const uint32_t tid = threadIdx.x, lane = tid & 63;
-        list.v[0] = lane < a.T ? a.tile_base[1 + lane] : 0xffffffffu;              // every wave counts for itself
+        if constexpr (TENANTS == 0) {
+            list.fetch(a.tile_base, a.T);
+        } else {
+            const uint32_t tid = threadIdx.x, lane = tid & 63;
+            list.v[0] = lane < a.T ? a.tile_base[1 + lane] : 0xffffffffu;              // every wave counts for itself
 #pragma unroll
-        for (uint32_t i = 0; i < PIECES; ++i) {
-            const uint32_t q = i * THREADS + tid, t = q / PER, c = q % PER;
-            if (t < a.T) piece[i] = ((const u32x4*)(a.layers + (t * MT_MAX_LAYERS + a.layer)))[c];
+            for (uint32_t i = 0; i < PIECES; ++i) {
+                const uint32_t q = i * THREADS + tid, t = q / PER, c = q % PER;
+                if (t < a.T) piece[i] = ((const u32x4*)(a.layers + (t * MT_MAX_LAYERS + a.layer)))[c];
+            }
+            if (tid < a.T) { requests = a.M[tid]; off = a.off[tid]; first_tile = a.tile_base[tid]; }
         }
-        if (tid < a.T) { requests = a.M[tid]; off = a.off[tid]; first_tile = a.tile_base[tid]; }
     }
     // wave-uniform results; every thread of the workgroup must call it
-    __device__ __forceinline__ void find_rows(const GemmArgs& a, uint32_t idx, uint32_t* part, uint8_t* lds, uint32_t* tenant, LayerDev (&L)[ROWS], uint32_t* Mt, uint32_t* seg0, uint32_t* local) const
-    {
-        if (TENANTS == 0 || a.T > TENANTS) {
-            const uint32_t t = list.owner(a.T, idx, part);                          // uniform: the tenant's facts come through scalar loads
-            *tenant = t;
-#pragma unroll
-            for (uint32_t r = 0; r < ROWS; ++r) L[r] = a.layers[t * MT_MAX_LAYERS + a.layer + r];
-            *Mt = a.M[t]; *seg0 = a.off[t]; *local = idx - a.tile_base[t];
-            return;
-        }
-        const uint32_t tid = threadIdx.x, lane = tid & 63;
-        uint32_t* words = (uint32_t*)lds;
-#pragma unroll
-        for (uint32_t i = 0; i < PIECES; ++i) {
-            const uint32_t q = i * THREADS + tid, t = q / PER, c = q % PER;
-            if (t < a.T) *(u32x4*)(words + t * W + c * 4) = piece[i];
-        }
-        if (tid < a.T) {
-            uint32_t* w = words + tid * W + ROWS * kRowWords;
-            w[0] = requests; w[1] = off; w[2] = first_tile;
-        }
-        const uint32_t t = (uint32_t)__builtin_popcountll(__ballot(list.v[0] <= idx));
-        *tenant = t;
-        lds_barrier();
-        const uint32_t word = words[t * W + min(lane, ROWS * kRowWords - 1)], more = words[t * W + ROWS * kRowWords + lane % 4];
-        struct Words { uint32_t w[kRowWords]; } row;
-#pragma unroll
-        for (uint32_t r = 0; r < ROWS; ++r) {
-#pragma unroll
-            for (uint32_t i = 0; i < kRowWords; ++i) row.w[i] = __builtin_amdgcn_readlane(word, r * kRowWords + i);
-            L[r] = __builtin_bit_cast(LayerDev, row);
-        }
-        *Mt = __builtin_amdgcn_readlane(more, 0); *seg0 = __builtin_amdgcn_readlane(more, 1); *local = idx - __builtin_amdgcn_readlane(more, 2);
-    }
     __device__ __forceinline__ void find(const GemmArgs& a, uint32_t idx, uint32_t* part, uint8_t* lds, uint32_t* tenant, LayerDev* L, uint32_t* Mt, uint32_t* seg0, uint32_t* local) const
     {
-        static_assert(ROWS == 1, "one row");
-        LayerDev rows[ROWS];
-        find_rows(a, idx, part, lds, tenant, rows, Mt, seg0, local);
-        *L = rows[0];
+        if constexpr (TENANTS == 0) {
+            const uint32_t t = list.owner(a.T, idx, part);                              // uniform: the tenant's facts come through scalar loads
+            *tenant = t;
+            *L = a.layers[t * MT_MAX_LAYERS + a.layer];
+            *Mt = a.M[t]; *seg0 = a.off[t]; *local = idx - a.tile_base[t];
+        } else {
+            const uint32_t tid = threadIdx.x, lane = tid & 63;
+            uint32_t* words = (uint32_t*)lds;
+#pragma unroll
+            for (uint32_t i = 0; i < PIECES; ++i) {
+                const uint32_t q = i * THREADS + tid, t = q / PER, c = q % PER;
+                if (t < a.T) *(u32x4*)(words + t * kFactsWords + c * 4) = piece[i];
+            }
+            if (tid < a.T) {
+                uint32_t* w = words + tid * kFactsWords + kRowWords;
+                w[0] = requests; w[1] = off; w[2] = first_tile;
+            }
+            const uint32_t t = (uint32_t)__builtin_popcountll(__ballot(list.v[0] <= idx));
+            *tenant = t;
+            lds_barrier();
+            const uint32_t word = words[t * kFactsWords + min(lane, kFactsWords - 1)];
+            struct Words { uint32_t w[kRowWords]; } row;
+#pragma unroll
+            for (uint32_t i = 0; i < kRowWords; ++i) row.w[i] = __builtin_amdgcn_readlane(word, i);
+            *L = __builtin_bit_cast(LayerDev, row);
+            *Mt = __builtin_amdgcn_readlane(word, kRowWords); *seg0 = __builtin_amdgcn_readlane(word, kRowWords + 1); *local = idx - __builtin_amdgcn_readlane(word, kRowWords + 2);
+        }
     }
 };
 

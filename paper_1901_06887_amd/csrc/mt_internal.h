@@ -56,7 +56,7 @@ inline __host__ __device__ uint32_t big_rows(uint32_t rows)
 // (c5's last layer: 35 -> 19 us; the hidden layers would go from 39 to 44 us, their weights read once more).
 constexpr int kBigRemSplitMaxCols = 1024;
 inline __host__ __device__ bool big_remainder_split_k(uint32_t n_pad) { return n_pad <= (uint32_t)kBigRemSplitMaxCols; }
-constexpr uint32_t kEntryMaxRows = 256, kEntryMaxTenants = 64;   // runs whose first launch may do the batcher's work: a few rows and one tenant to a lane
+constexpr uint32_t kEntryMaxRows = 256, kEntryWideRows = 4096, kEntryMaxTenants = 64;   // runs whose first launch may do the batcher's work: a few rows and one tenant to a lane
 constexpr int kRankRows = 1024;     // rows per workgroup of the ranking kernel
 constexpr int kRankMinRows = 8192;  // smaller batches are ranked by the batcher's single workgroup (one launch less)
 constexpr int kRankMaxTenants = 512;
@@ -216,7 +216,6 @@ struct BatchArgs {
     // The batcher turns hist_g into prefixes over the groups, and a third kernel places the rows.
     uint32_t n_rank_groups; uint32_t* hist_g;
     const void** row_src;  // [R] device address of each submitted row's input
-    const void** packed_src;   // [P] ... of each packed row's (real rows only); null in runs whose scratch has no room for it
     int32_t* pos_of;       // [R] packed position of each submitted row, -1 if rejected
     int32_t* perm;         // [P] packed position -> submission index, -1 for padding rows
     uint32_t* M;           // [T]
@@ -234,7 +233,7 @@ inline __host__ __device__ bool serves(const BatchArgs& a, const TenantDev& t) {
 struct ActBufs { void* p[kActBuffers]; };
 
 struct GatherArgs {
-    const void* const* row_src; const void* const* packed_src; uint32_t P;      // P = upper bound of packed rows (multiple of 32)
+    const void* const* row_src; uint32_t P;      // P = upper bound of packed rows (multiple of 32)
     const TenantDev* tenants; const LayerDev* layers; const int32_t* perm;
     const uint32_t* off; const uint32_t* M; uint32_t T;
     void* act; uint32_t S; uint32_t elem_size;
@@ -252,7 +251,7 @@ struct GemmArgs {
     uint32_t first_cap;           // launch of first convolutions on the submitted images: most rows of a tile
     // FC layer 0 can read the submitted rows itself (16-byte aligned rows whose length is a
     // whole number of 16-byte chunks), which saves the staging pass:
-    uint32_t gather; const int32_t* perm; const void* const* row_src; const void* const* packed_src;
+    uint32_t gather; const int32_t* perm; const void* const* row_src;
     // a last layer whose classes all lie inside one tile finishes its rows itself (softmax, argmax,
     // outputs): at most fuse_head_max classes (32: one column block; 128: a whole tile of four, not
     // in runs whose tiles are single column blocks); out_vec_ok: output rows take 16-byte stores
@@ -283,7 +282,7 @@ hipError_t launch_batcher(const BatchArgs& a, hipStream_t s);   // three launche
 hipError_t launch_gather(const GatherArgs& a, uint32_t slices, hipStream_t s);   // `slices` workgroups share a block of 32 rows
 hipError_t launch_gather_image(const GatherArgs& a, uint32_t slices, hipStream_t s);   // `slices` workgroups share a row
 hipError_t launch_fc(const GemmArgs& a, uint32_t dtype, bool narrow, uint32_t grid, hipStream_t s);
-hipError_t launch_fc_entry(const GemmArgs& a, const BatchArgs& b, uint32_t dtype, uint32_t grid, hipStream_t s);   // layer 0 of a small run, the batcher's work in it
+hipError_t launch_fc_entry(const GemmArgs& a, const BatchArgs& b, uint32_t dtype, bool wide, uint32_t grid, hipStream_t s);   // layer 0 with the batcher's work in it; wide: any tiles, up to kEntryWideRows rows
 hipError_t launch_fc_big(const GemmArgs& a, uint32_t dtype, uint32_t grid, uint32_t walk_grid, hipStream_t s);   // walk_grid > 0: that many workgroups walk the tiles (a multiple of 8)
 hipError_t launch_copy(void* dst, const void* src, uint64_t bytes, hipStream_t s);
 hipError_t launch_mfma_rate(float* out, uint32_t iters, uint32_t grid, hipStream_t s);   // out: grid * 512 floats

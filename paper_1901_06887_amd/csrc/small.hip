@@ -25,9 +25,10 @@ __device__ __forceinline__ bool packed_row_tenant(const uint32_t* __restrict__ o
 // channels are padded with zeros to a multiple of 8 so that every tap of the implicit GEMM is
 // a whole number of 16-byte chunks.
 template <typename T>
-__device__ void gather_image(const GatherArgs& a, const TenantDev& td, uint32_t p, const T* src)
+__device__ void gather_image(const GatherArgs& a, const TenantDev& td, uint32_t p, uint32_t r)
 {
     constexpr uint32_t EPC = 16 / sizeof(T);
+    const T* src = (const T*)a.row_src[r];
     T* dst = (T*)a.act + (size_t)p * a.S;
     const uint32_t ci = td.in_cin ? td.in_cin : kChanPad, cp = td.in_cin ? td.in_cin_pad : kChanPad;
     const uint32_t npix = td.in_len / ci;
@@ -76,14 +77,12 @@ __device__ void gather_image(const GatherArgs& a, const TenantDev& td, uint32_t 
 __global__ __launch_bounds__(256) void gather_image_kernel(GatherArgs a)
 {
     const uint32_t p = blockIdx.x;
-    const int32_t r = a.packed_src ? 0 : a.perm[p];          // (a packed row past the last one holds whatever an earlier run left there)
-    const void* packed = a.packed_src ? a.packed_src[p] : nullptr;
+    const int32_t r = a.perm[p];                             // (a packed row past the last one holds whatever an earlier run left there)
     uint32_t t;
     if (!packed_row_tenant<256>(a.off, a.M, a.T, p, &t)) return;
     const TenantDev td = a.tenants[t];
     if (td.in_layout == kLayoutBricks) return;
-    const void* src = a.packed_src ? packed : a.row_src[r];
-    if (a.elem_size == 2) gather_image<__bf16>(a, td, p, (const __bf16*)src); else gather_image<float>(a, td, p, (const float*)src);
+    if (a.elem_size == 2) gather_image<__bf16>(a, td, p, (uint32_t)r); else gather_image<float>(a, td, p, (uint32_t)r);
 }
 
 // Vectors (first layer is FC): one workgroup per block of 32 packed rows, written as bricks.
@@ -95,9 +94,8 @@ __device__ void gather_bricks(const GatherArgs& a, const TenantDev& td, uint32_t
     const uint32_t li = lane & 31, lh = lane >> 5;
     const uint32_t nKB = a.layers[t * MT_MAX_LAYERS].K / KB;
     const uint32_t seg0 = a.off[t];
-    bool real;
-    const T* src = (const T*)submitted_row(a.row_src, a.packed_src, a.perm, p0, li, &real);
-    if (!real) src = nullptr;
+    const int32_t r = a.perm[p0 + li];
+    const T* src = r >= 0 ? (const T*)a.row_src[r] : nullptr;
     u32x4* dst = (u32x4*)((T*)a.act + (size_t)seg0 * a.S) + (size_t)((p0 - seg0) / kBrickRows) * nKB * 64 + lane;
     const uint32_t n = td.in_len;
     // Rows that are 16-byte aligned and a whole number of chunks long (the usual case) are copied

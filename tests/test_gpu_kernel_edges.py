@@ -548,3 +548,39 @@ def test_facts_of_few_and_many_tenants(dtype, n_tenants, rows):
         gpu.append(gpu_run(ctx, w, poison=True))
     compare(w, gpu[1], oracle_rows(w), what="%d tenants, %d rows" % (n_tenants, rows), deep=dtype == "bf16")
     assert all(np.array_equal(a, b) for a, b in zip(*gpu))
+
+
+# layer 0 does the batcher's work in runs of any tiles: rows at the edges of a wave's share and of the range, one tenant to a full wave of them, tiles of one to four
+# column blocks and rows that fill none; requests of nobody.  Against the oracle, and to the bit against the batcher's launch
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_tenants", [1, 9, 64])
+@pytest.mark.parametrize("rows", [288, 513, 1024, 4095, 4096, 4097])
+def test_runs_of_any_tiles_without_a_batcher(monkeypatch, dtype, n_tenants, rows):
+    shapes = ([48, 24, 5], [48, 64, 40, 130], [48, 200, 33, 7, 64])
+    tenants = {t: wl.make_model(wl.mlp_layers(shapes[t % 3], wl.ACT_RELU), dtype, 395, t) for t in range(n_tenants) if t != 7}
+    rng = np.random.default_rng(395)
+    x = rng.standard_normal((rows, 48)).astype(np.float32)
+    ids = np.minimum(rng.zipf(1.3, rows) - 1, n_tenants - 1).astype(np.int32)
+    ids[ids == 7] = 3
+    w = wl.Workload("entry", dtype, tenants, ids, wl.round_to_bf16(x) if dtype == "bf16" else x)
+    odd = ids.copy()
+    odd[rng.random(rows) < 0.2] = rng.choice([-1, n_tenants, 255, 1 << 30, min(7, n_tenants)])
+    got = {}
+    for off in ("0", "1"):
+        monkeypatch.setenv("MT_NO_ENTRY", off)
+        ctx = make_context(w, max_tenants=n_tenants)
+        got[off] = [check(w, "%s, %d tenants, %d rows" % (dtype, n_tenants, rows), ctx) if off == "0" else gpu_run(ctx, w, poison=True)]
+        launches = ctx.stats()["last_run_launches"]
+        got[off].append(gpu_run(ctx, w, ids=odd, poison=True))
+        got[off].append((ctx.last_counts(), [ctx.tenant_account(t)["requests"] for t in tenants]))
+        one = torch_io.to_device(w.inputs, dtype)                    # all of them one tenant's, named by the submission
+        out = torch_io.alloc_outputs(rows, ctx.cfg.max_classes)
+        ctx.submit(0, one.data_ptr(), rows)
+        ctx.run(torch.cuda.current_stream().cuda_stream, out.labels.data_ptr(), out.probs.data_ptr(), out.logits.data_ptr(), out.n_classes.data_ptr(), rows, ctx.cfg.max_classes)
+        torch.cuda.synchronize()
+        got[off].append((out.logits.cpu().numpy(), out.labels.cpu().numpy(), ctx.last_counts()))
+        got[off + "n"] = launches
+        ctx.close()
+    for a, b in zip(got["0"], got["1"]):
+        assert all(np.array_equal(u, v) for u, v in zip(a, b))
+    assert got["0n"] == got["1n"] - (rows <= 4096)
