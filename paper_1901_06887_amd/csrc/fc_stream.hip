@@ -1,5 +1,6 @@
 // Grouped FC layer, weight-streaming tiles (see mt_device.h for the overview).
 #include "mt_device.h"
+#include <type_traits>
 
 namespace mt {
 
@@ -24,11 +25,41 @@ constexpr uint32_t kStageBytes = kChunkBricks * kBrickBytes;
 // transposition scratch at kTrOffset; both alias the stages, separated from them by barriers.
 constexpr uint32_t kTrOffset = kRedFloats * 4;
 constexpr uint32_t kFcLdsBytes = kTrOffset + 4 * kTrBytes;
+template <int ROWS> constexpr uint32_t fc_lds_bytes() { return kFcLdsBytes + (ROWS == kRowsAny ? 4 * kBrickBytes : 0); }      // (the tails of rows of any length)
 static_assert(kFcLdsBytes >= 2 * kStageBytes, "the two activation stages must fit");
 
 // split == 4: activations through LDS, weights through the register ring.
+// A lane's row of any length at any address: chunks that lie in it whole come as 16 bytes, wherever they begin; the others from a block of zeros (no lane reads past
+// its row), and the elements behind the last whole chunk, asked for one by one up front, take the place of the chunk that they begin.
+template <typename T> struct AnyChunk;
+template <> struct AnyChunk<__bf16> { typedef u32x4 type __attribute__((aligned(2))); };
+template <> struct AnyChunk<float> { typedef u32x4 type __attribute__((aligned(4))); };
+template <typename T> struct AnyRow {
+    static constexpr uint32_t EPC = 16 / sizeof(T);
+    typedef const __attribute__((address_space(1))) typename AnyChunk<T>::type* cptr_t;
+    typedef const __attribute__((address_space(1))) T* eptr_t;
+    eptr_t row;
+    uint32_t whole;            // elements in whole chunks (none: a padding row)
+    uint32_t rest;             // where the tail belongs
+    u32x4 tail;
+    __device__ __forceinline__ void init(const void* at, bool ok, uint32_t n)
+    {
+        row = (eptr_t)at;
+        rest = n / EPC * EPC;
+        whole = ok ? rest : 0;
+        T t[EPC];
+#pragma unroll
+        for (uint32_t e = 0; e < EPC; ++e) t[e] = row[min(rest + e, n - 1)];
+#pragma unroll
+        for (uint32_t e = 0; e < EPC; ++e) t[e] = ok && rest + e < n ? t[e] : (T)0.0f;
+        tail = __builtin_bit_cast(u32x4, t);
+    }
+    __device__ __forceinline__ u32x4 load(uint32_t k, const void* zeros) const { return *(k < whole ? (cptr_t)(row + k) : (cptr_t)zeros); }
+    __device__ __forceinline__ u32x4 at(uint32_t k, const u32x4& v) const { return k == rest ? tail : v; }
+};
+
 // row_of(block of 32 rows of the tile, lane, real): the submitted row of a lane (GATHER).
-template <typename T, int RB, bool GATHER, typename ROWS>
+template <typename T, int RB, int GATHER, typename ROWS>
 __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t seg0,
                                                      uint32_t nb, bool active, const ROWS& row_of, uint8_t* stages, f32x16 (&acc)[RB])
 {
@@ -58,13 +89,21 @@ __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Ti
     typedef const __attribute__((address_space(1))) u32x4* gptr_t;     // submitted rows live in global memory
     gptr_t rowp = nullptr;
     bool row_ok = false;
+    AnyRow<T> any;
     if (GATHER) {
-        rowp = (gptr_t)row_of(min(wave * 4 / KC, nrb - 1), lane & 31, &row_ok);
+        const void* at = row_of(min(wave * 4 / KC, nrb - 1), lane & 31, &row_ok);
+        rowp = (gptr_t)at;
+        if constexpr (GATHER == kRowsAny) {                  // the tail waits in LDS: these tiles use all the registers there are
+            any.init(at, row_ok, L.k_valid);
+            *(u32x4*)(stages + kFcLdsBytes + wave * kBrickBytes + lane * 16) = any.tail;
+        }
     }
     auto load_chunk = [&](uint32_t c, u32x4 (&xr)[4]) {
 #pragma unroll
         for (uint32_t j = 0; j < 4; ++j) {
-            if (GATHER) {
+            if (GATHER == kRowsAny) {
+                xr[j] = any.load((c * KC + xkk[j]) * KB + (lane >> 5) * EPC, a.zeros);
+            } else if (GATHER) {
                 const uint32_t k = (c * KC + xkk[j]) * KB + (lane >> 5) * EPC;
                 const bool ok = row_ok && k < L.k_valid;
                 const u32x4 v = rowp[(ok ? k : 0) / EPC];
@@ -74,9 +113,16 @@ __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Ti
             }
         }
     };
-    auto store_chunk = [&](uint32_t stage, const u32x4 (&xr)[4]) {
+    auto store_chunk = [&](uint32_t c, const u32x4 (&xr)[4]) {
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) *(u32x4*)(stages + stage * kStageBytes + (wave * 4 + j) * kBrickBytes + lane * 16) = xr[j];
+        for (uint32_t j = 0; j < 4; ++j) {
+            u32x4 v = xr[j];
+            if constexpr (GATHER == kRowsAny) {
+                const uint32_t k = (c * KC + xkk[j]) * KB;
+                if (k == any.rest / KB * KB) v = any.rest - k == (lane >> 5) * EPC ? *(const u32x4*)(stages + kFcLdsBytes + wave * kBrickBytes + lane * 16) : v;      // (uniform: one step of all)
+            }
+            *(u32x4*)(stages + (c & 1) * kStageBytes + (wave * 4 + j) * kBrickBytes + lane * 16) = v;
+        }
     };
 
     // K is walked in blocks of U steps, unrolled, so that ring slots (step % P) and, where a
@@ -102,7 +148,7 @@ __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Ti
     const uint8_t* st = stages + lane * 16;
     auto next_chunk = [&](uint32_t slot) {                    // slot = (c + 1) % NX, a constant at every call site
         lds_barrier();                                        // stage c&1 is complete; stage (c+1)&1 is free again
-        store_chunk((c + 1) & 1, xr[slot]);
+        store_chunk(c + 1, xr[slot]);
         load_chunk(c + 1 + NX, xr[slot]);
         st = stages + (c & 1) * kStageBytes + lane * 16;
         ++c;
@@ -134,7 +180,7 @@ __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Ti
 }
 
 // split < 4: every wave reads the activation bricks of its own K range directly.
-template <typename T, bool GATHER>
+template <typename T, int GATHER>
 __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t seg0,
                                                      uint32_t nb, uint32_t kq, uint32_t ks, const void* row, bool row_ok, f32x16& acc)     // GATHER: this lane's submitted row (a padding row: any)
 {
@@ -147,15 +193,21 @@ __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Ti
     const u32x4* xp = (const u32x4*)((const T*)act_of(a.act, L.in_buf) + (size_t)seg0 * a.S) + lane + ((size_t)(tl.m0 / kBrickRows) * nKB + kb0) * 64;
     typedef const __attribute__((address_space(1))) u32x4* gptr_t;     // submitted rows live in global memory
     const gptr_t rowp = (gptr_t)row;
+    AnyRow<T> any;
+    if constexpr (GATHER == kRowsAny) any.init(row, row_ok, L.k_valid);
     // (a submitted row's chunk is masked where it is used, not where it is asked for: that would wait for it)
     auto chunk_of = [&](uint32_t kk) { return (kb0 + kk) * KB + (lane >> 5) * EPC; };
     auto in_row = [&](uint32_t k) { return row_ok && k < L.k_valid; };
     auto load_x = [&](uint32_t kk) -> u32x4 {
         if (!GATHER) return xp[(size_t)kk * 64];
         const uint32_t k = chunk_of(kk);
+        if (GATHER == kRowsAny) return any.load(k, a.zeros);
         return rowp[(in_row(k) ? k : 0) / EPC];
     };
-    auto masked = [&](const u32x4& v, uint32_t kk) -> u32x4 { return !GATHER || in_row(chunk_of(kk)) ? v : u32x4{0, 0, 0, 0}; };
+    auto masked = [&](const u32x4& v, uint32_t kk) -> u32x4 {
+        if (GATHER == kRowsAny) return any.at(chunk_of(kk), v);
+        return !GATHER || in_row(chunk_of(kk)) ? v : u32x4{0, 0, 0, 0};
+    };
     u32x4 bq[P], aq[P];
 #pragma unroll
     for (int j = 0; j < P; ++j) {
@@ -320,7 +372,7 @@ __device__ __forceinline__ void fc_finish_split(const GemmArgs& a, const Tile& t
 }
 
 // A tile whose waves split K: 32 rows (fc_shape).
-template <typename T, bool GATHER>
+template <typename T, int GATHER>
 __device__ __forceinline__ void fc_split_tile(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t Mt, uint32_t seg0, const void* row, bool row_ok, T* xout, uint8_t* smem)
 {
     const uint32_t split = tl.split, ks = 4 / split, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -333,7 +385,7 @@ __device__ __forceinline__ void fc_split_tile(const GemmArgs& a, const Tile& tl,
     fc_finish_split<T>(a, tl, L, Mt, seg0, nb, kq, ks, active, xout, acc, smem);
 }
 
-template <typename T, int RB, bool GATHER, typename ROWS>
+template <typename T, int RB, int GATHER, typename ROWS>
 __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t Mt, uint32_t seg0, const ROWS& row_of, T* xout, uint8_t* smem)     // xout: the tenant's first output row
 {
     const uint32_t split = tl.split;
@@ -480,10 +532,10 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
 // for four workgroups per CU.  GATHER: layer 0 reads the submitted rows itself.  In the general kernel the wide tiles stand first
 // and the two kinds of layer 0 in kernels of their own: with both and the K-split tiles in front, 40 scalar registers were
 // spilled and layer 0 of 256 models of mixed depths took 175.9 us instead of 171.3.
-template <typename T, bool NARROW, bool GATHER, bool FEW>
+template <typename T, bool NARROW, int GATHER, bool FEW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 : 3, NARROW ? 4 : 3))) void fc_kernel(GemmArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t smem[kFcLdsBytes];
+    __shared__ __attribute__((aligned(16))) uint8_t smem[NARROW ? kFcLdsBytes : fc_lds_bytes<GATHER>()];
     __shared__ uint32_t owner_part[4];
     TileLookup<256, FEW ? 64 : 0> lookup;
     lookup.fetch(a);
@@ -567,7 +619,7 @@ __device__ __forceinline__ void entry_lists(const BatchArgs& b, uint32_t lane, u
     }
 }
 
-template <typename T>
+template <typename T, int ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void fc_entry_kernel(GemmArgs a, BatchArgs b)
 {
     constexpr uint32_t NIT = kEntryMaxRows / 64;
@@ -651,7 +703,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     const bool row_ok = (lane & 31) < tl.rows;
     const int32_t r = rows_of[wave][row_ok ? lane & 31 : 0];
     const void* row = (const uint8_t*)b.first.src + (size_t)(uint32_t)r * b.first.row_stride * sizeof(T);
-    fc_split_tile<T, true>(a, tl, L, Mt, seg0, row, row_ok, (T*)act_of(a.act, L.out_buf) + (size_t)seg0 * a.S, smem);
+    fc_split_tile<T, ROWS>(a, tl, L, Mt, seg0, row, row_ok, (T*)act_of(a.act, L.out_buf) + (size_t)seg0 * a.S, smem);
 }
 
 // The same for one submission of at most 4096 rows and any tiles: the workgroup's waves take a quarter of the rows each, count them by tenant in LDS and, once the
@@ -659,11 +711,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // the rows' addresses and the rows; the batcher's launch, alone on the chip for 5-7 us, is gone.  Passes and the line beside run_entry.  Bound as fc_kernel is: by the weight
 // stream, behind 2-3 us until the first weight load.  (With the ids in registers and masks from ballots, as above, 16 unrolled steps of them spilled 91 registers and the tiles took
 // half as long again; without the leader's addition 64 rows of one tenant added one by one, 4096 requests to one tenant 113 -> 123 us.)
-template <typename T>
+template <typename T, int ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void fc_entry_wide_kernel(GemmArgs a, BatchArgs b)
 {
     constexpr uint32_t NIT = kEntryWideRows / 256;
-    __shared__ __attribute__((aligned(16))) uint8_t smem[kFcLdsBytes];
+    __shared__ __attribute__((aligned(16))) uint8_t smem[fc_lds_bytes<ROWS>()];
     __shared__ uint32_t counts[4][65];                        // (the last one: rows of no tenant)
     __shared__ int32_t rows_of[kTileRows];
     uint8_t* const ids = smem + kStageBytes;                  // every row's tenant (0xff: none); until the second stage is written, behind a barrier
@@ -753,13 +805,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     };
     T* xout = (T*)act_of(a.act, L.out_buf) + (size_t)seg0 * a.S;
     if (__builtin_expect(tl.split == 4, 1)) {
-        if (__builtin_expect(tl.rows > (uint32_t)kBrickRows, 1)) fc_tile<T, 2, true>(a, tl, L, Mt, seg0, row_of, xout, smem);
-        else fc_tile<T, 1, true>(a, tl, L, Mt, seg0, row_of, xout, smem);
+        if (__builtin_expect(tl.rows > (uint32_t)kBrickRows, 1)) fc_tile<T, 2, ROWS>(a, tl, L, Mt, seg0, row_of, xout, smem);
+        else fc_tile<T, 1, ROWS>(a, tl, L, Mt, seg0, row_of, xout, smem);
         return;
     }
     bool row_ok;
     const void* row = row_of(0, lane & 31, &row_ok);
-    fc_split_tile<T, true>(a, tl, L, Mt, seg0, row, row_ok, xout, smem);
+    fc_split_tile<T, ROWS>(a, tl, L, Mt, seg0, row, row_ok, xout, smem);
 }
 
 // ---- launcher ------------------------------------------------------------
@@ -767,10 +819,15 @@ template <typename T>
 static void launch_fc_t(const GemmArgs& a, bool narrow, uint32_t grid, hipStream_t s)
 {
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, a); };
-    if (narrow && a.T <= 64) { if (a.gather) launch(fc_kernel<T, true, true, true>); else launch(fc_kernel<T, true, false, true>); }
-    else if (narrow) { if (a.gather) launch(fc_kernel<T, true, true, false>); else launch(fc_kernel<T, true, false, false>); }
-    else if (a.gather) launch(fc_kernel<T, false, true, false>);
-    else launch(fc_kernel<T, false, false, false>);
+    auto with = [&](auto rows_) {
+        constexpr int rows = decltype(rows_)::value;
+        if (!narrow) launch(fc_kernel<T, false, rows, false>);
+        else if (a.T <= 64) launch(fc_kernel<T, true, rows, true>);
+        else launch(fc_kernel<T, true, rows, false>);
+    };
+    if (a.gather == kRowsAny) with(std::integral_constant<int, kRowsAny>{});
+    else if (a.gather) with(std::integral_constant<int, kRowsChunked>{});
+    else with(std::integral_constant<int, kRowsStaged>{});
 }
 
 // grid: a bound of the tiles; eight workgroups more, of which the last does the batcher's part
@@ -778,13 +835,14 @@ hipError_t launch_fc_entry(const GemmArgs& a, const BatchArgs& b, uint32_t dtype
 {
     if (b.R > kEntryWideRows || b.T > kEntryMaxTenants || (!wide && b.R > kEntryMaxRows)) return hipErrorInvalidValue;
     grid = (grid + 7) / 8 * 8 + 8;
-    if (wide) {
-        if (dtype == MT_BF16) hipLaunchKernelGGL(fc_entry_wide_kernel<__bf16>, dim3(grid), dim3(256), 0, s, a, b);
-        else hipLaunchKernelGGL(fc_entry_wide_kernel<float>, dim3(grid), dim3(256), 0, s, a, b);
-        return hipGetLastError();
-    }
-    if (dtype == MT_BF16) hipLaunchKernelGGL(fc_entry_kernel<__bf16>, dim3(grid), dim3(256), 0, s, a, b);
-    else hipLaunchKernelGGL(fc_entry_kernel<float>, dim3(grid), dim3(256), 0, s, a, b);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, a, b); };
+    auto with = [&](auto rows_) {
+        constexpr int rows = decltype(rows_)::value;
+        if (wide) { if (dtype == MT_BF16) launch(fc_entry_wide_kernel<__bf16, rows>); else launch(fc_entry_wide_kernel<float, rows>); }
+        else if (dtype == MT_BF16) launch(fc_entry_kernel<__bf16, rows>);
+        else launch(fc_entry_kernel<float, rows>);
+    };
+    if (a.gather == kRowsAny) with(std::integral_constant<int, kRowsAny>{}); else with(std::integral_constant<int, kRowsChunked>{});
     return hipGetLastError();
 }
 

@@ -124,7 +124,7 @@ struct mt_ctx {
 
     // per layer index, over registered tenants: bounds that size the grouped launches
     uint32_t n_layer_slots = 0;
-    uint32_t max_in_len = 0;
+    uint32_t max_in_len = 0, max_fc_in_len = 0;      // longest input; ... of a model that starts with an FC layer
     // [kind][layer]: kind 0 = FC tiles, 1 = conv tiles, 2 = big FC tiles
     uint32_t max_nt[kListKinds][MT_MAX_LAYERS]{}, has_gap[MT_MAX_LAYERS]{};
     uint64_t gap_chunks[MT_MAX_LAYERS]{};            // most 16-byte pieces that a workgroup of a pooling layer of the index can have in flight (launch_gap)
@@ -634,7 +634,7 @@ void recompute_pool_fusion(mt_ctx* c)
 void recompute_bounds(mt_ctx* c)
 {
     c->n_layer_slots = 0;
-    c->max_in_len = 0; c->max_image_pixels = 0; c->min_layers = 0xffffffffu;
+    c->max_in_len = c->max_fc_in_len = 0; c->max_image_pixels = 0; c->min_layers = 0xffffffffu;
     c->fc_first_chunked = true; c->any_conv_first = c->any_fc_first = false;
     for (uint32_t& m : c->list_mask) m = 0;
     c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
@@ -677,6 +677,7 @@ void recompute_bounds(mt_ctx* c)
         c->min_reg_classes = std::min(c->min_reg_classes, t.dev.n_classes);
         if (t.dev.in_layout == kLayoutBricks) {
             c->any_fc_first = true;
+            c->max_fc_in_len = std::max(c->max_fc_in_len, t.dev.in_len);
             if ((t.dev.in_len * c->elem_size) % 16) c->fc_first_chunked = false;
         } else {
             c->max_image_pixels = std::max(c->max_image_pixels, t.dev.in_len / (t.dev.in_cin ? t.dev.in_cin : (uint32_t)kChanPad));
@@ -947,6 +948,26 @@ ConvPlan plan_conv(const mt_ctx* c, uint32_t l, uint64_t R, const std::vector<Na
     }
     if (split) { p.split = true; p.frames = false; p.tiles = tiles; }
     return p;
+}
+
+// How the FC layers of index 0 get their rows.  They read them themselves where every row is a whole number of 16-byte chunks at such addresses, and
+// else (a lane's 16 bytes begin anywhere, in two cache lines as often as not) while that is few lane addresses: a compute unit takes 2.4 clocks for each,
+// and all of a layer's column groups ask for every row.  Staged, and read so, us a pass, bf16: 301-333-520-37, 8 tenants, 5 / 200 / 20000 requests 28.7 / 30.6 / 86.1 -> 21.8 / 24.1 / 79.9;
+// 787-1024-512-10, 32 tenants, 200 / 1000 / 5000 (15300 lane addresses to a compute unit) 52.7 / 58.5 / 73.4 -> 41.4 / 52.2 / 73.1; 1023-4000-64, 1 tenant, 200 / 1000 (16400) / 5000
+// (82000) 43.8 / 55.7 / 111.9 -> 40.6 / 58.1 / 186.4; 3001-2500-10, 2 tenants, 200 (23000) 49.8 -> 64.9.  fp32, whose tiles wait for their MFMAs: 1023-4000-64, 1000 / 5000 (164000) 133.1 / 403.3 ->
+// 123.1 / 416.1, 3001-2500-10, 1000 (58000) 232.9 -> 232.4.
+// pending: as submitted, else chunked wherever the models allow.
+constexpr uint64_t kAnyRowsLanes = 14000, kAnyRowsLanesF32 = 128000;
+int first_rows(const mt_ctx* c, uint64_t R, bool split_k, bool big_possible, bool pending)
+{
+    if (!c->any_fc_first || c->no_fused_gather || big_possible) return kRowsStaged;
+    bool chunked = c->fc_first_chunked;
+    if (pending)
+        for (const Segment& sg : c->pending) chunked = chunked && ((uintptr_t)sg.src & 15) == 0 && ((uint64_t)sg.row_stride * c->elem_size) % 16 == 0;
+    if (chunked) return kRowsChunked;
+    const uint64_t chunks = (uint64_t)c->max_fc_in_len * c->elem_size / 16 + 1, groups = split_k ? (c->max_fc_per64_sk[0] + 1) / 2 : c->max_fc_per64[0];
+    const uint64_t lanes = std::max<uint64_t>((split_k ? kBrickRows : kTileRows) * chunks, R * groups * chunks / c->n_cus);
+    return lanes <= (c->elem_size == 2 ? kAnyRowsLanes : kAnyRowsLanesF32) ? kRowsAny : kRowsStaged;
 }
 
 // Whether layer 0 does the batcher's work in a run of one submission of R rows that it reads itself: few tenants, nothing but FC layers, and no model that is
@@ -1900,16 +1921,14 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
         hipLaunchKernelGGL(fill_zero_kernel, dim3((static_descr_words + 255) / 256), dim3(256), 0, s, rs.d_M, static_descr_words);
         HIP_TRY(c, hipGetLastError()); ++launches;
     }
-    // The FC kernel of layer 0 reads the submitted rows itself when every row is 16-byte aligned
-    // and a whole number of 16-byte chunks long; otherwise (and for CNN models, whose images are
+    // The FC kernel of layer 0 reads the submitted rows itself (first_rows); otherwise (and for CNN models, whose images are
     // channel-padded) a gather pass stages the inputs first.
     // The big-tile kernel reads bricks only (it was measured slower when it gathers rows itself,
     // since every row is then fetched in 16-byte pieces by each of a layer's column tiles):
     // whenever a tenant could reach it at layer 0, stage.
     const bool big_possible = big_enabled && c->max_nt[2][0] > 0 && tile_bound(c, 2, 0, R) >= c->big_min_tiles;
-    bool fuse_gather = c->any_fc_first && c->fc_first_chunked && !c->no_fused_gather && !big_possible;
-    for (const Segment& sg : c->pending)
-        if (((uintptr_t)sg.src & 15) || ((uint64_t)sg.row_stride * c->elem_size) % 16) fuse_gather = false;
+    const int rows = first_rows(c, R, split_k, big_possible, true);
+    const bool fuse_gather = rows != kRowsStaged;
     // Every workgroup of fc_entry_kernel looks up for itself which tenants there are, so it goes by those registered now.  What is
     // captured goes on to serve models registered later, which the one workgroup of the batcher can look up.
     const int entry = n_segs == 1 && fuse_gather && !captured ? run_entry(c, R, split_k) : kEntryNone;
@@ -1944,7 +1963,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             GemmArgs ga{};
             ga.tile_base = c->d_tile_base + ((size_t)kind * MT_MAX_LAYERS + l) * (T + 1);
             ga.T = T; ga.layer = l; ga.fc_split_k = split_k; ga.big_layers = b.big_layers;
-            ga.gather = (kind == 0 && l == 0 && fuse_gather); ga.perm = c->d_perm; ga.row_src = c->d_row_src;
+            ga.gather = kind == 0 && l == 0 ? rows : kRowsStaged; ga.perm = c->d_perm; ga.row_src = c->d_row_src;
             ga.fuse_head = fuse_head; ga.fuse_head_max = fuse_head_max; ga.out_vec_ok = out_vec_ok; ga.out = outp; ga.pool = kind == 1 && c->pool_fused[l];
             ga.store_through = kind == 1 && R * c->max_conv_work[l] * kBrickRows * c->elem_size <= kStoreThroughMaxBytes;
             ga.layers = c->d_layers; ga.off = c->d_off; ga.M = c->d_M; ga.act = bufs; ga.arena = c->d_arena;
@@ -2121,8 +2140,7 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
     const double run_flops = 2.0 * R * (c->n_registered ? c->sum_macs / c->n_registered : 0.0);
     const bool big_enabled = R >= (uint64_t)kBigMinBatch && run_flops >= kRidgeFlopsPerByte * (double)c->arena_used;
     const bool big_possible = big_enabled && c->max_nt[2][0] > 0 && tile_bound(c, 2, 0, R) >= c->big_min_tiles;
-    const bool fuse_gather = c->any_fc_first && c->fc_first_chunked && !c->no_fused_gather && !big_possible;
-    const bool split_k = run_split_k(c, R);
+    const bool split_k = run_split_k(c, R), fuse_gather = first_rows(c, R, split_k, big_possible, c->pending_rows == R) != kRowsStaged;
     const uint32_t fuse_head_max = fused_head_classes(c, split_k);
     const bool fuse_head = fuse_head_max > 0 && c->min_reg_classes <= fuse_head_max;
     uint32_t Tp = 64;

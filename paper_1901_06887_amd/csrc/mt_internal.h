@@ -94,6 +94,7 @@ constexpr uint32_t kPairMaxBlocks = 4, kPairLdsBytes = 52 * 1024;               
 constexpr uint32_t kFirstTilePixels = 1024, kFirstFrameBytes = 32 * 1024, kFirstPoolFrameBytes = 78 * 1024, kFirstMaxBytes = 152 * 1024;
 inline __host__ __device__ constexpr uint32_t first_scratch_bytes(uint32_t es) { return 8 * kBrickRows * (kBrickRows * es + 16 + 8); }
 
+enum : int { kRowsStaged = 0, kRowsChunked = 1, kRowsAny = 2 };     // GemmArgs::gather
 enum : uint32_t { kLayoutRows = 0, kLayoutBricks = 1 };
 constexpr uint32_t kKindNone = 0xffu;     // a layer index at which this tenant has nothing to run (its work was taken over by the layer before)
 
@@ -249,8 +250,8 @@ struct GemmArgs {
     uint32_t img_lds;             // conv launch with LDS-resident input: bytes of dynamic LDS (the largest frame)
     uint32_t mid_lds;             // launch of first convolutions with the ones behind them: bytes of LDS for the first layer's rows
     uint32_t first_cap;           // launch of first convolutions on the submitted images: most rows of a tile
-    // FC layer 0 can read the submitted rows itself (16-byte aligned rows whose length is a
-    // whole number of 16-byte chunks), which saves the staging pass:
+    // FC layer 0 can read the submitted rows itself, which saves the staging pass (kRowsChunked: 16-byte aligned rows whose length is a
+    // whole number of 16-byte chunks; kRowsAny):
     uint32_t gather; const int32_t* perm; const void* const* row_src;
     // a last layer whose classes all lie inside one tile finishes its rows itself (softmax, argmax,
     // outputs): at most fuse_head_max classes (32: one column block; 128: a whole tile of four, not

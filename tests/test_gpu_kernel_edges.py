@@ -584,3 +584,39 @@ def test_runs_of_any_tiles_without_a_batcher(monkeypatch, dtype, n_tenants, rows
     for a, b in zip(got["0"], got["1"]):
         assert all(np.array_equal(u, v) for u, v in zip(a, b))
     assert got["0n"] == got["1n"] - (rows <= 4096)
+
+
+# layer 0 reads rows of any length at any address: lengths around whole chunks and steps, rows that begin at odd elements with undefined values behind each, every kernel that
+# does so (few rows and many without the batcher, more tenants than it takes, several submissions).  Against the oracle, and to the bit against staged rows
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_in", [1, 3, 7, 8, 9, 31, 63, 64, 65, 301])
+@pytest.mark.parametrize("rows,n_tenants", [(19, 3), (700, 3), (90, 70)])
+def test_rows_of_any_length_at_any_address(monkeypatch, dtype, n_in, rows, n_tenants):
+    shapes = ([n_in, 40, 5], [n_in, 200, 70], [n_in, 300, 64, 7])
+    tenants = {t: wl.make_model(wl.mlp_layers(shapes[t % 3], wl.ACT_RELU), dtype, 396, t) for t in range(n_tenants)}
+    rng = np.random.default_rng(396)
+    x = rng.standard_normal((rows, n_in)).astype(np.float32)
+    ids = rng.integers(0, n_tenants, rows).astype(np.int32)
+    w = wl.Workload("any", dtype, tenants, ids, wl.round_to_bf16(x) if dtype == "bf16" else x)
+    stride = n_in + 4 + n_in % 2                                     # odd or even, and no two rows need be alike in alignment
+    buf = np.full(rows * stride + 1, np.nan, np.float32)
+    for r in range(rows):
+        buf[1 + r * stride:1 + r * stride + n_in] = w.inputs[r]
+    d_buf, d_ids = torch_io.to_device(buf[None], dtype), torch.from_numpy(ids).cuda()
+    at, es = d_buf.data_ptr() + d_buf.element_size(), d_buf.element_size()
+    got = {}
+    for off in ("0", "1"):
+        monkeypatch.setenv("MT_NO_FUSED_GATHER", off)
+        ctx = make_context(w, max_tenants=n_tenants)
+        got[off] = [check(w, "%s %d x %d" % (dtype, rows, n_in), ctx)]
+        for cuts in ([0, rows], [0, rows // 3, rows // 2, rows]):
+            out = torch_io.alloc_outputs(rows, ctx.cfg.max_classes)
+            for a, b in zip(cuts[:-1], cuts[1:]):
+                ctx.submit_batch(d_ids.data_ptr() + 4 * a, at + a * stride * es, b - a, stride)
+            ctx.debug_poison()
+            ctx.run(torch.cuda.current_stream().cuda_stream, out.labels.data_ptr(), out.probs.data_ptr(), out.logits.data_ptr(), out.n_classes.data_ptr(), rows, ctx.cfg.max_classes)
+            torch.cuda.synchronize()
+            got[off].append((out.logits.cpu().numpy().astype(np.float64), out.probs.cpu().numpy().astype(np.float64), out.labels.cpu().numpy(), out.n_classes.cpu().numpy()))
+            assert all(np.array_equal(u, v) for u, v in zip(got[off][0], got[off][-1]))
+        ctx.close()
+    assert all(np.array_equal(u, v) for u, v in zip(got["0"][0], got["1"][0]))
