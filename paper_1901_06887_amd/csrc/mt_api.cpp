@@ -96,6 +96,11 @@ constexpr size_t kPlansKept = 64;
 
 struct NamedRows { uint32_t tenant, rows; };   // requests of a tenant in the submissions that named it
 
+// The event behind every run orders runs of other streams of the same device behind it, on the device; nothing on the host or another device looks at it.  So it needs no
+// fence of the whole system, which wrote back the L2s at the end of every run: 64 fp32 requests to MLPs 22.5 -> 20.7 us a pass, 150 fp32 images to CNNs 132.9 -> 130.9,
+// 4096 requests to MLPs 100.4 -> 99.4.  (Whoever waits for the stream, or copies from it, has a fence of their own.)
+constexpr unsigned kSlotEvent = hipEventDisableTiming | hipEventDisableSystemFence;
+
 // Device scratch of one run in flight: batch descriptors, activation buffers, logits.  A run owns
 // one slot from its batcher to its last kernel; the weights and model tables are shared.
 struct RunSlot {
@@ -1386,11 +1391,11 @@ mt_status mt_create(mt_ctx** out, const mt_config* cfg)
             CREATE_TRY(hipMalloc(&r.d_act[i], (uint64_t)c->P_cap * c->S * c->elem_size));
         }
         CREATE_TRY(hipMalloc((void**)&r.d_logits, (uint64_t)c->P_cap * c->C_pad * 4));
-        CREATE_TRY(hipEventCreateWithFlags(&r.done, hipEventDisableTiming));
+        CREATE_TRY(hipEventCreateWithFlags(&r.done, kSlotEvent));
     }
     bind_slot(c, c->slots[0]);
     CREATE_TRY(hipGetSymbolAddress((void**)&c->static_scratch, HIP_SYMBOL(scratch)));      // this device's copy of the array
-    CREATE_TRY(hipEventCreateWithFlags(&c->static_slot.done, hipEventDisableTiming));
+    CREATE_TRY(hipEventCreateWithFlags(&c->static_slot.done, kSlotEvent));
     if (c->cache) {
         CREATE_TRY(hipEventCreateWithFlags(&c->cache_event, hipEventDisableTiming));
     }
