@@ -328,7 +328,7 @@ __global__ __launch_bounds__(kBatchThreads) void batcher_kernel(BatchArgs a)
             const uint32_t x = f[j].x, y = f[j].y, M = Mt[j];
             const bool conv = x >> 31, sk = a.fc_split_k && !conv && x;                // this run's FC tiles: one column block each, 32 rows
             const uint32_t blocks = x & 0x7fffffffu;                                   // (a convolution's)
-            const uint32_t groups = sk ? y / kBrickRows : x & 0x3fffffffu;
+            const uint32_t groups = sk ? ((x >> 29) & 1 && a.fc_whole ? 1 : y / kBrickRows) : x & 0x1fffffffu;
             const bool big = big_here && !conv && x && fc_is_big(M, y);
             // conv: rows = requests * output pixels per tile; FC: tiles of 64 or 32 rows over the rows that big tiles leave
             // (the few rows that big tiles leave in a narrow layer are tiled one column block and 32 rows at a time,

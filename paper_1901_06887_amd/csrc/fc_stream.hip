@@ -180,16 +180,19 @@ __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Ti
 }
 
 // split < 4: every wave reads the activation bricks of its own K range directly.
-template <typename T, int GATHER>
+// NB: column blocks at once (nb, and nb2).
+template <typename T, int GATHER, int NB = 1>
 __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t seg0,
-                                                     uint32_t nb, uint32_t kq, uint32_t ks, const void* row, bool row_ok, f32x16& acc)     // GATHER: this lane's submitted row (a padding row: any)
+                                                     uint32_t nb, uint32_t nb2, uint32_t kq, uint32_t ks, const void* row, bool row_ok, f32x16 (&acc)[NB])     // GATHER: this lane's submitted row (a padding row: any)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC;
-    constexpr int P = 8;                                      // bricks of either operand in flight per wave
+    constexpr int P = NB == 1 ? 8 : 4;                        // steps in flight per wave
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t nKB = L.K / KB;
     const uint32_t cnt = nKB / ks, kb0 = kq * cnt;
-    const u32x4* wp = (const u32x4*)(a.arena + L.w_off) + ((size_t)nb * nKB + kb0) * 64 + lane;
+    const u32x4* wp[NB];
+#pragma unroll
+    for (int c = 0; c < NB; ++c) wp[c] = (const u32x4*)(a.arena + L.w_off) + ((size_t)(c ? nb2 : nb) * nKB + kb0) * 64 + lane;
     const u32x4* xp = (const u32x4*)((const T*)act_of(a.act, L.in_buf) + (size_t)seg0 * a.S) + lane + ((size_t)(tl.m0 / kBrickRows) * nKB + kb0) * 64;
     typedef const __attribute__((address_space(1))) u32x4* gptr_t;     // submitted rows live in global memory
     const gptr_t rowp = (gptr_t)row;
@@ -208,11 +211,20 @@ __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Ti
         if (GATHER == kRowsAny) return any.at(chunk_of(kk), v);
         return !GATHER || in_row(chunk_of(kk)) ? v : u32x4{0, 0, 0, 0};
     };
-    u32x4 bq[P], aq[P];
+    u32x4 bq[P][NB], aq[P];
+    auto load_w = [&](int j, uint32_t kk) {
+#pragma unroll
+        for (int c = 0; c < NB; ++c) bq[j][c] = wp[c][(size_t)kk * 64];
+    };
+    auto step = [&](int j, uint32_t kk) {
+        const u32x4 x = masked(aq[j], kk);
+#pragma unroll
+        for (int c = 0; c < NB; ++c) Mma<T>::run(acc[c], x, bq[j][c]);
+    };
 #pragma unroll
     for (int j = 0; j < P; ++j) {
         const uint32_t kk = min((uint32_t)j, cnt - 1);
-        bq[j] = wp[(size_t)kk * 64];
+        load_w(j, kk);
         aq[j] = load_x(kk);
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -223,9 +235,9 @@ __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Ti
     for (uint32_t g = 0; g < full; ++g) {
 #pragma unroll
         for (int j = 0; j < P; ++j) {
-            Mma<T>::run(acc, masked(aq[j], g * P + j), bq[j]);
+            step(j, g * P + j);
             const uint32_t kk = min(g * P + j + P, cnt - 1);
-            bq[j] = wp[(size_t)kk * 64];
+            load_w(j, kk);
             aq[j] = load_x(kk);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -233,7 +245,69 @@ __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Ti
     const uint32_t rem = cnt - full * P;                      // the slots already hold the remaining bricks
 #pragma unroll
     for (int j = 0; j < P; ++j)
-        if ((uint32_t)j < rem) Mma<T>::run(acc, masked(aq[j], full * P + j), bq[j]);
+        if ((uint32_t)j < rem) step(j, full * P + j);
+}
+
+// The rows of a tile whose logits stand in LDS as [row][class], LRS floats to a row, at most 32 Q classes: softmax, argmax, outputs in submission order, eight
+// threads a row.
+template <uint32_t Q, uint32_t LRS>
+__device__ __forceinline__ void fc_finish_rows(const GemmArgs& a, const float* lt, uint32_t C, uint32_t mb, uint32_t Mt, uint32_t seg0)
+{
+    const uint32_t tid = threadIdx.x, row = tid >> 3, part = tid & 7, m = mb + row;
+    if (m >= Mt) return;                                                 // the eight threads of a row are neighbours in one wave
+    const uint32_t sub = (uint32_t)a.perm[seg0 + m];
+    f32x4 z[Q], ez[Q];
+    float mx = -INFINITY; int32_t best = 0x7fffffff;
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q) {                                   // thread `part` holds classes 4 part + 32 q + {0..3}
+        z[q] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        if (q * kBrickRows < C) z[q] = *(const f32x4*)(lt + row * LRS + q * kBrickRows + part * 4);
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) {
+            const uint32_t c = q * kBrickRows + part * 4 + e;
+            if (c >= C) z[q][e] = -INFINITY;
+            if (z[q][e] > mx) { mx = z[q][e]; best = (int32_t)c; }      // increasing index: the first hit is this thread's lowest
+        }
+    }
+#pragma unroll
+    for (int d = 4; d >= 1; d >>= 1) {
+        const float omx = __shfl_xor(mx, d);
+        const int32_t ob = __shfl_xor(best, d);
+        if (omx > mx || (omx == mx && ob < best)) { mx = omx; best = ob; }
+    }
+    best = head_label(best, lt[row * LRS]);
+    float sum = 0.0f;
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q)
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) { ez[q][e] = q * kBrickRows + part * 4 + e < C ? __expf(z[q][e] - mx) : 0.0f; sum += ez[q][e]; }
+#pragma unroll
+    for (int d = 4; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+    const float inv = 1.0f / sum;
+    if (part == 0) {
+        a.out.labels[sub] = best;
+        if (a.out.n_classes) a.out.n_classes[sub] = (int32_t)C;
+    }
+    float* pr = a.out.probs ? a.out.probs + (size_t)sub * a.out.row_stride : nullptr;
+    float* lg = a.out.logits ? a.out.logits + (size_t)sub * a.out.row_stride : nullptr;
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q) {
+        const uint32_t c0 = q * kBrickRows + part * 4;
+        f32x4 pv, lv;
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) { const bool in = c0 + e < C; pv[e] = in ? ez[q][e] * inv : 0.0f; lv[e] = in ? z[q][e] : 0.0f; }
+        if (a.out_vec_ok) {
+            if (c0 < a.out.row_stride) { if (pr) *(f32x4*)(pr + c0) = pv; if (lg) *(f32x4*)(lg + c0) = lv; }
+        } else {
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e)
+                if (c0 + e < a.out.row_stride) { if (pr) pr[c0 + e] = pv[e]; if (lg) lg[c0 + e] = lv[e]; }
+        }
+    }
+    for (uint32_t c = Q * kBrickRows + part; c < a.out.row_stride; c += 8) {      // wider output rows: zeros past the tile
+        if (pr) pr[c] = 0.0f;
+        if (lg) lg[c] = 0.0f;
+    }
 }
 
 // End of a tile whose waves split K (split < 4; ks = 4 / split waves share a column block): the partial sums meet in LDS and are
@@ -287,62 +361,7 @@ __device__ __forceinline__ void fc_finish_split(const GemmArgs& a, const Tile& t
                 for (uint32_t e = 0; e < 4; ++e) lt[(8 * (kq * ng + i) + 4 * lh + e) * LRS + cb * kBrickRows + li] = y[i][e];
             }
         __syncthreads();
-        const uint32_t C = L.N, row = tid >> 3, part = tid & 7, m = mb + row;
-        if (m < Mt) {                                                    // the eight threads of a row are neighbours in one wave
-            const uint32_t sub = (uint32_t)a.perm[seg0 + m];
-            f32x4 z[MAXG], ez[MAXG];
-            float mx = -INFINITY; int32_t best = 0x7fffffff;
-#pragma unroll
-            for (uint32_t q = 0; q < MAXG; ++q) {                        // thread `part` holds classes 4 part + 32 q + {0..3}
-                z[q] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-                if (q < split) z[q] = *(const f32x4*)(lt + row * LRS + q * kBrickRows + part * 4);
-#pragma unroll
-                for (uint32_t e = 0; e < 4; ++e) {
-                    const uint32_t c = q * kBrickRows + part * 4 + e;
-                    if (c >= C) z[q][e] = -INFINITY;
-                    if (z[q][e] > mx) { mx = z[q][e]; best = (int32_t)c; }      // increasing index: the first hit is this thread's lowest
-                }
-            }
-#pragma unroll
-            for (int d = 4; d >= 1; d >>= 1) {
-                const float omx = __shfl_xor(mx, d);
-                const int32_t ob = __shfl_xor(best, d);
-                if (omx > mx || (omx == mx && ob < best)) { mx = omx; best = ob; }
-            }
-            best = head_label(best, lt[row * LRS]);
-            float sum = 0.0f;
-#pragma unroll
-            for (uint32_t q = 0; q < MAXG; ++q)
-#pragma unroll
-                for (uint32_t e = 0; e < 4; ++e) { ez[q][e] = q * kBrickRows + part * 4 + e < C ? __expf(z[q][e] - mx) : 0.0f; sum += ez[q][e]; }
-#pragma unroll
-            for (int d = 4; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
-            const float inv = 1.0f / sum;
-            if (part == 0) {
-                a.out.labels[sub] = best;
-                if (a.out.n_classes) a.out.n_classes[sub] = (int32_t)C;
-            }
-            float* pr = a.out.probs ? a.out.probs + (size_t)sub * a.out.row_stride : nullptr;
-            float* lg = a.out.logits ? a.out.logits + (size_t)sub * a.out.row_stride : nullptr;
-#pragma unroll
-            for (uint32_t q = 0; q < MAXG; ++q) {
-                const uint32_t c0 = q * kBrickRows + part * 4;
-                f32x4 pv, lv;
-#pragma unroll
-                for (uint32_t e = 0; e < 4; ++e) { const bool in = c0 + e < C; pv[e] = in ? ez[q][e] * inv : 0.0f; lv[e] = in ? z[q][e] : 0.0f; }
-                if (a.out_vec_ok) {
-                    if (c0 < a.out.row_stride) { if (pr) *(f32x4*)(pr + c0) = pv; if (lg) *(f32x4*)(lg + c0) = lv; }
-                } else {
-#pragma unroll
-                    for (uint32_t e = 0; e < 4; ++e)
-                        if (c0 + e < a.out.row_stride) { if (pr) pr[c0 + e] = pv[e]; if (lg) lg[c0 + e] = lv[e]; }
-                }
-            }
-            for (uint32_t c = MAXG * kBrickRows + part; c < a.out.row_stride; c += 8) {      // wider output rows: zeros past the tile
-                if (pr) pr[c] = 0.0f;
-                if (lg) lg[c] = 0.0f;
-            }
-        }
+        fc_finish_rows<MAXG, LRS>(a, lt, L.N, mb, Mt, seg0);
         return;
     }
     if (L.is_last) {
@@ -378,11 +397,47 @@ __device__ __forceinline__ void fc_split_tile(const GemmArgs& a, const Tile& tl,
     const uint32_t split = tl.split, ks = 4 / split, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t nb = tl.n0 / kBrickRows + (wave % split), kq = wave / split;
     const bool active = nb < L.N_pad / kBrickRows;
-    f32x16 acc;
+    f32x16 acc[1];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-    if (active) fc_accumulate_direct<T, GATHER>(a, tl, L, seg0, nb, kq, ks, row, row_ok, acc);
-    fc_finish_split<T>(a, tl, L, Mt, seg0, nb, kq, ks, active, xout, acc, smem);
+    for (int v = 0; v < 16; ++v) acc[0][v] = 0.0f;
+    if (active) fc_accumulate_direct<T, GATHER>(a, tl, L, seg0, nb, nb, kq, ks, row, row_ok, acc);
+    fc_finish_split<T>(a, tl, L, Mt, seg0, nb, kq, ks, active, xout, acc[0], smem);
+}
+
+// A last layer of 33 to 128 classes in a run whose tiles split K: the tile takes all its column blocks, two at a time, and finishes its rows, where a tile per block left them to a
+// launch of their own.  Sums as in those.  Bound by its chain of trips like them: the second pair of blocks adds 1 us, the head's launch took 4 (and 3 of the host).
+template <typename T>
+__device__ __forceinline__ void fc_whole_tile(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t Mt, uint32_t seg0, uint8_t* smem)
+{
+    constexpr uint32_t LRS = kTileCols + 4;                                  // floats per row of the logits tile
+    static_assert(kTrOffset + kBrickRows * LRS * 4 <= kFcLdsBytes, "behind the partial sums");
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5, blocks = L.N_pad / kBrickRows;
+    float *red = (float*)smem, *lt = (float*)(smem + kTrOffset);
+    const float* bias = (const float*)(a.arena + L.b_off);
+    for (uint32_t nb = 0; nb < blocks; nb += 2) {
+        const uint32_t nb2 = min(nb + 1, blocks - 1);
+        const float bv[2] = {bias[nb * kBrickRows + li], bias[nb2 * kBrickRows + li]};
+        f32x16 acc[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[c][v] = 0.0f;
+        fc_accumulate_direct<T, kRowsStaged, 2>(a, tl, L, seg0, nb, nb2, wave, 4, nullptr, false, acc);
+#pragma unroll
+        for (uint32_t c = 0; c < 2; ++c) {
+            __syncthreads();
+#pragma unroll
+            for (uint32_t g = 0; g < 4; ++g) *(f32x4*)(red + wave * 1024 + g * 256 + lane * 4) = f32x4{acc[c][4 * g], acc[c][4 * g + 1], acc[c][4 * g + 2], acc[c][4 * g + 3]};
+            __syncthreads();
+            f32x4 y = *(const f32x4*)(red + wave * 256 + lane * 4);
+#pragma unroll
+            for (uint32_t q = 1; q < 4; ++q) y += *(const f32x4*)(red + q * 1024 + wave * 256 + lane * 4);
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) lt[(8 * wave + 4 * lh + e) * LRS + (c ? nb2 : nb) * kBrickRows + li] = y[e] + bv[c];      // (an odd last block is written twice)
+        }
+    }
+    __syncthreads();
+    fc_finish_rows<kTileCols / kBrickRows, LRS>(a, lt, L.N, tl.m0, Mt, seg0);
 }
 
 template <typename T, int RB, int GATHER, typename ROWS>
@@ -553,6 +608,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 
     const bool big = ((*a.big_layers >> a.layer) & 1) && fc_is_big(Mt, L.N_pad);
     uint32_t groups, trows;
     fc_shape(L.N_pad, a.fc_split_k || (big && big_remainder_split_k(L.N_pad)), &tl.split, &groups, &trows);
+    const bool whole = NARROW && GATHER == kRowsStaged && a.fc_whole && L.is_last && fc_whole(L.N_pad);      // all column blocks in one tile (local / mt_ is 0)
     const uint32_t first = big ? big_rows(Mt) : 0;
     const uint32_t mt_ = ceil_div(Mt - first, trows);
     tl.m0 = first + (local % mt_) * trows;
@@ -578,6 +634,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 
     if (GATHER) {
         row = row_of(0, threadIdx.x & 31, &row_ok);
     }
+    if constexpr (NARROW && GATHER == kRowsStaged) {
+        if (whole) { fc_whole_tile<T>(a, tl, L, Mt, seg0, smem); return; }
+    }
     fc_split_tile<T, GATHER>(a, tl, L, Mt, seg0, row, row_ok, xout, smem);
 }
 
@@ -592,7 +651,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 
 __device__ __forceinline__ uint32_t entry_tiles(const BatchArgs& b, const uint4& f, uint32_t M)      // streaming FC tiles of a tenant, as the batcher counts them
 {
     const bool sk = b.fc_split_k && f.x;
-    const uint32_t groups = sk ? f.y / kBrickRows : f.x & 0x3fffffffu, sh = sk || ((f.x >> 30) & 1) ? 5 : 6;
+    const uint32_t groups = sk ? ((f.x >> 29) & 1 && b.fc_whole ? 1 : f.y / kBrickRows) : f.x & 0x1fffffffu, sh = sk || ((f.x >> 30) & 1) ? 5 : 6;
     return f.x >> 31 ? 0 : ((M + (1u << sh) - 1) >> sh) * groups;
 }
 // What the launches behind the first one read, by one wave: counts and offsets (a lane is a tenant), padding rows.

@@ -178,6 +178,7 @@ struct mt_ctx {
     uint32_t max_image_pixels = 0;             // most pixels in a submitted image (models whose first layer is a convolution)
     uint32_t act_buffers = 2;      // activation buffers every run slot holds (grows when a model with skip connections needs more)
     uint32_t max_reg_classes = 0, min_reg_classes = 0;
+    bool first_is_wide_last = false;           // some registered model is one layer of 33 to 128 classes
     uint32_t no_fused_head = 0;    // tuning/testing: always run the separate head kernel
     uint32_t no_fused_pool = 0;    // tuning/testing: always run the separate pooling kernel
     uint32_t no_fused_add = 0;     // tuning/testing: residual additions always run as launches of their own
@@ -495,7 +496,7 @@ void fill_facts(const mt_ctx* c, const HostTenant& ht, uint32_t (*w)[kFactWords]
     for (uint32_t l = 0; l < ht.n_layers; ++l) {
         const LayerDev& L = ht.layers[l].dev;
         if (L.kind == MT_FC) {
-            w[l][0] = fc_groups(L.N_pad, c->fc_split_k) | (fc_tile_rows(L.N_pad, c->fc_split_k) == kTileRows ? 0u : 1u << 30);
+            w[l][0] = fc_groups(L.N_pad, c->fc_split_k) | (fc_tile_rows(L.N_pad, c->fc_split_k) == kTileRows ? 0u : 1u << 30) | (l > 0 && L.is_last && fc_whole(L.N_pad) ? 1u << 29 : 0u);
             w[l][1] = L.N_pad;
         } else if (L.kind == MT_CONV2D) {
             w[l][0] = L.N_pad / kBrickRows | 1u << 31;
@@ -642,7 +643,7 @@ void recompute_bounds(mt_ctx* c)
     c->max_in_len = c->max_fc_in_len = 0; c->max_image_pixels = 0; c->min_layers = 0xffffffffu;
     c->fc_first_chunked = true; c->any_conv_first = c->any_fc_first = false;
     for (uint32_t& m : c->list_mask) m = 0;
-    c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->sum_macs = 0.0;
+    c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->first_is_wide_last = false; c->sum_macs = 0.0;
     c->first_on = !c->no_conv_first; c->first_pool = c->first_plain = false; c->pair_on = !c->no_conv_pair;
     c->first_max_ks = c->first_max_rows = c->pair_blocks = c->n_conv_first = 0; c->first_max_tiles = 0;
     for (const HostTenant& t : c->tenants) {         // (ahead of the others: it says which max-pools have a launch)
@@ -682,6 +683,7 @@ void recompute_bounds(mt_ctx* c)
         c->min_reg_classes = std::min(c->min_reg_classes, t.dev.n_classes);
         if (t.dev.in_layout == kLayoutBricks) {
             c->any_fc_first = true;
+            if (t.layers[0].dev.is_last && fc_whole(t.layers[0].dev.N_pad)) c->first_is_wide_last = true;
             c->max_fc_in_len = std::max(c->max_fc_in_len, t.dev.in_len);
             if ((t.dev.in_len * c->elem_size) % 16) c->fc_first_chunked = false;
         } else {
@@ -991,13 +993,16 @@ int run_entry(const mt_ctx* c, uint64_t R, bool split_k)
     return R >= kEntryWideMin && R <= kEntryWideRows && tile_bound(c, 0, 0, R, split_k) <= kEntryWideTiles ? kEntryWide : kEntryNone;
 }
 
-// Most classes a last layer may have for its FC tiles to finish their rows themselves (softmax,
-// argmax, outputs) in a run: one column block (32), or a whole tile of four (128) where the run's
-// tiles are not single column blocks; 0: the head kernel does every row.
-uint32_t fused_head_classes(const mt_ctx* c, bool split_k)
+// Whether last layers of 33 to 128 classes take tiles of all their column blocks in a run whose tiles split K (fc_whole_tile).  Not where such a layer is a model's first, which
+// reads submitted rows; nor in captured runs, whose replays may meet such a model.
+bool run_whole(const mt_ctx* c, bool split_k, bool captured) { return split_k && !captured && !c->no_fused_head && !c->first_is_wide_last; }
+
+// Most classes a last layer may have for its FC tiles to finish their rows themselves (softmax, argmax, outputs): one column block (32), or a whole tile of
+// four (128) where the run's tiles are not single column blocks, or take all of such a layer's; 0: the head kernel does every row.
+uint32_t fused_head_classes(const mt_ctx* c, bool split_k, bool whole)
 {
     if (c->no_fused_head) return 0;
-    return split_k ? (uint32_t)kBrickRows : (uint32_t)kTileCols;
+    return split_k && !whole ? (uint32_t)kBrickRows : (uint32_t)kTileCols;
 }
 
 // ---- validation of a layer chain; fills dev layouts (without arena offsets) -------------
@@ -1902,12 +1907,12 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
     }
     const OutPtrs outp{out->labels, out->probs, out->logits, out->n_classes, out->row_stride};
     b.out = outp;
-    // A last layer of at most 32 classes is one column block: its FC tiles finish their rows
-    // themselves.
-    // ... and one of at most 128 classes is one tile of four column blocks, unless this run's tiles
-    // are single column blocks (the K-split shape of small runs).
-    const uint32_t fuse_head_max = fused_head_classes(c, split_k);
+    // A last layer of at most 32 classes is one column block: its FC tiles finish their rows themselves; and one of at most 128 classes is one tile of four column blocks,
+    // or (the K-split shape of small runs) one that takes them in turn.
+    const bool whole = run_whole(c, split_k, captured);
+    const uint32_t fuse_head_max = fused_head_classes(c, split_k, whole);
     const bool fuse_head = fuse_head_max > 0 && c->min_reg_classes <= fuse_head_max;
+    b.fc_whole = whole;
     const uint32_t head_min_classes = fuse_head ? fuse_head_max + 1 : 0;
     const bool out_vec_ok = out->row_stride % 4 == 0 && ((uintptr_t)out->probs & 15) == 0 && ((uintptr_t)out->logits & 15) == 0;
     if (c->profiling) for (uint32_t i = 0; i < kProfSlots; ++i) c->prof_used[i] = false;
@@ -1967,7 +1972,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             if (grid == 0 || (kind == 2 && (!big_enabled || grid < c->big_min_tiles))) continue;   // no big tiles possible: the batcher made none
             GemmArgs ga{};
             ga.tile_base = c->d_tile_base + ((size_t)kind * MT_MAX_LAYERS + l) * (T + 1);
-            ga.T = T; ga.layer = l; ga.fc_split_k = split_k; ga.big_layers = b.big_layers;
+            ga.T = T; ga.layer = l; ga.fc_split_k = split_k; ga.fc_whole = whole; ga.big_layers = b.big_layers;
             ga.gather = kind == 0 && l == 0 ? rows : kRowsStaged; ga.perm = c->d_perm; ga.row_src = c->d_row_src;
             ga.fuse_head = fuse_head; ga.fuse_head_max = fuse_head_max; ga.out_vec_ok = out_vec_ok; ga.out = outp; ga.pool = kind == 1 && c->pool_fused[l];
             ga.store_through = kind == 1 && R * c->max_conv_work[l] * kBrickRows * c->elem_size <= kStoreThroughMaxBytes;
@@ -2146,7 +2151,7 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
     const bool big_enabled = R >= (uint64_t)kBigMinBatch && run_flops >= kRidgeFlopsPerByte * (double)c->arena_used;
     const bool big_possible = big_enabled && c->max_nt[2][0] > 0 && tile_bound(c, 2, 0, R) >= c->big_min_tiles;
     const bool split_k = run_split_k(c, R), fuse_gather = first_rows(c, R, split_k, big_possible, c->pending_rows == R) != kRowsStaged;
-    const uint32_t fuse_head_max = fused_head_classes(c, split_k);
+    const uint32_t fuse_head_max = fused_head_classes(c, split_k, run_whole(c, split_k, false));
     const bool fuse_head = fuse_head_max > 0 && c->min_reg_classes <= fuse_head_max;
     uint32_t Tp = 64;
     while (Tp < T) Tp <<= 1;

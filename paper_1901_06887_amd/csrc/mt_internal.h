@@ -56,6 +56,8 @@ inline __host__ __device__ uint32_t big_rows(uint32_t rows)
 // (c5's last layer: 35 -> 19 us; the hidden layers would go from 39 to 44 us, their weights read once more).
 constexpr int kBigRemSplitMaxCols = 1024;
 inline __host__ __device__ bool big_remainder_split_k(uint32_t n_pad) { return n_pad <= (uint32_t)kBigRemSplitMaxCols; }
+// Last layers of more than one column block whose rows one tile can finish all the same: in runs whose tiles split K such a tile takes all the blocks.
+inline __host__ __device__ bool fc_whole(uint32_t n_pad) { return n_pad > (uint32_t)kBrickRows && n_pad <= (uint32_t)kTileCols; }
 constexpr uint32_t kEntryMaxRows = 256, kEntryWideRows = 4096, kEntryMaxTenants = 64;   // runs whose first launch may do the batcher's work: a few rows and one tenant to a lane
 constexpr int kRankRows = 1024;     // rows per workgroup of the ranking kernel
 constexpr int kRankMinRows = 8192;  // smaller batches are ranked by the batcher's single workgroup (one launch less)
@@ -191,6 +193,7 @@ struct BatchArgs {
     Segment first;         // copy of segs[0]: the common one-segment run never reads host memory
     uint32_t elem_size;
     uint32_t fc_split_k;   // 1: FC tiles take one column block each and split K four ways
+    uint32_t fc_whole;     // 1: ... but last layers of 33 to 128 classes a tile for all their blocks, which finishes its rows
     uint32_t conv_split[(MT_MAX_LAYERS + 31) / 32];   // layer indices (bit l % 32 of word l / 32) whose convolution launch takes tiles of 32 pixels and one channel block
     uint32_t plan;         // registrations and removals before the run was enqueued, and one: which tenants it serves (`serves`)
     uint32_t captured;     // ... by TenantDev::covered
@@ -201,7 +204,7 @@ struct BatchArgs {
     const TenantDev* tenants;
     // What the tile lists need to know of every tenant-layer: facts[layer][T tenants][kFactWords], so that the 64 tenants of
     // a wave's load lie side by side.
-    // Word 0, FC: column groups of the layer's tiles, bit 30: tiles of 32 rows instead of 64; convolution: bit 31 and the
+    // Word 0, FC: column groups of the layer's tiles, bit 30: tiles of 32 rows instead of 64, bit 29: a last layer, not the first, that fc_whole holds for; convolution: bit 31 and the
     // channel blocks of 32 (a tile takes four of them, or one where the launch splits K); 0: no tiles (pooling, or no such layer).
     // Word 1: padded outputs (FC), rows per request by which the tiles are counted (convolution: conv_tile_rows).  Word 2: a convolution's output pixels.
     // Word 3, a first convolution that can read the submitted images: rows of an image, and above 16 bits most rows of a tile; the same of a second
@@ -242,7 +245,7 @@ struct GatherArgs {
 };
 
 struct GemmArgs {
-    const uint32_t* tile_base; uint32_t T; uint32_t layer; uint32_t fc_split_k;
+    const uint32_t* tile_base; uint32_t T; uint32_t layer; uint32_t fc_split_k; uint32_t fc_whole;
     const uint32_t* big_layers;   // the batcher's decision per layer index (see BatchArgs)
     uint32_t big_vgrid;           // big-tile launch whose workgroups walk several tiles: the grid of one tile per workgroup that they walk
     uint32_t pool;                // conv launch: the layers with pool_fill write the pooled activation instead of their own
