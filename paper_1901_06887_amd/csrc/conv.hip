@@ -273,6 +273,7 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
     typedef const __attribute__((address_space(1))) u32x4* gptr_t;
     __shared__ __attribute__((aligned(16))) uint8_t lds[NS * kStageBytes];
     __shared__ uint32_t owner_part[4 * (1 + PW)];
+    __shared__ __attribute__((aligned(16))) float bias_l[kBrickBytes / 4];      // the tile's bias (whole bricks are loaded)
     const uint32_t tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
     const uint32_t wave_all = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave_all % 4;
     const bool loader = !PW || wave_all >= 4, worker = !PW || wave_all < 4;     // who issues the loads, who multiplies
@@ -395,6 +396,8 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
     // the L1 -> LDS path ~270 clocks to accept, during which every wave stood at its load instructions
     // with no MFMA in flight: a workgroup alone on its CU spent as long on that as on its MFMAs.
     if (loader) {
+        // the bias goes ahead of the chunks: behind the K loop it was a trip to memory of its own (lanes past the tile's channels repeat its last ones)
+        if (wave == 0) lds_dma16((gptr_t)(const u32x4*)((const float*)(a.arena + L.b_off) + nb0 * kBrickRows) + min(lane, ncb * (kBrickRows / 4) - 1), bias_l);
 #pragma unroll
         for (uint32_t c = 0; c < NS - 1; ++c) fetch_chunk(c);
     }
@@ -468,14 +471,9 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
     }
     // trailing loads have landed and every wave is done with the ring: its memory now serves as
     // the waves' store scratch
-    // (this wave's bias values, the same for all its pixel blocks, are fetched in front of that
-    // wait: fetched block by block they put a memory round trip per block on the tile's tail)
-    const float* bias = (const float*)(a.arena + L.b_off);
     const uint32_t nbase = (nb0 + (active ? wc : 0)) * kBrickRows;
-    f32x4 bias_q[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias + nbase + 8 * g + 4 * lh);   // bias is padded to N_pad
-    // (what an addition done here adds likewise; fp32 tiles with four pixel blocks to a wave have no registers for it)
+    // (what an addition done here adds is asked for in front of that wait: unit by unit behind it, it was a trip to memory each; fp32 tiles with four pixel blocks to a wave have no
+    // registers for it)
     constexpr bool EARLY = sizeof(T) == 2 || RBW == 2;
     const uint32_t nvalid = min((uint32_t)kBrickRows, L.N - nbase);
     T* out[RBW];
@@ -498,6 +496,9 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
 
     // epilogue: lane holds, for pixel li of each of its pixel blocks, channels 8g + 4 lh + {0..3}
     if (!active) return;
+    f32x4 bias_q[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias_l + wc * kBrickRows + 8 * g + 4 * lh);
     uint8_t* scratch = lds + wave * unit_scratch_bytes<T>();
     if (a.pool && L.pool_fill) {
         // The next layer averages every channel over the image, and the one or two pixel blocks of an
@@ -590,6 +591,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     typedef const __attribute__((address_space(1))) u32x4* gptr_t;
     extern __shared__ __attribute__((aligned(16))) uint8_t img[];
     __shared__ uint32_t owner_part[4];
+    __shared__ __attribute__((aligned(16))) float bias_l[kTileCols];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
     __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes(kFewTenants)];
     TileLookup<256, FEW ? kFewTenants : 0> lookup;            // (not with one channel block: 64 registers)
@@ -631,6 +633,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     u32x4 wq[P];
 #pragma unroll
     for (uint32_t j = 0; j < P; ++j) wq[j] = wp[(size_t)min(j, nKBv - 1) * 64];
+    const float bias_of = ((const float*)(a.arena + L.b_off))[nb0 * kBrickRows + min(tid, ncb * kBrickRows - 1)];      // padded to N_pad; likewise, not behind the K loop
 
     const uint32_t cpp = cin * (uint32_t)sizeof(T) / 16, cpr = iw_n * cpp;       // 16-byte chunks per pixel, per image row
     for (uint32_t i = 0; i < ni; ++i) {
@@ -659,6 +662,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
             }
         }
     }
+    if (tid < kTileCols) bias_l[tid] = bias_of;
     __syncthreads();
 
     f32x16 acc[RBW];
@@ -798,7 +802,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
         else if (half) k_loop(half_blocks);
         else k_loop(all_blocks);
     }
-    // Where this lane's pixels go.  What an addition done here adds to them is asked for together with the bias, in front of the barrier, not unit by unit
+    // Where this lane's pixels go.  What an addition done here adds to them is asked for all at once, in front of the barrier, not unit by unit
     // behind it (fp32 tiles of four pixel blocks have no registers for that; asked for while the frame is filled, bf16 ones have none either).  64 images, 56x56x64 with an addition 31.7 -> 29.4 us, 28x28x128 26.5 -> 25.4, 14x14x256 27.2 -> 26.2,
     // 7x7x512 27.4 -> 27.5, the 1x1 projections (conv_lds_kernel) 12.4 / 11.6 / 12.5 -> 11.6 / 10.4 / 11.4; one image, K split: 13 launches 0.2-0.6 us each.
     constexpr bool EARLY = RBW == 2 || (sizeof(T) == 2 && RBW == 4);
@@ -821,12 +825,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
             if (L.fuse_add) residual[r].fetch(other(out[r]), (const T*)act_of(a.act, L.in2_buf) + (size_t)seg0 * a.S, lh, nvalid);
         }
     }
-    const float* bias = (const float*)(a.arena + L.b_off);
-    f32x4 bias_q[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias + nbase + 8 * g + 4 * lh);   // bias is padded to N_pad
     __syncthreads();                                               // every wave is done with the frame: it now serves as store scratch
     if (!active) return;
+    f32x4 bias_q[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias_l + wc * kBrickRows + 8 * g + 4 * lh);
     uint8_t* scratch = img + wave * unit_scratch_bytes<T>();
 #pragma unroll
     for (uint32_t r = 0; r < RBW; ++r) {
@@ -894,6 +897,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     divmod_uniform(row_ok ? m : m0, rpr, &req, &pix);              // rows past the end repeat the first one and are dropped
     divmod_uniform(pix, L.out_w, &oh, &ow);
     const size_t at = (size_t)(seg0 + req) * a.S;
+    // thread (g = wave, lane) of the first four waves: channels 8g + 4 lh + {0..3} of pixel li
+    const uint32_t g = wave & 3, nbase = nb * kBrickRows, ch0 = 8 * g + 4 * lh;
+    const f32x4 bias = *(const f32x4*)((const float*)(a.arena + L.b_off) + nbase + ch0);   // bias is padded to N_pad
+    const size_t to = at + (size_t)pix * L.N + nbase + ch0;
+    typename Residual<T>::vec skip{};                              // asked for, like the bias, in front of the sums
+    const bool mine = wave < 4 && row_ok && ch0 < L.N - nbase;     // channel counts are multiples of 8: a run of four exists whole or not at all
+    if (L.fuse_add && mine) skip = *(const typename Residual<T>::vec*)((const T*)act_of(a.act, L.in2_buf) + to);
     f32x16 acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
@@ -1013,13 +1023,6 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
             if (s + j < cnt) Mma<T>::run(acc, wq[j], aq[j]);
     }
 
-    // thread (g = wave, lane) of the first four waves: channels 8g + 4 lh + {0..3} of pixel li
-    const uint32_t g = wave & 3, nbase = nb * kBrickRows, ch0 = 8 * g + 4 * lh;
-    const f32x4 bias = *(const f32x4*)((const float*)(a.arena + L.b_off) + nbase + ch0);   // bias is padded to N_pad
-    const size_t to = at + (size_t)pix * L.N + nbase + ch0;
-    typename Residual<T>::vec skip{};                              // asked for in front of the barrier, not behind it
-    const bool mine = wave < 4 && row_ok && ch0 < L.N - nbase;     // channel counts are multiples of 8: a run of four exists whole or not at all
-    if (L.fuse_add && mine) skip = *(const typename Residual<T>::vec*)((const T*)act_of(a.act, L.in2_buf) + to);
 #pragma unroll
     for (uint32_t q = 0; q < 4; ++q)
         *(f32x4*)(red + wave * 4096 + q * 1024 + lane * 16) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};

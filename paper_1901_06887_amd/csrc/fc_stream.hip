@@ -248,14 +248,15 @@ __device__ __forceinline__ void fc_accumulate_direct(const GemmArgs& a, const Ti
         if ((uint32_t)j < rem) step(j, full * P + j);
 }
 
+__device__ __forceinline__ int32_t submission_of(const GemmArgs& a, const LayerDev& L, uint32_t seg0, uint32_t m0) { return L.is_last ? a.perm[seg0 + m0 + (threadIdx.x >> 3)] : -1; }
+
 // The rows of a tile whose logits stand in LDS as [row][class], LRS floats to a row, at most 32 Q classes: softmax, argmax, outputs in submission order, eight
-// threads a row.
+// threads a row, whose place there they have asked for before the sums (submission_of).
 template <uint32_t Q, uint32_t LRS>
-__device__ __forceinline__ void fc_finish_rows(const GemmArgs& a, const float* lt, uint32_t C, uint32_t mb, uint32_t Mt, uint32_t seg0)
+__device__ __forceinline__ void fc_finish_rows(const GemmArgs& a, const float* lt, uint32_t C, uint32_t mb, uint32_t Mt, int32_t submitted)
 {
-    const uint32_t tid = threadIdx.x, row = tid >> 3, part = tid & 7, m = mb + row;
+    const uint32_t tid = threadIdx.x, row = tid >> 3, part = tid & 7, m = mb + row, sub = (uint32_t)submitted;
     if (m >= Mt) return;                                                 // the eight threads of a row are neighbours in one wave
-    const uint32_t sub = (uint32_t)a.perm[seg0 + m];
     f32x4 z[Q], ez[Q];
     float mx = -INFINITY; int32_t best = 0x7fffffff;
 #pragma unroll
@@ -320,14 +321,13 @@ __device__ __forceinline__ void fc_finish_rows(const GemmArgs& a, const float* l
 // with GELU 59.0 -> 57.1 -> 57.0; the last layer of 64 residual nets 8.6 -> 6.9.
 template <typename T>
 __device__ __forceinline__ void fc_finish_split(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t Mt, uint32_t seg0,
-                                                uint32_t nb, uint32_t kq, uint32_t ks, bool active, T* xout, const f32x16& acc, uint8_t* smem)
+                                                uint32_t nb, uint32_t kq, uint32_t ks, bool active, float bv, int32_t sub, T* xout, const f32x16& acc, uint8_t* smem)
 {
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC, MAXG = 2;         // (ks is 2 or 4)
     constexpr uint32_t TRS = 32 * sizeof(T) + 16;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
     const uint32_t split = tl.split, cb = wave % split, ng = 4 / ks;
     const uint32_t n = nb * kBrickRows + li;
-    const float bv = active ? ((const float*)(a.arena + L.b_off))[n] : 0.0f;
     float* red = (float*)smem;
     uint8_t* trw = smem + kTrOffset + cb * kTrBytes;
     const bool head = L.is_last && a.fuse_head && L.N <= a.fuse_head_max && L.N_pad <= split * kBrickRows;
@@ -361,7 +361,7 @@ __device__ __forceinline__ void fc_finish_split(const GemmArgs& a, const Tile& t
                 for (uint32_t e = 0; e < 4; ++e) lt[(8 * (kq * ng + i) + 4 * lh + e) * LRS + cb * kBrickRows + li] = y[i][e];
             }
         __syncthreads();
-        fc_finish_rows<MAXG, LRS>(a, lt, L.N, mb, Mt, seg0);
+        fc_finish_rows<MAXG, LRS>(a, lt, L.N, mb, Mt, sub);
         return;
     }
     if (L.is_last) {
@@ -397,11 +397,14 @@ __device__ __forceinline__ void fc_split_tile(const GemmArgs& a, const Tile& tl,
     const uint32_t split = tl.split, ks = 4 / split, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t nb = tl.n0 / kBrickRows + (wave % split), kq = wave / split;
     const bool active = nb < L.N_pad / kBrickRows;
+    // what the end of the tile needs is asked for in front of the sums: behind them it was a trip to memory each
+    const float bv = active ? ((const float*)(a.arena + L.b_off))[nb * kBrickRows + (threadIdx.x & 31)] : 0.0f;
+    const int32_t sub = submission_of(a, L, seg0, tl.m0);
     f32x16 acc[1];
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[0][v] = 0.0f;
     if (active) fc_accumulate_direct<T, GATHER>(a, tl, L, seg0, nb, nb, kq, ks, row, row_ok, acc);
-    fc_finish_split<T>(a, tl, L, Mt, seg0, nb, kq, ks, active, xout, acc[0], smem);
+    fc_finish_split<T>(a, tl, L, Mt, seg0, nb, kq, ks, active, bv, sub, xout, acc[0], smem);
 }
 
 // A last layer of 33 to 128 classes in a run whose tiles split K: the tile takes all its column blocks, two at a time, and finishes its rows, where a tile per block left them to a
@@ -414,6 +417,7 @@ __device__ __forceinline__ void fc_whole_tile(const GemmArgs& a, const Tile& tl,
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5, blocks = L.N_pad / kBrickRows;
     float *red = (float*)smem, *lt = (float*)(smem + kTrOffset);
     const float* bias = (const float*)(a.arena + L.b_off);
+    const int32_t sub = submission_of(a, L, seg0, tl.m0);
     for (uint32_t nb = 0; nb < blocks; nb += 2) {
         const uint32_t nb2 = min(nb + 1, blocks - 1);
         const float bv[2] = {bias[nb * kBrickRows + li], bias[nb2 * kBrickRows + li]};
@@ -437,7 +441,7 @@ __device__ __forceinline__ void fc_whole_tile(const GemmArgs& a, const Tile& tl,
         }
     }
     __syncthreads();
-    fc_finish_rows<kTileCols / kBrickRows, LRS>(a, lt, L.N, tl.m0, Mt, seg0);
+    fc_finish_rows<kTileCols / kBrickRows, LRS>(a, lt, L.N, tl.m0, Mt, sub);
 }
 
 template <typename T, int RB, int GATHER, typename ROWS>
