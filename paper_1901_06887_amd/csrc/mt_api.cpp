@@ -982,8 +982,8 @@ int first_rows(const mt_ctx* c, uint64_t R, bool split_k, bool big_possible, boo
 // every tile of a second round does the segmentation once more behind the first.  us a pass, with the batcher's launch and so, bf16: 64 tenants of 784-1024-1024-10,
 // 300 / 1024 / 2048 requests 55.6 / 72.2 / 73.8 -> 53.4 / 69.7 / 71.1, 16 of 512-512-512-10 26.2 / 31.3 / 35.4 -> 23.6 / 28.8 / 32.5, one of 1024-2048-2048-40, 2048 and 3000 (at most 766
 // tiles) 66.5 / 85.9 -> 65.2 / 84.1, 4096 (1040) 110.2 -> 112.7; at most 1024 tiles (4096 requests of the first) 100.9 -> 100.2, three runs in flight 215.0 -> 221.6.  (It gains as much from 65 rows on:
-// 54.6 -> 52.4 at 257.  Up to there runs of ordinary tiles keep the launches that they are known to have.)
-constexpr uint32_t kEntryWideMin = 288;
+// 54.6 -> 52.4 at 257, the 300 above.  Up to 319 runs of ordinary tiles keep the launches that they are known to have.)
+constexpr uint32_t kEntryWideMin = 320;
 constexpr uint64_t kEntryWideTiles = 768;
 enum : int { kEntryNone = 0, kEntryNarrow, kEntryWide };
 int run_entry(const mt_ctx* c, uint64_t R, bool split_k)
