@@ -554,7 +554,7 @@ def test_facts_of_few_and_many_tenants(dtype, n_tenants, rows):
 # column blocks and rows that fill none; requests of nobody.  Against the oracle, and to the bit against the batcher's launch
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n_tenants", [1, 9, 64])
-@pytest.mark.parametrize("rows", [288, 513, 1024, 4095, 4096, 4097])
+@pytest.mark.parametrize("rows", [320, 513, 1024, 4095, 4096, 4097])
 def test_runs_of_any_tiles_without_a_batcher(monkeypatch, dtype, n_tenants, rows):
     shapes = ([48, 24, 5], [48, 64, 40, 130], [48, 200, 33, 7, 64])
     tenants = {t: wl.make_model(wl.mlp_layers(shapes[t % 3], wl.ACT_RELU), dtype, 395, t) for t in range(n_tenants) if t != 7}
@@ -620,3 +620,29 @@ def test_rows_of_any_length_at_any_address(monkeypatch, dtype, n_in, rows, n_ten
             assert all(np.array_equal(u, v) for u, v in zip(got[off][0], got[off][-1]))
         ctx.close()
     assert all(np.array_equal(u, v) for u, v in zip(got["0"][0], got["1"][0]))
+
+
+# last layers of 33 to 128 classes finished by tiles of all their column blocks in runs whose tiles split K: classes at the edges of a block and of the range, sums shorter than
+# the waves that share them, rows that fill a tile and not; beside a model whose only layer is such a one, the head does them all.  Against the oracle
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("classes", [32, 33, 64, 65, 97, 128, 129])
+@pytest.mark.parametrize("rows", [1, 32, 70])
+def test_small_runs_finish_wide_last_layers_in_their_tiles(monkeypatch, dtype, classes, rows):
+    shapes = ([40, 24, classes], [40, 200, 72, classes], [40, 136, 5])
+    models = [wl.make_model(wl.mlp_layers(s, wl.ACT_RELU), dtype, 397, i) for i, s in enumerate(shapes + ([40, 40],))]
+    rng = np.random.default_rng(397)
+    x = rng.standard_normal((rows, 40)).astype(np.float32)
+    for n in (3, 4):                                                 # with the model of one layer, and without
+        tenants = dict(enumerate(models[:n]))
+        w = wl.Workload("whole", dtype, tenants, (np.arange(rows) % n).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
+        launches = []
+        for off in ("0", "1"):
+            monkeypatch.setenv("MT_NO_FUSED_HEAD", off)
+            ctx = make_context(w)
+            check(w, "%s, %d classes, %d rows, %d models" % (dtype, classes, rows, n), ctx)
+            launches.append(ctx.stats()["last_run_launches"])
+            ctx.close()
+        if n == 3:
+            assert launches[0] == launches[1] - (classes <= 128)
+        else:
+            assert launches[0] == launches[1]
