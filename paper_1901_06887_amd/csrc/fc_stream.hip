@@ -462,11 +462,9 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[r][v] = 0.0f;
 
-    fc_accumulate_shared<T, RB, GATHER>(a, tl, L, seg0, nb, active, row_of, smem, acc);
-
     const uint32_t n = nb * kBrickRows + li;
-    const float* bias = (const float*)(a.arena + L.b_off);
-    const float bv = active ? bias[n] : 0.0f;
+    const float bv = active ? ((const float*)(a.arena + L.b_off))[n] : 0.0f;      // (in front of the sums, as above)
+    fc_accumulate_shared<T, RB, GATHER>(a, tl, L, seg0, nb, active, row_of, smem, acc);
     if (L.is_last && a.fuse_head && L.N <= a.fuse_head_max && L.N_pad <= split * kBrickRows) {
         // 33 .. 128 classes, all of them inside this tile (one column group): the waves put their
         // 32x32 blocks of logits side by side in LDS as [row][class], then eight threads share a
