@@ -397,7 +397,7 @@ __device__ __forceinline__ void fc_split_tile(const GemmArgs& a, const Tile& tl,
     const uint32_t split = tl.split, ks = 4 / split, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t nb = tl.n0 / kBrickRows + (wave % split), kq = wave / split;
     const bool active = nb < L.N_pad / kBrickRows;
-    // what the end of the tile needs is asked for in front of the sums: behind them it was a trip to memory each
+    // what the end of the tile needs is asked for in front of the sums: behind them it was a trip to memory each (64 fp32 requests to MLPs 20.7 -> 20.6 us, one bf16 19.7 -> 19.4)
     const float bv = active ? ((const float*)(a.arena + L.b_off))[nb * kBrickRows + (threadIdx.x & 31)] : 0.0f;
     const int32_t sub = submission_of(a, L, seg0, tl.m0);
     f32x16 acc[1];
@@ -463,7 +463,7 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
         for (int v = 0; v < 16; ++v) acc[r][v] = 0.0f;
 
     const uint32_t n = nb * kBrickRows + li;
-    const float bv = active ? ((const float*)(a.arena + L.b_off))[n] : 0.0f;      // (in front of the sums, as above)
+    const float bv = active ? ((const float*)(a.arena + L.b_off))[n] : 0.0f;      // (asked for in front of the sums: 4096 requests to 64 MLPs 99.4 -> 97.3 us)
     fc_accumulate_shared<T, RB, GATHER>(a, tl, L, seg0, nb, active, row_of, smem, acc);
     if (L.is_last && a.fuse_head && L.N <= a.fuse_head_max && L.N_pad <= split * kBrickRows) {
         // 33 .. 128 classes, all of them inside this tile (one column group): the waves put their
