@@ -585,12 +585,16 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
     }
 }
 
-// FEW: at most 64 tenants (for launches of nothing but K-split tiles; those of many tiles gain nothing: 1024 tiles of 64 tenants 99.3 -> 100.0 us a pass).  NARROW: every tile of the launch splits K (small runs, layer indices with at most 64 outputs): a kernel a third the size, with registers
-// for four workgroups per CU.  GATHER: layer 0 reads the submitted rows itself.  In the general kernel the wide tiles stand first
+// FEW: at most 64 tenants (for launches of nothing but K-split tiles; those of many tiles gain nothing: 1024 tiles of 64 tenants
+// 99.3 -> 100.0 us a pass).  NARROW: every tile of the launch splits K (small runs, layer indices with at most 64 outputs): a kernel a
+// third the size, with registers for four workgroups per CU.  WHOLE: some last layer of the index takes tiles of all its column blocks
+// (fc_whole_tile), which need the registers of three: in the plain narrow kernel they spilled, and every launch brought their code
+// (64 bf16 requests to 256-256-256-256-256-256-256-10 models 35.9 -> 34.8 us a pass without, four 256-512-512-40 20.3 -> 20.5).
+// GATHER: layer 0 reads the submitted rows itself.  In the general kernel the wide tiles stand first
 // and the two kinds of layer 0 in kernels of their own: with both and the K-split tiles in front, 40 scalar registers were
 // spilled and layer 0 of 256 models of mixed depths took 175.9 us instead of 171.3.
-template <typename T, bool NARROW, int GATHER, bool FEW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 : 3, NARROW ? 4 : 3))) void fc_kernel(GemmArgs a)
+template <typename T, bool NARROW, int GATHER, bool FEW, bool WHOLE = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW && !WHOLE ? 4 : 3, NARROW && !WHOLE ? 4 : 3))) void fc_kernel(GemmArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint8_t smem[NARROW ? kFcLdsBytes : fc_lds_bytes<GATHER>()];
     __shared__ uint32_t owner_part[4];
@@ -610,7 +614,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 
     const bool big = ((*a.big_layers >> a.layer) & 1) && fc_is_big(Mt, L.N_pad);
     uint32_t groups, trows;
     fc_shape(L.N_pad, a.fc_split_k || (big && big_remainder_split_k(L.N_pad)), &tl.split, &groups, &trows);
-    const bool whole = NARROW && GATHER == kRowsStaged && a.fc_whole && L.is_last && fc_whole(L.N_pad);      // all column blocks in one tile (local / mt_ is 0)
+    static_assert(!WHOLE || (NARROW && GATHER == kRowsStaged), "in runs whose tiles split K, behind layer 0");
     const uint32_t first = big ? big_rows(Mt) : 0;
     const uint32_t mt_ = ceil_div(Mt - first, trows);
     tl.m0 = first + (local % mt_) * trows;
@@ -636,8 +640,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 
     if (GATHER) {
         row = row_of(0, threadIdx.x & 31, &row_ok);
     }
-    if constexpr (NARROW && GATHER == kRowsStaged) {
-        if (whole) { fc_whole_tile<T>(a, tl, L, Mt, seg0, smem); return; }
+    if constexpr (WHOLE) {                                    // (local / mt_ is 0)
+        if (L.is_last && fc_whole(L.N_pad)) { fc_whole_tile<T>(a, tl, L, Mt, seg0, smem); return; }
     }
     fc_split_tile<T, GATHER>(a, tl, L, Mt, seg0, row, row_ok, xout, smem);
 }
@@ -886,6 +890,8 @@ static void launch_fc_t(const GemmArgs& a, bool narrow, uint32_t grid, hipStream
         else if (a.T <= 64) launch(fc_kernel<T, true, rows, true>);
         else launch(fc_kernel<T, true, rows, false>);
     };
+    if (a.fc_whole && a.T <= 64) { launch(fc_kernel<T, true, kRowsStaged, true, true>); return; }
+    if (a.fc_whole) { launch(fc_kernel<T, true, kRowsStaged, false, true>); return; }
     if (a.gather == kRowsAny) with(std::integral_constant<int, kRowsAny>{});
     else if (a.gather) with(std::integral_constant<int, kRowsChunked>{});
     else with(std::integral_constant<int, kRowsStaged>{});
@@ -911,6 +917,7 @@ hipError_t launch_fc_entry(const GemmArgs& a, const BatchArgs& b, uint32_t dtype
 hipError_t launch_fc(const GemmArgs& a, uint32_t dtype, bool narrow, uint32_t grid, hipStream_t s)
 {
     if (grid == 0) return hipSuccess;
+    if (a.fc_whole && (!narrow || a.gather != kRowsStaged)) return hipErrorInvalidValue;
     grid = (grid + 7) / 8 * 8;
     if (dtype == MT_BF16) launch_fc_t<__bf16>(a, narrow, grid, s); else launch_fc_t<float>(a, narrow, grid, s);
     return hipGetLastError();

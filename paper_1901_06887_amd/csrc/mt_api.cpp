@@ -179,6 +179,7 @@ struct mt_ctx {
     uint32_t act_buffers = 2;      // activation buffers every run slot holds (grows when a model with skip connections needs more)
     uint32_t max_reg_classes = 0, min_reg_classes = 0;
     bool first_is_wide_last = false;           // some registered model is one layer of 33 to 128 classes
+    bool wide_last[MT_MAX_LAYERS]{};           // some registered model ends with such a layer at the index
     uint32_t no_fused_head = 0;    // tuning/testing: always run the separate head kernel
     uint32_t no_fused_pool = 0;    // tuning/testing: always run the separate pooling kernel
     uint32_t no_fused_add = 0;     // tuning/testing: residual additions always run as launches of their own
@@ -670,7 +671,7 @@ void recompute_bounds(mt_ctx* c)
         }
     }
     for (uint32_t l = 0; l < MT_MAX_LAYERS; ++l) {
-        c->has_gap[l] = 0; c->gap_chunks[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1; c->conv_frame_share[l] = 0.0;
+        c->has_gap[l] = 0; c->gap_chunks[l] = 0; c->has_image_ops[l] = 0; c->image_op_fill[l] = 0; c->min_conv_k[l] = 0xffffffffu; c->max_conv_k[l] = 0; c->max_conv_work[l] = 0; c->max_conv_tile_rows[l] = 0; c->sum_conv_work[l] = 0; c->max_conv_blocks[l] = 0; c->sum_conv_blocks[l] = 0; c->min_fc_k[l] = 0xffffffffu; c->max_fc_cols[l] = 0; c->wide_last[l] = false; c->max_conv_cb[l] = 0; c->conv_quad[l] = true; c->conv_uniform[l] = true; c->pool_fused[l] = false; c->conv_img_lds[l] = 1; c->conv_img_two[l] = -1; c->conv_frame_share[l] = 0.0;
         for (int k = 0; k < kListKinds; ++k) { c->max_nt[k][l] = 0; c->sum_nt[k][l] = 0; }
         c->max_fc_per64[l] = 0; c->max_fc_per64_sk[l] = 0; c->sum_nt_sk[l] = 0; c->max_big_blocks[l] = 0;
     }
@@ -705,6 +706,7 @@ void recompute_bounds(mt_ctx* c)
             if (k == 0) {
                 c->min_fc_k[l] = std::min(c->min_fc_k[l], L.K);
                 c->max_fc_cols[l] = std::max(c->max_fc_cols[l], L.N_pad);
+                if (L.is_last && fc_whole(L.N_pad)) c->wide_last[l] = true;
                 c->max_fc_per64[l] = std::max(c->max_fc_per64[l], nt * (kTileRows / fc_tile_rows(L.N_pad, c->fc_split_k)));
                 const uint32_t nt_sk = fc_groups(L.N_pad, 1);
                 c->sum_nt_sk[l] += nt_sk;
@@ -1972,7 +1974,7 @@ mt_status run_impl(mt_ctx* c, void* hip_stream, const mt_outputs* out, uint32_t*
             if (grid == 0 || (kind == 2 && (!big_enabled || grid < c->big_min_tiles))) continue;   // no big tiles possible: the batcher made none
             GemmArgs ga{};
             ga.tile_base = c->d_tile_base + ((size_t)kind * MT_MAX_LAYERS + l) * (T + 1);
-            ga.T = T; ga.layer = l; ga.fc_split_k = split_k; ga.fc_whole = whole; ga.big_layers = b.big_layers;
+            ga.T = T; ga.layer = l; ga.fc_split_k = split_k; ga.fc_whole = kind == 0 && whole && c->wide_last[l]; ga.big_layers = b.big_layers;
             ga.gather = kind == 0 && l == 0 ? rows : kRowsStaged; ga.perm = c->d_perm; ga.row_src = c->d_row_src;
             ga.fuse_head = fuse_head; ga.fuse_head_max = fuse_head_max; ga.out_vec_ok = out_vec_ok; ga.out = outp; ga.pool = kind == 1 && c->pool_fused[l];
             ga.store_through = kind == 1 && R * c->max_conv_work[l] * kBrickRows * c->elem_size <= kStoreThroughMaxBytes;

@@ -245,7 +245,8 @@ struct GatherArgs {
 };
 
 struct GemmArgs {
-    const uint32_t* tile_base; uint32_t T; uint32_t layer; uint32_t fc_split_k; uint32_t fc_whole;
+    const uint32_t* tile_base; uint32_t T; uint32_t layer; uint32_t fc_split_k;
+    uint32_t fc_whole;            // FC launch: last layers of 33 to 128 classes, of which there are some, take a tile for all their column blocks
     const uint32_t* big_layers;   // the batcher's decision per layer index (see BatchArgs)
     uint32_t big_vgrid;           // big-tile launch whose workgroups walk several tiles: the grid of one tile per workgroup that they walk
     uint32_t pool;                // conv launch: the layers with pool_fill write the pooled activation instead of their own
