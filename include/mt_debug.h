@@ -69,6 +69,11 @@ uint32_t mt_debug_big_tile_walk(uint32_t in_features);
 int mt_debug_conv_row_tiling(uint32_t in_h, uint32_t in_w, uint32_t in_channels, uint32_t ksize, uint32_t stride, uint32_t elem_size,
                              uint32_t* rows_per_tile, uint32_t* images_per_tile, uint32_t* tiles_per_image, uint64_t* frame_bytes);
 
+/* Test aid: 1 if a launch of so many workgroups with input rows of frame_bytes in LDS, whose layers have up to
+ * channel_blocks blocks of 32 channels (at most 4), fetches the facts of all max_tenants tenants ahead of its tiles
+ * (into LDS beside the input rows), else 0.  Pure function of its arguments; needs no context and no device. */
+uint32_t mt_debug_conv_frame_ahead(uint32_t max_tenants, uint32_t channel_blocks, uint32_t frame_bytes, uint64_t workgroups);
+
 /* Measurement and test aid: how a run of `rows` requests launches the convolutions of one layer index over the models
  * registered now.  counts[t] ([max_tenants]) is the number of requests of tenant t, adding up to `rows`, in a run whose
  * submissions all named their tenant; NULL: the tenants stand in a device-resident id array.  *split is 1 if the launch

@@ -119,6 +119,8 @@ def load_library() -> ctypes.CDLL:
     L.mt_debug_big_tile_rows.restype = u32
     L.mt_debug_big_tile_walk.argtypes = [u32]
     L.mt_debug_big_tile_walk.restype = u32
+    L.mt_debug_conv_frame_ahead.argtypes = [u32, u32, u32, ctypes.c_uint64]
+    L.mt_debug_conv_frame_ahead.restype = u32
     L.mt_debug_conv_row_tiling.argtypes = [u32, u32, u32, u32, u32, u32, ctypes.POINTER(u32), ctypes.POINTER(u32), ctypes.POINTER(u32), ctypes.POINTER(ctypes.c_uint64)]
     L.mt_debug_conv_row_tiling.restype = ctypes.c_int
     L.mt_debug_conv_launch.argtypes = [vp, u32, u32, ctypes.POINTER(u32), ctypes.POINTER(u32), ctypes.POINTER(ctypes.c_uint64)]
@@ -334,6 +336,11 @@ def debug_big_tile_rows(rows: int, out_features: int) -> int:
 def debug_big_tile_walk(in_features: int) -> bool:
     """Whether the big tiles of a layer index with this shortest fan-in are walked by one workgroup per compute unit."""
     return bool(load_library().mt_debug_big_tile_walk(in_features))
+
+
+def debug_conv_frame_ahead(max_tenants: int, channel_blocks: int, frame_bytes: int, workgroups: int) -> bool:
+    """Whether a launch of convolution tiles with their input rows in LDS fetches its tenants' facts ahead."""
+    return bool(load_library().mt_debug_conv_frame_ahead(max_tenants, channel_blocks, frame_bytes, workgroups))
 
 
 def debug_conv_row_tiling(in_h: int, in_w: int, in_channels: int, ksize: int = 3, stride: int = 1, elem_size: int = 2):

@@ -188,7 +188,7 @@ __device__ __forceinline__ void conv_wave(const GemmArgs& a, const LayerDev& L, 
     }
 }
 
-constexpr uint32_t kFewTenants = 32;      // whose facts are fetched ahead of a tile's lookup where more would cost a workgroup per compute unit
+constexpr uint32_t kFewTenants = 32;      // whose facts are fetched ahead of a tile's lookup where those of 64 would take too much LDS
 // MAXCB bounds the channel blocks of any tile in the launch: narrow layers get a kernel with
 // few registers and many resident waves, which is what hides the latency of their short K loops.
 template <typename T, int MAXCB, bool FEW>
@@ -592,10 +592,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     typedef const __attribute__((address_space(1))) u32x4* gptr_t;
     extern __shared__ __attribute__((aligned(16))) uint8_t img[];
     __shared__ uint32_t owner_part[4];
-    __shared__ __attribute__((aligned(16))) float bias_l[kTileCols];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, lh = lane >> 5;
     __shared__ __attribute__((aligned(16))) uint8_t facts[ahead_bytes(kFewTenants)];
-    TileLookup<256, FEW ? kFewTenants : 0> lookup;            // (not with one channel block: 64 registers)
+    TileLookup<256, FEW ? kFewTenants : 0> lookup;            // (not with one channel block: 64 registers; conv_img_few)
     lookup.fetch(a);
     const uint32_t n_tiles = a.tile_base[a.T];
     // the frame starts as zeros (its border, rows past the image, sub-images past the tenant's last request);
@@ -634,7 +633,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     u32x4 wq[P];
 #pragma unroll
     for (uint32_t j = 0; j < P; ++j) wq[j] = wp[(size_t)min(j, nKBv - 1) * 64];
-    const float bias_of = ((const float*)(a.arena + L.b_off))[nb0 * kBrickRows + min(tid, ncb * kBrickRows - 1)];      // padded to N_pad; likewise, not behind the K loop
+    // padded to N_pad; likewise, not behind the K loop (a register of the wave's lanes: LDS of its own would cost large frames a workgroup)
+    const float bias_of = ((const float*)(a.arena + L.b_off))[(nb0 + (active ? wc : 0)) * kBrickRows + li];
 
     const uint32_t cpp = cin * (uint32_t)sizeof(T) / 16, cpr = iw_n * cpp;       // 16-byte chunks per pixel, per image row
     for (uint32_t i = 0; i < ni; ++i) {
@@ -663,7 +663,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
             }
         }
     }
-    if (tid < kTileCols) bias_l[tid] = bias_of;
     __syncthreads();
 
     f32x16 acc[RBW];
@@ -828,10 +827,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     }
     __syncthreads();                                               // every wave is done with the frame: it now serves as store scratch
     if (!active) return;
+    uint8_t* scratch = img + wave * unit_scratch_bytes<T>();
+    ((float*)scratch)[li] = bias_of;                               // each lane's channels from those that hold them, by way of the wave's scratch
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     f32x4 bias_q[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)(bias_l + wc * kBrickRows + 8 * g + 4 * lh);
-    uint8_t* scratch = img + wave * unit_scratch_bytes<T>();
+    for (int g = 0; g < 4; ++g) bias_q[g] = *(const f32x4*)((const float*)scratch + 8 * g + 4 * lh);
 #pragma unroll
     for (uint32_t r = 0; r < RBW; ++r) {
         T* const to = EARLY ? out[r] : locate(r);
@@ -1073,6 +1074,19 @@ static hipError_t allow_frame(K kernel)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kConvFrameMaxBytes);
 }
 
+// Whether a launch of LDS frames fetches its tenants' facts ahead.  They take 4.5 KiB beside the frame, which may be the room of a workgroup per compute unit: only
+// where as many fit with them (LDS is dealt out in 1280 bytes; the registers are for four, or three), or all of the launch's workgroups start together as it is.
+// Chains of layers, without / with them where one workgroup less fits, us a pass: 4096 images 8x8x192 (two) 726 / 874, 2048 16x16x128 (three) 499 / 528,
+// 1024 24x24x128 (three) 623 / 671; 2048 20x20, 96 and 64 channels in turn (four) 476 / 487.
+bool conv_img_few(uint32_t tenants, uint32_t max_cb, uint32_t frame, uint64_t workgroups)
+{
+    constexpr uint32_t kLds = 160 * 1024, kLdsGranule = 1280, kComputeUnits = 256, kWithout = 16;      // (of the lookup by loads of its own)
+    if (tenants > kFewTenants || max_cb <= 1) return false;
+    auto fit = [&](uint32_t lds) { return std::min(max_cb <= 2 ? 4u : 3u, kLds / ((lds + kLdsGranule - 1) / kLdsGranule * kLdsGranule)); };
+    const uint32_t with = fit(frame + ahead_bytes(kFewTenants));
+    return with == fit(frame + kWithout) || workgroups <= (uint64_t)with * kComputeUnits;
+}
+
 template <typename T>
 static hipError_t launch_conv_img_t(const GemmArgs& a, uint32_t max_cb, bool two, uint32_t lds_bytes, uint32_t grid, hipStream_t s)
 {
@@ -1087,7 +1101,7 @@ static hipError_t launch_conv_img_t(const GemmArgs& a, uint32_t max_cb, bool two
         else launch(conv_img_kernel<T, 4, false, few>);
     };
     if (max_cb <= 1) { if (two && sizeof(T) == 2) launch(conv_img_kernel<T, 1, sizeof(T) == 2, false>); else launch(conv_img_kernel<T, 1, false, false>); }
-    else if (a.T <= kFewTenants) wide(std::true_type{});
+    else if (conv_img_few(a.T, max_cb, lds_bytes, grid)) wide(std::true_type{});
     else wide(std::false_type{});
     return hipGetLastError();
 }

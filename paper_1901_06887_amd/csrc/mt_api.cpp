@@ -2387,6 +2387,11 @@ uint32_t mt_debug_big_tile_walk(uint32_t in_features)
     return round_up(in_features, (uint32_t)kWidthAlign) >= kBigWalkMinK ? 1 : 0;
 }
 
+uint32_t mt_debug_conv_frame_ahead(uint32_t max_tenants, uint32_t channel_blocks, uint32_t frame_bytes, uint64_t workgroups)
+{
+    return conv_img_few(max_tenants, channel_blocks, frame_bytes, workgroups) ? 1 : 0;
+}
+
 int mt_debug_conv_row_tiling(uint32_t in_h, uint32_t in_w, uint32_t in_channels, uint32_t ksize, uint32_t stride, uint32_t elem_size,
                              uint32_t* rows_per_tile, uint32_t* images_per_tile, uint32_t* tiles_per_image, uint64_t* frame_bytes)
 {

@@ -294,6 +294,7 @@ hipError_t launch_mfma_rate(float* out, uint32_t iters, uint32_t grid, hipStream
 hipError_t prepare_conv(uint32_t dtype);   // once per device, before the first launch_conv: lets the frame kernels ask for more than 64 KiB of LDS
 // max_cb: the widest tile of this layer index over the registered tenants, in 32-channel blocks (1..4)
 // quad: every tenant's input channels at this layer index are a multiple of four 16-byte chunks
+bool conv_img_few(uint32_t tenants, uint32_t max_cb, uint32_t frame, uint64_t workgroups);   // whether launch_conv takes the kernel with facts fetched ahead
 hipError_t launch_conv(const GemmArgs& a, uint32_t dtype, uint32_t max_cb, bool quad, uint32_t img_lds_bytes, bool img_two, bool long_k, bool uniform_walk, uint32_t grid, hipStream_t s);
 // Waves of a tile that splits K: a wave should have a few steps to itself (a 7x7x8 window is 25 steps: 784 tiles of 16 waves,
 // one workgroup per CU, took 14.6 us, of 8 waves 8.5), a long walk is worth all 16 (1x1 over 64 channels: 4.9 us with
