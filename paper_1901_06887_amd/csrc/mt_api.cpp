@@ -178,7 +178,7 @@ struct mt_ctx {
     uint32_t max_image_pixels = 0;             // most pixels in a submitted image (models whose first layer is a convolution)
     uint32_t act_buffers = 2;      // activation buffers every run slot holds (grows when a model with skip connections needs more)
     uint32_t max_reg_classes = 0, min_reg_classes = 0;
-    bool first_is_wide_last = false;           // some registered model is one layer of 33 to 128 classes
+    bool wide_last_unfit = false;              // some registered model ends with a layer of 33 to 128 classes that tiles of all its blocks do not pay for (whole_pays)
     bool wide_last[MT_MAX_LAYERS]{};           // some registered model ends with such a layer at the index
     uint32_t no_fused_head = 0;    // tuning/testing: always run the separate head kernel
     uint32_t no_fused_pool = 0;    // tuning/testing: always run the separate pooling kernel
@@ -638,13 +638,24 @@ void recompute_pool_fusion(mt_ctx* c)
     }
 }
 
+// Whether a last layer of 33 to 128 classes takes less time in tiles of all its column blocks than in one per block with the head's launch behind them.  Two blocks at once, and
+// the pairs in turn, are a longer walk through K than one block by itself: some 0.12 us for each k step of a wave's quarter in fp32, 0.04 in bf16; the launch takes 1 to 3.  One request
+// to one model of 256-K-C / 64 to four / 300 to one, us a pass with the head's launch and so: fp32, C = 64, K = 512 24.3 / 24.6 / 27.2 -> 21.9 / 22.2 / 27.2, 768 24.4 / 25.2 / 28.6 ->
+// 23.7 / 24.2 / 29.1 (2048: 30.0 -> 34.1); C = 128, 128 23.6 / 23.8 / 27.0 -> 21.6 / 21.6 / 26.4, 192 23.8 / 23.9 / 27.1 -> 22.5 / 22.6 / 27.3 (2048: 29.9 -> 50.8); bf16, C = 64, 2048
+// 23.4 / 23.5 / 27.2 -> 20.8 / 20.9 / 26.3, 4096 21.9 / - / 34.1 -> 21.2 / - / 34.1; C = 128, 1024 23.0 / 23.3 / 27.0 -> 21.2 / 21.2 / 26.0, 1536 23.2 / 23.4 / 27.3 -> 21.5 / 21.9 / 27.7.
+bool whole_pays(const mt_ctx* c, const LayerDev& L)
+{
+    const uint32_t steps = L.K * c->elem_size / 128, pairs = (L.N_pad / kBrickRows + 1) / 2;
+    return steps * (2 * pairs - 1) <= (c->elem_size == 2 ? 64 : 16);
+}
+
 void recompute_bounds(mt_ctx* c)
 {
     c->n_layer_slots = 0;
     c->max_in_len = c->max_fc_in_len = 0; c->max_image_pixels = 0; c->min_layers = 0xffffffffu;
     c->fc_first_chunked = true; c->any_conv_first = c->any_fc_first = false;
     for (uint32_t& m : c->list_mask) m = 0;
-    c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->first_is_wide_last = false; c->sum_macs = 0.0;
+    c->max_reg_classes = 0; c->min_reg_classes = 0xffffffffu; c->wide_last_unfit = false; c->sum_macs = 0.0;
     c->first_on = !c->no_conv_first; c->first_pool = c->first_plain = false; c->pair_on = !c->no_conv_pair;
     c->first_max_ks = c->first_max_rows = c->pair_blocks = c->n_conv_first = 0; c->first_max_tiles = 0;
     for (const HostTenant& t : c->tenants) {         // (ahead of the others: it says which max-pools have a launch)
@@ -684,7 +695,6 @@ void recompute_bounds(mt_ctx* c)
         c->min_reg_classes = std::min(c->min_reg_classes, t.dev.n_classes);
         if (t.dev.in_layout == kLayoutBricks) {
             c->any_fc_first = true;
-            if (t.layers[0].dev.is_last && fc_whole(t.layers[0].dev.N_pad)) c->first_is_wide_last = true;
             c->max_fc_in_len = std::max(c->max_fc_in_len, t.dev.in_len);
             if ((t.dev.in_len * c->elem_size) % 16) c->fc_first_chunked = false;
         } else {
@@ -706,7 +716,7 @@ void recompute_bounds(mt_ctx* c)
             if (k == 0) {
                 c->min_fc_k[l] = std::min(c->min_fc_k[l], L.K);
                 c->max_fc_cols[l] = std::max(c->max_fc_cols[l], L.N_pad);
-                if (L.is_last && fc_whole(L.N_pad)) c->wide_last[l] = true;
+                if (L.is_last && fc_whole(L.N_pad)) { c->wide_last[l] = true; c->wide_last_unfit = c->wide_last_unfit || l == 0 || !whole_pays(c, L); }
                 c->max_fc_per64[l] = std::max(c->max_fc_per64[l], nt * (kTileRows / fc_tile_rows(L.N_pad, c->fc_split_k)));
                 const uint32_t nt_sk = fc_groups(L.N_pad, 1);
                 c->sum_nt_sk[l] += nt_sk;
@@ -995,9 +1005,9 @@ int run_entry(const mt_ctx* c, uint64_t R, bool split_k)
     return R >= kEntryWideMin && R <= kEntryWideRows && tile_bound(c, 0, 0, R, split_k) <= kEntryWideTiles ? kEntryWide : kEntryNone;
 }
 
-// Whether last layers of 33 to 128 classes take tiles of all their column blocks in a run whose tiles split K (fc_whole_tile).  Not where such a layer is a model's first, which
-// reads submitted rows; nor in captured runs, whose replays may meet such a model.
-bool run_whole(const mt_ctx* c, bool split_k, bool captured) { return split_k && !captured && !c->no_fused_head && !c->first_is_wide_last; }
+// Whether last layers of 33 to 128 classes take tiles of all their column blocks in a run whose tiles split K (fc_whole_tile): where it pays for all of them, as the head's launch
+// does the rows of all or of none.  Not where such a layer is a model's first, which reads submitted rows; nor in captured runs, whose replays may meet such a model.
+bool run_whole(const mt_ctx* c, bool split_k, bool captured) { return split_k && !captured && !c->no_fused_head && !c->wide_last_unfit; }
 
 // Most classes a last layer may have for its FC tiles to finish their rows themselves (softmax, argmax, outputs): one column block (32), or a whole tile of
 // four (128) where the run's tiles are not single column blocks, or take all of such a layer's; 0: the head kernel does every row.

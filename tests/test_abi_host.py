@@ -598,3 +598,21 @@ def test_launches_of_first_convolutions_hold_the_requests_that_have_images():
     assert workgroups(512) == 512 * 4                                  # ... a quarter of them by an even spread: tiles for 128
     c.unregister_model(1), c.unregister_model(2), c.unregister_model(3)
     assert workgroups(512) == 512
+
+
+@pytest.mark.parametrize("dtype,k,classes,head", [
+    (B.MT_BF16, 64, 100, False), (B.MT_BF16, 1280, 128, False), (B.MT_BF16, 1408, 97, True), (B.MT_BF16, 4096, 64, False), (B.MT_BF16, 4096, 65, True),
+    (B.MT_F32, 128, 100, False), (B.MT_F32, 256, 65, True), (B.MT_F32, 512, 64, False), (B.MT_F32, 640, 33, True), (B.MT_F32, 2048, 128, True),
+    (B.MT_F32, 2048, 32, False), (B.MT_F32, 64, 129, True)])
+def test_small_runs_finish_wide_last_layers_where_that_is_not_slower(dtype, k, classes, head):
+    # one tile for all the column blocks of a last layer walks them two at a time: short sums only, else the head has a launch, and then it does every model's rows
+    c = host_ctx(dtype=dtype, arena=1 << 24, max_classes=256, max_tenants=2)
+    specs = [fc(64, k, B.MT_ACT_RELU), fc(k, classes)]
+    c.register_model(0, specs, *zeros_for(specs, dtype))
+    assert c.estimate_run([40, 0])["launches"] == 2 + head
+    short = [fc(64, 128, B.MT_ACT_RELU), fc(128, 40)]
+    c.register_model(1, short, *zeros_for(short, dtype))
+    assert c.estimate_run([20, 20])["launches"] == 2 + head
+    c.unregister_model(0)
+    assert c.estimate_run([0, 40])["launches"] == 2
+    c.close()
