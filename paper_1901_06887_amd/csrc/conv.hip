@@ -486,7 +486,7 @@ __global__ __launch_bounds__(256 * (1 + PW)) __attribute__((amdgpu_waves_per_eu(
         divmod_uniform(m, rpr, &req, &pix);
         const size_t at = (size_t)(seg0 + req) * a.S + (size_t)pix * L.N + nbase;
         out[r] = m < rows_total ? (T*)act_of(a.act, L.out_buf) + at : nullptr;
-        if (EARLY && L.fuse_add) {
+        if (EARLY && worker && active && L.fuse_add) {        // (waves that add nothing ask for nothing: the barrier waits for all of it)
             const T* other = (const T*)act_of(a.act, L.in2_buf);
             residual[r].fetch(m < rows_total ? other + at : nullptr, other + (size_t)seg0 * a.S, lh, nvalid);
         }
@@ -822,7 +822,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
 #pragma unroll
         for (uint32_t r = 0; r < RBW; ++r) {
             out[r] = locate(r);
-            if (L.fuse_add) residual[r].fetch(other(out[r]), (const T*)act_of(a.act, L.in2_buf) + (size_t)seg0 * a.S, lh, nvalid);
+            if (active && L.fuse_add) residual[r].fetch(other(out[r]), (const T*)act_of(a.act, L.in2_buf) + (size_t)seg0 * a.S, lh, nvalid);
         }
     }
     __syncthreads();                                               // every wave is done with the frame: it now serves as store scratch
