@@ -2112,7 +2112,9 @@ constexpr double kUsConvFramePerKStep = 0.095, kConvFrameMflopPerUs = 0.6e3;   /
 constexpr double kUsConvFirstFixed = 8.0, kConvFirstMbPerUs = 5.2, kConvFirstMflopPerUs = 0.38e3;     // first convolutions on the submitted images, by the multiplications that they need
 constexpr double kUsConvSplitFixed = 1.0, kUsConvSplitPerKStep = 0.034;     // launches whose tiles split K among their waves: per k-step of a tile, one tile per compute unit at a time
 constexpr double kUsConvPerKStep = 0.21;     // a convolution tile's walk through K, per k-step of 32 bytes per pixel: a launch lasts at least as long as its longest tile
+constexpr double kUsBatcher = 7.0, kUsBatcherPer1024 = 1.1;     // kernel trace: 7.0 us at 64 rows, 9.2 at 2048, 11.3 at 4096
 constexpr double kUsEntry = 3.0;             // what the segmentation costs a small run's first layer
+constexpr double kUsEntryWideSaves = 2.5;    // what it saves where it is done by tiles of any kind: of the batcher's launch and the gap behind it (measured 1.3 to 2.9, beside run_entry)
 constexpr double kUsSmallFixed = 3.0, kCopyMbPerUs = 3.7, kHeadMbPerUs = 5.7, kUsHeadPerRow = 0.0008;
 constexpr double kComputeUnits = 256.0;
 constexpr double kUploadBytesPerMs = 55e6, kUsUploadFixed = 20.0;     // pinned host memory to HBM over the host link: 55 GB/s measured
@@ -2183,9 +2185,12 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
     auto launch = [&](double t) { us += t + (launches ? kUsLaunchGap : 0.0); ++launches; };
     // one submission, unless these are the requests that are pending in several
     const bool one_submission = c->pending.size() <= 1 || c->pending_rows != R;
-    if (one_submission && fuse_gather && run_entry(c, R, split_k)) us += kUsEntry;           // done by the first layer's launch
+    const double batcher_us = kUsBatcher + kUsBatcherPer1024 * R / 1024.0;
+    const int entry = one_submission && fuse_gather ? run_entry(c, R, split_k) : kEntryNone;
+    if (entry == kEntryNarrow) us += kUsEntry;                             // done by the first layer's launch
+    else if (entry == kEntryWide) us += batcher_us + kUsLaunchGap - kUsEntryWideSaves;
     else if (spread) { launch(20.0 + 0.15 * R / 1024.0); launches += 2; }       // ranking, scan, placement
-    else launch(7.0 + 1.1 * R / 1024.0);                                   // kernel trace: 7.0 us at 64 rows, 9.2 at 2048, 11.3 at 4096
+    else launch(batcher_us);
 
     double fc_in_mb = 0.0, img_in_mb = 0.0, img_out_mb = 0.0;
     for (uint32_t t = 0; t < T; ++t) {
