@@ -2140,10 +2140,14 @@ mt_status mt_tenant_account_get(mt_ctx* c, uint32_t tenant, mt_tenant_account* o
     return MT_OK;
 }
 
-mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* out)
+namespace {
+
+// mt_estimate_run.  *plan: a number that grows with the requests and differs wherever the run's launches or the kernels that serve it do: between counts of the
+// same number, the larger take longer.
+mt_status estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* out, uint64_t* plan)
 {
-    if (!c || !counts || !out) return MT_EINVAL;
     *out = mt_run_estimate{};
+    *plan = 0;
     const uint32_t T = c->cfg.max_tenants;
     const double es = c->elem_size, MB = 1e6;
     uint64_t R = 0;
@@ -2179,6 +2183,10 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
         request_cost(c, c->tenants[t], &f, &wb, &io);
         weights_mb += wb / MB;
     }
+    // (each of these turns once as R grows, those that go by the tiles' shape once in either shape)
+    *plan = (split_k ? 0u : 1u << 20) + (first_rows(c, R, split_k, big_possible, false) == kRowsStaged) + big_enabled + (R >= (uint64_t)kRankMinRows) + (R >= (uint64_t)kRankMinRows && !spread) +
+            (R > kEntryMaxRows) + (R >= kEntryWideMin) + (R > kEntryWideRows) + (tile_bound(c, 0, 0, R, split_k) > kEntryWideTiles);
+
     const double us_per_mb = weights_mb <= kCachedMb ? kUsPerMbCached : kUsPerMbHbm;
     double us = 0.0;
     uint32_t launches = 0;
@@ -2214,10 +2222,12 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
                     big_tiles += (uint64_t)((big_rows(counts[t]) + kBigTile - 1) / kBigTile) * ((d.N_pad + kBigTile - 1) / kBigTile);
             }
         const bool big_layer = big_tiles >= c->big_min_tiles;
+        *plan += big_layer + (big_enabled && tile_bound(c, 2, l, R) >= c->big_min_tiles);
         double w_mb = 0.0, l2_mb = 0.0, chain = 0.0, big_us = 0.0, conv_mb = 0.0, conv_mflop = 0.0, gap_mb = 0.0, ops_mb = 0.0;
         double big_rounds_k = 0.0, conv_chain = 0.0, first_mb = 0.0, first_mflop = 0.0;
         const ConvPlan conv_plan = plan_conv(c, l, R, nullptr);                                      // the launch decision of run_impl where the tenants stand in an id array
         const bool conv_frames = conv_plan.frames;
+        *plan += !conv_plan.split;
         double split_steps = 0.0, split_longest = 0.0;
         for (uint32_t t = 0; t < T; ++t) {
             if (!counts[t] || l >= c->tenants[t].n_layers) continue;
@@ -2286,6 +2296,15 @@ mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* ou
     return MT_OK;
 }
 
+}  // namespace
+
+mt_status mt_estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* out)
+{
+    if (!c || !counts || !out) return MT_EINVAL;
+    uint64_t plan;
+    return estimate_run(c, counts, out, &plan);
+}
+
 mt_status mt_admit(mt_ctx* c, const uint32_t* pending, double budget_ms, uint32_t* admitted, mt_run_estimate* est)
 {
     if (!c || !pending || !admitted) return MT_EINVAL;
@@ -2297,23 +2316,55 @@ mt_status mt_admit(mt_ctx* c, const uint32_t* pending, double budget_ms, uint32_
         top = std::max(top, pending[t]);
     }
     std::vector<uint32_t> trial(T);
-    mt_run_estimate e{};
-    auto fits = [&](uint32_t level) {
+    auto rows_at = [&](uint32_t level) {
         uint64_t rows = 0;
-        for (uint32_t t = 0; t < T; ++t) { trial[t] = std::min(pending[t], level); rows += trial[t]; }
-        if (rows > c->cfg.max_requests) return false;
-        if (mt_estimate_run(c, trial.data(), &e) != MT_OK) return false;
-        return e.device_ms + e.upload_ms <= budget_ms;
+        for (uint32_t t = 0; t < T; ++t) rows += std::min(pending[t], level);
+        return rows;
     };
-    // the predicted time grows with the level (up to small steps where a larger batch changes
-    // the launch plan), so the highest level that fits is found by bisection and then verified
-    uint32_t lo = 0, hi = top;                  // invariant: level lo fits (0 always does)
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo + 1) / 2;
-        if (fits(mid)) lo = mid; else hi = mid - 1;
+    if (rows_at(top) > c->cfg.max_requests) {                        // the highest level that a run has room for
+        uint32_t lo = 0, hi = top - 1;
+        while (lo < hi) { const uint32_t mid = lo + (hi - lo + 1) / 2; if (rows_at(mid) <= c->cfg.max_requests) lo = mid; else hi = mid - 1; }
+        top = lo;
     }
-    while (lo > 0 && !fits(lo)) --lo;
-    fits(lo);
+    struct Level { uint32_t level; uint64_t plan; double ms; mt_run_estimate e; };
+    auto look = [&](uint32_t level) {
+        Level v{level, 0, 0.0, {}};
+        for (uint32_t t = 0; t < T; ++t) trial[t] = std::min(pending[t], level);
+        v.ms = estimate_run(c, trial.data(), &v.e, &v.plan) == MT_OK ? v.e.device_ms + v.e.upload_ms : HUGE_VAL;
+        return v;
+    };
+    // Among the levels of one plan the predicted time grows (but for the rows that big tiles leave), and the highest that fits is found by bisection; from one plan to the next
+    // it may fall (a launch less).  So the levels above are looked through plan by plan, as far as runs of twice the budget: no plan saves half of a run.
+    auto highest = [&](auto& self, const Level& lo, const Level& hi) -> Level {       // of [lo, hi]; level 0: none fits
+        if (hi.ms <= budget_ms) return hi;
+        if (lo.plan == hi.plan) {
+            if (lo.ms > budget_ms) return Level{};
+            Level a = lo, b = hi;                                    // a fits, b does not
+            while (b.level - a.level > 1) { const Level m = look(a.level + (b.level - a.level) / 2); (m.ms <= budget_ms ? a : b) = m; }
+            return a;
+        }
+        if (hi.level - lo.level <= 1) return lo.ms <= budget_ms ? lo : Level{};
+        const uint32_t mid = lo.level + (hi.level - lo.level) / 2;
+        const Level above = self(self, look(mid + 1), hi);
+        return above.level ? above : self(self, lo, look(mid));
+    };
+    Level best = look(top);
+    if (top > 0 && best.ms > budget_ms) {
+        best = Level{};
+        uint32_t none = top;                                         // some level that fits: the highest, if the time only grew
+        while (none - best.level > 1) { const Level m = look(best.level + (none - best.level) / 2); if (m.ms <= budget_ms) best = m; else none = m.level; }
+        uint32_t from = best.level + 1, to = std::min(top, from + best.level);
+        while (from <= top) {                                        // [from, to], more levels each time
+            const Level lo = look(from), hi = look(to);
+            const Level found = highest(highest, lo, hi);
+            if (found.level) best = found;
+            if (hi.ms > 2.0 * budget_ms && lo.ms > 2.0 * budget_ms) break;
+            from = to + 1;
+            to += std::min(top - to, to + 1);
+        }
+    }
+    for (uint32_t t = 0; t < T; ++t) trial[t] = std::min(pending[t], best.level);
+    const mt_run_estimate e = best.e;
     for (uint32_t t = 0; t < T; ++t) admitted[t] = trial[t];
     if (est) *est = e;
     return MT_OK;

@@ -633,3 +633,33 @@ def test_estimates_step_by_what_a_launch_less_saves(dtype, dims):
     assert all(-3.0 <= us <= -1.0 for d, us in steps if d < 0) and all(1.0 <= us <= 3.0 for d, us in steps if d > 0)
     assert all(us > -1e-6 for d, us in steps if d == 0)
     c.close()
+
+
+def test_admission_finds_the_highest_level_across_changes_of_the_launches():
+    # the prediction falls where a larger run has a launch less or other kernels: every level is tried here, over models of all kinds and budgets around each level's prediction
+    import paper_1901_06887_amd as mt
+    import workloads as wl
+    mlp = lambda dims: wl.mlp_layers(dims, wl.ACT_RELU)  # noqa: E731
+    fleets = [({t: mlp([784, 1024, 1024, 10]) for t in range(64)}, 64 * 20, [20] * 64),
+              ({t: mlp([784, 1024, 1024, 10]) for t in range(64)}, 4096, [1 + t % 9 * 7 for t in range(64)]),
+              ({t: mlp([301, 520, 37]) for t in range(12)}, 1500, [130] * 12),
+              ({t: mlp([256, 512, 100]) if t % 2 else mlp([256, 512, 512, 10]) for t in range(4)}, 900, [300, 280, 0, 300]),
+              ({t: wl.cnn_layers(hw=16, chans=(3, 32, 64, 128), strides=(1, 1, 2)) for t in range(6)}, 600, [90] * 6),
+              ({0: wl.resnet18_layers(hw=32, widths=(16, 32, 64, 128), classes=10), 1: wl.cnn_layers(hw=32), 2: mlp([3072, 256, 40])}, 300, [80, 100, 60])]
+    fell = 0
+    for layers, most, pending in fleets:
+        for dtype in ("bf16", "f32"):
+            tenants = {t: wl.make_model(m, dtype, 5, t) for t, m in layers.items()}
+            ctx = mt.context_for(tenants, dtype, most, device=-1)
+            mt.register_tenants(ctx, tenants)
+            at = lambda level: [min(p, level) for p in pending]  # noqa: E731
+            ms = [0.0] + [ctx.estimate_run(at(level))["device_ms"] for level in range(1, max(pending) + 1) if sum(at(level)) <= most]
+            fell += sum(b < a for a, b in zip(ms, ms[1:]))
+            for level in range(1, len(ms), 1 + len(ms) // 40):
+                for budget in (ms[level], ms[level] * 0.9999, ms[level] + 0.0015):
+                    admitted, est = ctx.admit(pending, budget)
+                    want = max(i for i, m in enumerate(ms) if m <= budget)
+                    assert list(admitted) == at(want), (dtype, budget, want)
+                    assert est["device_ms"] == ms[want] and est["rows"] == sum(admitted)
+            ctx.close()
+    assert fell > 0
