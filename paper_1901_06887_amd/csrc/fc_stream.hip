@@ -119,7 +119,11 @@ __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Ti
             u32x4 v = xr[j];
             if constexpr (GATHER == kRowsAny) {
                 const uint32_t k = (c * KC + xkk[j]) * KB;
-                if (k == any.rest / KB * KB) v = any.rest - k == (lane >> 5) * EPC ? *(const u32x4*)(stages + kFcLdsBytes + wave * kBrickBytes + lane * 16) : v;      // (uniform: one step of all)
+                if (k == any.rest / KB * KB) {                // (uniform: one step of all; the address is worked out there, see fc_tile)
+                    uint32_t at = lane;
+                    asm("" : "+v"(at));
+                    if (any.rest - k == (at >> 5) * EPC) v = *(const u32x4*)(stages + kFcLdsBytes + wave * kBrickBytes + at * 16);
+                }
             }
             *(u32x4*)(stages + (c & 1) * kStageBytes + (wave * 4 + j) * kBrickBytes + lane * 16) = v;
         }
@@ -444,13 +448,13 @@ __device__ __forceinline__ void fc_whole_tile(const GemmArgs& a, const Tile& tl,
     fc_finish_rows<kTileCols / kBrickRows, LRS>(a, lt, L.N, tl.m0, Mt, sub);
 }
 
-template <typename T, int RB, int GATHER, typename ROWS>
+// LAST: the layer may be a last one (not in fc_entry_wide_kernel, whose models all have a second).
+template <typename T, int RB, int GATHER, bool LAST, typename ROWS>
 __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t Mt, uint32_t seg0, const ROWS& row_of, T* xout, uint8_t* smem)     // xout: the tenant's first output row
 {
     const uint32_t split = tl.split;
     constexpr uint32_t EPC = 16 / sizeof(T), KB = 2 * EPC;
-    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t li = lane & 31, lh = lane >> 5;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t nb = tl.n0 / kBrickRows + wave;            // (split == 4)
     const bool active = nb < L.N_pad / kBrickRows;
     const uint32_t nrb = (tl.rows + kBrickRows - 1) / kBrickRows;
@@ -462,17 +466,21 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[r][v] = 0.0f;
 
-    const uint32_t n = nb * kBrickRows + li;
-    const float bv = active ? ((const float*)(a.arena + L.b_off))[n] : 0.0f;      // (asked for in front of the sums: 4096 requests to 64 MLPs 99.4 -> 97.3 us)
+    const float bv = active ? ((const float*)(a.arena + L.b_off))[nb * kBrickRows + (threadIdx.x & 31)] : 0.0f;      // (asked for in front of the sums: 4096 requests to 64 MLPs 99.4 -> 97.3 us)
     fc_accumulate_shared<T, RB, GATHER>(a, tl, L, seg0, nb, active, row_of, smem, acc);
-    if (L.is_last && a.fuse_head && L.N <= a.fuse_head_max && L.N_pad <= split * kBrickRows) {
+    // What follows goes by the lane, and is worked out from here on: kept through the K loop, which uses all the registers there are, it went to scratch memory in
+    // fc_entry_wide_kernel (64 tenants of 784-1024-1024-10, 1024 / 2048 requests 55.4 / 63.2 -> 54.0 / 60.5 us a pass; rows of 787 values, 32 tenants, 38.9 / 51.9 -> 36.4 / 48.6)
+    uint32_t tid_behind = threadIdx.x;
+    asm volatile("" : "+v"(tid_behind));
+    const uint32_t lane = tid_behind & 63, li = lane & 31, lh = lane >> 5, n = nb * kBrickRows + li;
+    if (LAST && L.is_last && a.fuse_head && L.N <= a.fuse_head_max && L.N_pad <= split * kBrickRows) {
         // 33 .. 128 classes, all of them inside this tile (one column group): the waves put their
         // 32x32 blocks of logits side by side in LDS as [row][class], then eight threads share a
         // row: softmax, argmax (lowest index on ties) and the outputs in submission order.
         constexpr uint32_t LRS = kTileCols + 4;                 // floats per row of the logits tile (16-byte aligned rows)
         static_assert(kBrickRows * LRS * 4 <= kFcLdsBytes, "the logits tile of one row block must fit the kernel's LDS");
         float* lt = (float*)smem;
-        const uint32_t C = L.N, tid = threadIdx.x, row = tid >> 3, part = tid & 7;
+        const uint32_t C = L.N, tid = tid_behind, row = tid >> 3, part = tid & 7;
         const bool vec = a.out_vec_ok;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
@@ -541,7 +549,7 @@ __device__ __forceinline__ void fc_tile(const GemmArgs& a, const Tile& tl, const
         }
         return;
     }
-    if (L.is_last) {
+    if (LAST && L.is_last) {
         if (!active || n >= L.N) return;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
@@ -630,8 +638,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW && !
     };
     if constexpr (!NARROW) {
         if (__builtin_expect(tl.split == 4, 1)) {
-            if (__builtin_expect(nrb > 1, 1)) fc_tile<T, 2, GATHER>(a, tl, L, Mt, seg0, row_of, xout, smem);
-            else fc_tile<T, 1, GATHER>(a, tl, L, Mt, seg0, row_of, xout, smem);
+            if (__builtin_expect(nrb > 1, 1)) fc_tile<T, 2, GATHER, true>(a, tl, L, Mt, seg0, row_of, xout, smem);
+            else fc_tile<T, 1, GATHER, true>(a, tl, L, Mt, seg0, row_of, xout, smem);
             return;
         }
     }
@@ -870,8 +878,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     };
     T* xout = (T*)act_of(a.act, L.out_buf) + (size_t)seg0 * a.S;
     if (__builtin_expect(tl.split == 4, 1)) {
-        if (__builtin_expect(tl.rows > (uint32_t)kBrickRows, 1)) fc_tile<T, 2, ROWS>(a, tl, L, Mt, seg0, row_of, xout, smem);
-        else fc_tile<T, 1, ROWS>(a, tl, L, Mt, seg0, row_of, xout, smem);
+        if (__builtin_expect(tl.rows > (uint32_t)kBrickRows, 1)) fc_tile<T, 2, ROWS, false>(a, tl, L, Mt, seg0, row_of, xout, smem);
+        else fc_tile<T, 1, ROWS, false>(a, tl, L, Mt, seg0, row_of, xout, smem);
         return;
     }
     bool row_ok;

@@ -74,3 +74,10 @@ def test_facts_ahead_cost_no_frame_tile_its_place(tmp_path):
                 taken += got and ahead < without
                 assert not mt.debug_conv_frame_ahead(33, blocks, frame, grid) and not mt.debug_conv_frame_ahead(32, 1, frame, grid)
     assert taken > 0
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
+def test_no_kernel_keeps_registers_in_scratch_memory(tmp_path):
+    kernels = kernel_resources(tmp_path)
+    assert len(kernels) > 100
+    assert not {n: r for n, r in kernels.items() if r[0]}
