@@ -586,8 +586,8 @@ def test_runs_of_any_tiles_without_a_batcher(monkeypatch, dtype, n_tenants, rows
     assert got["0n"] == got["1n"] - (rows <= 4096)
 
 
-# layer 0 reads rows of any length at any address: lengths around whole chunks and steps, rows that begin at odd elements with undefined values behind each, every kernel that
-# does so (few rows and many without the batcher, more tenants than it takes, several submissions).  Against the oracle, and to the bit against staged rows
+# layer 0 reads rows of any length at any address: lengths around whole chunks and steps, rows that begin at odd elements with undefined values behind each, in tiles that split K (few
+# rows and many without the batcher) and of four column blocks (more tenants than it takes, a row or two each), several submissions.  Against the oracle, and to the bit against staged rows
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n_in", [1, 3, 7, 8, 9, 31, 63, 64, 65, 301])
 @pytest.mark.parametrize("rows,n_tenants", [(19, 3), (700, 3), (90, 70)])
@@ -598,7 +598,7 @@ def test_rows_of_any_length_at_any_address(monkeypatch, dtype, n_in, rows, n_ten
     x = rng.standard_normal((rows, n_in)).astype(np.float32)
     ids = rng.integers(0, n_tenants, rows).astype(np.int32)
     w = wl.Workload("any", dtype, tenants, ids, wl.round_to_bf16(x) if dtype == "bf16" else x)
-    stride = n_in + 4 + n_in % 2                                     # odd or even, and no two rows need be alike in alignment
+    stride = n_in + 4 + n_in % 2                                     # even: every row begins at an odd element
     buf = np.full(rows * stride + 1, np.nan, np.float32)
     for r in range(rows):
         buf[1 + r * stride:1 + r * stride + n_in] = w.inputs[r]
@@ -620,6 +620,50 @@ def test_rows_of_any_length_at_any_address(monkeypatch, dtype, n_in, rows, n_ten
             assert all(np.array_equal(u, v) for u, v in zip(got[off][0], got[off][-1]))
         ctx.close()
     assert all(np.array_equal(u, v) for u, v in zip(got["0"][0], got["1"][0]))
+
+
+# the same in tiles of four column blocks and two row blocks, whose second one is full, ragged or missing, at odd strides (rows begin at odd and even elements by turns): without the
+# batcher, behind it, and in several submissions.  Against the oracle, and to the bit against staged rows
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_in", [1, 3, 7, 8, 9, 31, 63, 64, 65, 301])
+@pytest.mark.parametrize("counts", [(33, 64, 255), (95, 32, 401)])
+def test_wide_tiles_read_rows_of_any_length_at_any_address(monkeypatch, dtype, n_in, counts):
+    monkeypatch.setenv("MT_NO_AUTO_SPLIT_K", "1")
+    rows = sum(counts)
+    shapes = ([n_in, 130, 5], [n_in, 200, 70], [n_in, 300, 64, 7])
+    tenants = {t: wl.make_model(wl.mlp_layers(shapes[t], wl.ACT_RELU), dtype, 398, t) for t in range(3)}
+    rng = np.random.default_rng(398)
+    x = rng.standard_normal((rows, n_in)).astype(np.float32)
+    ids = rng.permutation(np.repeat(np.arange(3), counts)).astype(np.int32)
+    w = wl.Workload("wide any", dtype, tenants, ids, wl.round_to_bf16(x) if dtype == "bf16" else x)
+    stride = n_in + 4 + (n_in + 1) % 2
+    assert stride % 2
+    buf = np.full(rows * stride + 1, np.nan, np.float32)
+    for r in range(rows):
+        buf[1 + r * stride:1 + r * stride + n_in] = w.inputs[r]
+    d_buf, d_ids = torch_io.to_device(buf[None], dtype), torch.from_numpy(ids).cuda()
+    at, es = d_buf.data_ptr() + d_buf.element_size(), d_buf.element_size()
+    got, launches = {}, {}
+    for entry, gather in (("0", "0"), ("1", "0"), ("0", "1")):
+        monkeypatch.setenv("MT_NO_ENTRY", entry)
+        monkeypatch.setenv("MT_NO_FUSED_GATHER", gather)
+        ctx = make_context(w, max_tenants=3)
+        got[entry, gather], launches[entry, gather] = [], []
+        for cuts in ([0, rows], [0, rows // 3, rows // 2, rows]):
+            out = torch_io.alloc_outputs(rows, ctx.cfg.max_classes)
+            for a, b in zip(cuts[:-1], cuts[1:]):
+                ctx.submit_batch(d_ids.data_ptr() + 4 * a, at + a * stride * es, b - a, stride)
+            ctx.debug_poison()
+            ctx.run(torch.cuda.current_stream().cuda_stream, out.labels.data_ptr(), out.probs.data_ptr(), out.logits.data_ptr(), out.n_classes.data_ptr(), rows, ctx.cfg.max_classes)
+            torch.cuda.synchronize()
+            got[entry, gather].append((out.logits.cpu().numpy().astype(np.float64), out.probs.cpu().numpy().astype(np.float64), out.labels.cpu().numpy(), out.n_classes.cpu().numpy()))
+            launches[entry, gather].append(ctx.stats()["last_run_launches"])
+        ctx.close()
+    first = got["0", "0"][0]
+    compare(w, first, oracle_rows(w), what="%s %s x %d" % (dtype, counts, n_in))
+    assert all(np.array_equal(u, v) for runs in got.values() for g in runs for u, v in zip(first, g))
+    # layers; with the batcher's launch and, staged, that of the rows (one submission: layer 0 has the batcher's work where it reads the rows)
+    assert launches["0", "0"] == [3, 4] and launches["1", "0"] == [4, 4] and launches["0", "1"] == [5, 5]
 
 
 # last layers of 33 to 128 classes finished by tiles of all their column blocks in runs whose tiles split K: classes at the edges of a block and of the range, sums shorter than
