@@ -302,8 +302,9 @@ mt_status mt_tenant_account_get(mt_ctx* ctx, uint32_t tenant, mt_tenant_account*
  * what enters the next run from this).  flops and hbm_bytes are the algorithmic work
  * (weights of active tenants read once, activations written once and read once);
  * launches is the number of kernels mt_run will enqueue (for the requests as they are pending,
- * or for others in one submission: a small run of fully-connected models takes one launch more
- * in several submissions, or while its stream is being captured); device_ms is the predicted
+ * or for others in one submission: a run of fully-connected models may take one launch more in
+ * several submissions, and one more while its stream is being captured, or two if a model has
+ * 33 to 128 classes); device_ms is the predicted
  * time of the run alone on the GPU, from a per-kernel model (fixed cost per launch +
  * bytes through HBM + bytes re-read through L2, or tile rounds for compute-bound
  * launches) whose constants were fitted on one MI355X.  Works on a host-only context.

@@ -28,7 +28,6 @@ constexpr uint32_t kFcLdsBytes = kTrOffset + 4 * kTrBytes;
 template <int ROWS> constexpr uint32_t fc_lds_bytes() { return kFcLdsBytes + (ROWS == kRowsAny ? 4 * kBrickBytes : 0); }      // (the tails of rows of any length)
 static_assert(kFcLdsBytes >= 2 * kStageBytes, "the two activation stages must fit");
 
-// split == 4: activations through LDS, weights through the register ring.
 // A lane's row of any length at any address: chunks that lie in it whole come as 16 bytes, wherever they begin; the others from a block of zeros (no lane reads past
 // its row), and the elements behind the last whole chunk, asked for one by one up front, take the place of the chunk that they begin.
 template <typename T> struct AnyChunk;
@@ -58,6 +57,7 @@ template <typename T> struct AnyRow {
     __device__ __forceinline__ u32x4 at(uint32_t k, const u32x4& v) const { return k == rest ? tail : v; }
 };
 
+// split == 4: activations through LDS, weights through the register ring.
 // row_of(block of 32 rows of the tile, lane, real): the submitted row of a lane (GATHER).
 template <typename T, int RB, int GATHER, typename ROWS>
 __device__ __forceinline__ void fc_accumulate_shared(const GemmArgs& a, const Tile& tl, const LayerDev& L, uint32_t seg0,
@@ -655,13 +655,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW && !
 }
 
 // ---- layer 0 of a small run, with the segmentation in it ------------------------------------------
-// One submission of at most 256 rows, at most 64 tenants: the batcher's launch, one workgroup, is a sixth of such a pass.
-// Here every wave of every workgroup works the segmentation out for itself, with the tenants in its lanes: the rows of a lane's tenant
-// are a bit mask per 64 rows, from one ballot per id bit; tile counts and offsets are two wave scans, a tile's owner one
-// ballot.  That takes one round trip to memory (ids, tenants, facts) where the tile list, the row order and the rows' addresses took
-// three.  The last workgroup has no tile and writes what the launches behind this one read, as the batcher leaves it: counts, offsets,
-// row order and the tile lists of layers 1 on (streaming FC tiles only: models with images are not served this way).
-// 1 request to 8 tenants' 784-1024-1024-10 models: 23.8 -> 20.2 us, 64 fp32 requests to four 256-512-512-10 models 26.5 -> 23.1.
 __device__ __forceinline__ uint32_t entry_tiles(const BatchArgs& b, const uint4& f, uint32_t M)      // streaming FC tiles of a tenant, as the batcher counts them
 {
     const bool sk = b.fc_split_k && f.x;
@@ -692,6 +685,13 @@ __device__ __forceinline__ void entry_lists(const BatchArgs& b, uint32_t lane, u
     }
 }
 
+// One submission of at most 256 rows, at most 64 tenants: the batcher's launch, one workgroup, is a sixth of such a pass.
+// Here every wave of every workgroup works the segmentation out for itself, with the tenants in its lanes: the rows of a lane's tenant
+// are a bit mask per 64 rows, from one ballot per id bit; tile counts and offsets are two wave scans, a tile's owner one
+// ballot.  That takes one round trip to memory (ids, tenants, facts) where the tile list, the row order and the rows' addresses took
+// three.  The last workgroup has no tile and writes what the launches behind this one read, as the batcher leaves it: counts, offsets,
+// row order and the tile lists of layers 1 on (streaming FC tiles only: models with images are not served this way).
+// 1 request to 8 tenants' 784-1024-1024-10 models: 23.8 -> 20.2 us, 64 fp32 requests to four 256-512-512-10 models 26.5 -> 23.1.
 template <typename T, int ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void fc_entry_kernel(GemmArgs a, BatchArgs b)
 {
@@ -781,9 +781,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 
 // The same for one submission of at most 4096 rows and any tiles: the workgroup's waves take a quarter of the rows each, count them by tenant in LDS and, once the
 // tile's tenant is known, note those that are the tile's.  A tile waits for ids and facts, the layer's row and the submitted rows, in place of the tile list, that row,
-// the rows' addresses and the rows; the batcher's launch, alone on the chip for 5-7 us, is gone.  Passes and the line beside run_entry.  Bound as fc_kernel is: by the weight
-// stream, behind 2-3 us until the first weight load.  (With the ids in registers and masks from ballots, as above, 16 unrolled steps of them spilled 91 registers and the tiles took
-// half as long again; without the leader's addition 64 rows of one tenant added one by one, 4096 requests to one tenant 113 -> 123 us.)
+// the rows' addresses and the rows; the batcher's launch, alone on the chip for 5-7 us, is gone.  Passes and the line beside run_entry.  Bound as fc_kernel is: by the
+// weight stream, behind 2-3 us until the first weight load.  (With the ids in registers and masks from ballots, as above, 16 unrolled steps of them spilled 91 registers
+// and the tiles took half as long again.  Of 64 rows the first one's tenant is counted at once, every other row by an addition of its lane: without that, all rows one
+// tenant's, 4096 requests 113 -> 123 us.)
 template <typename T, int ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void fc_entry_wide_kernel(GemmArgs a, BatchArgs b)
 {

@@ -97,8 +97,8 @@ constexpr size_t kPlansKept = 64;
 struct NamedRows { uint32_t tenant, rows; };   // requests of a tenant in the submissions that named it
 
 // The event behind every run orders runs of other streams of the same device behind it, on the device; nothing on the host or another device looks at it.  So it needs no
-// fence of the whole system, which wrote back the L2s at the end of every run: 64 fp32 requests to MLPs 22.5 -> 20.7 us a pass, 150 fp32 images to CNNs 132.9 -> 130.9,
-// 4096 requests to MLPs 100.4 -> 99.4.  (Whoever waits for the stream, or copies from it, has a fence of their own.)
+// fence of the whole system, which wrote back the L2s at the end of every run: 64 fp32 requests to MLPs 23.0 -> 21.3 us a pass, and where the labels are copied out
+// behind every pass 43.7 -> 42.7, one bf16 request 39.8 -> 38.5, 150 fp32 images to CNNs 151.4 -> 149.5.  (Whoever waits for the stream, or copies from it, has a fence of their own.)
 constexpr unsigned kSlotEvent = hipEventDisableTiming | hipEventDisableSystemFence;
 
 // Device scratch of one run in flight: batch descriptors, activation buffers, logits.  A run owns
@@ -214,7 +214,6 @@ struct mt_ctx {
     uint32_t* d_row_rank = nullptr;
     uint32_t* d_hist_g = nullptr;      // [kHistEntries] per-workgroup tenant histograms of the ranking kernel
     const void** d_row_src = nullptr;
-   
     int32_t* d_pos_of = nullptr;
     int32_t* d_perm = nullptr;
     uint32_t* d_M = nullptr;
@@ -990,19 +989,21 @@ int first_rows(const mt_ctx* c, uint64_t R, bool split_k, bool big_possible, boo
 }
 
 // Whether layer 0 does the batcher's work in a run of one submission of R rows that it reads itself: few tenants, nothing but FC layers, and no model that is
-// finished there.  kEntryNarrow: few rows and nothing but tiles that split K; kEntryWide: any tiles, as long as they start together (three workgroups to a compute unit):
-// every tile of a second round does the segmentation once more behind the first.  us a pass, with the batcher's launch and so, bf16: 64 tenants of 784-1024-1024-10,
-// 300 / 1024 / 2048 requests 55.6 / 72.2 / 73.8 -> 53.4 / 69.7 / 71.1, 16 of 512-512-512-10 26.2 / 31.3 / 35.4 -> 23.6 / 28.8 / 32.5, one of 1024-2048-2048-40, 2048 and 3000 (at most 766
-// tiles) 66.5 / 85.9 -> 65.2 / 84.1, 4096 (1040) 110.2 -> 112.7; at most 1024 tiles (4096 requests of the first) 100.9 -> 100.2, three runs in flight 215.0 -> 221.6.  (It gains as much from 65 rows on:
-// 54.6 -> 52.4 at 257, the 300 above.  Up to 319 runs of ordinary tiles keep the launches that they are known to have.)
+// finished there.  kEntryNarrow: few rows and nothing but tiles that split K; kEntryWide: any tiles, as long as they start together (three workgroups to a compute
+// unit): every tile of a second round does the segmentation once more behind the first.  us a pass, with the batcher's launch and so, bf16: 64 tenants of
+// 784-1024-1024-10, 320 / 1024 / 2048 requests 58.1 / 58.7 / 66.0 -> 53.9 / 54.3 / 61.3; 16 of 512-512-512-10, 320 / 1024 / 2048 / 4096 22.9 / 29.3 / 33.0 / 41.8 ->
+// 18.9 / 25.4 / 28.8 / 37.4; one of 1024-2048-2048-40, 320 / 2048 / 3000 (at most 766 tiles) 39.7 / 66.7 / 86.3 -> 36.4 / 63.8 / 82.5.  Beyond the upper line, when
+// these tiles still spilled registers: 4096 of the last (1040 tiles) 110.2 -> 112.7, of the first (1024) 100.9 -> 100.2, three runs in flight 215.0 -> 221.6.
+// The lower line is no measured crossing: 257 requests to the first took 52.4 in place of 54.6, and by the same trips to memory so would any from 65 on.  Up to
+// 319 rows runs of ordinary tiles keep a launch per layer and one, which is what their estimates have promised.
 constexpr uint32_t kEntryWideMin = 320;
-constexpr uint64_t kEntryWideTiles = 768;
+constexpr uint64_t kEntryWideTilesPerCu = 3;
 enum : int { kEntryNone = 0, kEntryNarrow, kEntryWide };
 int run_entry(const mt_ctx* c, uint64_t R, bool split_k)
 {
     if (c->cfg.max_tenants > kEntryMaxTenants || c->no_entry || c->any_conv_first || !c->any_fc_first || c->min_layers < 2) return kEntryNone;
     if (R <= kEntryMaxRows && (split_k || c->max_fc_cols[0] <= 2 * (uint32_t)kBrickRows)) return kEntryNarrow;
-    return R >= kEntryWideMin && R <= kEntryWideRows && tile_bound(c, 0, 0, R, split_k) <= kEntryWideTiles ? kEntryWide : kEntryNone;
+    return R >= kEntryWideMin && R <= kEntryWideRows && tile_bound(c, 0, 0, R, split_k) <= kEntryWideTilesPerCu * c->n_cus ? kEntryWide : kEntryNone;
 }
 
 // Whether last layers of 33 to 128 classes take tiles of all their column blocks in a run whose tiles split K (fc_whole_tile): where it pays for all of them, as the head's launch
@@ -2114,7 +2115,7 @@ constexpr double kUsConvSplitFixed = 1.0, kUsConvSplitPerKStep = 0.034;     // l
 constexpr double kUsConvPerKStep = 0.21;     // a convolution tile's walk through K, per k-step of 32 bytes per pixel: a launch lasts at least as long as its longest tile
 constexpr double kUsBatcher = 7.0, kUsBatcherPer1024 = 1.1;     // kernel trace: 7.0 us at 64 rows, 9.2 at 2048, 11.3 at 4096
 constexpr double kUsEntry = 3.0;             // what the segmentation costs a small run's first layer
-constexpr double kUsEntryWideSaves = 2.5;    // what it saves where it is done by tiles of any kind: of the batcher's launch and the gap behind it (measured 1.3 to 2.9, beside run_entry)
+constexpr double kUsEntryWideSaves = 3.7;    // what it saves where tiles of any kind do it: of the batcher's launch and the gap behind it (measured 2.9 to 4.7, beside run_entry)
 constexpr double kUsSmallFixed = 3.0, kCopyMbPerUs = 3.7, kHeadMbPerUs = 5.7, kUsHeadPerRow = 0.0008;
 constexpr double kComputeUnits = 256.0;
 constexpr double kUploadBytesPerMs = 55e6, kUsUploadFixed = 20.0;     // pinned host memory to HBM over the host link: 55 GB/s measured
@@ -2185,7 +2186,7 @@ mt_status estimate_run(mt_ctx* c, const uint32_t* counts, mt_run_estimate* out, 
     }
     // (each of these turns once as R grows, those that go by the tiles' shape once in either shape)
     *plan = (split_k ? 0u : 1u << 20) + (first_rows(c, R, split_k, big_possible, false) == kRowsStaged) + big_enabled + (R >= (uint64_t)kRankMinRows) + (R >= (uint64_t)kRankMinRows && !spread) +
-            (R > kEntryMaxRows) + (R >= kEntryWideMin) + (R > kEntryWideRows) + (tile_bound(c, 0, 0, R, split_k) > kEntryWideTiles);
+            (R > kEntryMaxRows) + (R >= kEntryWideMin) + (R > kEntryWideRows) + (tile_bound(c, 0, 0, R, split_k) > kEntryWideTilesPerCu * c->n_cus);
 
     const double us_per_mb = weights_mb <= kCachedMb ? kUsPerMbCached : kUsPerMbHbm;
     double us = 0.0;

@@ -423,8 +423,9 @@ struct TileOwner {
     }
 };
 
-// The same, together with what a tile needs to know of its tenant: the layer's row, the tenant's requests and first packed row, and its first tile.  With at most TENANTS tenants (0: any number, by loads of its own) the workgroup fetches those of all of them beside the tile list, a
-// 16-byte piece or two per thread, and finds its own in LDS: one trip to memory at the head of a tile instead of two that depend on each other.
+// The same, together with what a tile needs to know of its tenant: the layer's row, the tenant's requests and first packed row, and its first tile.  With at most
+// TENANTS tenants (0: any number, by loads of its own) the workgroup fetches those of all of them beside the tile list, a 16-byte piece or two per thread, and finds
+// its own in LDS: one trip to memory at the head of a tile instead of two that depend on each other.
 // A launch of few tiles lasts as long as its chain of trips: residual nets of one request 161.9 -> 151.4 us a pass, MLPs, CNNs and residual nets side by side
 // 193.8 -> 182.0, residual nets of 64 images 531 -> 518, one request to an MLP 20.3 -> 19.7.  LDS: ahead_bytes(), not read behind the next barrier.
 constexpr uint32_t kRowWords = sizeof(LayerDev) / 4, kFactsWords = kRowWords + 4;      // of a tenant's row; with three more, and padding

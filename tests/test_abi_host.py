@@ -621,7 +621,7 @@ def test_small_runs_finish_wide_last_layers_where_that_is_not_slower(dtype, k, c
 @pytest.mark.parametrize("dtype", [B.MT_BF16, B.MT_F32])
 @pytest.mark.parametrize("dims", [(784, 1024, 1024, 10), (512, 512, 512, 10)])
 def test_estimates_step_by_what_a_launch_less_saves(dtype, dims):
-    # where layer 0 does the batcher's work the run has a launch less and is measured 1.3 to 2.9 us shorter: no larger steps at either end of the range
+    # where layer 0 does the batcher's work the run has a launch less and is measured 2.9 to 4.7 us shorter: no larger steps at either end of the range
     c = host_ctx(dtype=dtype, arena=1 << 29, max_classes=16, max_requests=4200, max_tenants=64)
     specs = [fc(a, b) for a, b in zip(dims, dims[1:])]
     for t in range(64):
@@ -630,7 +630,7 @@ def test_estimates_step_by_what_a_launch_less_saves(dtype, dims):
     est = [c.estimate_run(spread(rows)) for rows in range(300, 4201)]
     steps = [(b["launches"] - a["launches"], (b["device_ms"] - a["device_ms"]) * 1e3) for a, b in zip(est, est[1:])]
     assert sum(d for d, _ in steps if d < 0) == -1 and sum(d for d, _ in steps if d > 0) == 1
-    assert all(-3.0 <= us <= -1.0 for d, us in steps if d < 0) and all(1.0 <= us <= 3.0 for d, us in steps if d > 0)
+    assert all(-4.7 <= us <= -2.0 for d, us in steps if d < 0) and all(2.0 <= us <= 4.7 for d, us in steps if d > 0)
     assert all(us > -1e-6 for d, us in steps if d == 0)
     c.close()
 
