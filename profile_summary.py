@@ -67,9 +67,9 @@ def split_warm_cold(trace_csv: str, kernel: str) -> str:
         dur = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
         if "elementwise_kernel" in name and dur > 100.0:
             flushed = True                       # the benchmark's 1 GiB rewrite in front of a step
-        elif "batcher_kernel" in name:           # every step has exactly one
+        elif "batcher_kernel" in name or "fc_entry_" in name:          # every step has exactly one of them
             step_cold, flushed = flushed, False
-        elif kernel in short_name(name):
+        if kernel in short_name(name):
             acc[step_cold].append(dur)
     out = []
     for cold in (False, True):
@@ -86,7 +86,7 @@ def launches(trace_csv: str) -> str:
     runs = []
     for r in rows:
         name = short_name(r["Kernel_Name"])
-        if "rank_kernel" in name or "fc_entry_kernel" in name or ("batcher_kernel" in name and not (runs and "rank_kernel" in runs[-1][-1][0])):
+        if "rank_kernel" in name or "fc_entry_" in name or ("batcher_kernel" in name and not (runs and "rank_kernel" in runs[-1][-1][0])):
             runs.append([])
         if runs and "mt::" in name:
             runs[-1].append((name, (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3, r))
