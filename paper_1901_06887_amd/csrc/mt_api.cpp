@@ -639,7 +639,7 @@ void recompute_pool_fusion(mt_ctx* c)
 
 // Whether a last layer of 33 to 128 classes takes less time in tiles of all its column blocks than in one per block with the head's launch behind them.  Two blocks at once, and
 // the pairs in turn, are a longer walk through K than one block by itself: some 0.12 us for each k step of a wave's quarter in fp32, 0.04 in bf16; the launch takes 1 to 3.  One request
-// to one model of 256-K-C / 64 to four / 300 to one, us a pass with the head's launch and so: fp32, C = 64, K = 512 24.3 / 24.6 / 27.2 -> 21.9 / 22.2 / 27.2, 768 24.4 / 25.2 / 28.6 ->
+// to one model of 256-256-K-C / 64 to four / 300 to one, us a pass with the head's launch and so: fp32, C = 64, K = 512 24.3 / 24.6 / 27.2 -> 21.9 / 22.2 / 27.2, 768 24.4 / 25.2 / 28.6 ->
 // 23.7 / 24.2 / 29.1 (2048: 30.0 -> 34.1); C = 128, 128 23.6 / 23.8 / 27.0 -> 21.6 / 21.6 / 26.4, 192 23.8 / 23.9 / 27.1 -> 22.5 / 22.6 / 27.3 (2048: 29.9 -> 50.8); bf16, C = 64, 2048
 // 23.4 / 23.5 / 27.2 -> 20.8 / 20.9 / 26.3, 4096 21.9 / - / 34.1 -> 21.2 / - / 34.1; C = 128, 1024 23.0 / 23.3 / 27.0 -> 21.2 / 21.2 / 26.0, 1536 23.2 / 23.4 / 27.3 -> 21.5 / 21.9 / 27.7.
 bool whole_pays(const mt_ctx* c, const LayerDev& L)
