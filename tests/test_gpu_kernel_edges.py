@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import paper_1901_06887_amd as mt
 import workloads as wl
 from gpu_common import compare, gpu_run, make_context, oracle_rows
 from paper_1901_06887_amd import torch_io
@@ -690,3 +691,41 @@ def test_small_runs_finish_wide_last_layers_in_their_tiles(monkeypatch, dtype, c
             assert launches[0] == launches[1] - (classes <= 128)
         else:
             assert launches[0] == launches[1]
+
+
+# on either side of the line for tiles of all a last layer's column blocks (sums of a last layer, its blocks): the launches that the estimate says, the oracle's results
+@pytest.mark.parametrize("dtype,k,classes", [("bf16", 1344, 128), ("bf16", 1408, 97), ("bf16", 4096, 64), ("bf16", 4160, 33), ("f32", 128, 100), ("f32", 192, 65), ("f32", 512, 64), ("f32", 576, 40)])
+def test_wide_last_layers_around_the_line_of_whole_tiles(dtype, k, classes):
+    tenants = {t: wl.make_model(wl.mlp_layers([40, k, classes], wl.ACT_RELU), dtype, 399, t) for t in range(2)}
+    x = np.random.default_rng(399).standard_normal((45, 40)).astype(np.float32)
+    w = wl.Workload("line", dtype, tenants, (np.arange(45) % 2).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
+    ctx = make_context(w)
+    launches = ctx.estimate_run(np.bincount(w.tenant_ids))["launches"]
+    check(w, "%s %d %d" % (dtype, k, classes), ctx)
+    assert ctx.stats()["last_run_launches"] == launches
+    ctx.close()
+
+
+# frames of which one tile fewer fits a compute unit with their tenants' facts beside them: a launch that starts at once has the facts ahead, a larger one of the same tenants not.
+# The same images in both, and against the oracle
+@pytest.mark.parametrize("dtype,hw,chans", [("bf16", 8, (3, 192, 192, 192)), ("bf16", 10, (3, 128, 64, 128)), ("f32", 8, (3, 96, 96, 96))])
+def test_frames_with_and_without_facts_beside_them(dtype, hw, chans):
+    es, frames = 2 if dtype == "bf16" else 4, []
+    for cin, cout in zip(chans[1:], chans[2:]):
+        t = mt.debug_conv_row_tiling(hw, hw, cin, elem_size=es)
+        grid = lambda rows, t=t: -(-rows // t["images_per_tile"]) * t["tiles_per_image"]  # noqa: E731
+        frames.append([mt.debug_conv_frame_ahead(3, -(-cout // 32), t["frame_bytes"], grid(rows)) for rows in (160, 1600)])
+    assert [True, False] in frames
+    tenants = {t: wl.make_model(wl.cnn_layers(hw=hw, chans=chans, strides=(1,) * (len(chans) - 1)), dtype, 400, t) for t in range(3)}
+    rng = np.random.default_rng(400)
+    x = rng.standard_normal((1600, hw * hw * 3)).astype(np.float32)
+    w = wl.Workload("frames", dtype, tenants, rng.integers(0, 3, 1600).astype(np.int32), wl.round_to_bf16(x) if dtype == "bf16" else x)
+    ctx = make_context(w)
+    every, few = gpu_run(ctx, w, poison=True), gpu_run(ctx, w, ids=w.tenant_ids[:160], inputs=w.inputs[:160], poison=True)
+    ctx.close()
+    # (the pooling launch adds an image's 64 pixels in another order from some number of rows on: fp32 logits and probabilities may differ by 64 roundings of 2^-24)
+    for a, b in zip(every, few):
+        assert np.array_equal(a[:160], b) or (dtype == "f32" and np.linalg.norm(a[:160] - b) <= 64 * 2.0 ** -24 * np.linalg.norm(b))
+    assert np.array_equal(every[2][:160], few[2])
+    pick = np.arange(0, 1600, 53)
+    compare(w, tuple(v[pick] for v in every), oracle_rows(w, pick), rows=pick, what="frames")
